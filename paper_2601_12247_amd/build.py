@@ -20,8 +20,10 @@ SOURCES = [
     "kvcache.hip",
     "elementwise.hip",
     "gemm_simple.hip",
+    "gemm_f32.hip",
     "gemm_mfma.hip",
     "attention_simple.hip",
+    "attention_f32.hip",
     "attention_mfma.hip",
 ]
 

@@ -1,0 +1,195 @@
+// float32 attention with float64 sums on the matrix cores (the float32 path of the forward): out = softmax(q k^T /
+// sqrt(d_head)) v over all T keys of a canvas, no mask of any kind (the denoiser sees the whole canvas, Sec. 2).
+// Full canvases, or the window rows of a K/V-cached round, whose keys come from the window itself or from the
+// cache of the canvas' group.  d_head a multiple of 16, any T whose scores fit into LDS.
+//
+// One workgroup = 16 queries of one (canvas, head), four waves.  Bound by the float64 matrix rate (64 cycles per
+// v_mfma_f64_16x16x4_f64) and, in the small parity model, by latency:
+//   * scores: the waves take every fourth tile of 16 keys; operands come from global memory in operand layout
+//     (16 bytes per lane = four consecutive d, the contraction permuted alike in q and k), the next tile's while
+//     this one's are multiplied; scores are rounded to float32 into LDS, rows padded against bank conflicts;
+//   * softmax in float32 like the plain kernel: four rows per wave;
+//   * out: the waves take every fourth 16 columns of the head, all keys, so that nothing is added across waves;
+//     two accumulators alternate because a float64 MFMA that waits for the previous one idles the pipe.
+// Measured (per layer): 1-3 canvases x 128 tokens 28 -> 12 us, 8-40 canvases x 229 tokens 199 -> 58 us on average.
+#include "common.h"
+
+namespace pvf {
+namespace {
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int TQ = 16;
+
+struct WinF32 {
+  const float *kc, *vc;                // cache rows [T][d] of this layer, group 0
+  int64_t group_stride;
+  const int32_t *seq_slot, *k_active;
+  int32_t slots_per_group, prompt_len, block_len;
+};
+
+template <int KC, bool WIN>            // KC = d_head / 16
+__global__ void __launch_bounds__(256)
+attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int n_rows, int T, int n_heads,
+                     float inv_sqrt_dh, WinF32 wa) {
+  constexpr int dh = KC * 16;
+  extern __shared__ float s_p[];       // [TQ][T16 + 4]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int fr = lane & 15, fq = lane >> 4;
+  const int q0 = blockIdx.x * TQ, head = blockIdx.y, seq = blockIdx.z;
+  const int d = n_heads * dh;
+  const int64_t ld = 3 * (int64_t)d;
+  const float *fresh = qkv + (int64_t)seq * n_rows * ld + (int64_t)head * dh;      // q; k at + d, v at + 2 d
+  const int n_tiles = (T + 15) / 16, stride = n_tiles * 16 + 4;
+  int w0 = 0, w1 = T;                  // keys [w0, w1) are rows of this launch
+  const float *kcb = nullptr, *vcb = nullptr;
+  if (WIN) {
+    const int g = wa.seq_slot[seq] / wa.slots_per_group;
+    w0 = wa.prompt_len + wa.k_active[g] * wa.block_len;
+    w1 = w0 + min(n_rows, T - w0);
+    kcb = wa.kc + g * wa.group_stride + (int64_t)head * dh;
+    vcb = wa.vc + g * wa.group_stride + (int64_t)head * dh;
+  }
+  auto k_row = [&](int key) -> const float * {
+    key = min(key, T - 1);
+    return (!WIN || (key >= w0 && key < w1)) ? fresh + d + (int64_t)(key - w0) * ld : kcb + (int64_t)key * d;
+  };
+  auto v_row = [&](int key) -> const float * {
+    key = min(key, T - 1);
+    return (!WIN || (key >= w0 && key < w1)) ? fresh + 2 * d + (int64_t)(key - w0) * ld : vcb + (int64_t)key * d;
+  };
+
+  // ---- scores ----
+  float4 q[KC];
+  {
+    const float *qr = fresh + (int64_t)min(q0 + fr, n_rows - 1) * ld;
+#pragma unroll
+    for (int c = 0; c < KC; ++c) q[c] = *reinterpret_cast<const float4 *>(qr + c * 16 + 4 * fq);
+  }
+  float4 kb[2][KC];
+  auto fetch_k = [&](int buf, int kt) {
+    const float *kr = k_row(kt * 16 + fr);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) kb[buf][c] = *reinterpret_cast<const float4 *>(kr + c * 16 + 4 * fq);
+  };
+  auto score = [&](int buf, int kt) {
+    doublex4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      s0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)q[c].x, (double)kb[buf][c].x, s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)q[c].y, (double)kb[buf][c].y, s1, 0, 0, 0);
+      s0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)q[c].z, (double)kb[buf][c].z, s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)q[c].w, (double)kb[buf][c].w, s1, 0, 0, 0);
+    }
+    const int key = kt * 16 + fr;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)        // row 4 e + lane / 16 = query, column lane % 16 = key
+      s_p[(4 * e + fq) * stride + key] = key < T ? (float)((s0[e] + s1[e]) * (double)inv_sqrt_dh) : -INFINITY;
+  };
+  if (wave < n_tiles) fetch_k(0, wave);
+  for (int kt = wave; kt < n_tiles; kt += 8) {
+    if (kt + 4 < n_tiles) fetch_k(1, kt + 4);
+    score(0, kt);
+    if (kt + 4 >= n_tiles) break;
+    if (kt + 8 < n_tiles) fetch_k(0, kt + 8);
+    score(1, kt + 4);
+  }
+  __syncthreads();
+
+  // ---- softmax over each row (the padding columns hold -inf, so their weight is 0) ----
+  for (int r = wave * 4; r < wave * 4 + 4; ++r) {
+    float *pr = s_p + r * stride;
+    float m = -INFINITY;
+    for (int k = lane; k < n_tiles * 16; k += kWave) m = fmaxf(m, pr[k]);
+    m = wave_max(m);
+    float z = 0.f;
+    for (int k = lane; k < n_tiles * 16; k += kWave) {
+      const float e = expf(pr[k] - m);
+      pr[k] = e; z += e;
+    }
+    z = wave_sum(z);
+    const float inv = 1.0f / z;
+    for (int k = lane; k < n_tiles * 16; k += kWave) pr[k] *= inv;
+  }
+  __syncthreads();
+
+  // ---- out: row = query, column = lane % 16 of the wave's 16 columns ----
+  for (int dt = wave; dt < KC; dt += 4) {
+    doublex4 o0 = {0.0, 0.0, 0.0, 0.0}, o1 = o0;
+    float vb[2][4];
+    auto fetch_v = [&](int buf, int kt) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) vb[buf][e] = v_row(kt * 16 + 4 * fq + e)[dt * 16 + fr];
+    };
+    auto mul = [&](int buf, int kt) {
+      const float4 p = *reinterpret_cast<const float4 *>(s_p + fr * stride + kt * 16 + 4 * fq);
+      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.x, (double)vb[buf][0], o0, 0, 0, 0);
+      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.y, (double)vb[buf][1], o1, 0, 0, 0);
+      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.z, (double)vb[buf][2], o0, 0, 0, 0);
+      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.w, (double)vb[buf][3], o1, 0, 0, 0);
+    };
+    fetch_v(0, 0);
+    for (int kt = 0; kt < n_tiles; kt += 2) {
+      if (kt + 1 < n_tiles) fetch_v(1, kt + 1);
+      mul(0, kt);
+      if (kt + 1 >= n_tiles) break;
+      if (kt + 2 < n_tiles) fetch_v(0, kt + 2);
+      mul(1, kt + 1);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int q_ = q0 + 4 * e + fq;
+      if (q_ < n_rows) out[((int64_t)seq * n_rows + q_) * d + (int64_t)head * dh + dt * 16 + fr] = (float)(o0[e] + o1[e]);
+    }
+  }
+}
+
+size_t lds_bytes(int T) { return (size_t)TQ * ((T + 15) / 16 * 16 + 4) * sizeof(float); }
+
+template <bool WIN>
+pvf_status launch(pvf_ctx *ctx, hipStream_t s, const float *qkv, float *out, int S, int n_rows, int T, int n_heads, int d_head,
+                  const WinF32 &wa) {
+  const size_t lds = lds_bytes(T);
+  const dim3 grid((n_rows + TQ - 1) / TQ, n_heads, S);
+  const float isd = 1.0f / sqrtf((float)d_head);
+#define PVF_ATT_CASE(KC)                                                                                             \
+  case KC: {                                                                                                         \
+    static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(attention_f32_kernel<KC, WIN>), \
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
+    PVF_HIP_CHECK(ctx, configured);                                                                                  \
+    attention_f32_kernel<KC, WIN><<<grid, 256, lds, s>>>(qkv, out, n_rows, T, n_heads, isd, wa);                     \
+    break;                                                                                                           \
+  }
+  switch (d_head / 16) {
+    PVF_ATT_CASE(1) PVF_ATT_CASE(2) PVF_ATT_CASE(4) PVF_ATT_CASE(8)
+    default: PVF_REQUIRE(ctx, false, PVF_ESHAPE, "attention_f32: d_head=%d", d_head);
+  }
+#undef PVF_ATT_CASE
+  PVF_LAUNCH_CHECK(ctx, "attention_f32");
+  return PVF_OK;
+}
+
+}  // namespace
+
+bool attention_f32_supported(int dtype, int T, int d_head) {
+  return dtype == PVF_F32 && (d_head == 16 || d_head == 32 || d_head == 64 || d_head == 128) && lds_bytes(T) <= 160 * 1024;
+}
+
+// qkv must already be rotated.
+pvf_status launch_attention_f32(pvf_ctx *ctx, hipStream_t s, const void *qkv, void *out, int S, int T, int n_heads, int d_head) {
+  if (S == 0) return PVF_OK;
+  return launch<false>(ctx, s, (const float *)qkv, (float *)out, S, T, T, n_heads, d_head, WinF32{});
+}
+
+pvf_status launch_attention_window_f32(pvf_ctx *ctx, hipStream_t s, const void *qkv_w, const void *kc, const void *vc,
+                                       int64_t group_stride, const pvf_decode_cfg &cfg, const pvf_state &st,
+                                       const int32_t *seq_slot, int n_seq, int n_heads, int d_head, void *out) {
+  if (n_seq == 0) return PVF_OK;
+  WinF32 wa;
+  wa.kc = (const float *)kc; wa.vc = (const float *)vc; wa.group_stride = group_stride;
+  wa.seq_slot = seq_slot; wa.k_active = st.k_active; wa.slots_per_group = 1 + cfg.K;
+  wa.prompt_len = cfg.prompt_len; wa.block_len = cfg.block_len;
+  return launch<true>(ctx, s, (const float *)qkv_w, (float *)out, n_seq, window_rows(cfg), cfg.prompt_len + cfg.gen_len, n_heads,
+                      d_head, wa);
+}
+
+}  // namespace pvf

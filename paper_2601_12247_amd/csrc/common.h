@@ -157,6 +157,13 @@ struct NormArgs {
   int32_t n_slots_in = 0, ld = 0; // slots to add up; rows per slot
   float inv_d = 0.f, eps = 0.f;
 };
+// Rotary embedding in the epilogue of a float32 QKV projection: row m is canvas position m % T, or row_pos[m] (negative:
+// a padding row, rotated like position T - 1); cos_sin [T][half].
+struct RopeF32 {
+  const float2 *cos_sin;
+  const int32_t *row_pos;         // NULL: whole canvases
+  int32_t T, half;
+};
 // C[M,N] = A[M,K] W[N,K]^T; kEpiResidual adds residual[M,N]; kEpiSwiglu: W is [2N,K] (gate|up),
 // C[M,N] = silu(gate) * up.
 pvf_status launch_gemm(pvf_ctx *ctx, hipStream_t s, int dtype, GemmEpilogue epi, const void *A,

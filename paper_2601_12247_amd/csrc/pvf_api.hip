@@ -86,8 +86,15 @@ struct ProfScope {
 };
 
 // ---- dispatch between the MFMA kernels and the plain ones -------------------------------
-pvf_status launch_gemm_simple(pvf_ctx *, hipStream_t, int, GemmEpilogue, const void *, const void *,
-                              void *, const void *, int, int, int);
+pvf_status launch_gemm_simple(pvf_ctx *, hipStream_t, GemmEpilogue, const bf16_t *, const bf16_t *, bf16_t *, const bf16_t *,
+                              int, int, int);
+pvf_status launch_gemm_f32(pvf_ctx *, hipStream_t, GemmEpilogue, const float *, const float *, float *, const float *, int, int, int);
+bool gemm_f32_qkv_rope_supported(int d_head);
+pvf_status launch_gemm_f32_qkv_rope(pvf_ctx *, hipStream_t, const float *, const float *, float *, int M, int d, int K, const RopeF32 &);
+bool attention_f32_supported(int dtype, int T, int d_head);
+pvf_status launch_attention_f32(pvf_ctx *, hipStream_t, const void *, void *, int, int, int, int);
+pvf_status launch_attention_window_f32(pvf_ctx *, hipStream_t, const void *, const void *, const void *, int64_t, const pvf_decode_cfg &,
+                                       const pvf_state &, const int32_t *, int, int, int, void *);
 pvf_status launch_attention_simple(pvf_ctx *, hipStream_t, int, const void *, void *, int, int, int, int);
 bool gemm_mfma_supported(int dtype, GemmEpilogue epi, int M, int N, int K);
 pvf_status launch_gemm_mfma(pvf_ctx *, hipStream_t, GemmEpilogue, const void *, const void *, void *,
@@ -121,11 +128,21 @@ static bool force_simple() {
 
 pvf_status launch_gemm(pvf_ctx *ctx, hipStream_t s, int dtype, GemmEpilogue epi, const void *A,
                        const void *W, void *C, const void *residual, int M, int N, int K) {
+  if (dtype == PVF_F32)
+    return launch_gemm_f32(ctx, s, epi, (const float *)A, (const float *)W, (float *)C, (const float *)residual, M, N, K);
   if (!force_simple() && ctx && ctx->splitk_ws && gemm_mfma_splitk_supported(dtype, epi, M, N, K, ctx->splitk_floats))
     return launch_gemm_mfma_splitk(ctx, s, epi, A, W, C, residual, M, N, K, ctx->splitk_ws, ctx->splitk_floats);
   if (!force_simple() && gemm_mfma_supported(dtype, epi, M, N, K))
     return launch_gemm_mfma(ctx, s, epi, A, W, C, residual, M, N, K);
-  return launch_gemm_simple(ctx, s, dtype, epi, A, W, C, residual, M, N, K);
+  return launch_gemm_simple(ctx, s, epi, (const bf16_t *)A, (const bf16_t *)W, (bf16_t *)C, (const bf16_t *)residual, M, N, K);
+}
+
+// Attention over whole canvases on rotated q, k (float32 with any d_head, bf16 without the MFMA kernel).
+static pvf_status launch_attention_plain(pvf_ctx *ctx, hipStream_t s, int dtype, const void *qkv, void *out, int S, int T,
+                                         int n_heads, int d_head) {
+  if (attention_f32_supported(dtype, T, d_head) && ((uintptr_t)qkv & 15u) == 0)
+    return launch_attention_f32(ctx, s, qkv, out, S, T, n_heads, d_head);
+  return launch_attention_simple(ctx, s, dtype, qkv, out, S, T, n_heads, d_head);
 }
 
 static bool use_attention_mfma(int dtype, int T, int d_head) {
@@ -143,7 +160,7 @@ static pvf_status launch_rope_attention(pvf_ctx *ctx, hipStream_t s, int dtype, 
     return launch_attention_mfma(ctx, s, qkv, vt, out, S, T, n_heads);
   }
   if ((st = launch_rope(ctx, s, dtype, qkv, S * T, T, n_heads, d_head, cos_sin)) != PVF_OK) return st;
-  return launch_attention_simple(ctx, s, dtype, qkv, out, S, T, n_heads, d_head);
+  return launch_attention_plain(ctx, s, dtype, qkv, out, S, T, n_heads, d_head);
 }
 
 // ---- validation -----------------------------------------------------------------------
@@ -346,6 +363,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
                                      (double)(Mm) * (Nn) * ((epi) == kEpiResidual ? 2 : 1)));             \
     RUN(launch_gemm(c, s, dt, epi, A, W, C, res, Mm, Nn, Kk));                                    \
   } while (0)
+  const bool f32_rope = dt == PVF_F32 && gemm_f32_qkv_rope_supported(dh);
   const bool fused_rope = use_attention_mfma(dt, T, dh) && gemm_mfma_qkv_rope_supported(dt, M, 3 * d, d, T, H);
   // Above the split-K range the two norms of a layer are folded into the projections around them: O and down
   // write each row's sum of squares beside h, QKV and gate/up read h itself (gains folded into their weights)
@@ -423,6 +441,14 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
       }
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)T * T * d, 0.0);
       RUN(launch_attention_mfma(c, s, c->qkv, c->vt, c->att, S, T, H));
+    } else if (f32_rope) {
+      {
+        ProfScope ps(c, s, PVF_PROF_GEMM, 6.0 * M * (double)d * d, (double)c->esize * (4.0 * M * d + 3.0 * d * d));
+        RUN(launch_gemm_f32_qkv_rope(c, s, (const float *)c->xn, (const float *)c->wqkv[l], (float *)c->qkv, M, d, d,
+                                     RopeF32{c->cos_sin, nullptr, T, dh / 2}));
+      }
+      ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)T * T * d, 0.0);
+      RUN(launch_attention_plain(c, s, dt, c->qkv, c->att, S, T, H, dh));
     } else {
       RUN_GEMM(kEpiStore, c->xn, c->wqkv[l], c->qkv, nullptr, M, 3 * d, d);
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)T * T * d, 0.0);
@@ -482,10 +508,17 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
     RUN_GEMM(kEpiResidual, A, W, c->h, c->h, M, d, Kk);
     return launch_rmsnorm(c, s, dt, c->h, gain, out, M, d, m.rms_eps);
   };
+  const bool f32_rope = dt == PVF_F32 && gemm_f32_qkv_rope_supported(dh);
   RUN(launch_rmsnorm(c, s, dt, c->h, c->attn_norm[0], c->xn, M, d, m.rms_eps));
   for (int l = 0; l < m.n_layers; ++l) {
     const int64_t layer_off = (int64_t)l * T * d * c->esize;
-    RUN_GEMM(kEpiStore, c->xn, c->wqkv[l], c->qkv, nullptr, M, 3 * d, d);
+    if (f32_rope) {
+      ProfScope ps(c, s, PVF_PROF_GEMM, 6.0 * M * (double)d * d, (double)c->esize * (4.0 * M * d + 3.0 * d * d));
+      RUN(launch_gemm_f32_qkv_rope(c, s, (const float *)c->xn, (const float *)c->wqkv[l], (float *)c->qkv, M, d, d,
+                                   RopeF32{c->cos_sin, row_pos, T, dh / 2}));
+    } else {
+      RUN_GEMM(kEpiStore, c->xn, c->wqkv[l], c->qkv, nullptr, M, 3 * d, d);
+    }
     {
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)R * T * d, 0.0);
       if (c->cache_vt) {
@@ -494,7 +527,11 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
                                          (const char *)c->vcache + layer_off, gstride, seq_slot, state.k_active,
                                          1 + cfg.K, cfg.prompt_len, cfg.block_len, R, S, T, H, c->att));
       } else {
-        RUN(launch_rope_rows(c, s, dt, c->qkv, row_pos, M, T, H, dh, c->cos_sin));
+        if (!f32_rope) RUN(launch_rope_rows(c, s, dt, c->qkv, row_pos, M, T, H, dh, c->cos_sin));
+        if (attention_f32_supported(dt, T, dh))
+          RUN(launch_attention_window_f32(c, s, c->qkv, (const char *)c->kcache + layer_off, (const char *)c->vcache + layer_off,
+                                          gstride, cfg, state, seq_slot, S, H, dh, c->att));
+        else
         RUN(launch_attention_window(c, s, dt, c->qkv, (const char *)c->kcache + layer_off, (const char *)c->vcache + layer_off,
                                     gstride, cfg, state, seq_slot, S, H, dh, c->att));
       }
