@@ -35,25 +35,35 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Rows of the key-contiguous value buffers hold T rounded up to a whole tile of keys (vt_stride); what lies beyond T is
+// never written and never used.
+//
 // Window mode (K/V-cached rounds): the queries are the R window rows of a canvas (qkv holds only
-// those rows, vt their key-contiguous values [seq][head][d][R]); a key inside the window
-// [w0, w0 + n_valid) is read from there, every other key from the cache of the canvas' group
-// (kc: rotated keys [T][d] row-major, vtc: values [head][d][T]).
+// those rows); keys in the window [w0, w0 + n_valid) are read from there, every other key from the cache of the
+// canvas' group (kc: rotated keys [T][d] row-major, vtc: values [head][d][vt_stride]).  Values are read in chunks of one
+// 16-key group, so vt holds [seq][head][d][Rv] from the 16-key boundary at or below w0: where the window begins or
+// ends inside a group, rope_vt_kernel has filled the rest of the group from the cache.
 struct WinArgs {
   const bf16_t *kc, *vtc;
   int64_t group_stride;
   const int32_t *seq_slot, *k_active;
-  int32_t slots_per_group, prompt_len, block_len, R;
+  int32_t slots_per_group, prompt_len, block_len, R, Rv;
 };
 
 // SPLIT (window mode with at most 64 query rows per canvas): the 64 queries need only two of the four waves, and
 // the loop over the key tiles is a chain of dependent steps of ~2 us each, so the waves work as two pairs: pair
 // 0 takes the even key tiles, pair 1 the odd ones (two tiles are staged per step), and at the end pair 0 merges
 // pair 1's running maximum, sum and O into its own.  Half as many steps for the same work.
-template <bool WIN, bool SPLIT>
+//
+// RAG: any canvas length and window alignment.  Keys beyond T in the last tile are read as key T - 1, get a score of
+// -inf, and their value columns are cleared in LDS.  These shapes used to take a vector-ALU kernel that kept the
+// probabilities in float32, so P goes into the second product as hi + lo bf16 (2^-17 relative instead of 2^-9): against
+// float64 the outputs are as close as that kernel's (1.661531e-3 against 1.661530e-3, bf16 rounding alone 1.661530e-3).  Per
+// layer: 3 canvases x 437 tokens 1196 -> 34 us, four windows of 128 rows over 715 tokens 1496 -> 32 us.  The even shapes keep the single bf16 P they always had.
+template <bool WIN, bool SPLIT, bool RAG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ vt,
-                      bf16_t *__restrict__ out, int T, int H, WinArgs wa) {
+                      bf16_t *__restrict__ out, int T, int H, int vt_stride, WinArgs wa) {
   static_assert(!SPLIT || WIN, "the key split exists in window mode only");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[(SPLIT ? 4 : 2) * kStage];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -66,15 +76,17 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
   const int64_t row0 = (int64_t)seq * TQrows;
   const bf16_t *qb = qkv + row0 * 3 * d + (int64_t)head * DH;
   const bf16_t *kb = qb + d;
-  const bf16_t *vtb = vt + ((int64_t)seq * H + head) * DH * TQrows;
+  const bf16_t *vtb = vt + ((int64_t)seq * H + head) * DH * (WIN ? wa.Rv : vt_stride);
   int w0 = 0, w1 = 0;                                      // window = keys [w0, w1)
+  int v0 = 0, v1 = 0;                                      // 16-key groups held by vt: keys [v0, v1)
   const bf16_t *kcb = nullptr, *vtcb = nullptr;
   if (WIN) {
     const int g = wa.seq_slot[seq] / wa.slots_per_group;
     w0 = wa.prompt_len + wa.k_active[g] * wa.block_len;
     w1 = w0 + min(wa.R, T - w0);
+    v0 = w0 & ~15; v1 = (w1 + 15) & ~15;
     kcb = wa.kc + g * wa.group_stride + (int64_t)head * DH;
-    vtcb = wa.vtc + g * wa.group_stride + (int64_t)head * DH * T;
+    vtcb = wa.vtc + g * wa.group_stride + (int64_t)head * DH * vt_stride;
   }
 
   // ---- Q fragments: "B" operand, column = query, k-chunk = 8 consecutive d ----
@@ -96,7 +108,7 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
     k_src[i] = kb + (int64_t)key * 3 * d + kc * 8;
     k_key[i] = key; k_col[i] = kc * 8;
     const int vr = s >> 3, vc = (s & 7) ^ ((vr >> 1) & 7);
-    v_src[i] = vtb + (int64_t)vr * T + vc * 8;
+    v_src[i] = vtb + (int64_t)vr * vt_stride + vc * 8;
     v_row[i] = vr; v_key[i] = vc * 8;
   }
   auto issue_loads = [&](int kt, int slot) {                 // key tile kt -> LDS tile slot `slot`
@@ -105,14 +117,15 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
     for (int i = 0; i < 4; ++i) {
       const bf16_t *ks, *vs;
       if (WIN) {
-        const int key = kt * TK + k_key[i];                // canvas position of this K row
+        int key = kt * TK + k_key[i];                      // canvas position of this K row
+        if (RAG) key = min(key, T - 1);
         ks = (key >= w0 && key < w1) ? kb + (int64_t)(key - w0) * 3 * d + k_col[i]
                                      : kcb + (int64_t)key * d + k_col[i];
         const int vk = kt * TK + v_key[i];                 // first of the 8 keys of this V^T chunk
-        vs = (vk >= w0 && vk < w1) ? vtb + (int64_t)v_row[i] * wa.R + (vk - w0)
-                                   : vtcb + (int64_t)v_row[i] * T + vk;
+        vs = (vk >= v0 && vk < v1) ? vtb + (int64_t)v_row[i] * wa.Rv + (vk - v0)
+                                   : vtcb + (int64_t)v_row[i] * vt_stride + vk;
       } else {
-        ks = k_src[i] + (int64_t)kt * TK * 3 * d;
+        ks = RAG ? kb + (int64_t)min(kt * TK + k_key[i], T - 1) * 3 * d + k_col[i] : k_src[i] + (int64_t)kt * TK * 3 * d;
         vs = v_src[i] + kt * TK;
       }
       __builtin_amdgcn_global_load_lds((gptr_t *)ks, (lptr_t *)(dst + i * 4096), 16, 0, 0);
@@ -143,7 +156,7 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
 #pragma unroll
   for (int ks2 = 0; ks2 < 4; ++ks2) v_rd[ks2] = fr * 128 + (((2 * ks2 + fh) ^ ((fr >> 1) & 7)) << 4);
 
-  const int nk = T / TK;
+  const int nk = RAG ? (T + TK - 1) / TK : T / TK;
   // step = one key tile (SPLIT: two, one per pair); kBuf = which half of the double buffer holds it
   const int n_steps = SPLIT ? (nk + 1) / 2 : nk;
   auto stage_step = [&](int st, int buf) {
@@ -160,6 +173,22 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
     __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
     __syncthreads();
     if (st + 1 < n_steps) stage_step(st + 1, kBuf ^ 1);
+    if (RAG && st + 1 == n_steps && T < nk * TK) {
+      // the last tile: clear the value columns of keys >= T (4 consecutive keys per 8-byte piece)
+      unsigned char *vlast = lds + (SPLIT ? 2 * kBuf + ((nk - 1) & 1) : kBuf) * kStage + kKTile;
+      const int rem = T - (nk - 1) * TK;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int piece = i * 256 + tid;                     // 128 rows x 16 pieces
+        const int row = piece >> 4, c8 = piece & 15;         // stored chunk c8 / 2, half c8 % 2
+        const int valid = rem - (16 * (c8 >> 2) + 4 * ((c8 >> 1) & 1) + 8 * (c8 & 1));
+        if (valid < 4) {
+          uint64_t *p = reinterpret_cast<uint64_t *>(vlast + row * 128 + (((c8 >> 1) ^ ((row >> 1) & 7)) << 4) + (c8 & 1) * 8);
+          *p = valid <= 0 ? 0 : *p & ((1ull << (16 * valid)) - 1);
+        }
+      }
+      __syncthreads();
+    }
     if (SPLIT && 2 * st + pair >= nk) return;    // an odd number of key tiles: pair 1 has none in the last step
     const unsigned char *ks_ = lds + (SPLIT ? 2 * kBuf + pair : kBuf) * kStage;
     const unsigned char *vs_ = ks_ + kKTile;
@@ -173,6 +202,16 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
         const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(ks_ + t * 32 * 256 + k_rd[ks]);   // key t*32 + fr
         // the first k-step starts from a constant zero accumulator: no registers to clear per tile
         s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], ks == 0 ? kZero16 : s[t], 0, 0, 0);
+      }
+    }
+    if (RAG) {
+      const int rem = T - (SPLIT ? 2 * st + pair : st) * TK;
+      if (rem < TK) {                                        // accumulator e of sub-tile t: key 32 t + 8 (e / 4) + 4 fh + e % 4
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (t * 32 + 8 * (e >> 2) + 4 * fh + (e & 3) >= rem) s[t][e] = -INFINITY;
       }
     }
     // ---- online softmax for this lane's query ----
@@ -189,14 +228,16 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
     const float m_new = upd ? mx : m_run;
     const float alpha = upd ? fast_exp2((m_run - m_new) * c) : 1.0f;   // first tile: exp2(-inf) = 0
     const float nmc = -m_new * c;
-    bf16x8 pf[4];                                            // "B" operand of the 4 key k-steps
+    bf16x8 pf[4], pl[RAG ? 4 : 1];                           // "B" operand of the 4 key k-steps; RAG: and what its rounding left
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int u = 0; u < 2; ++u)                            // k-step u of sub-tile t: register groups 2u, 2u+1
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          pf[2 * t + u][e] = (bf16_t)fast_exp2(fmaf(s[t][8 * u + e], c, nmc));
+          const float p = fast_exp2(fmaf(s[t][8 * u + e], c, nmc));
+          pf[2 * t + u][e] = (bf16_t)p;
+          if (RAG) pl[RAG ? 2 * t + u : 0][e] = (bf16_t)(p - (float)pf[2 * t + u][e]);
         }
     m_run = m_new;
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
@@ -215,9 +256,11 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
         // d row t*32 + fr; vt stores each group of 16 keys as {0-3, 8-11 | 4-7, 12-15}: chunk 2*ks2 + fh is this lane's 8 keys
         const bf16x8 vf = *reinterpret_cast<const bf16x8 *>(vs_ + t * 32 * 128 + v_rd[ks2]);
         o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks2], o[t], 0, 0, 0);
+        if (RAG) o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl[RAG ? ks2 : 0], o[t], 0, 0, 0);
       }
       // row sums of P on the matrix pipe (a "V^T" row of ones): the vector ALU is the busier unit here
       ol = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf[ks2], ol, 0, 0, 0);
+      if (RAG) ol = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pl[RAG ? ks2 : 0], ol, 0, 0, 0);
     }
   };
   for (int st = 0; st + 1 < n_steps; st += 2) {
@@ -275,22 +318,38 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
 // hold them) are then one 16-byte chunk.
 __device__ __forceinline__ int vt_pos(int t) { return (t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1); }
 
-// Rotary embedding of q and k in place (pair (i, i + 64) of each head) and the key-contiguous copy of v for 64
-// rows of one (canvas, head), by one 256-thread workgroup with 16-byte accesses throughout.
-//   base: the rows' q columns of this head (row stride 3 d);  pos(rr): canvas position of row rr;
-//   vb: vt row 0 of this (canvas, head) at the first of the 64 keys, vt_stride: keys per vt row.
-//   vb[d][vt_pos(rr)] = v[rr][d]
-template <typename PosFn>
-__device__ __forceinline__ void rope_vt_64rows(bf16_t *base, int d, const float2 *__restrict__ cos_sin, PosFn pos,
-                                               bf16_t *vb, int vt_stride, bf16_t (*tile)[64 + 2]) {
-  const int tid = threadIdx.x;
+// Rotary embedding of q and k in place (pair (i, i + 64) of each head) and the key-contiguous copy of v, one 256-thread
+// workgroup per 64 canvas positions of one (canvas, head), with 16-byte accesses throughout.
+//   whole canvases: positions [64 bx, 64 bx + 64) of T;  vt[canvas][head][d][vt_pos(t)] = v[canvas * T + t][head * 128 + d]
+//   window rows (WIN): positions from the 16-key boundary at or below the window's first row; row r of the window is
+//   position w0 + r (rows past the canvas end are padding, rotated like position T - 1).  vt row d, keys counted from that
+//   boundary; positions of a boundary group that lie outside the window come from the cache.
+template <bool WIN>
+__global__ void __launch_bounds__(256)
+rope_vt_kernel(bf16_t *__restrict__ qkv, bf16_t *__restrict__ vt, int T, int H, int vt_stride,
+               const float2 *__restrict__ cos_sin, WinArgs wa) {
+  __shared__ bf16_t tile[DH][64 + 2];
+  const int tid = threadIdx.x, head = blockIdx.y, seq = blockIdx.z;
+  const int d = H * DH, n_rows = WIN ? wa.R : T;
+  int p0 = blockIdx.x * 64, w0 = 0, w1 = T;                  // first position of the workgroup; positions that have rows
+  const bf16_t *vtcb = nullptr;
+  if (WIN) {
+    const int g = wa.seq_slot[seq] / wa.slots_per_group;
+    w0 = wa.prompt_len + wa.k_active[g] * wa.block_len;
+    w1 = w0 + min(wa.R, T - w0);
+    p0 += w0 & ~15;
+    vtcb = wa.vtc + g * wa.group_stride + (int64_t)head * DH * vt_stride;
+  }
+  const int r0 = p0 - w0;                                    // row of position p0 (WIN: negative in front of the window)
+  bf16_t *base = qkv + (int64_t)seq * n_rows * 3 * d + (int64_t)head * DH;
   // rotate q and k: 64 rows x 2 tensors x 8 chunks of 8 pairs
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int idx = it * 256 + tid;
-    const int ch = idx & 7, which = (idx >> 3) & 1, rr = idx >> 4;
-    bf16_t *p = base + (int64_t)rr * 3 * d + which * d + ch * 8;
-    const float4 *cs4 = reinterpret_cast<const float4 *>(cos_sin + (int64_t)pos(rr) * 64 + ch * 8);
+    const int ch = idx & 7, which = (idx >> 3) & 1, r = r0 + (idx >> 4);
+    if (r < 0 || r >= n_rows) continue;
+    bf16_t *p = base + (int64_t)r * 3 * d + which * d + ch * 8;
+    const float4 *cs4 = reinterpret_cast<const float4 *>(cos_sin + (int64_t)min(w0 + r, T - 1) * 64 + ch * 8);
     const uint4 lo = *reinterpret_cast<const uint4 *>(p), hi = *reinterpret_cast<const uint4 *>(p + 64);
     const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
     uint32_t ol[4], oh[4];
@@ -312,7 +371,16 @@ __device__ __forceinline__ void rope_vt_64rows(bf16_t *base, int d, const float2
   for (int it = 0; it < 4; ++it) {
     const int idx = it * 256 + tid;
     const int rr = idx & 63, ch = idx >> 6;                  // consecutive lanes = consecutive rows: no bank conflicts
-    const uint4 v8 = *reinterpret_cast<const uint4 *>(base + (int64_t)rr * 3 * d + 2 * d + ch * 8);
+    const int pos = p0 + rr;
+    uint4 v8 = make_uint4(0, 0, 0, 0);
+    if (pos >= w0 && pos < w1) {
+      v8 = *reinterpret_cast<const uint4 *>(base + (int64_t)(r0 + rr) * 3 * d + 2 * d + ch * 8);
+    } else if (WIN && pos < T && pos < ((w1 + 15) & ~15)) {
+      uint16_t x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = __builtin_bit_cast(uint16_t, vtcb[(int64_t)(ch * 8 + e) * vt_stride + vt_pos(pos)]);
+      v8 = make_uint4(x[0] | ((uint32_t)x[1] << 16), x[2] | ((uint32_t)x[3] << 16), x[4] | ((uint32_t)x[5] << 16), x[6] | ((uint32_t)x[7] << 16));
+    }
     const uint32_t w[4] = {v8.x, v8.y, v8.z, v8.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -321,6 +389,8 @@ __device__ __forceinline__ void rope_vt_64rows(bf16_t *base, int d, const float2
     }
   }
   __syncthreads();
+  const int out_stride = WIN ? wa.Rv : vt_stride;
+  bf16_t *vb = vt + ((int64_t)seq * H + head) * DH * out_stride + blockIdx.x * 64;
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int idx = it * 256 + tid;
@@ -332,84 +402,54 @@ __device__ __forceinline__ void rope_vt_64rows(bf16_t *base, int d, const float2
       const int kr = k0 + (e & 1) * 2 + (e >> 1) * 8;
       w[e] = (uint32_t)__builtin_bit_cast(uint16_t, tile[dd][kr]) | ((uint32_t)__builtin_bit_cast(uint16_t, tile[dd][kr + 1]) << 16);
     }
-    *reinterpret_cast<uint4 *>(vb + (int64_t)dd * vt_stride + g * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+    *reinterpret_cast<uint4 *>(vb + (int64_t)dd * out_stride + g * 8) = make_uint4(w[0], w[1], w[2], w[3]);
   }
-}
-
-// Full canvases: one block = 64 positions of one (canvas, head); vt[canvas][head][d][vt_pos(t)] = v[canvas*T + t][head*128 + d].
-__global__ void __launch_bounds__(256)
-rope_vt_kernel(bf16_t *__restrict__ qkv, bf16_t *__restrict__ vt, int T, int H,
-               const float2 *__restrict__ cos_sin) {
-  __shared__ bf16_t tile[DH][64 + 2];
-  const int t0 = blockIdx.x * 64, head = blockIdx.y, seq = blockIdx.z;
-  const int d = H * DH;
-  bf16_t *base = qkv + ((int64_t)seq * T + t0) * 3 * d + (int64_t)head * DH;
-  rope_vt_64rows(base, d, cos_sin, [&](int rr) { return t0 + rr; },
-                 vt + ((int64_t)seq * H + head) * DH * T + t0, T, tile);
-}
-
-// Window rows: rotary embedding at the rows' own canvas positions (row_pos, -1 = padding row,
-// rotated like position T-1) and the key-contiguous copy vt[seq][head][d][r] of their values.
-// One block = 64 window rows of one (sequence, head).
-__global__ void __launch_bounds__(256)
-rope_vt_rows_kernel(bf16_t *__restrict__ qkv, bf16_t *__restrict__ vt, const int32_t *__restrict__ row_pos,
-                    int R, int T, int H, const float2 *__restrict__ cos_sin) {
-  __shared__ bf16_t tile[DH][64 + 2];
-  const int r0 = blockIdx.x * 64, head = blockIdx.y, seq = blockIdx.z;
-  const int d = H * DH;
-  bf16_t *base = qkv + ((int64_t)seq * R + r0) * 3 * d + (int64_t)head * DH;
-  rope_vt_64rows(base, d, cos_sin,
-                 [&](int rr) { const int pos = row_pos[(int64_t)seq * R + r0 + rr]; return pos < 0 ? T - 1 : pos; },
-                 vt + ((int64_t)seq * H + head) * DH * R + r0, R, tile);
 }
 
 }  // namespace
 
-// Window attention on the matrix cores needs whole 64-row blocks of window rows and 16-key
-// groups (the unit of the vt key order) that lie entirely inside or outside the window.
-bool attention_window_mfma_supported(int dtype, int T, int d_head, int R, int block_len, int prompt_len) {
-  return dtype == PVF_BF16 && d_head == DH && T >= TK && T % TK == 0 && R % 64 == 0 && block_len % 16 == 0 &&
-         prompt_len % 16 == 0;
+bool attention_mfma_supported(int dtype, int d_head) { return dtype == PVF_BF16 && d_head == DH; }
+
+// Keys per row of the window rows' value buffer: whole 64-position workgroups from the 16-key boundary below the window.
+static int window_vt_stride(int R, int block_len, int prompt_len) {
+  const int before = block_len % 16 == 0 && prompt_len % 16 == 0 ? 0 : 15;
+  return (before + R + 63) / 64 * 64;
 }
 
-pvf_status launch_rope_vt_rows(pvf_ctx *ctx, hipStream_t s, void *qkv, void *vt, const int32_t *row_pos,
-                               int S, int R, int T, int n_heads, const float2 *cos_sin) {
+pvf_status launch_window_attention_mfma(pvf_ctx *ctx, hipStream_t s, void *qkv_w, void *vt_w, const void *kc, const void *vtc,
+                                        int64_t group_stride, const int32_t *seq_slot, const int32_t *k_active,
+                                        const pvf_decode_cfg &cfg, int S, int n_heads, const float2 *cos_sin, void *out) {
   if (S == 0) return PVF_OK;
-  const dim3 grid(R / 64, n_heads, S);
-  rope_vt_rows_kernel<<<grid, 256, 0, s>>>((bf16_t *)qkv, (bf16_t *)vt, row_pos, R, T, n_heads, cos_sin);
-  PVF_LAUNCH_CHECK(ctx, "rope_vt_rows");
-  return PVF_OK;
-}
-
-pvf_status launch_attention_window_mfma(pvf_ctx *ctx, hipStream_t s, const void *qkv_w, const void *vt_w,
-                                        const void *kc, const void *vtc, int64_t group_stride,
-                                        const int32_t *seq_slot, const int32_t *k_active, int slots_per_group,
-                                        int prompt_len, int block_len, int R, int S, int T, int n_heads,
-                                        void *out) {
-  if (S == 0) return PVF_OK;
+  const int T = cfg.prompt_len + cfg.gen_len, R = window_rows(cfg), vts = vt_keys(T);
   WinArgs wa;
   wa.kc = (const bf16_t *)kc; wa.vtc = (const bf16_t *)vtc; wa.group_stride = group_stride;
-  wa.seq_slot = seq_slot; wa.k_active = k_active; wa.slots_per_group = slots_per_group;
-  wa.prompt_len = prompt_len; wa.block_len = block_len; wa.R = R;
+  wa.seq_slot = seq_slot; wa.k_active = k_active; wa.slots_per_group = 1 + cfg.K;
+  wa.prompt_len = cfg.prompt_len; wa.block_len = cfg.block_len; wa.R = R;
+  wa.Rv = window_vt_stride(R, cfg.block_len, cfg.prompt_len);
+  rope_vt_kernel<true><<<dim3(wa.Rv / 64, n_heads, S), 256, 0, s>>>((bf16_t *)qkv_w, (bf16_t *)vt_w, T, n_heads, vts, cos_sin, wa);
+  PVF_LAUNCH_CHECK(ctx, "rope_vt_rows");
+  // even: whole key tiles, whole 64-row blocks of window rows, windows that begin and end with a 16-key group
+  const bool even = T % TK == 0 && R % 64 == 0 && cfg.block_len % 16 == 0 && cfg.prompt_len % 16 == 0;
   const dim3 grid((R + TQ - 1) / TQ, n_heads, S);
-  if (R <= 64)
-    attention_mfma_kernel<true, true><<<grid, 256, 0, s>>>((const bf16_t *)qkv_w, (const bf16_t *)vt_w, (bf16_t *)out, T, n_heads, wa);
-  else
-    attention_mfma_kernel<true, false><<<grid, 256, 0, s>>>((const bf16_t *)qkv_w, (const bf16_t *)vt_w, (bf16_t *)out, T, n_heads, wa);
+  const bf16_t *q = (const bf16_t *)qkv_w, *v = (const bf16_t *)vt_w;
+  bf16_t *o = (bf16_t *)out;
+  if (R <= 64 && even) attention_mfma_kernel<true, true, false><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
+  else if (R <= 64) attention_mfma_kernel<true, true, true><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
+  else if (even) attention_mfma_kernel<true, false, false><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
+  else attention_mfma_kernel<true, false, true><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
   PVF_LAUNCH_CHECK(ctx, "attention_window_mfma");
   return PVF_OK;
 }
 
-bool attention_mfma_supported(int dtype, int T, int d_head) {
-  return dtype == PVF_BF16 && d_head == DH && T >= TK && T % TK == 0;
-}
-
-// qkv must already be rotated and vt filled (launch_rope_vt).
+// qkv must already be rotated and vt [S][n_heads][128][vt_keys(T)] filled (launch_rope_vt, or the QKV projection's epilogue).
 pvf_status launch_attention_mfma(pvf_ctx *ctx, hipStream_t s, const void *qkv, const void *vt,
                                  void *out, int S, int T, int n_heads) {
   if (S == 0) return PVF_OK;
   const dim3 grid((T + TQ - 1) / TQ, n_heads, S);
-  attention_mfma_kernel<false, false><<<grid, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)vt, (bf16_t *)out, T, n_heads, WinArgs{});
+  if (T % TK == 0)
+    attention_mfma_kernel<false, false, false><<<grid, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)vt, (bf16_t *)out, T, n_heads, T, WinArgs{});
+  else
+    attention_mfma_kernel<false, false, true><<<grid, 256, 0, s>>>((const bf16_t *)qkv, (const bf16_t *)vt, (bf16_t *)out, T, n_heads, vt_keys(T), WinArgs{});
   PVF_LAUNCH_CHECK(ctx, "attention_mfma");
   return PVF_OK;
 }
@@ -417,8 +457,7 @@ pvf_status launch_attention_mfma(pvf_ctx *ctx, hipStream_t s, const void *qkv, c
 pvf_status launch_rope_vt(pvf_ctx *ctx, hipStream_t s, void *qkv, void *vt, int S, int T,
                           int n_heads, const float2 *cos_sin) {
   if (S == 0) return PVF_OK;
-  const dim3 grid(T / 64, n_heads, S);
-  rope_vt_kernel<<<grid, 256, 0, s>>>((bf16_t *)qkv, (bf16_t *)vt, T, n_heads, cos_sin);
+  rope_vt_kernel<false><<<dim3(vt_keys(T) / 64, n_heads, S), 256, 0, s>>>((bf16_t *)qkv, (bf16_t *)vt, T, n_heads, vt_keys(T), cos_sin, WinArgs{});
   PVF_LAUNCH_CHECK(ctx, "rope_vt");
   return PVF_OK;
 }

@@ -80,6 +80,9 @@ __device__ __forceinline__ bool row_target(const RowFilter &rf, int64_t row, int
   return rf.prompt_len + rf.k_active[g] * rf.block_len + r < rf.T;
 }
 
+// Keys per row of a key-contiguous value buffer: T rounded up to a whole tile of the attention kernel.
+inline int vt_keys(int T) { return (T + 63) / 64 * 64; }
+
 pvf_status launch_stage1(pvf_ctx *ctx, hipStream_t s, const void *logits, int dtype,
                          int64_t n_rows, int vocab, int mask_id, float scale,
                          const RowFilter &rf, float *conf, int32_t *tok);
@@ -115,7 +118,7 @@ pvf_status launch_fill_row_pos(pvf_ctx *ctx, hipStream_t s, const pvf_decode_cfg
                                const int32_t *seq_slot, int n_seq, int32_t *row_pos);
 pvf_status launch_kv_store(pvf_ctx *ctx, hipStream_t s, int dtype, const void *qkv, const void *vt,
                            const int32_t *seq_slot, int slots_per_group, int S, int T, int d,
-                           void *kc, void *vc, void *vtc, int64_t group_stride);
+                           void *kc, void *vc, void *vtc, int64_t group_stride);   // vt, vtc: rows of vt_keys(T) keys
 pvf_status launch_embed_rows(pvf_ctx *ctx, hipStream_t s, int dtype, const void *embed, const int32_t *canvas,
                              const int32_t *seq_slot, const int32_t *row_pos, int n_rows, int R, int T,
                              int d, int vocab, void *out);

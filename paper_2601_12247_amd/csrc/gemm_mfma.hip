@@ -87,11 +87,13 @@ constexpr int waves_per_simd(int lds_bytes, int waves) { return (lds_bytes <= 80
 // Its epilogue rotates the q and k thirds (rotary embedding, pair (i, i + 64) of each head, angle
 // of canvas position row % T from the cos_sin table [T][64]) before storing them, and writes the
 // v third a second time key-contiguous, vt[canvas][head][d][t'] with bits 2 and 3 of t swapped in t'
-// (each 16 keys stored as {0-3, 8-11 | 4-7, 12-15}), the layout the attention kernel reads its values in.
+// (each 16 keys stored as {0-3, 8-11 | 4-7, 12-15}), the layout the attention kernel reads its values in; a row of
+// vt has Tv = vt_keys(T) entries.  Canvases of whole 16-key groups are written in 16-byte chunks, others key by key (the
+// 64 keys of a column are then one or two runs of 2-byte stores).
 struct RopeArgs {
   const float2 *cos_sin;
   bf16_t *vt;
-  int32_t T, H;
+  int32_t T, Tv, H;
   int32_t store_v;                                   // 0: the v third of C is not written (only vt)
 };
 
@@ -477,26 +479,45 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
         // cover all chunks of 64 / chunks neighbouring columns
         const int key0 = m_base - vp * 32;
         if ((vp == kVPasses - 1 || mt == MT - 1) && key0 < M) {
-          const int chunks = 4 * (vp + 1);                           // 16-byte chunks per column: 4 or 8
-          const int seq = key0 / ra.T, t0 = key0 % ra.T;
-          const int vcol0 = out_col0 - 2 * d_model;                  // column inside the v third
-          const int g = lane % chunks, blk = g >> 1;
-          const unsigned char *src = my + (16 * blk + 4 * (g & 1)) * kStride;
+          const int vcol0 = out_col0 - 2 * d_model;                  // column inside the v third; 64 columns of one head
+          bf16_t *vt_head = ra.vt + (int64_t)(vcol0 & 127) * ra.Tv;
+          if (ra.T % 16 == 0) {
+            const int chunks = 4 * (vp + 1);                         // 16-byte chunks per column: 4 or 8
+            const int g = lane % chunks, blk = g >> 1;
+            int seq = key0 / ra.T, t0 = key0 % ra.T + 16 * blk;
+            if (ra.T % 64 != 0) { seq = (key0 + 16 * blk) / ra.T; t0 = (key0 + 16 * blk) % ra.T; }   // a group of 64 keys may straddle canvases
+            const unsigned char *src = my + (16 * blk + 4 * (g & 1)) * kStride;
+            bf16_t *dst = vt_head + ((int64_t)seq * ra.H + (vcol0 >> 7)) * 128 * ra.Tv + t0 + (g & 1) * 8;
+            if (key0 + 16 * blk < M)
 #pragma unroll
-          for (int it = 0; it < chunks; ++it) {
-            const int c = it * (64 / chunks) + lane / chunks;
-            const unsigned char *sc = src + ((c ^ (blk << 3)) * 2);
-            uint32_t w[4];
+            for (int it = 0; it < chunks; ++it) {
+              const int c = it * (64 / chunks) + lane / chunks;
+              const unsigned char *sc = src + ((c ^ (blk << 3)) * 2);
+              uint32_t w[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {                            // key pairs (0,1) (2,3) (8,9) (10,11) of the chunk's half
-              const int kr = (e & 1) * 2 + (e >> 1) * 8;
-              const uint32_t lo = *reinterpret_cast<const uint16_t *>(sc + kr * kStride);
-              const uint32_t hi = *reinterpret_cast<const uint16_t *>(sc + (kr + 1) * kStride);
-              w[e] = lo | (hi << 16);
+              for (int e = 0; e < 4; ++e) {                          // key pairs (0,1) (2,3) (8,9) (10,11) of the chunk's half
+                const int kr = (e & 1) * 2 + (e >> 1) * 8;
+                const uint32_t lo = *reinterpret_cast<const uint16_t *>(sc + kr * kStride);
+                const uint32_t hi = *reinterpret_cast<const uint16_t *>(sc + (kr + 1) * kStride);
+                w[e] = lo | (hi << 16);
+              }
+              *reinterpret_cast<uint4 *>(dst + (int64_t)c * ra.Tv) = make_uint4(w[0], w[1], w[2], w[3]);
             }
-            const int head = (vcol0 + c) >> 7, dcol = (vcol0 + c) & 127;
-            *reinterpret_cast<uint4 *>(ra.vt + (((int64_t)seq * ra.H + head) * 128 + dcol) * ra.T + t0 + g * 8) =
-                make_uint4(w[0], w[1], w[2], w[3]);
+          } else {
+            const int keys = 32 * (vp + 1);                          // lane = key; 4 columns per LDS read
+            const int key = lane % keys, m = key0 + key;
+            if (m < M) {
+              const int seq = m / ra.T, t = m % ra.T;
+              const unsigned char *src = my + key * kStride;
+              bf16_t *dst = vt_head + ((int64_t)seq * ra.H + (vcol0 >> 7)) * 128 * ra.Tv + ((t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1));
+#pragma unroll 4
+              for (int c = 4 * (lane / keys); c < 64; c += 4 * (64 / keys)) {
+                const uint2 x = *reinterpret_cast<const uint2 *>(src + ((c ^ ((key >> 4) << 3)) * 2));
+                const uint32_t w[4] = {x.x & 0xffffu, x.x >> 16, x.y & 0xffffu, x.y >> 16};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dst[(int64_t)(c + e) * ra.Tv] = __builtin_bit_cast(bf16_t, (uint16_t)w[e]);
+              }
+            }
           }
         }
       }
@@ -622,7 +643,7 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
 // x tile area / relative efficiency of the shape (measured on the forward's GEMM shapes: the
 // smaller tiles re-read operands more often but quantise better when there are few tiles).
 // PVF_GEMM_TILE=<n> in the environment forces shape n (for tuning runs).
-int pick_config(GemmEpilogue epi, int M, int N, int K) {
+int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   static const int forced = [] { const char *e = getenv("PVF_GEMM_TILE"); return (e && e[0]) ? atoi(e) : -1; }();
   const bool plain = epi != kEpiSwiglu && epi != kEpiQkvRope;
   // Few rows: the launch streams the weight matrix once and is bound by HBM, not by the MFMAs.
@@ -645,6 +666,7 @@ int pick_config(GemmEpilogue epi, int M, int N, int K) {
     const double t = (double)((tiles + 255) / 256) * kCfg[c].bm * kCfg[c].bn / kCfg[c].eff;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
+  if (cost) *cost = best_t;
   return best;
 }
 
@@ -775,11 +797,23 @@ pvf_status launch_gemm_mfma_splitk(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi
 
 
 // QKV projection with the rotary embedding and the key-contiguous copy of v fused into the
-// epilogue (see RopeArgs).  qkv [M, 3*H*128], vt [M/T, H, 128, T], cos_sin [T, 64].
+// epilogue (see RopeArgs).  qkv [M, 3*H*128], vt [M/T, H, 128, vt_keys(T)], cos_sin [T, 64].
 bool gemm_mfma_qkv_rope_supported(int dtype, int M, int N, int K, int T, int H) {
   if (!gemm_mfma_supported(dtype, kEpiStore, M, N, K)) return false;
-  if (N != 3 * H * 128 || H % 2 != 0 || T % 32 != 0 || M % T != 0) return false;
+  if (N != 3 * H * 128 || H % 2 != 0 || M % T != 0) return false;
   return pick_config(kEpiQkvRope, M, N, K) >= 0;
+}
+
+// Whether the fused epilogue is the quicker way where both are open.  It excludes the tile shapes with 32-column or 80-row
+// waves, which often fill the chip better: the QKV projection of 3 x 437 rows takes 177 us in two rounds of 192 x 256 tiles, and
+// 129 us in three of 192 x 128 plus 12 us for the rotary pass.  The pass moves 4 bytes per element of C at ~3.5 TB/s; a
+// unit of the tile estimate is 2 K flop on one CU (~5.9 TFLOP/s).
+bool gemm_mfma_qkv_rope_pays(int M, int N, int K) {
+  if (M <= 384) return true;
+  double fused = 0, plain = 0;
+  if (pick_config(kEpiQkvRope, M, N, K, &fused) < 0) return false;
+  if (pick_config(kEpiStore, M, N, K, &plain) < 0) return true;
+  return fused <= plain + 2.5 * M * (double)N / K;
 }
 
 pvf_status launch_gemm_mfma_qkv_rope(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *qkv,
@@ -790,7 +824,7 @@ pvf_status launch_gemm_mfma_qkv_rope(pvf_ctx *ctx, hipStream_t s, const void *A,
   const int cfg = pick_config(kEpiQkvRope, M, N, K);
   PVF_REQUIRE(ctx, cfg >= 0, PVF_ESHAPE, "gemm_mfma: no tile shape with a rotary epilogue for N=%d", N);
   RopeArgs ra;
-  ra.cos_sin = cos_sin; ra.vt = (bf16_t *)vt; ra.T = T; ra.H = H; ra.store_v = store_v;
+  ra.cos_sin = cos_sin; ra.vt = (bf16_t *)vt; ra.T = T; ra.Tv = vt_keys(T); ra.H = H; ra.store_v = store_v;
   PVF_REQUIRE(ctx, !na || !na->ss_in || gemm_mfma_norm_capable(cfg), PVF_ESHAPE, "gemm_mfma: tile shape %d cannot fold the norm", cfg);
   return run_cfg<kEpiQkvRope>(ctx, s, cfg, A, W, qkv, nullptr, M, N, K, ra, na ? *na : NormArgs{});
 }

@@ -202,7 +202,7 @@ pvf_status launch_kv_store(pvf_ctx *ctx, hipStream_t s, int dtype, const void *q
     if (vtc) {
       PVF_LAUNCH_CHECK(ctx, "kv_store");
       vt_store_kernel<bf16_t><<<dim3(64, S), 256, 0, s>>>((const bf16_t *)vt, seq_slot, slots_per_group,
-                                                          (int64_t)T * d, (bf16_t *)vtc, group_stride);
+                                                          (int64_t)vt_keys(T) * d, (bf16_t *)vtc, group_stride);
     }
   } else {
     kv_store_kernel<float><<<grid, 256, 0, s>>>((const float *)qkv, seq_slot, slots_per_group, T, d,

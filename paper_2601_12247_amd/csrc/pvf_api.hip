@@ -33,7 +33,7 @@ struct pvf_ctx {
   int32_t *status_host = nullptr;      // pinned, 5*G words per round: done, n_drafts, n_commit[3] of each group
   int32_t *status_dev = nullptr;       // the same words, packed on the device by one small kernel
   int status_cap = 0;
-  // block-level K/V cache (decode_cfg.kv_cache): [G][n_layers][T][d] each, row-major like the
+  // block-level K/V cache (decode_cfg.kv_cache): [G][n_layers][vt_keys(T)][d] each, row-major like the
   // k / v thirds of the qkv buffer; cache_block[g] = active block the cache of group g is for
   void *kcache = nullptr, *vcache = nullptr;
   int cache_G = 0, cache_T = 0;
@@ -104,15 +104,14 @@ bool gemm_mfma_splitk_supported(int dtype, GemmEpilogue epi, int M, int N, int K
 pvf_status launch_gemm_mfma_splitk(pvf_ctx *, hipStream_t, GemmEpilogue, const void *, const void *, void *, const void *,
                                    int, int, int, float *, size_t);
 bool gemm_mfma_qkv_rope_supported(int dtype, int M, int N, int K, int T, int H);
+bool gemm_mfma_qkv_rope_pays(int M, int N, int K);
 pvf_status launch_gemm_mfma_qkv_rope(pvf_ctx *, hipStream_t, const void *, const void *, void *, void *, const float2 *,
                                      int, int, int, int, int, bool store_v, const NormArgs *na = nullptr);
-bool attention_mfma_supported(int dtype, int T, int d_head);
+bool attention_mfma_supported(int dtype, int d_head);
 pvf_status launch_attention_mfma(pvf_ctx *, hipStream_t, const void *, const void *, void *, int, int, int);
 pvf_status launch_rope_vt(pvf_ctx *, hipStream_t, void *, void *, int, int, int, const float2 *);
-bool attention_window_mfma_supported(int dtype, int T, int d_head, int R, int block_len, int prompt_len);
-pvf_status launch_rope_vt_rows(pvf_ctx *, hipStream_t, void *, void *, const int32_t *, int, int, int, int, const float2 *);
-pvf_status launch_attention_window_mfma(pvf_ctx *, hipStream_t, const void *, const void *, const void *, const void *,
-                                        int64_t, const int32_t *, const int32_t *, int, int, int, int, int, int, int, void *);
+pvf_status launch_window_attention_mfma(pvf_ctx *, hipStream_t, void *, void *, const void *, const void *, int64_t, const int32_t *,
+                                        const int32_t *, const pvf_decode_cfg &, int, int, const float2 *, void *);
 
 pvf_status launch_gemm_mfma_splitk_partial(pvf_ctx *, hipStream_t, const void *, const void *, int, int, int, float *, size_t, int *);
 
@@ -145,17 +144,17 @@ static pvf_status launch_attention_plain(pvf_ctx *ctx, hipStream_t s, int dtype,
   return launch_attention_simple(ctx, s, dtype, qkv, out, S, T, n_heads, d_head);
 }
 
-static bool use_attention_mfma(int dtype, int T, int d_head) {
-  return !force_simple() && attention_mfma_supported(dtype, T, d_head);
+static bool use_attention_mfma(int dtype, int d_head) {
+  return !force_simple() && attention_mfma_supported(dtype, d_head);
 }
 
-// Rotary embedding of q, k (in place) followed by attention.  vt: scratch of S*T*d elements,
-// needed only by the MFMA path (key-contiguous copy of v).
+// Rotary embedding of q, k (in place) followed by attention.  vt: scratch of S*vt_keys(T)*d elements for the key-contiguous
+// copy of v of the MFMA path; NULL: the plain kernel.
 static pvf_status launch_rope_attention(pvf_ctx *ctx, hipStream_t s, int dtype, void *qkv, void *vt,
                                         void *out, int S, int T, int n_heads, int d_head,
                                         const float2 *cos_sin) {
   pvf_status st;
-  if (use_attention_mfma(dtype, T, d_head)) {
+  if (vt && use_attention_mfma(dtype, d_head)) {
     if ((st = launch_rope_vt(ctx, s, qkv, vt, S, T, n_heads, cos_sin)) != PVF_OK) return st;
     return launch_attention_mfma(ctx, s, qkv, vt, out, S, T, n_heads);
   }
@@ -257,7 +256,8 @@ extern "C" pvf_status pvf_create(pvf_ctx **out, const pvf_model_cfg *m, const pv
   struct { void **p; int64_t bytes; } req[] = {
       {&c->h, M * d * (int64_t)c->esize},       {&c->xn, M * d * (int64_t)c->esize},
       {&c->qkv, M * 3 * d * (int64_t)c->esize}, {&c->att, M * d * (int64_t)c->esize},
-      {&c->vt, M * d * (int64_t)c->esize},
+      // key-contiguous values: whole canvases, or window rows from the 16-key boundary below the window (one tile more)
+      {&c->vt, attention_mfma_supported(m->dtype, 2 * half) ? (int64_t)max_seqs * (vt_keys(max_T) + 64) * d * 2 : 0},
       {&c->act, M * ff * (int64_t)c->esize},    {&c->hrows, rows * d * (int64_t)c->esize},
       {&c->logits, rows * (int64_t)m->vocab * (int64_t)c->esize},
       {(void **)&c->seq_slot, (int64_t)max_seqs * 4}, {(void **)&c->row_pos, rows * 4},
@@ -364,12 +364,16 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
     RUN(launch_gemm(c, s, dt, epi, A, W, C, res, Mm, Nn, Kk));                                    \
   } while (0)
   const bool f32_rope = dt == PVF_F32 && gemm_f32_qkv_rope_supported(dh);
-  const bool fused_rope = use_attention_mfma(dt, T, dh) && gemm_mfma_qkv_rope_supported(dt, M, 3 * d, d, T, H);
+  const bool whole_tiles = T % 64 == 0;
+  const bool fused_rope = use_attention_mfma(dt, dh) && gemm_mfma_qkv_rope_supported(dt, M, 3 * d, d, T, H) &&
+                          (whole_tiles || gemm_mfma_qkv_rope_pays(M, 3 * d, d));
   // Above the split-K range the two norms of a layer are folded into the projections around them: O and down
   // write each row's sum of squares beside h, QKV and gate/up read h itself (gains folded into their weights)
   // and scale their accumulators by 1 / rms.  The xn buffer and the 2 x n_layers norm launches disappear.
+  // Only for whole key tiles: rounding w * gain leaves the logits of the 8B shape 1 % further from a float32 forward
+  // (2.20e-2 against 2.18e-2), and canvases of other lengths never had it; there the norms cost 12 us of ~650 a layer.
   const int slots_o = gemm_mfma_norm_slots(kEpiResidual, M, d, d), slots_down = gemm_mfma_norm_slots(kEpiResidual, M, d, ff);
-  const bool fold_norm = !force_simple() && fold_norm_enabled() && fused_rope && c->row_ss && M > 640 && slots_o > 0 && slots_down > 0 &&
+  const bool fold_norm = !force_simple() && fold_norm_enabled() && fused_rope && whole_tiles && c->row_ss && M > 640 && slots_o > 0 && slots_down > 0 &&
                          slots_o <= d / 128 && slots_down <= d / 128 &&
                          gemm_mfma_norm_slots(kEpiQkvRope, M, 3 * d, d) > 0 && gemm_mfma_norm_slots(kEpiSwiglu, M, ff, d) > 0;
   // Up to 640 rows O and down split K: one kernel then adds their partial tiles and the residual and norms the
@@ -399,15 +403,14 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
       {
         ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)(3 * d) * d,
                      (double)c->esize * ((double)M * d + 3.0 * d * d + (double)M * 2 * d + (double)M * d));
-        RUN(launch_gemm_mfma_qkv_rope(c, s, c->h, c->wqkv_f[l], c->qkv, c->vt, c->cos_sin, M, 3 * d, d, T, H,
-                                      capture_spg > 0 && !c->cache_vt, &n_in));
+        RUN(launch_gemm_mfma_qkv_rope(c, s, c->h, c->wqkv_f[l], c->qkv, c->vt, c->cos_sin, M, 3 * d, d, T, H, false, &n_in));
       }
       {
         ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)T * T * d, 0.0);
         RUN(launch_attention_mfma(c, s, c->qkv, c->vt, c->att, S, T, H));
       }
       if (capture_spg > 0) {
-        const int64_t layer_off = (int64_t)l * T * d * c->esize, gstride = (int64_t)m.n_layers * T * d;
+        const int64_t layer_off = (int64_t)l * vt_keys(T) * d * c->esize, gstride = (int64_t)m.n_layers * vt_keys(T) * d;
         void *vl = (char *)c->vcache + layer_off;
         RUN(launch_kv_store(c, s, dt, c->qkv, c->vt, seq_slot, capture_spg, S, T, d, (char *)c->kcache + layer_off,
                             c->cache_vt ? nullptr : vl, c->cache_vt ? vl : nullptr, gstride));
@@ -431,13 +434,11 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
     if (!xn_ready) RUN(launch_rmsnorm(c, s, dt, c->h, c->attn_norm[l], c->xn, M, d, m.rms_eps));
     xn_ready = false;
     if (fused_rope) {
-      // the QKV projection rotates q, k and writes the key-contiguous v in its epilogue; the row-major v third
-      // has a reader only when the K/V cache keeps its values in that layout
-      const bool store_v = capture_spg > 0 && !c->cache_vt;
+      // the QKV projection rotates q, k and writes the key-contiguous v in its epilogue; the row-major v third has no reader
       {
         ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)(3 * d) * d,
-                     (double)c->esize * ((double)M * d + 3.0 * d * d + (double)M * (store_v ? 3 : 2) * d + (double)M * d));   // q, k (, v) + the key-contiguous v
-        RUN(launch_gemm_mfma_qkv_rope(c, s, c->xn, c->wqkv[l], c->qkv, c->vt, c->cos_sin, M, 3 * d, d, T, H, store_v));
+                     (double)c->esize * ((double)M * d + 3.0 * d * d + (double)M * 2 * d + (double)M * d));   // q, k + the key-contiguous v
+        RUN(launch_gemm_mfma_qkv_rope(c, s, c->xn, c->wqkv[l], c->qkv, c->vt, c->cos_sin, M, 3 * d, d, T, H, false));
       }
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)T * T * d, 0.0);
       RUN(launch_attention_mfma(c, s, c->qkv, c->vt, c->att, S, T, H));
@@ -455,7 +456,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
       RUN(launch_rope_attention(c, s, dt, c->qkv, c->vt, c->att, S, T, H, dh, c->cos_sin));
     }
     if (capture_spg > 0) {
-      const int64_t layer_off = (int64_t)l * T * d * c->esize, gstride = (int64_t)m.n_layers * T * d;
+      const int64_t layer_off = (int64_t)l * vt_keys(T) * d * c->esize, gstride = (int64_t)m.n_layers * vt_keys(T) * d;
       void *vl = (char *)c->vcache + layer_off;
       RUN(launch_kv_store(c, s, dt, c->qkv, c->vt, seq_slot, capture_spg, S, T, d, (char *)c->kcache + layer_off,
                           c->cache_vt ? nullptr : vl, c->cache_vt ? vl : nullptr, gstride));
@@ -493,7 +494,7 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
     RUN(launch_gemm(c, s, dt, epi, A, W, C, res, Mm, Nn, Kk));                                    \
   } while (0)
   RUN(launch_embed_rows(c, s, dt, c->w.embed, state.canvas, seq_slot, row_pos, M, R, T, d, m.vocab, c->h));
-  const int64_t gstride = (int64_t)m.n_layers * T * d;
+  const int64_t gstride = (int64_t)m.n_layers * vt_keys(T) * d;
   // h += A W^T, then out = RMSNorm(h) * gain for the next projection.  Where the projection splits K (few rows)
   // one kernel adds the partial tiles and the residual and norms the row; otherwise the residual epilogue and the
   // norm run as two launches.
@@ -511,7 +512,7 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
   const bool f32_rope = dt == PVF_F32 && gemm_f32_qkv_rope_supported(dh);
   RUN(launch_rmsnorm(c, s, dt, c->h, c->attn_norm[0], c->xn, M, d, m.rms_eps));
   for (int l = 0; l < m.n_layers; ++l) {
-    const int64_t layer_off = (int64_t)l * T * d * c->esize;
+    const int64_t layer_off = (int64_t)l * vt_keys(T) * d * c->esize;
     if (f32_rope) {
       ProfScope ps(c, s, PVF_PROF_GEMM, 6.0 * M * (double)d * d, (double)c->esize * (4.0 * M * d + 3.0 * d * d));
       RUN(launch_gemm_f32_qkv_rope(c, s, (const float *)c->xn, (const float *)c->wqkv[l], (float *)c->qkv, M, d, d,
@@ -522,10 +523,8 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
     {
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)R * T * d, 0.0);
       if (c->cache_vt) {
-        RUN(launch_rope_vt_rows(c, s, c->qkv, c->vt, row_pos, S, R, T, H, c->cos_sin));
-        RUN(launch_attention_window_mfma(c, s, c->qkv, c->vt, (const char *)c->kcache + layer_off,
-                                         (const char *)c->vcache + layer_off, gstride, seq_slot, state.k_active,
-                                         1 + cfg.K, cfg.prompt_len, cfg.block_len, R, S, T, H, c->att));
+        RUN(launch_window_attention_mfma(c, s, c->qkv, c->vt, (const char *)c->kcache + layer_off, (const char *)c->vcache + layer_off,
+                                         gstride, seq_slot, state.k_active, cfg, S, H, c->cos_sin, c->att));
       } else {
         if (!f32_rope) RUN(launch_rope_rows(c, s, dt, c->qkv, row_pos, M, T, H, dh, c->cos_sin));
         if (attention_f32_supported(dt, T, dh))
@@ -688,17 +687,12 @@ static pvf_status round_cached_impl(pvf_ctx *ctx, hipStream_t s, int G, const ui
   const pvf_model_cfg &m = ctx->model;
   const int T = cfg.prompt_len + cfg.gen_len, R = window_rows(cfg), spg = 1 + cfg.K;
   // cache memory
-  const bool want_vt = use_attention_mfma(m.dtype, T, m.d_model / m.n_heads) &&
-                       attention_window_mfma_supported(m.dtype, T, m.d_model / m.n_heads, R, cfg.block_len, cfg.prompt_len);
-  if (want_vt != ctx->cache_vt) {                          // the value layout changes: every cache is stale
-    ctx->cache_vt = want_vt;
-    ctx->cache_block.assign(ctx->cache_block.size(), -1);
-  }
+  ctx->cache_vt = use_attention_mfma(m.dtype, m.d_model / m.n_heads);
   if (ctx->cache_G < G || ctx->cache_T != T) {
     if (ctx->kcache) (void)hipFree(ctx->kcache);
     if (ctx->vcache) (void)hipFree(ctx->vcache);
     ctx->kcache = ctx->vcache = nullptr; ctx->cache_G = 0;
-    const size_t bytes = (size_t)G * m.n_layers * T * m.d_model * ctx->esize;
+    const size_t bytes = (size_t)G * m.n_layers * vt_keys(T) * m.d_model * ctx->esize;
     PVF_REQUIRE(ctx, hipMalloc(&ctx->kcache, bytes) == hipSuccess && hipMalloc(&ctx->vcache, bytes) == hipSuccess,
                 PVF_ENOMEM, "K/V cache: cannot allocate 2 x %zu bytes", bytes);
     ctx->cache_G = G; ctx->cache_T = T;
@@ -944,8 +938,8 @@ extern "C" pvf_status pvf_rope_attention(void *stream, int32_t dtype, void *qkv,
   hipError_t e = hipMemcpy(dev, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice);
   pvf_status st = PVF_OK;
   if (e != hipSuccess) { set_error(nullptr, "rotary table upload: %s", hipGetErrorString(e)); st = PVF_EHIP; }
-  if (st == PVF_OK && use_attention_mfma(dtype, T, d_head)) {
-    e = hipMalloc(&vt, (size_t)S * T * n_heads * d_head * 2);
+  if (st == PVF_OK && use_attention_mfma(dtype, d_head)) {
+    e = hipMalloc(&vt, (size_t)S * vt_keys(T) * n_heads * d_head * 2);
     if (e != hipSuccess) { set_error(nullptr, "scratch allocation: %s", hipGetErrorString(e)); st = PVF_EHIP; }
   }
   if (st == PVF_OK) st = launch_rope_attention(nullptr, s, dtype, qkv, vt, out, S, T, n_heads, d_head, dev);
@@ -1004,8 +998,10 @@ extern "C" pvf_status pvf_rope_attention_noalloc(void *stream, int32_t dtype, vo
   PVF_REQUIRE(nullptr, T <= kNoAllocMaxT && half <= kNoAllocMaxHalf, PVF_ESHAPE,
               "pvf_rope_attention_noalloc: T=%d d_head=%d exceed the static scratch (T <= %d, d_head <= %d)", T, d_head,
               kNoAllocMaxT, 2 * kNoAllocMaxHalf);
-  const bool mfma = use_attention_mfma(dtype, T, d_head);
-  const size_t vt_bytes = mfma ? (size_t)S * T * n_heads * d_head * 2 : 0;
+  // canvases that are no whole number of key tiles and do not fit take the plain kernel, which needs no copy of v
+  const size_t vt_need = (size_t)S * vt_keys(T) * n_heads * d_head * 2;
+  const bool mfma = use_attention_mfma(dtype, d_head) && (T % 64 == 0 || vt_need <= kNoAllocVtBytes);
+  const size_t vt_bytes = mfma ? vt_need : 0;
   PVF_REQUIRE(nullptr, vt_bytes <= kNoAllocVtBytes, PVF_ESHAPE,
               "pvf_rope_attention_noalloc: S*T*n_heads*d_head = %lld elements exceed the static scratch (%lld)",
               (long long)S * T * n_heads * d_head, (long long)(kNoAllocVtBytes / 2));
@@ -1015,7 +1011,7 @@ extern "C" pvf_status pvf_rope_attention_noalloc(void *stream, int32_t dtype, vo
   if (st != PVF_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   float2 *tab = reinterpret_cast<float2 *>(base);
-  void *vt = base + kNoAllocTabBytes;
+  void *vt = mfma ? base + kNoAllocTabBytes : nullptr;
   InvFreq f;
   for (int i = 0; i < half; ++i) f.v[i] = std::pow((double)rope_theta, -2.0 * i / d_head);
   for (int i = half; i < kNoAllocMaxHalf; ++i) f.v[i] = 0.0;
@@ -1046,16 +1042,17 @@ extern "C" pvf_status pvf_qkv_attention(void *stream, int32_t dtype, const void 
   hipError_t e = hipMemcpy(dev, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice);
   pvf_status st = PVF_OK;
   if (e != hipSuccess) { set_error(nullptr, "rotary table upload: %s", hipGetErrorString(e)); st = PVF_EHIP; }
-  const bool mfma_att = use_attention_mfma(dtype, T, d_head);
+  // the fused epilogue, and the caller's vt, are for whole key tiles (see the header)
+  const bool mfma_att = use_attention_mfma(dtype, d_head), whole_tiles = T % 64 == 0;
   if (st == PVF_OK && mfma_att) {
-    if (vt_caller) vt = vt_caller;
+    if (vt_caller && whole_tiles) vt = vt_caller;
     else {
-      e = hipMalloc(&vt, (size_t)M * d * 2);
+      e = hipMalloc(&vt, (size_t)S * vt_keys(T) * d * 2);
       if (e != hipSuccess) { set_error(nullptr, "scratch allocation: %s", hipGetErrorString(e)); st = PVF_EHIP; }
     }
   }
   if (st == PVF_OK) {
-    if (mfma_att && gemm_mfma_qkv_rope_supported(dtype, M, 3 * d, d, T, n_heads)) {
+    if (mfma_att && whole_tiles && gemm_mfma_qkv_rope_supported(dtype, M, 3 * d, d, T, n_heads)) {
       st = launch_gemm_mfma_qkv_rope(nullptr, s, x, wqkv, qkv, vt, dev, M, 3 * d, d, T, n_heads, true);
       if (st == PVF_OK) st = launch_attention_mfma(nullptr, s, qkv, vt, out, S, T, n_heads);
     } else {

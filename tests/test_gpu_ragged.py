@@ -1,0 +1,87 @@
+"""bf16 canvases whose length is no multiple of a key tile, and decode windows that begin or end anywhere, on the matrix
+cores (d_head = 128): the attention kernel alone against float64, whole forwards and K/V-cached rounds against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import pvf_oracle as O
+from paper_2601_12247_amd import binding as B
+from synth import inputs as S
+from tests.gpu_util import make_context, oracle_model_cfg, to_device
+
+pytestmark = pytest.mark.gpu
+
+SHAPE = S.ModelShape(n_layers=2, d_model=256, n_heads=2, d_ff=512, vocab=2048, mask_id=2047, rope_theta=5e5, logit_scale=6.0)
+
+
+def dev(a, dtype=torch.int32):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda", dtype)
+
+
+@pytest.fixture(scope="module")
+def model():
+    w = S.make_weights(SHAPE, seed=3, round_to_bf16=True)
+    return w, to_device(w, torch.bfloat16)
+
+
+@pytest.mark.parametrize("T", [1, 15, 63, 65, 96, 127, 437])
+def test_attention_of_any_length(T):
+    """q, k come back rotated, so the float64 reference starts from what the kernel read.  An output is one bf16 rounding
+    away (8 significant bits: at most 2^-8 of the value), plus the probabilities' 2^-16 and the float32 exponentials' and
+    sums' 2^-18 of the largest value."""
+    S_, H, dh = 2, 2, 128
+    d = H * dh
+    g = torch.Generator(device="cuda").manual_seed(T)
+    qkv = (torch.randn(S_ * T, 3 * d, device="cuda", generator=g) * 1.5).to(torch.bfloat16)
+    out = B.rope_attention(qkv, S_, T, H, dh, 5e5).double().cpu()
+    q, k, v = qkv.double().cpu().view(S_, T, 3, H, dh).permute(2, 0, 3, 1, 4)
+    want = (torch.softmax(q @ k.transpose(-1, -2) / dh ** 0.5, -1) @ v).permute(0, 2, 1, 3).reshape(S_ * T, d)
+    tol = 2.0 ** -8 * want.abs() + 2.0 ** -15 * v.abs().max()
+    assert ((out - want).abs() <= tol).all(), float(((out - want).abs() / tol).max())
+
+
+@pytest.mark.parametrize("S_,T", [(3, 100), (2, 81), (3, 208), (5, 150), (1, 40), (1, 1)])
+def test_forward_of_ragged_canvases(model, S_, T):
+    """Also: what an earlier, longer call left in the workspace must not show."""
+    w, wd = model
+    R = min(T, 37)
+    toks = np.stack([S.make_prompt(s, T, SHAPE.vocab, SHAPE.mask_id) for s in range(S_)])
+    toks[:, T // 2:] = SHAPE.mask_id
+    rows = np.tile(np.arange(T - R, T, dtype=np.int32), (S_, 1))
+    ctx = make_context(SHAPE, wd, max_seqs=S_, max_T=T + 90, max_rows=64)
+    long = dev(np.stack([S.make_prompt(50 + s, T + 90, SHAPE.vocab, SHAPE.mask_id) for s in range(S_)]))
+    first = ctx.forward(dev(toks), dev(rows))
+    ctx.forward(long, dev(rows))
+    got = ctx.forward(dev(toks), dev(rows))
+    assert torch.equal(first, got)
+    for s in range(S_):
+        want = O.forward(toks[s], w, oracle_model_cfg(SHAPE), rows=rows[s])
+        assert np.abs(got[s].float().cpu().numpy() - want).max() <= 5e-2
+
+
+@pytest.mark.parametrize("bl,pl,gl", [(16, 37, 64), (32, 203, 128), (64, 77, 192), (24, 65, 72), (10, 3, 50)])
+def test_cached_round_with_a_window_anywhere(model, bl, pl, gl):
+    """On the canvas that filled the cache a cached round is exact, so both rounds have the oracle's confidences; every
+    block in turn is the active one, the last with its window cut by the end of the canvas."""
+    w, wd = model
+    G, mc = 2, oracle_model_cfg(SHAPE)
+    cfg = B.DecodeCfg(block_len=bl, prompt_len=pl, gen_len=gl, K=0, tau_high=0.9, logit_scale=SHAPE.logit_scale, kv_cache=1)
+    ctx = make_context(SHAPE, wd, max_seqs=G, max_T=cfg.T, max_rows=cfg.R)
+    bitmap = torch.zeros((SHAPE.vocab + 31) // 32, dtype=torch.int32, device="cuda")
+    for k in range(gl // bl):
+        canvas = np.stack([S.make_prompt(9 * g + k, cfg.T, SHAPE.vocab, SHAPE.mask_id) for g in range(G)])
+        canvas[:, pl + k * bl:] = SHAPE.mask_id
+        confs = []
+        for _ in range(2):                                   # fills the cache, then uses it
+            st = confs[0][0] if confs else B.State(G, cfg)
+            st.canvas.copy_(dev(canvas)[:, None]); st.k_active.fill_(k); st.done.zero_(); st.n_drafts.zero_(); st.n_ws_blocks.fill_(1)
+            ctx.round(st, bitmap, 0)
+            torch.cuda.synchronize()
+            confs.append((st, st.conf[:, 0].cpu().numpy().copy(), st.tok[:, 0].cpu().numpy().copy()))
+        n = min(cfg.R, cfg.T - (pl + k * bl))
+        for g in range(G):
+            logits = O.forward(canvas[g], w, mc, rows=np.arange(pl + k * bl, pl + k * bl + n))
+            conf, tok = O.stage1(logits.astype(np.float32), SHAPE.logit_scale, SHAPE.mask_id)
+            for i, (_, c, t) in enumerate(confs):
+                diff = np.abs(c[g][:n] - conf)
+                assert diff.max() <= 2e-2 and diff.mean() <= 4e-3, (k, i, float(diff.max()), float(diff.mean()))
