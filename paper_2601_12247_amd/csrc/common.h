@@ -170,7 +170,7 @@ struct RopeF32 {
 // C[M,N] = A[M,K] W[N,K]^T; kEpiResidual adds residual[M,N]; kEpiSwiglu: W is [2N,K] (gate|up),
 // C[M,N] = silu(gate) * up.
 pvf_status launch_gemm(pvf_ctx *ctx, hipStream_t s, int dtype, GemmEpilogue epi, const void *A,
-                       const void *W, void *C, const void *residual, int M, int N, int K);
+                       const void *W, void *C, const void *residual, int M, int N, int K, bool split_ok = true);
 // Pieces of the split-K path for launches of few rows.
 // out[M, N] = epilogue(sum over splits of partial[z][M][Nw]) in split order (store, + residual, SwiGLU of gate | up halves)
 pvf_status launch_splitk_finalize(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const float *partial, int splits,

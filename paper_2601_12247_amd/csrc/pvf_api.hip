@@ -126,10 +126,10 @@ static bool force_simple() {
 }
 
 pvf_status launch_gemm(pvf_ctx *ctx, hipStream_t s, int dtype, GemmEpilogue epi, const void *A,
-                       const void *W, void *C, const void *residual, int M, int N, int K) {
+                       const void *W, void *C, const void *residual, int M, int N, int K, bool split_ok) {
   if (dtype == PVF_F32)
     return launch_gemm_f32(ctx, s, epi, (const float *)A, (const float *)W, (float *)C, (const float *)residual, M, N, K);
-  if (!force_simple() && ctx && ctx->splitk_ws && gemm_mfma_splitk_supported(dtype, epi, M, N, K, ctx->splitk_floats))
+  if (split_ok && !force_simple() && ctx && ctx->splitk_ws && gemm_mfma_splitk_supported(dtype, epi, M, N, K, ctx->splitk_floats))
     return launch_gemm_mfma_splitk(ctx, s, epi, A, W, C, residual, M, N, K, ctx->splitk_ws, ctx->splitk_floats);
   if (!force_simple() && gemm_mfma_supported(dtype, epi, M, N, K))
     return launch_gemm_mfma(ctx, s, epi, A, W, C, residual, M, N, K);
@@ -345,6 +345,34 @@ extern "C" int64_t pvf_workspace_bytes(const pvf_ctx *ctx) { return ctx ? ctx->w
 // =========================================================================================
 // forward
 // =========================================================================================
+// One projection of a forward, timed; split_ok: launches of few rows may divide K over workgroups (their rounding order then
+// depends on the number of rows).
+static pvf_status project(pvf_ctx *c, hipStream_t s, GemmEpilogue epi, const void *A, const void *W, void *C, const void *res,
+                          int M, int N, int K, bool split_ok = true) {
+  const double mats = epi == kEpiSwiglu ? 2 : 1;
+  ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)N * K * mats,
+               (double)c->esize * ((double)M * K + (double)N * K * mats + (double)M * N * (epi == kEpiResidual ? 2 : 1)));
+  return launch_gemm(c, s, c->model.dtype, epi, A, W, C, res, M, N, K, split_ok);
+}
+
+// h += A W^T, then (gain given) out = RMSNorm(h) * gain for the next projection.  Where the projection splits K (few rows) one
+// kernel adds the partial tiles and the residual and norms the row; otherwise the residual epilogue and the norm run as two.
+static pvf_status project_residual_norm(pvf_ctx *c, hipStream_t s, const void *A, const void *W, int M, int K, void *h,
+                                        const void *gain, void *out, bool split_ok = true) {
+  const int d = c->model.d_model, dt = c->model.dtype;
+  if (gain && split_ok && !force_simple() && c->splitk_ws && reduce_residual_rmsnorm_supported(dt, d) &&
+      gemm_mfma_splitk_supported(dt, kEpiResidual, M, d, K, c->splitk_floats)) {
+    int splits = 0;
+    ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)d * K, (double)c->esize * ((double)M * K + (double)d * K + 2.0 * M * d));
+    pvf_status st = launch_gemm_mfma_splitk_partial(c, s, A, W, M, d, K, c->splitk_ws, c->splitk_floats, &splits);
+    if (st != PVF_OK) return st;
+    return launch_reduce_residual_rmsnorm(c, s, c->splitk_ws, splits, M, d, h, gain, out, c->model.rms_eps);
+  }
+  pvf_status st = project(c, s, kEpiResidual, A, W, h, h, M, d, K, split_ok);
+  if (st != PVF_OK || !gain) return st;
+  return launch_rmsnorm(c, s, dt, h, gain, out, M, d, c->model.rms_eps);
+}
+
 // tokens: [*, T] rows addressed through seq_slot (NULL = identity).  Writes logits [S, R, V].
 // capture_spg > 0: the rotated keys and the values of every backbone canvas of the batch (slot
 // index divisible by capture_spg) are stored into the context's K/V cache after each layer.
@@ -356,13 +384,6 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
   const int M = S * T;
   pvf_status st;
 #define RUN(x) do { st = (x); if (st != PVF_OK) return st; } while (0)
-#define RUN_GEMM(epi, A, W, C, res, Mm, Nn, Kk)                                                   \
-  do {                                                                                            \
-    ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * (Mm) * (double)(Nn) * (Kk) * ((epi) == kEpiSwiglu ? 2 : 1),   \
-                 (double)c->esize * ((double)(Mm) * (Kk) + (double)(Nn) * (Kk) * ((epi) == kEpiSwiglu ? 2 : 1) + \
-                                     (double)(Mm) * (Nn) * ((epi) == kEpiResidual ? 2 : 1)));             \
-    RUN(launch_gemm(c, s, dt, epi, A, W, C, res, Mm, Nn, Kk));                                    \
-  } while (0)
   const bool f32_rope = dt == PVF_F32 && gemm_f32_qkv_rope_supported(dh);
   const bool whole_tiles = T % 64 == 0;
   const bool fused_rope = use_attention_mfma(dt, dh) && gemm_mfma_qkv_rope_supported(dt, M, 3 * d, d, T, H) &&
@@ -376,29 +397,17 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
   const bool fold_norm = !force_simple() && fold_norm_enabled() && fused_rope && whole_tiles && c->row_ss && M > 640 && slots_o > 0 && slots_down > 0 &&
                          slots_o <= d / 128 && slots_down <= d / 128 &&
                          gemm_mfma_norm_slots(kEpiQkvRope, M, 3 * d, d) > 0 && gemm_mfma_norm_slots(kEpiSwiglu, M, ff, d) > 0;
-  // Up to 640 rows O and down split K: one kernel then adds their partial tiles and the residual and norms the
-  // row for the next projection (instead of a reduce kernel followed by a norm kernel).
-  const bool split_norm_o_down = !fold_norm && !force_simple() && c->splitk_ws && reduce_residual_rmsnorm_supported(dt, d) &&
-                                 gemm_mfma_splitk_supported(dt, kEpiResidual, M, d, d, c->splitk_floats) &&
-                                 gemm_mfma_splitk_supported(dt, kEpiResidual, M, d, ff, c->splitk_floats);
-  // h += A W^T; with_norm: xn = RMSNorm(h) * gain as well
-  auto project_residual_norm = [&](const void *A, const void *W, int Kk, const void *gain, void *out, bool with_norm) -> pvf_status {
-    if (split_norm_o_down && with_norm) {
-      int splits = 0;
-      ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)d * Kk, (double)c->esize * ((double)M * Kk + (double)d * Kk + 2.0 * M * d));
-      RUN(launch_gemm_mfma_splitk_partial(c, s, A, W, M, d, Kk, c->splitk_ws, c->splitk_floats, &splits));
-      return launch_reduce_residual_rmsnorm(c, s, c->splitk_ws, splits, M, d, c->h, gain, out, m.rms_eps);
-    }
-    RUN_GEMM(kEpiResidual, A, W, c->h, c->h, M, d, Kk);
-    if (with_norm) return launch_rmsnorm(c, s, dt, c->h, gain, out, M, d, m.rms_eps);
-    return PVF_OK;
-  };
+  // Logits are wanted for R rows of each canvas, so behind the attention of the last layer only those rows go on (compact,
+  // [S * R]): 3 of 4 of that layer's projections shrink to R / T of their rows.  Above 640 rows a canvas's logits do not
+  // depend on what rides along, so K stays undivided there; the norm of these rows is a launch of its own.
+  const bool few_last = R < T;
   bool xn_ready = false;
   NormArgs n_in, n_out;
   n_in.ss_in = c->row_ss; n_in.ld = M; n_in.inv_d = 1.0f / (float)d; n_in.eps = m.rms_eps; n_in.n_slots_in = 1;
   n_out.ss_out = c->row_ss; n_out.ld = M;
   RUN(launch_embed(c, s, dt, c->w.embed, tokens, seq_slot, S, T, d, m.vocab, c->h, fold_norm ? c->row_ss : nullptr));
   for (int l = 0; l < m.n_layers; ++l) {
+    const bool cut = few_last && l + 1 == m.n_layers;
     if (fold_norm) {
       {
         ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)(3 * d) * d,
@@ -415,6 +424,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
         RUN(launch_kv_store(c, s, dt, c->qkv, c->vt, seq_slot, capture_spg, S, T, d, (char *)c->kcache + layer_off,
                             c->cache_vt ? nullptr : vl, c->cache_vt ? vl : nullptr, gstride));
       }
+      if (cut) break;
       {
         ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)d * d, (double)c->esize * ((double)M * d + (double)d * d + 2.0 * M * d));
         RUN(launch_gemm_mfma(c, s, kEpiResidual, c->att, c->wo[l], c->h, c->h, M, d, d, &n_out));
@@ -451,7 +461,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)T * T * d, 0.0);
       RUN(launch_attention_plain(c, s, dt, c->qkv, c->att, S, T, H, dh));
     } else {
-      RUN_GEMM(kEpiStore, c->xn, c->wqkv[l], c->qkv, nullptr, M, 3 * d, d);
+      RUN(project(c, s, kEpiStore, c->xn, c->wqkv[l], c->qkv, nullptr, M, 3 * d, d));
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)T * T * d, 0.0);
       RUN(launch_rope_attention(c, s, dt, c->qkv, c->vt, c->att, S, T, H, dh, c->cos_sin));
     }
@@ -461,17 +471,28 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
       RUN(launch_kv_store(c, s, dt, c->qkv, c->vt, seq_slot, capture_spg, S, T, d, (char *)c->kcache + layer_off,
                           c->cache_vt ? nullptr : vl, c->cache_vt ? vl : nullptr, gstride));
     }
-    RUN(project_residual_norm(c->att, c->wo[l], d, c->ffn_norm[l], c->xn, true));
-    RUN_GEMM(kEpiSwiglu, c->xn, c->w_gate_up[l], c->act, nullptr, M, ff, d);
+    if (cut) break;
+    RUN(project_residual_norm(c, s, c->att, c->wo[l], M, d, c->h, c->ffn_norm[l], c->xn));
+    RUN(project(c, s, kEpiSwiglu, c->xn, c->w_gate_up[l], c->act, nullptr, M, ff, d));
     // the norm that follows the down projection is the next layer's (the final one runs on the gathered rows only)
     const bool has_next = l + 1 < m.n_layers;
-    RUN(project_residual_norm(c->act, c->w_down[l], ff, has_next ? c->attn_norm[l + 1] : nullptr, c->xn, has_next));
+    RUN(project_residual_norm(c, s, c->act, c->w_down[l], M, ff, c->h, has_next ? c->attn_norm[l + 1] : nullptr, c->xn));
     xn_ready = has_next;
   }
+  const int Mr = S * R;
   RUN(launch_gather_rows(c, s, dt, c->h, row_pos, S, T, R, d, c->hrows));
-  RUN(launch_rmsnorm(c, s, dt, c->hrows, c->w.final_norm, c->hrows, S * R, d, m.rms_eps));
-  RUN_GEMM(kEpiStore, c->hrows, c->w.out_head, logits, nullptr, S * R, m.vocab, d);
-#undef RUN_GEMM
+  if (!few_last) {
+    RUN(launch_rmsnorm(c, s, dt, c->hrows, c->w.final_norm, c->hrows, Mr, d, m.rms_eps));
+    RUN(project(c, s, kEpiStore, c->hrows, c->w.out_head, logits, nullptr, Mr, m.vocab, d));
+    return PVF_OK;
+  }
+  const int l = m.n_layers - 1;
+  const bool split_ok = M <= 640;
+  RUN(launch_gather_rows(c, s, dt, c->att, row_pos, S, T, R, d, c->xn));
+  RUN(project_residual_norm(c, s, c->xn, c->wo[l], Mr, d, c->hrows, c->ffn_norm[l], c->att, split_ok));
+  RUN(project(c, s, kEpiSwiglu, c->att, c->w_gate_up[l], c->act, nullptr, Mr, ff, d, split_ok));
+  RUN(project_residual_norm(c, s, c->act, c->w_down[l], Mr, ff, c->hrows, c->w.final_norm, c->xn, split_ok));
+  RUN(project(c, s, kEpiStore, c->xn, c->w.out_head, logits, nullptr, Mr, m.vocab, d));
 #undef RUN
   return PVF_OK;
 }
@@ -486,29 +507,8 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
   const int M = S * R;
   pvf_status st;
 #define RUN(x) do { st = (x); if (st != PVF_OK) return st; } while (0)
-#define RUN_GEMM(epi, A, W, C, res, Mm, Nn, Kk)                                                   \
-  do {                                                                                            \
-    ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * (Mm) * (double)(Nn) * (Kk) * ((epi) == kEpiSwiglu ? 2 : 1),   \
-                 (double)c->esize * ((double)(Mm) * (Kk) + (double)(Nn) * (Kk) * ((epi) == kEpiSwiglu ? 2 : 1) + \
-                                     (double)(Mm) * (Nn) * ((epi) == kEpiResidual ? 2 : 1)));             \
-    RUN(launch_gemm(c, s, dt, epi, A, W, C, res, Mm, Nn, Kk));                                    \
-  } while (0)
   RUN(launch_embed_rows(c, s, dt, c->w.embed, state.canvas, seq_slot, row_pos, M, R, T, d, m.vocab, c->h));
   const int64_t gstride = (int64_t)m.n_layers * vt_keys(T) * d;
-  // h += A W^T, then out = RMSNorm(h) * gain for the next projection.  Where the projection splits K (few rows)
-  // one kernel adds the partial tiles and the residual and norms the row; otherwise the residual epilogue and the
-  // norm run as two launches.
-  const bool fuse_norm = !force_simple() && c->splitk_ws && reduce_residual_rmsnorm_supported(dt, d);
-  auto project_residual_norm = [&](const void *A, const void *W, int Kk, const void *gain, void *out) -> pvf_status {
-    if (fuse_norm && gemm_mfma_splitk_supported(dt, kEpiResidual, M, d, Kk, c->splitk_floats)) {
-      int splits = 0;
-      ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)d * Kk, (double)c->esize * ((double)M * Kk + (double)d * Kk + 2.0 * M * d));
-      RUN(launch_gemm_mfma_splitk_partial(c, s, A, W, M, d, Kk, c->splitk_ws, c->splitk_floats, &splits));
-      return launch_reduce_residual_rmsnorm(c, s, c->splitk_ws, splits, M, d, c->h, gain, out, m.rms_eps);
-    }
-    RUN_GEMM(kEpiResidual, A, W, c->h, c->h, M, d, Kk);
-    return launch_rmsnorm(c, s, dt, c->h, gain, out, M, d, m.rms_eps);
-  };
   const bool f32_rope = dt == PVF_F32 && gemm_f32_qkv_rope_supported(dh);
   RUN(launch_rmsnorm(c, s, dt, c->h, c->attn_norm[0], c->xn, M, d, m.rms_eps));
   for (int l = 0; l < m.n_layers; ++l) {
@@ -518,7 +518,7 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
       RUN(launch_gemm_f32_qkv_rope(c, s, (const float *)c->xn, (const float *)c->wqkv[l], (float *)c->qkv, M, d, d,
                                    RopeF32{c->cos_sin, row_pos, T, dh / 2}));
     } else {
-      RUN_GEMM(kEpiStore, c->xn, c->wqkv[l], c->qkv, nullptr, M, 3 * d, d);
+      RUN(project(c, s, kEpiStore, c->xn, c->wqkv[l], c->qkv, nullptr, M, 3 * d, d));
     }
     {
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)R * T * d, 0.0);
@@ -535,13 +535,12 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
                                     gstride, cfg, state, seq_slot, S, H, dh, c->att));
       }
     }
-    RUN(project_residual_norm(c->att, c->wo[l], d, c->ffn_norm[l], c->xn));
-    RUN_GEMM(kEpiSwiglu, c->xn, c->w_gate_up[l], c->act, nullptr, M, ff, d);
+    RUN(project_residual_norm(c, s, c->att, c->wo[l], M, d, c->h, c->ffn_norm[l], c->xn));
+    RUN(project(c, s, kEpiSwiglu, c->xn, c->w_gate_up[l], c->act, nullptr, M, ff, d));
     const bool last = l + 1 == m.n_layers;
-    RUN(project_residual_norm(c->act, c->w_down[l], ff, last ? c->w.final_norm : c->attn_norm[l + 1], last ? c->hrows : c->xn));
+    RUN(project_residual_norm(c, s, c->act, c->w_down[l], M, ff, c->h, last ? c->w.final_norm : c->attn_norm[l + 1], last ? c->hrows : c->xn));
   }
-  RUN_GEMM(kEpiStore, c->hrows, c->w.out_head, logits, nullptr, M, m.vocab, d);
-#undef RUN_GEMM
+  RUN(project(c, s, kEpiStore, c->hrows, c->w.out_head, logits, nullptr, M, m.vocab, d));
 #undef RUN
   return PVF_OK;
 }
