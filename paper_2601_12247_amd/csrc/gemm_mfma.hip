@@ -80,6 +80,14 @@ __device__ __forceinline__ int w_row(int r, int tile_n, int ff) {
   return (t & 1) ? ff + col : col;
 }
 
+// Quadrant schedule: LDS row r of an operand tile holds tile row half_row(r): first the lower halves of all wave tiles, then
+// the upper ones, so that a half is a run of whole load instructions.
+template <int BT, int WT> __device__ __forceinline__ int half_row(int r) {
+  constexpr int kHalfTile = BT / 2, kHalfWave = BT / WT / 2;
+  const int h = r / kHalfTile, rr = r % kHalfTile;
+  return (rr / kHalfWave) * (2 * kHalfWave) + h * kHalfWave + rr % kHalfWave;
+}
+
 // workgroups per CU (by LDS) x waves per workgroup / 4 SIMDs
 constexpr int waves_per_simd(int lds_bytes, int waves) { return (lds_bytes <= 80 * 1024 ? 2 : 1) * waves / 4; }
 
@@ -125,11 +133,13 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   constexpr int LA = (BM + RPI - 1) / RPI, LW = BN / RPI;        // direct loads per thread per stage
   constexpr int KS = BK / 32;                        // MFMA k-steps per stage
   constexpr int kRowBytes = BK * 2;
-  // With a ring of only two stages the refill of a slot is issued as soon as the slot is free (right
+  // With a ring of only two stages (and wave tiles that the quadrant schedule cannot take) the refill of a slot is issued as soon as the slot is free (right
   // after the barrier in the last k-step of the stage that was read from it), all of it in that one
   // k-step: the loads of stage kt + 2 then have a whole stage to land.  Deeper rings spread the refill
   // of the slot freed one stage ago over the first k-steps of a stage.
   constexpr bool kLate = kStages == 2;
+  // Rings of two stages whose wave tiles split into four equal quadrants run the quadrant schedule (quad_stage below).
+  constexpr bool kQuad = kLate && MT16 % 2 == 0 && NT16 == 4;
   constexpr int kAhead = kLate ? kStages : kStages - 1;     // stages in flight after the prologue
   static_assert(BM % (RPI / 2) == 0 && (!kHalfA || LA >= 2) && BN % RPI == 0 && BK == 64 && BM % (16 * WM) == 0 && BN % (32 * WN) == 0, "tile shape");
   static_assert((EPI != kEpiQkvRope && EPI != kEpiSwiglu) || BM % (32 * WM) == 0, "the rotary and SwiGLU epilogues take whole 32-row passes");
@@ -157,29 +167,51 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   const int ld_chunk = (tid % CPR) ^ (CPR == 8 ? (ld_row >> 1) & 7 : (ld_row >> 2) & 3);
   // Per-lane byte offsets (32 bit) from the operand base; the k advance goes into the uniform
   // base pointer, so a load needs no per-lane address arithmetic.
-  uint32_t a_off[LA], w_off[LW];
+  uint32_t a_off[LA], w_off[kQuad ? 1 : LW];
+  uint32_t w_step[LW];                               // quadrant schedule (short of registers): uniform part of the W offsets
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
-    const int am = min(m0 + i * RPI + ld_row, M - 1);         // ragged last tile: re-read a valid row
+    const int ar = kQuad ? half_row<BM, WM>(i * RPI + ld_row) : i * RPI + ld_row;
+    const int am = min(m0 + ar, M - 1);                       // ragged last tile: re-read a valid row
     a_off[i] = ((uint32_t)am * (uint32_t)K + ld_chunk * 8) * 2u;
   }
 #pragma unroll
-  for (int i = 0; i < LW; ++i)
-    w_off[i] = ((uint32_t)w_row<EPI, BN, WN>(i * RPI + ld_row, tile_n, N_out) * (uint32_t)K + ld_chunk * 8) * 2u;
-  const char *Ab = reinterpret_cast<const char *>(A), *Wb = reinterpret_cast<const char *>(W);
-  if (EPI == kEpiPartial) {                                  // this split's range of k
-    Ab += (size_t)blockIdx.y * sk.nk_per * (BK * 2);
-    Wb += (size_t)blockIdx.y * sk.nk_per * (BK * 2);
+  for (int i = 0; i < LW; ++i) {
+    if (kQuad) {                                     // the W row of a lane is that of lane 0 plus a distance that is the same for all i
+      const int first = w_row<EPI, BN, WN>(half_row<BN, WN>(i * RPI), tile_n, N_out);
+      w_step[i] = (uint32_t)first * (uint32_t)K * 2u;
+      if (i == 0) w_off[0] = ((uint32_t)(w_row<EPI, BN, WN>(half_row<BN, WN>(ld_row), tile_n, N_out) - first) * (uint32_t)K + ld_chunk * 8) * 2u;
+    } else {
+      w_off[i] = ((uint32_t)w_row<EPI, BN, WN>(i * RPI + ld_row, tile_n, N_out) * (uint32_t)K + ld_chunk * 8) * 2u;
+    }
   }
+  const char *Ab = reinterpret_cast<const char *>(A), *Wb = reinterpret_cast<const char *>(W);
+  const uint32_t k_shift = EPI == kEpiPartial ? blockIdx.y * sk.nk_per * (BK * 2) : 0;     // this split's range of k
+  Ab += k_shift;
+  Wb += k_shift;
   constexpr int kLoadsPerStage = LA + LW;
+  // The quadrant schedule loads through buffer descriptors: base + 32-bit lane offset + scalar offset, where the compiler
+  // turns the global form into a 64-bit address per load and lane (16 registers that are not there).
+  const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;
+#ifdef __HIP_DEVICE_COMPILE__                                // the descriptor type does not exist in the host pass
+  const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc((void *)Ab, 0, (int)((uint32_t)M * (uint32_t)K * 2u - k_shift), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc((void *)Wb, 0, (int)((uint32_t)w_rows * (uint32_t)K * 2u - k_shift), 0x00020000);
+#endif
   auto issue_one = [&](int kt, int i) {                      // load i (A loads first, then W) of stage kt
     unsigned char *dst = lds + (kt % kStages) * kStage + wave * 1024;
+    if constexpr (kQuad) {
+#ifdef __HIP_DEVICE_COMPILE__
+      if (i < LA) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lptr_t *)(dst + i * kInstrBytes), 16, a_off[i], kt * (BK * 2), 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, w_off[0], w_step[i - LA] + kt * (BK * 2), 0, 0);
+#endif
+      return;
+    }
     const size_t koff = (size_t)kt * (BK * 2);
     if (i < LA) {
       const int ia = (kHalfA && i == LA - 1 && wave >= WM * WN / 2) ? i - 1 : i;      // uniform
       __builtin_amdgcn_global_load_lds((gptr_t *)(Ab + koff + a_off[ia]), (lptr_t *)(dst + ia * kInstrBytes), 16, 0, 0);
     } else
-      __builtin_amdgcn_global_load_lds((gptr_t *)(Wb + koff + w_off[i - LA]), (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr_t *)(Wb + koff + w_off[kQuad ? 0 : i - LA]), (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, 0, 0);
   };
 
   // ---- LDS -> MFMA operands: lane reads row (base + lane%16), chunk (4*kk + lane/16) ----
@@ -200,11 +232,23 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
       for (int e = 0; e < 4; ++e) acc[nt][mt][e] = 0.f;
 
   const int nk = EPI == kEpiPartial ? sk.nk_per : K / BK;
+  // Quadrant schedule: a stage's loads in the order in which their LDS rows are freed.  Group 1: the loads that lie in the
+  // lower halves; group 2: a load across the halves of A (192 rows) first, then the upper halves, W's before A's.
+  constexpr int kLoA = (BM / 2) / RPI, kStraddle = (BM / 2) % RPI != 0, kLoW = LW / 2;
+  constexpr int kG1 = kLoA + kLoW, kG2 = kLoadsPerStage - kG1;
+  static_assert(!kQuad || (BN / 2) % RPI == 0, "halves of the W tile are whole loads");
+  auto quad_load = [](int q) {                               // q-th load of a stage in that order
+    if (q < kLoA) return q;
+    if (q < kG1) return LA + q - kLoA;
+    if (q < kG1 + kStraddle) return kLoA;
+    if (q < kG1 + kStraddle + LW - kLoW) return LA + kLoW + q - kG1 - kStraddle;
+    return q - LW;                                           // upper rows of A
+  };
 #pragma unroll
   for (int s = 0; s < kAhead; ++s)
     if (s < nk) {
 #pragma unroll
-      for (int i = 0; i < kLoadsPerStage; ++i) issue_one(s, i);
+      for (int i = 0; i < kLoadsPerStage; ++i) issue_one(s, kQuad ? quad_load(i) : i);
     }
 
   // Folded RMSNorm on the operand side: thread t < BM adds up the sums of squares of operand row m0 + t now,
@@ -224,6 +268,81 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
     my_rnorm = rsqrtf(t * na.inv_d + na.eps);
   }
 
+  if constexpr (kQuad) {
+    // A wave tile is computed in quadrants, each over the whole 64 k of a stage: (lower A, lower W), (lower, upper),
+    // (upper, upper), (upper, lower).  An operand half is read from LDS one quadrant before it is first used, which frees its
+    // rows early: one barrier per half stage hands half of a slot to the refill, so the loads of a stage are issued evenly
+    // over a whole stage (all in the second half of one, they fill the CU's load path and the waves stand behind it) and
+    // have 1-1.5 stages to land instead of 0.5-1.  Every element still adds its k in the same order.
+    // Bound by the power budget and the load path (64 bytes a clock and CU).  Against the k-step schedule below, whole
+    // forwards: 9 x 1280 rows 132.5 -> 125.5 ms, 5 x 512 29.3 -> 28.5, 80 x 1024 891 -> 870, 1 x 512 9.24 -> 8.88.
+    constexpr int MH = MT16 / 2, NH = NT16 / 2, kPer = MH * NH * KS;
+    constexpr int kBarrierAt = 4;                            // MFMAs of a half stage issued before its barrier
+    constexpr int kSlots = 2 * kPer - kBarrierAt;            // MFMAs of a half stage behind it
+    bf16x8 a0[MH][KS], a1[MH][KS], b[2][NH][KS];             // b[kt % 2]: the lower W half of stage kt
+    const int a_off0 = wm * (BM / WM / 2) * kRowBytes, w_off0 = kATile + wn * (BN / WN / 2) * kRowBytes;
+    auto rd_a = [&](const unsigned char *st, int half, int j) {          // j-th fragment in the order of use
+      return *reinterpret_cast<const bf16x8 *>(st + a_off0 + half * (BM / 2) * kRowBytes + (j % MH) * 16 * kRowBytes + frag_off[j / MH]);
+    };
+    auto rd_w = [&](const unsigned char *st, int half, int j) {
+      return *reinterpret_cast<const bf16x8 *>(st + w_off0 + half * (BN / 2) * kRowBytes + (j % NH) * 16 * kRowBytes + frag_off[j / NH]);
+    };
+    if (nk > 1) wait_vmcnt<kG2 - kStraddle + kLoadsPerStage>(); else wait_vmcnt<kG2 - kStraddle>();
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int j = 0; j < NH * KS; ++j) b[0][j % NH][j / NH] = rd_w(lds, 0, j);
+#pragma unroll
+    for (int j = 0; j < MH * KS; ++j) a0[j % MH][j / MH] = rd_a(lds, 0, j);
+    auto quad_stage = [&](int kt, auto kind, auto parity) {   // kind: 0 = a stage that prefetches, 1 = the last but one, 2 = the last
+      constexpr int P = decltype(parity)::value;
+      constexpr bool kSteady = decltype(kind)::value == 0, more = decltype(kind)::value < 2;
+      const unsigned char *stage = lds + P * kStage, *next = lds + (P ^ 1) * kStage;
+#pragma unroll
+      for (int ph = 0; ph < 4; ++ph) {
+        const int mh = ph >> 1, nh = ph == 1 || ph == 2;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+          const int kk = i / (MH * NH), mt = i % (MH * NH) / NH, nt = i % NH;
+          if (i == kBarrierAt && (ph == 0 || (ph == 2 && more))) {
+            // ph 0: all of stage kt has landed; ph 2: the lower halves of stage kt + 1 have (my parts of them)
+            if (ph == 0) { if (more) wait_vmcnt<kLoadsPerStage>(); else wait_vmcnt<0>(); }
+            else { if (kSteady) wait_vmcnt<kG2 - kStraddle + kG1>(); else wait_vmcnt<kG2 - kStraddle>(); }
+            __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): my reads of the rows that are refilled now are done
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          floatx4 &c = acc[nh * NH + nt][mh * MH + mt];
+          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[nh ^ P][nt][kk], mh ? a1[mt][kk] : a0[mt][kk], c, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < (ph == 0 || ph == 3 ? NH : MH) * KS; ++j) {
+            constexpr int nA = MH * KS, nW = NH * KS;
+            if (ph == 0 && i == kBarrierAt + j * (kPer - kBarrierAt - 2) / nW) b[P ^ 1][j % NH][j / NH] = rd_w(stage, 1, j);
+            if (ph == 1 && i == j * (kPer - 2) / nA) a1[j % MH][j / MH] = rd_a(stage, 1, j);
+            if (ph == 2 && more && i == kBarrierAt + j * (kPer - kBarrierAt) / nA) a0[j % MH][j / MH] = rd_a(next, 0, j);
+            if (ph == 3 && more && i == j * (kPer - 4) / nW) b[P ^ 1][j % NH][j / NH] = rd_w(next, 0, j);
+          }
+          if (kSteady) {
+            const int at = (ph & 1) * kPer + i - kBarrierAt;                  // MFMAs since the half's barrier
+            constexpr int n1 = kG1, n2 = kG2;
+#pragma unroll
+            for (int q = 0; q < (ph < 2 ? n1 : n2); ++q)
+              if (at == 1 + q * kSlots / (ph < 2 ? n1 : n2)) issue_one(kt + 2, quad_load(ph < 2 ? q : n1 + q));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    constexpr std::integral_constant<int, 0> k0{};
+    constexpr std::integral_constant<int, 1> k1{};
+    constexpr std::integral_constant<int, 2> k2{};
+    for (int kt = 0; kt + 2 < nk; kt += 2) {
+      quad_stage(kt, k0, k0);
+      quad_stage(kt + 1, k0, k1);
+    }
+    quad_stage(nk - 2, k1, k0);                              // nk is even (pick_config)
+    quad_stage(nk - 1, k2, k1);
+  } else {
   // Waits until at most n whole stages of this wave's direct loads are still in flight.
   auto wait_stages = [&](int n) {
     if (kStages >= 4 && n >= 2) wait_vmcnt<2 * kLoadsPerStage>();
@@ -317,6 +436,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   int kt = 0;
   for (; kt < n_loading; ++kt) run_stage(kt, std::true_type{});
   for (; kt < nk; ++kt) run_stage(kt, std::false_type{});
+  }
 
   // ---- epilogue ----
   // A lane holds, for sub-tile (nt, mt), the 4 consecutive columns nt*16 + 4*(lane/16) + {0..3}
@@ -602,7 +722,7 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   return PVF_OK;
 }
 
-struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only; };
+struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only, quad; };   // quad: runs the quadrant schedule, which takes stages in pairs
 constexpr int kNumCfg = 10;
 // Every shape for many rows runs 8 waves, two per SIMD (the two small ones 4 waves, two workgroups per CU):
 // with one wave per SIMD the 256 x 256 tile (wave tiles of 128 x 128, a third fewer LDS reads) measured 2-4 %
@@ -610,15 +730,15 @@ constexpr int kNumCfg = 10;
 // plain_only: wave tiles 32 columns wide, which the SwiGLU and rotary epilogues cannot pair up, or 80 rows high
 // (a last epilogue pass of 16 rows, which only the plain epilogues handle).
 constexpr TileCfg kCfg[kNumCfg] = {
-    {256, 256, 64, 2, 1.00, false},   // the wide layers
-    {128, 256, 64, 3, 0.89, false}, {256, 128, 64, 3, 0.885, false},
-    {128, 128, 64, 5, 0.70, false},   // launches of a single round of tiles: the smallest area finishes first
-    {192, 256, 64, 2, 0.93, false},   // fills the chip when M / 256 leaves many CUs idle
-    {320, 128, 64, 2, 0.78, true},    // 2560 rows = 8 tile rows: with N = 4096 exactly one tile per CU (wave tiles 80 x 64)
-    {64, 64, 64, 5, 0.0, true},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights,
-    {64, 128, 64, 3, 0.0, false},     // so many small workgroups with deep rings; chosen by pick_config for M <= 384
-    {192, 128, 64, 3, 0.86, true},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU
-    {160, 256, 64, 3, 0.85, true}};   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
+    {256, 256, 64, 2, 1.00, false, true},   // the wide layers
+    {128, 256, 64, 3, 0.89, false, false}, {256, 128, 64, 3, 0.885, false, false},
+    {128, 128, 64, 5, 0.70, false, false},   // launches of a single round of tiles: the smallest area finishes first
+    {192, 256, 64, 2, 0.93, false, true},   // fills the chip when M / 256 leaves many CUs idle
+    {320, 128, 64, 2, 0.78, true, false},    // 2560 rows = 8 tile rows: with N = 4096 exactly one tile per CU (wave tiles 80 x 64)
+    {64, 64, 64, 5, 0.0, true, false},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights,
+    {64, 128, 64, 3, 0.0, false, false},     // so many small workgroups with deep rings; chosen by pick_config for M <= 384
+    {192, 128, 64, 3, 0.86, true, false},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU
+    {160, 256, 64, 3, 0.85, true, false}};   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
 
 template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
@@ -659,7 +779,7 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   double best_t = 0;
   for (int c = 0; c < kNumCfg; ++c) {
     const int ncols = (epi == kEpiSwiglu) ? kCfg[c].bn / 2 : kCfg[c].bn;
-    if (N % ncols != 0 || K % kCfg[c].bk != 0 || (kCfg[c].plain_only && !plain)) continue;
+    if (N % ncols != 0 || K % kCfg[c].bk != 0 || (kCfg[c].quad && K % 128 != 0) || (kCfg[c].plain_only && !plain)) continue;
     if (forced == c) return c;
     if (kCfg[c].eff <= 0.0) continue;
     const int64_t tiles = (int64_t)((M + kCfg[c].bm - 1) / kCfg[c].bm) * (N / ncols);
