@@ -3,10 +3,10 @@
 //
 // entropy   H = -sum_w p_w ln p_w of softmax(logit_scale * logits) per row, the [MASK] column
 //           excluded.  With t_w = x_w - max x:  H = ln S - U / S,  S = sum e^t,  U = sum t e^t.
-//           One workgroup per row, two passes over the row (max, then the sums; the second
-//           pass comes from L2: a full-width bf16 row is 253 KB).  The sums run in float64:
-//           this kernel serves calibration runs, not the decoding loop, and is sized for
-//           accuracy.  x_w is rounded to float32 once (fl32(scale * logit)) like in stage 1.
+//           This kernel takes short rows (below 256 vectors of 16 bytes): one workgroup per row,
+//           two passes over it (max, then the sums), float64 exponentials and sums.  Longer rows
+//           get their entropy from stage 1's pass (epilogue.hip).
+//           x_w is rounded to float32 once (fl32(scale * logit)) like in stage 1.
 // select    the filtering rule: one thread per 32 vocabulary ids builds one bitmap word.
 #include "common.h"
 
@@ -87,11 +87,9 @@ __global__ void plan_vocab_select_kernel(const uint32_t *__restrict__ cal_n, con
 
 }  // namespace
 
-pvf_status launch_entropy(pvf_ctx *ctx, hipStream_t s, const void *logits, int dtype,
+pvf_status launch_entropy_short(pvf_ctx *ctx, hipStream_t s, const void *logits, int dtype,
                           int64_t n_rows, int vocab, int mask_id, float scale,
                           const RowFilter &rf, float *ent) {
-  if (n_rows == 0) return PVF_OK;
-  PVF_REQUIRE(ctx, n_rows > 0 && n_rows < (1ll << 31), PVF_EINVAL, "entropy: n_rows=%lld out of range", (long long)n_rows);
   const dim3 grid((unsigned)n_rows);
   if (dtype == PVF_BF16)
     entropy_kernel<bf16_t><<<grid, kEntBlock, 0, s>>>(static_cast<const bf16_t *>(logits), vocab, mask_id, scale, rf, ent);

@@ -85,13 +85,14 @@ inline int vt_keys(int T) { return (T + 63) / 64 * 64; }
 
 pvf_status launch_stage1(pvf_ctx *ctx, hipStream_t s, const void *logits, int dtype,
                          int64_t n_rows, int vocab, int mask_id, float scale,
-                         const RowFilter &rf, float *conf, int32_t *tok);
+                         const RowFilter &rf, float *conf, int32_t *tok, float *ent = nullptr);
 
 // rows of the decision window: min(c * block_len, gen_len), c = 2, or 4 with n_sparse > 0
 int window_rows(const pvf_decode_cfg &c);
 
-// entropy per logits row (calibration only); rows are filtered like stage 1
-pvf_status launch_entropy(pvf_ctx *ctx, hipStream_t s, const void *logits, int dtype,
+// entropy of short logits rows (calibration only); rows are filtered like stage 1.  launch_stage1 with ent != NULL takes rows
+// of any length (conf and tok may then be NULL).
+pvf_status launch_entropy_short(pvf_ctx *ctx, hipStream_t s, const void *logits, int dtype,
                           int64_t n_rows, int vocab, int mask_id, float scale,
                           const RowFilter &rf, float *ent);
 

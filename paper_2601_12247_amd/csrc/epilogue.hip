@@ -17,6 +17,22 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -INFINITY;
+constexpr float kLog2eLo = 1.9259629911266174e-08f;     // log2 e - kLog2e
+constexpr float kLn2 = 0.6931471805599453f;
+
+__device__ __forceinline__ float mul_rn(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
+// Sums of two float64 values over a wave
+__device__ __forceinline__ void wave_sum2(double &a, double &b) {
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, kWave);
+    b += __shfl_xor(b, o, kWave);
+  }
+}
 
 // 2^x by the hardware instruction (no denormal fix-up: results below 2^-126 flush to 0).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -52,46 +68,134 @@ __device__ __forceinline__ uint4 load_stream(const uint4 *p) {
   return make_uint4(t.x, t.y, t.z, t.w);
 }
 
-// Running (max, scaled sum) of one thread.  Values v live in the "compare domain": the raw
-// logit for bf16 rows (scaling by a positive factor keeps order and ties of bf16 values), or
-// logit_scale * logit for float rows.  Terms are 2^(v*c + nmc) with nmc = -fl(m*c); every
-// term of the thread is therefore off by the same factor 2^delta, delta = m*c - fl(m*c),
-// which is known exactly and divided out when the thread's sum is handed on.
-struct Running {
+// log2(e) (times the logit scale) as the sum of two floats, the second above zero: an infinite t below the max then gives
+// t * hi + t * lo = -inf and not a NaN.
+struct Log2e {
+  float hi, lo;
+  __device__ __forceinline__ explicit Log2e(float scale) {
+    hi = scale * kLog2e;
+    lo = fmaf(scale, kLog2e, -hi) + scale * kLog2eLo;
+    if (!(lo > 0.f)) {
+      hi = __uint_as_float(__float_as_uint(hi) - 1);
+      lo = fmaf(scale, kLog2e, -hi) + scale * kLog2eLo;
+    }
+  }
+  __device__ __forceinline__ float exp(float t) const { return fast_exp2(fmaf(t, lo, t * hi)); }
+};
+
+// Running (max, sum of exponentials) of one thread.  Values v live in the "compare domain": the raw
+// logit for bf16 rows (scaling by a positive factor keeps order and ties of bf16 values; differences of bf16 values are
+// exact), or logit_scale * logit for float rows.
+//   fine:  terms 2^((v - m) c) with c in two parts, and what adding a group to the sum rounds off kept beside it: conf is
+//          1e-10 (one-hot rows) to 2e-7 (many small terms beside a large one) from float64.
+//   plain: terms 2^(v*c + nmc) with nmc = -fl(m*c), three instructions fewer; every term of the thread is therefore off by
+//          the same factor 2^delta, delta = m*c - fl(m*c), which is known exactly and divided out when the thread's sum is
+//          handed on: 7e-8 to 3e-7 from float64.
+// Aligned rows of 4096 vectors and more keep the plain terms: the instructions of the fine ones show there (16 rows of 126464
+// bf16 10.4 -> 13.2 us, 1190 rows of 50264 23.3 -> 25.0).  All others take the fine ones and wait for memory all the same.
+template <bool kFine> struct Running;
+template <> struct Running<true> {
+  const Log2e c;
+  float m = kNegInf, z = 0.f, zc = 0.f;
+  int first = INT_MAX, cnt = 0;      // vectors first, first+BLOCK, .. (cnt of them) held the value that raised m; cnt = 0: element first
+  __device__ __forceinline__ explicit Running(float scale) : c(scale) {}
+  __device__ __forceinline__ void raise(float gm, int first_vec, int n_vec) {
+    if (m > kNegInf) { const float f = c.exp(m - gm); z *= f; zc *= f; }
+    m = gm; first = first_vec; cnt = n_vec;
+  }
+  __device__ __forceinline__ float term(float v) const { return c.exp(v - m); }
+  __device__ __forceinline__ void add(float a) {
+    const float s = z + a, b = s - z;
+    zc += (z - (s - b)) + (a - b);
+    z = s;
+  }
+  __device__ __forceinline__ float sum_for(float M) const { return (z + zc) * c.exp(m - M); }     // relative to M >= m
+};
+template <> struct Running<false> {
+  const float c;
   float m = kNegInf, z = 0.f, nmc = 0.f, delta = 0.f;
-  int first = 0, cnt = 0;      // vectors first, first+BLOCK, .. (cnt of them) held the value that raised m
-  __device__ __forceinline__ void raise(float gm, float c, int first_vec, int n_vec) {
+  int first = INT_MAX, cnt = 0;
+  __device__ __forceinline__ explicit Running(float scale) : c(scale * kLog2e) {}
+  __device__ __forceinline__ void raise(float gm, int first_vec, int n_vec) {
     const float nmc2 = -(gm * c);
     const float d2 = fmaf(gm, c, nmc2);
     z *= fast_exp2((m - gm) * c - delta + d2);   // m = -inf on first use: z stays 0
     m = gm; nmc = nmc2; delta = d2; first = first_vec; cnt = n_vec;
   }
-  __device__ __forceinline__ float true_sum() const { return z * fast_exp2(-delta); }
+  __device__ __forceinline__ float term(float v) const { return fast_exp2(fmaf(v, c, nmc)); }
+  __device__ __forceinline__ void add(float a) { z += a; }
+  __device__ __forceinline__ float sum_for(float M) const { return z * fast_exp2(-delta) * fast_exp2((m - M) * c); }
 };
 
-template <typename T, int BLOCK, int U>
+// Entropy sums of one thread (calibration), relative to its own running max m of the scaled logits x:
+// S = sum e^t, U = sum t e^t, t = fl32(x - m), both in float64.  e^t = 2^(t log2 e) by the hardware exponential; the
+// rounding error of the product is put back to first order, so a term is off by about an ulp of float32 besides what
+// rounding t costs, and not by |t| ulps.  A float64 exponential per element and a pass of its own took 5x as long
+// (2112 bf16 rows of 126464: 751 us behind stage 1's 83; this pass does both in 144).  Bound by the vector ALU, about 17
+// slots an element; its entropies are as far from float64 as the ones with float64 exponentials (2e-8 to 3e-8, the rounding of t).
+struct EntropySums {
+  double S = 0.0, U = 0.0;
+  float m = kNegInf;
+  __device__ __forceinline__ void raise(float x) {
+    if (m > kNegInf) {
+      const double d = (double)m - (double)x, f = exp(d);
+      U = (U + d * S) * f;
+      S *= f;
+    }
+    m = x;
+  }
+  template <bool kGuard> __device__ __forceinline__ void add(float x) {
+#pragma clang fp contract(off)
+    const float t = x - m;
+    if (kGuard && (x == kNegInf || t < -1000.f)) return;           // e^t = 0; a NaN goes through to the sums
+    const float y = t * kLog2e;
+    const float lo = fmaf(t, kLog2e, -y) * kLn2;                     // what rounding y took off, as a difference of t
+    const float e0 = fast_exp2(y);
+    const double e = (double)fmaf(e0, fmaf(t, kLog2eLo * kLn2, lo), e0);
+    S += e;
+    U = fma((double)t, e, U);
+  }
+};
+
+// kEnt: the row's entropy too, and conf from its sums (conf, tok may then be NULL).
+template <typename T, int BLOCK, int U, bool kEnt, bool kFine>
 __global__ void __launch_bounds__(BLOCK)
 stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float scale,
-                  RowFilter rf, float *__restrict__ conf, int32_t *__restrict__ tok) {
+                  RowFilter rf, float *__restrict__ conf, int32_t *__restrict__ tok, float *__restrict__ ent) {
   constexpr int N = Vec16<T>::N;
   constexpr bool kRaw = (sizeof(T) == 2);
   const int tid = threadIdx.x;
   int64_t out_row;
   if (!row_target(rf, blockIdx.x, &out_row)) {
-    if (tid == 0) { conf[out_row] = 0.f; tok[out_row] = -1; }
+    if (tid == 0) {
+      if (!kEnt || conf) { conf[out_row] = 0.f; tok[out_row] = -1; }
+      if (kEnt) ent[out_row] = 0.f;
+    }
     return;
   }
-  const uint4 *__restrict__ p =
-      reinterpret_cast<const uint4 *>(logits + (int64_t)blockIdx.x * vocab);
-  const int nvec = vocab / N;
-  const int mask_vec = mask_id / N, mask_lane = mask_id % N;
-  const float c = kRaw ? scale * kLog2e : kLog2e;
+  constexpr bool kAnywhere = kEnt || kFine;      // the plain terms are for aligned rows
+  // Rows of a vocabulary that is no multiple of N begin anywhere: up to N - 1 elements in front of the first whole vector and
+  // behind the last one are taken by single threads.
+  const T *__restrict__ row = logits + (int64_t)blockIdx.x * vocab;
+  const int head = !kAnywhere ? 0 : (int)((16u - ((uint32_t)reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) / (int)sizeof(T);
+  const uint4 *__restrict__ p = reinterpret_cast<const uint4 *>(row + head);
+  const int nvec = (vocab - head) / N;
+  const int mask_vec = mask_id >= head ? (mask_id - head) / N : INT_MAX, mask_lane = mask_id >= head ? (mask_id - head) % N : 0;
   constexpr int kStride = BLOCK * U;
 
   // Main loop: groups of U vectors per thread, no bounds checks; then a one-vector-at-a-time
   // tail.  A thread visits vector indices in increasing order, so the group in which its
   // running max was first raised to its final value holds the lowest id attaining it.
-  Running run;
+  Running<kFine> run(kRaw ? scale : 1.0f);
+  EntropySums es;
+  auto single = [&](int id) {                    // element id alone
+    if (id == mask_id) return;
+    const float v = kRaw ? to_float(row[id]) : to_float(row[id]) * scale;
+    if (v > run.m) { run.raise(v, id, 0); if (kEnt) es.raise(kRaw ? mul_rn(v, scale) : v); }
+    if (kEnt) es.add<true>(kRaw ? mul_rn(v, scale) : v);
+    else if (run.m > kNegInf) run.add(run.term(v));
+  };
+  if (kAnywhere && tid < head) single(tid);
   const int nfull = nvec / kStride;
   // The [MASK] column lies in exactly one group iteration of the whole block; only that
   // iteration pays for the per-vector check (the others would otherwise spend one predicated
@@ -121,13 +225,32 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int i = 0; i < N; ++i) gm = fmaxf(gm, f[u][i]);
-    if (gm > run.m) run.raise(gm, c, base, U);
-    float acc = 0.f;
+    if (gm > run.m) { run.raise(gm, base, U); if (kEnt) es.raise(kRaw ? mul_rn(gm, scale) : gm); }
+    if constexpr (kEnt) {
+      float lo = f[0][0];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int i = 0; i < N; ++i) acc += fast_exp2(fmaf(f[u][i], c, run.nmc));
-    run.z += acc;
+        for (int i = 0; i < N; ++i) lo = fminf(lo, f[u][i]);
+      if ((kRaw ? lo * scale : lo) - es.m > -1000.f) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int i = 0; i < N; ++i) es.add<false>(kRaw ? mul_rn(f[u][i], scale) : f[u][i]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int i = 0; i < N; ++i) es.add<true>(kRaw ? mul_rn(f[u][i], scale) : f[u][i]);
+      }
+    } else if (!kFine || run.m > kNegInf) {
+      float acc = 0.f;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc += run.term(f[u][i]);
+      run.add(acc);
+    }
   };
   const int split = it_mask < nfull ? it_mask : nfull;
   for (int it = 0; it < split; ++it) group(it, std::false_type{});
@@ -147,16 +270,22 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
     float gm = kNegInf;
 #pragma unroll
     for (int i = 0; i < N; ++i) gm = fmaxf(gm, f[i]);
-    if (gm > run.m) run.raise(gm, c, idx, 1);
-    if (run.m > kNegInf) {                       // a vector holding only the mask column has no live value
+    if (gm > run.m) { run.raise(gm, idx, 1); if (kEnt) es.raise(kRaw ? mul_rn(gm, scale) : gm); }
+    if constexpr (kEnt) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) run.z += fast_exp2(fmaf(f[i], c, run.nmc));
+      for (int i = 0; i < N; ++i) es.add<true>(kRaw ? mul_rn(f[i], scale) : f[i]);
+    } else if (run.m > kNegInf) {                       // a vector holding only the mask column has no live value
+#pragma unroll
+      for (int i = 0; i < N; ++i) run.add(run.term(f[i]));
     }
   }
+
+  if (kAnywhere && tid < vocab - head - nvec * N) single(head + nvec * N + tid);
 
   // ---- block reduction: max, then sum rescaled to the block max ----
   __shared__ float s_f[BLOCK / kWave];
   __shared__ int s_i[BLOCK / kWave];
+  __shared__ double s_d[kEnt ? 2 * (BLOCK / kWave) : 1];
   const int lane = tid % kWave, wid = tid / kWave;
   float M = wave_max(run.m);
   if (lane == 0) s_f[wid] = M;
@@ -165,14 +294,21 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
 #pragma unroll
   for (int i = 1; i < BLOCK / kWave; ++i) M = fmaxf(M, s_f[i]);
   __syncthreads();
-  float zt = (run.m > kNegInf) ? run.true_sum() * fast_exp2((run.m - M) * c) : 0.f;
-  zt = wave_sum(zt);
-  if (lane == 0) s_f[wid] = zt;
+  if constexpr (kEnt) {
+    es.raise(kRaw ? mul_rn(M, scale) : M);              // a thread without a live value has empty sums
+    wave_sum2(es.S, es.U);
+    if (lane == 0) { s_d[2 * wid] = es.S; s_d[2 * wid + 1] = es.U; }
+  } else {
+    float zt = (run.m > kNegInf) ? run.sum_for(M) : 0.f;
+    zt = wave_sum(zt);
+    if (lane == 0) s_f[wid] = zt;
+  }
 
   // ---- arg-max: lowest id attaining M.  Each thread whose own max equals M rescans the
   // (at most U) vectors of the iteration in which it first reached that max. ----
   int cand = INT_MAX;
-  if (run.m == M) {
+  if (run.m == M && run.cnt == 0) cand = run.first;
+  else if (run.m == M) {
     for (int u = 0; u < run.cnt && cand == INT_MAX; ++u) {
       const int idx = run.first + u * BLOCK;
       float f[N];
@@ -180,7 +316,7 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
 #pragma unroll
       for (int i = N - 1; i >= 0; --i) {
         float v = kRaw ? f[i] : f[i] * scale;
-        if (idx * N + i != mask_id && v == M) cand = idx * N + i;
+        if (head + idx * N + i != mask_id && v == M) cand = head + idx * N + i;
       }
     }
   }
@@ -188,7 +324,43 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
   for (int o = kWave / 2; o > 0; o >>= 1) cand = min(cand, __shfl_xor(cand, o, kWave));
   if (lane == 0) s_i[wid] = cand;
   __syncthreads();
-  if (tid == 0) {
+  if constexpr (kEnt) {
+    double St = 0.0, Ut = 0.0;
+#pragma unroll
+    for (int i = 0; i < BLOCK / kWave; ++i) { St += s_d[2 * i]; Ut += s_d[2 * i + 1]; }
+    double H = log(St) - Ut / St;
+    // One-hot to 20 digits: what is left of H are terms below the range of the float32 exponential.  All threads
+    // hold the same sums, so the block takes this path as one.
+    if (H < 1e-20 && M > kNegInf) {
+      __syncthreads();
+      const float mx = kRaw ? mul_rn(M, scale) : M;
+      double S = 0.0, U2 = 0.0;
+      for (int w = tid; w < vocab; w += BLOCK) {
+        if (w == mask_id) continue;
+        const float t = mul_rn(scale, to_float(row[w])) - mx;
+        const double e = exp((double)t);
+        S += e;
+        if (t > kNegInf) U2 += (double)t * e;
+      }
+      wave_sum2(S, U2);
+      if (lane == 0) { s_d[2 * wid] = S; s_d[2 * wid + 1] = U2; }
+      __syncthreads();
+      St = Ut = 0.0;
+#pragma unroll
+      for (int i = 0; i < BLOCK / kWave; ++i) { St += s_d[2 * i]; Ut += s_d[2 * i + 1]; }
+      H = log(St) - Ut / St;
+    }
+    if (tid == 0) {
+      ent[out_row] = (float)H;
+      if (conf) {
+        int best = INT_MAX;
+#pragma unroll
+        for (int i = 0; i < BLOCK / kWave; ++i) best = min(best, s_i[i]);
+        conf[out_row] = (float)(1.0 / St);
+        tok[out_row] = best;
+      }
+    }
+  } else if (tid == 0) {
     float Z = 0.f;
     int best = INT_MAX;
 #pragma unroll
@@ -198,7 +370,7 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
   }
 }
 
-// Any vocab size / alignment: one element per load.  Used for small test shapes only.
+// Short rows (fewer than 256 vectors): one element per load.
 template <typename T, int BLOCK>
 __global__ void __launch_bounds__(BLOCK)
 stage1_scalar_kernel(const T *__restrict__ logits, int vocab, int mask_id, float scale,
@@ -250,30 +422,46 @@ stage1_scalar_kernel(const T *__restrict__ logits, int vocab, int mask_id, float
 // ------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------
+// Blocks of 1024 threads from 4096 vectors a row; below, a block that wide has one or two vectors a thread and its reductions
+// outweigh them (120 MB of rows, 1024 -> 256 threads: bf16 2048 119 -> 52 us, 4096 84 -> 31, 8192 50 -> 25, 24576 27 -> 25;
+// float32 4096 47 -> 21, 16384 alike).  Shorter rows than 256 vectors: one element per load.
+template <typename T, bool kEnt>
+static bool launch_vec(hipStream_t s, const T *logits, int64_t n_rows, int vocab, int mask_id, float scale, const RowFilter &rf,
+                       float *conf, int32_t *tok, float *ent) {
+  constexpr int N = Vec16<T>::N;
+  const int nvec = vocab / N;
+  const bool aligned = vocab % N == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0;
+  const dim3 grid((unsigned)n_rows);
+  constexpr int kWide = kEnt ? 512 : 1024;
+  if (nvec >= 4096 && aligned && !kEnt) stage1_vec_kernel<T, kWide, 2, kEnt, false><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
+  else if (nvec >= 4096) stage1_vec_kernel<T, kWide, 2, kEnt, true><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
+  else if (nvec >= 256) stage1_vec_kernel<T, 256, 2, kEnt, true><<<grid, 256, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
+  else return false;
+  return true;
+}
+
 template <typename T>
 static pvf_status launch_stage1_t(pvf_ctx *ctx, hipStream_t s, const T *logits, int64_t n_rows,
                                   int vocab, int mask_id, float scale, const RowFilter &rf,
-                                  float *conf, int32_t *tok) {
-  constexpr int N = Vec16<T>::N;
-  const bool vec_ok = (vocab % N == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15u) == 0);
-  const dim3 grid((unsigned)n_rows);
-  if (vec_ok && vocab / N >= 512) {
-    stage1_vec_kernel<T, 1024, 2><<<grid, 1024, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok);
-  } else {
-    stage1_scalar_kernel<T, 256><<<grid, 256, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok);
+                                  float *conf, int32_t *tok, float *ent) {
+  if (ent ? launch_vec<T, true>(s, logits, n_rows, vocab, mask_id, scale, rf, conf, tok, ent)
+          : launch_vec<T, false>(s, logits, n_rows, vocab, mask_id, scale, rf, conf, tok, nullptr)) {
+    PVF_LAUNCH_CHECK(ctx, "stage1");
+    return PVF_OK;
   }
+  if (conf) stage1_scalar_kernel<T, 256><<<dim3((unsigned)n_rows), 256, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok);
   PVF_LAUNCH_CHECK(ctx, "stage1");
-  return PVF_OK;
+  return ent ? launch_entropy_short(ctx, s, logits, sizeof(T) == 2 ? PVF_BF16 : PVF_F32, n_rows, vocab, mask_id, scale, rf, ent) : PVF_OK;
 }
 
 pvf_status launch_stage1(pvf_ctx *ctx, hipStream_t s, const void *logits, int dtype,
                          int64_t n_rows, int vocab, int mask_id, float scale,
-                         const RowFilter &rf, float *conf, int32_t *tok) {
+                         const RowFilter &rf, float *conf, int32_t *tok, float *ent) {
   if (n_rows == 0) return PVF_OK;
   PVF_REQUIRE(ctx, n_rows > 0 && n_rows < (1ll << 31), PVF_EINVAL, "stage1: n_rows=%lld out of range", (long long)n_rows);
   if (dtype == PVF_BF16)
-    return launch_stage1_t<bf16_t>(ctx, s, static_cast<const bf16_t *>(logits), n_rows, vocab, mask_id, scale, rf, conf, tok);
-  return launch_stage1_t<float>(ctx, s, static_cast<const float *>(logits), n_rows, vocab, mask_id, scale, rf, conf, tok);
+    return launch_stage1_t<bf16_t>(ctx, s, static_cast<const bf16_t *>(logits), n_rows, vocab, mask_id, scale, rf, conf, tok, ent);
+  return launch_stage1_t<float>(ctx, s, static_cast<const float *>(logits), n_rows, vocab, mask_id, scale, rf, conf, tok, ent);
 }
 
 }  // namespace pvf

@@ -580,7 +580,7 @@ extern "C" pvf_status pvf_entropy(void *stream, const void *logits, int32_t logi
   PVF_REQUIRE(nullptr, mask_id >= 0 && mask_id < vocab, PVF_EINVAL, "pvf_entropy: mask_id=%d outside [0,%d)", mask_id, vocab);
   PVF_REQUIRE(nullptr, logit_scale > 0.f && std::isfinite(logit_scale), PVF_EINVAL, "pvf_entropy: logit_scale=%g", logit_scale);
   RowFilter rf{};
-  return launch_entropy(nullptr, (hipStream_t)stream, logits, logits_dtype, n_rows, vocab, mask_id, logit_scale, rf, ent);
+  return launch_stage1(nullptr, (hipStream_t)stream, logits, logits_dtype, n_rows, vocab, mask_id, logit_scale, rf, nullptr, nullptr, ent);
 }
 
 extern "C" pvf_status pvf_plan_vocab_select(void *stream, const uint32_t *cal_n, const uint32_t *cal_m,
@@ -617,13 +617,10 @@ extern "C" pvf_status pvf_epilogue(pvf_ctx *ctx, void *stream, const void *logit
   const int64_t n_rows = (int64_t)G * (1 + cfg->K) * rf.R;
   {
     ProfScope ps(ctx, s, PVF_PROF_STAGE1, 0.0, (double)n_rows * vocab * (logits_dtype == PVF_BF16 ? 2.0 : 4.0));
-    st = launch_stage1(ctx, s, logits, logits_dtype, n_rows, vocab, mask_id, cfg->logit_scale, rf, state->conf, state->tok);
+    st = launch_stage1(ctx, s, logits, logits_dtype, n_rows, vocab, mask_id, cfg->logit_scale, rf, state->conf, state->tok,
+                       cfg->routes & PVF_ROUTES_CAL ? state->ent : nullptr);
   }
   if (st != PVF_OK) return st;
-  if (cfg->routes & PVF_ROUTES_CAL) {
-    st = launch_entropy(ctx, s, logits, logits_dtype, n_rows, vocab, mask_id, cfg->logit_scale, rf, state->ent);
-    if (st != PVF_OK) return st;
-  }
   ProfScope ps(ctx, s, PVF_PROF_STAGE2, 0.0, 0.0);
   return launch_stage2(ctx, s, G, vocab, mask_id, plan_bitmap, *cfg, *state);
 }
@@ -666,14 +663,10 @@ static pvf_status round_impl(pvf_ctx *ctx, hipStream_t s, int G, const uint32_t 
   {
     ProfScope ps(ctx, s, PVF_PROF_STAGE1, 0.0, (double)n_seq * R * ctx->model.vocab * (double)ctx->esize);
     st = launch_stage1(ctx, s, ctx->logits, ctx->model.dtype, (int64_t)n_seq * R, ctx->model.vocab,
-                       ctx->model.mask_id, cfg.logit_scale, rf, state.conf, state.tok);
+                       ctx->model.mask_id, cfg.logit_scale, rf, state.conf, state.tok,
+                       cfg.routes & PVF_ROUTES_CAL ? state.ent : nullptr);
   }
   if (st != PVF_OK) return st;
-  if (cfg.routes & PVF_ROUTES_CAL) {
-    st = launch_entropy(ctx, s, ctx->logits, ctx->model.dtype, (int64_t)n_seq * R, ctx->model.vocab,
-                        ctx->model.mask_id, cfg.logit_scale, rf, state.ent);
-    if (st != PVF_OK) return st;
-  }
   ProfScope ps(ctx, s, PVF_PROF_STAGE2, 0.0, 0.0);
   return launch_stage2(ctx, s, G, ctx->model.vocab, ctx->model.mask_id, plan_bitmap, cfg, state);
 }
@@ -751,13 +744,9 @@ static pvf_status round_cached_impl(pvf_ctx *ctx, hipStream_t s, int G, const ui
   {
     ProfScope ps(ctx, s, PVF_PROF_STAGE1, 0.0, (double)n_seq * R * m.vocab * (double)ctx->esize);
     st = launch_stage1(ctx, s, ctx->logits, m.dtype, (int64_t)n_seq * R, m.vocab, m.mask_id, cfg.logit_scale, rf,
-                       state.conf, state.tok);
+                       state.conf, state.tok, cfg.routes & PVF_ROUTES_CAL ? state.ent : nullptr);
   }
   if (st != PVF_OK) return st;
-  if (cfg.routes & PVF_ROUTES_CAL) {
-    st = launch_entropy(ctx, s, ctx->logits, m.dtype, (int64_t)n_seq * R, m.vocab, m.mask_id, cfg.logit_scale, rf, state.ent);
-    if (st != PVF_OK) return st;
-  }
   ProfScope ps(ctx, s, PVF_PROF_STAGE2, 0.0, 0.0);
   return launch_stage2(ctx, s, G, m.vocab, m.mask_id, plan_bitmap, cfg, state);
 }
