@@ -60,9 +60,9 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 
 // Row of W that feeds row r (0..BN-1) of the workgroup's W tile.
 //  plain:   consecutive rows tile_n*BN + r.
-//  SwiGLU:  the tile covers BN/2 output columns; inside each wave's BN/WN tile rows groups of 32
-//           rows alternate gate / up for the same 32 columns, so silu(g)*u pairs accumulators
-//           of one lane (16-row MFMA sub-tiles 4P, 4P+1 with 4P+2, 4P+3).
+//  SwiGLU:  the tile covers BN/2 output columns; the lower half of each wave's BN/WN tile rows is gate, the
+//           upper half up for the same columns, so silu(g)*u pairs accumulators of one lane (16-row MFMA
+//           sub-tiles c with NT16/2 + c).
 //  QKV with rotary embedding (ff = 3 d): in the q and k thirds a wave's 64 tile rows are columns
 //           [32g, 32g + 32) of a head followed by their rotation partners [64 + 32g, 64 + 32g + 32)
 //           (g = wave % 2), so the pair (i, i + 64) meets in one lane (sub-tiles t and t + 2).
@@ -75,9 +75,9 @@ __device__ __forceinline__ int w_row(int r, int tile_n, int ff) {
   }
   if (EPI != kEpiSwiglu) return tile_n * BN + r;
   constexpr int WT = BN / WN;
-  const int wn = r / WT, t = (r % WT) >> 5, e = r & 31;
-  const int col = tile_n * (BN / 2) + wn * (WT / 2) + (t >> 1) * 32 + e;
-  return (t & 1) ? ff + col : col;
+  const int wn = r / WT, e = r % (WT / 2);
+  const int col = tile_n * (BN / 2) + wn * (WT / 2) + e;
+  return r % WT >= WT / 2 ? ff + col : col;
 }
 
 // Quadrant schedule: LDS row r of an operand tile holds tile row half_row(r): first the lower halves of all wave tiles, then
@@ -139,11 +139,14 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   // of the slot freed one stage ago over the first k-steps of a stage.
   constexpr bool kLate = kStages == 2;
   // Rings of two stages whose wave tiles split into four equal quadrants run the quadrant schedule (quad_stage below).
-  constexpr bool kQuad = kLate && MT16 % 2 == 0 && NT16 == 4;
+  constexpr bool kQuad = kLate && MT16 % 2 == 0 && NT16 % 2 == 0;
+  // With whole load instructions per half of the W tile the W row of a lane is that of lane 0 plus a distance that is the
+  // same for all loads, and one offset register does.
+  constexpr bool kStepW = kQuad && (BN / 2) % RPI == 0;
   constexpr int kAhead = kLate ? kStages : kStages - 1;     // stages in flight after the prologue
-  static_assert(BM % (RPI / 2) == 0 && (!kHalfA || LA >= 2) && BN % RPI == 0 && BK == 64 && BM % (16 * WM) == 0 && BN % (32 * WN) == 0, "tile shape");
+  static_assert(BM % (RPI / 2) == 0 && (!kHalfA || LA >= 2) && BN % RPI == 0 && BK == 64 && BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "tile shape");
   static_assert((EPI != kEpiQkvRope && EPI != kEpiSwiglu) || BM % (32 * WM) == 0, "the rotary and SwiGLU epilogues take whole 32-row passes");
-  static_assert(EPI != kEpiSwiglu || NT16 % 4 == 0, "SwiGLU pairs 32-column gate/up groups inside a wave");
+  static_assert(EPI != kEpiSwiglu || NT16 % 2 == 0, "SwiGLU pairs the halves of a wave's columns");
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: LDS targets become scalar arithmetic
@@ -167,8 +170,8 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   const int ld_chunk = (tid % CPR) ^ (CPR == 8 ? (ld_row >> 1) & 7 : (ld_row >> 2) & 3);
   // Per-lane byte offsets (32 bit) from the operand base; the k advance goes into the uniform
   // base pointer, so a load needs no per-lane address arithmetic.
-  uint32_t a_off[LA], w_off[kQuad ? 1 : LW];
-  uint32_t w_step[LW];                               // quadrant schedule (short of registers): uniform part of the W offsets
+  uint32_t a_off[LA], w_off[kStepW ? 1 : LW];
+  uint32_t w_step[LW];                               // kStepW: uniform part of the W offsets
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
     const int ar = kQuad ? half_row<BM, WM>(i * RPI + ld_row) : i * RPI + ld_row;
@@ -177,12 +180,13 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   }
 #pragma unroll
   for (int i = 0; i < LW; ++i) {
-    if (kQuad) {                                     // the W row of a lane is that of lane 0 plus a distance that is the same for all i
+    if (kStepW) {
       const int first = w_row<EPI, BN, WN>(half_row<BN, WN>(i * RPI), tile_n, N_out);
       w_step[i] = (uint32_t)first * (uint32_t)K * 2u;
       if (i == 0) w_off[0] = ((uint32_t)(w_row<EPI, BN, WN>(half_row<BN, WN>(ld_row), tile_n, N_out) - first) * (uint32_t)K + ld_chunk * 8) * 2u;
     } else {
-      w_off[i] = ((uint32_t)w_row<EPI, BN, WN>(i * RPI + ld_row, tile_n, N_out) * (uint32_t)K + ld_chunk * 8) * 2u;
+      const int wr = kQuad ? half_row<BN, WN>(i * RPI + ld_row) : i * RPI + ld_row;
+      w_off[i] = ((uint32_t)w_row<EPI, BN, WN>(wr, tile_n, N_out) * (uint32_t)K + ld_chunk * 8) * 2u;
     }
   }
   const char *Ab = reinterpret_cast<const char *>(A), *Wb = reinterpret_cast<const char *>(W);
@@ -202,7 +206,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
     if constexpr (kQuad) {
 #ifdef __HIP_DEVICE_COMPILE__
       if (i < LA) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lptr_t *)(dst + i * kInstrBytes), 16, a_off[i], kt * (BK * 2), 0, 0);
-      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, w_off[0], w_step[i - LA] + kt * (BK * 2), 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, w_off[kStepW ? 0 : i - LA], (kStepW ? w_step[i - LA] : 0u) + kt * (BK * 2), 0, 0);
 #endif
       return;
     }
@@ -211,7 +215,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
       const int ia = (kHalfA && i == LA - 1 && wave >= WM * WN / 2) ? i - 1 : i;      // uniform
       __builtin_amdgcn_global_load_lds((gptr_t *)(Ab + koff + a_off[ia]), (lptr_t *)(dst + ia * kInstrBytes), 16, 0, 0);
     } else
-      __builtin_amdgcn_global_load_lds((gptr_t *)(Wb + koff + w_off[kQuad ? 0 : i - LA]), (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr_t *)(Wb + koff + w_off[kStepW ? 0 : i - LA]), (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, 0, 0);
   };
 
   // ---- LDS -> MFMA operands: lane reads row (base + lane%16), chunk (4*kk + lane/16) ----
@@ -233,16 +237,17 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
 
   const int nk = EPI == kEpiPartial ? sk.nk_per : K / BK;
   // Quadrant schedule: a stage's loads in the order in which their LDS rows are freed.  Group 1: the loads that lie in the
-  // lower halves; group 2: a load across the halves of A (192 rows) first, then the upper halves, W's before A's.
-  constexpr int kLoA = (BM / 2) / RPI, kStraddle = (BM / 2) % RPI != 0, kLoW = LW / 2;
+  // lower halves; group 2: the loads across the halves of an operand (192 rows) first, then the upper halves, W's before A's.
+  constexpr int kLoA = (BM / 2) / RPI, kLoW = (BN / 2) / RPI;
+  constexpr int kAcrossA = (BM / 2) % RPI != 0, kAcross = kAcrossA + ((BN / 2) % RPI != 0);
   constexpr int kG1 = kLoA + kLoW, kG2 = kLoadsPerStage - kG1;
-  static_assert(!kQuad || (BN / 2) % RPI == 0, "halves of the W tile are whole loads");
   auto quad_load = [](int q) {                               // q-th load of a stage in that order
     if (q < kLoA) return q;
     if (q < kG1) return LA + q - kLoA;
-    if (q < kG1 + kStraddle) return kLoA;
-    if (q < kG1 + kStraddle + LW - kLoW) return LA + kLoW + q - kG1 - kStraddle;
-    return q - LW;                                           // upper rows of A
+    if (q < kG1 + kAcrossA) return kLoA;
+    if (q < kG1 + kAcross) return LA + kLoW;
+    const int u = q - kG1 - kAcross, nW = LW - kLoW - (kAcross - kAcrossA);        // upper rows
+    return u < nW ? LW + LA - nW + u : LA - (kG2 - kAcross) + u;
   };
 #pragma unroll
   for (int s = 0; s < kAhead; ++s)
@@ -287,7 +292,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
     auto rd_w = [&](const unsigned char *st, int half, int j) {
       return *reinterpret_cast<const bf16x8 *>(st + w_off0 + half * (BN / 2) * kRowBytes + (j % NH) * 16 * kRowBytes + frag_off[j / NH]);
     };
-    if (nk > 1) wait_vmcnt<kG2 - kStraddle + kLoadsPerStage>(); else wait_vmcnt<kG2 - kStraddle>();
+    if (nk > 1) wait_vmcnt<kG2 - kAcross + kLoadsPerStage>(); else wait_vmcnt<kG2 - kAcross>();
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int j = 0; j < NH * KS; ++j) b[0][j % NH][j / NH] = rd_w(lds, 0, j);
@@ -306,7 +311,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
           if (i == kBarrierAt && (ph == 0 || (ph == 2 && more))) {
             // ph 0: all of stage kt has landed; ph 2: the lower halves of stage kt + 1 have (my parts of them)
             if (ph == 0) { if (more) wait_vmcnt<kLoadsPerStage>(); else wait_vmcnt<0>(); }
-            else { if (kSteady) wait_vmcnt<kG2 - kStraddle + kG1>(); else wait_vmcnt<kG2 - kStraddle>(); }
+            else { if (kSteady) wait_vmcnt<kG2 - kAcross + kG1>(); else wait_vmcnt<kG2 - kAcross>(); }
             __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): my reads of the rows that are refilled now are done
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
@@ -450,13 +455,19 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   constexpr int kElem = kStageF32 ? 4 : 2;
   constexpr int kStride = OC * kElem + 16;                           // padded row of the staging area
   constexpr int LPR = OC / 8;                                        // lanes per output row (8 columns each)
-  constexpr int kRowsPerInstr = 64 / LPR;
+  constexpr bool kWholeRows = 64 % LPR == 0;                         // a store instruction covers whole rows (not with 48 columns)
+  constexpr int kRowsPerInstr = 64 / LPR;                            // kWholeRows only
   static_assert(WM * WN * 32 * kStride <= kStages * kStage, "staging area exceeds the LDS ring");
   const int out_col0 = (EPI == kEpiSwiglu ? tile_n * (BN / 2) : tile_n * BN) + wn * OC;
-  const int rd_row = lane / LPR, rd_col = (lane % LPR) * 8;
+  const int rd_row = lane / LPR, rd_col0 = (lane % LPR) * 8;
+  // row (of the 32 of a pass) and columns that this lane stores with instruction j
+  auto st_row = [&](int j) { return kWholeRows ? j * kRowsPerInstr + rd_row : (j * 64 + lane) / LPR; };
+  auto st_col = [&](int j) { return kWholeRows ? rd_col0 : (j * 64 + lane) % LPR * 8; };
+  static_assert(32 * LPR % 64 == 0 && (kWholeRows || WTM % 32 == 0 || EPI == kEpiPartial), "whole store instructions per pass");
   // The residual rows of the whole wave tile are requested at once, before the staging starts:
   // fetched 32 rows at a time where they are added, each piece cost a full memory latency.
-  constexpr int kRowIters = 32 / kRowsPerInstr;
+  constexpr int kRowIters = 32 * LPR / 64;
+  static_assert(kWholeRows || EPI == kEpiPartial || EPI == kEpiSwiglu, "the other epilogues store whole rows per instruction");
   uint4 rs[EPI == kEpiResidual ? MT : 1][kRowIters];
   if (EPI == kEpiResidual) {
 #pragma unroll
@@ -466,7 +477,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
         if (mt * 32 + j * kRowsPerInstr >= WTM) continue;            // beyond a last pass of 16 rows
         const int m = m0 + wm * WTM + mt * 32 + j * kRowsPerInstr + rd_row;
         rs[mt][j] = make_uint4(0, 0, 0, 0);
-        if (m < M) rs[mt][j] = *reinterpret_cast<const uint4 *>(Res + (int64_t)m * N_out + out_col0 + rd_col);
+        if (m < M) rs[mt][j] = *reinterpret_cast<const uint4 *>(Res + (int64_t)m * N_out + out_col0 + rd_col0);
       }
   }
   __syncthreads();                                                   // every wave is done with the ring
@@ -477,7 +488,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   constexpr bool kNormRoom = kNormOff + WN * BM * 4 <= kStages * kStage;
   float *norm_x = reinterpret_cast<float *>(lds + kNormOff);
   const bool norm_in = kNormRoom && (EPI == kEpiSwiglu || EPI == kEpiQkvRope) && na.ss_in != nullptr;     // uniform
-  const bool norm_out = kNormRoom && EPI == kEpiResidual && na.ss_out != nullptr;                         // uniform
+  const bool norm_out = kNormRoom && kWholeRows && EPI == kEpiResidual && na.ss_out != nullptr;                         // uniform
   if (norm_in) {
     if (tid < BM) norm_x[tid] = my_rnorm;
     __syncthreads();
@@ -548,15 +559,12 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
         }
       } else if (EPI == kEpiSwiglu) {
 #pragma unroll
-        for (int P = 0; P < NT16 / 4; ++P)
+        for (int c = 0; c < NT16 / 2; ++c) {                  // gate sub-tile c, up sub-tile NT16/2 + c
+          float v[4];
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {                     // gate sub-tiles 4P, 4P+1; up sub-tiles 4P+2, 4P+3
-            float v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = silu_f(acc[4 * P + c][m16][j]) * acc[4 * P + 2 + c][m16][j];
-            *reinterpret_cast<uint2 *>(wrow + (P * 32 + c * 16 + 4 * fq) * 2) =
-                make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-          }
+          for (int j = 0; j < 4; ++j) v[j] = silu_f(acc[c][m16][j]) * acc[NT16 / 2 + c][m16][j];
+          *reinterpret_cast<uint2 *>(wrow + (c * 16 + 4 * fq) * 2) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        }
       } else {
 #pragma unroll
         for (int nt = 0; nt < NT16; ++nt) {
@@ -575,13 +583,13 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
       const int m_base = m0 + wm * WTM + mt * 32;
       if (rope_third < 2) {
         // staged row: 32 columns from 32g of the head, then the 32 from 64 + 32g
-        const int col = tile_n * BN + (wn >> 1) * 128 + rope_g * 32 + (rd_col < 32 ? rd_col : rd_col + 32);
+        const int col = tile_n * BN + (wn >> 1) * 128 + rope_g * 32 + (rd_col0 < 32 ? rd_col0 : rd_col0 + 32);
 #pragma unroll
         for (int j = 0; j < 32 / kRowsPerInstr; ++j) {
           const int r = j * kRowsPerInstr + rd_row;
           const int m = m_base + r;
           if (m < M) *reinterpret_cast<uint4 *>(C + (int64_t)m * N_out + col) =
-                         *reinterpret_cast<const uint4 *>(my + r * kStride + rd_col * 2);
+                         *reinterpret_cast<const uint4 *>(my + r * kStride + rd_col0 * 2);
         }
       } else {
         const int vp = mt % kVPasses;
@@ -591,8 +599,8 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
           const int r = j * kRowsPerInstr + rd_row;
           const int rl = vp * 32 + r;                                // row inside the staging group
           const int m = m_base + r;
-          if (m < M) *reinterpret_cast<uint4 *>(C + (int64_t)m * N_out + out_col0 + rd_col) =
-                         *reinterpret_cast<const uint4 *>(my + rl * kStride + ((rd_col ^ ((rl >> 4) << 3)) * 2));
+          if (m < M) *reinterpret_cast<uint4 *>(C + (int64_t)m * N_out + out_col0 + rd_col0) =
+                         *reinterpret_cast<const uint4 *>(my + rl * kStride + ((rd_col0 ^ ((rl >> 4) << 3)) * 2));
         }
         // ... and key-contiguous, once the group's passes are staged: a lane gathers the 8 keys of one 16-byte
         // chunk of one d column (each 16 keys are stored as {0-3, 8-11 | 4-7, 12-15}); the lanes of a store
@@ -644,9 +652,9 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
       continue;
     }
 #pragma unroll
-    for (int j = 0; j < 32 / kRowsPerInstr; ++j) {
-      if (mt * 32 + j * kRowsPerInstr >= WTM) continue;              // beyond a last pass of 16 rows
-      const int r = j * kRowsPerInstr + rd_row;
+    for (int j = 0; j < kRowIters; ++j) {
+      const int r = st_row(j), rd_col = st_col(j);
+      if (WTM % 32 != 0 && mt * 32 + (kWholeRows ? j * kRowsPerInstr : r) >= WTM) continue;      // beyond a last pass of 16 rows
       const int m = m0 + wm * WTM + mt * 32 + r;
       const int64_t o = (int64_t)m * N_out + out_col0 + rd_col;
       if (EPI == kEpiPartial) {
@@ -722,8 +730,8 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   return PVF_OK;
 }
 
-struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only, quad; };   // quad: runs the quadrant schedule, which takes stages in pairs
-constexpr int kNumCfg = 10;
+struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only, quad, swiglu_only = false; };   // quad: runs the quadrant schedule, which takes stages in pairs
+constexpr int kNumCfg = 11;
 // Every shape for many rows runs 8 waves, two per SIMD (the two small ones 4 waves, two workgroups per CU):
 // with one wave per SIMD the 256 x 256 tile (wave tiles of 128 x 128, a third fewer LDS reads) measured 2-4 %
 // slower, smaller wave tiles far slower.
@@ -738,7 +746,8 @@ constexpr TileCfg kCfg[kNumCfg] = {
     {64, 64, 64, 5, 0.0, true, false},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights,
     {64, 128, 64, 3, 0.0, false, false},     // so many small workgroups with deep rings; chosen by pick_config for M <= 384
     {192, 128, 64, 3, 0.86, true, false},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU
-    {160, 256, 64, 3, 0.85, true, false}};   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
+    {160, 256, 64, 3, 0.85, true, false},   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
+    {256, 192, 64, 2, 0.97, false, true, true}};   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
 
 template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
@@ -754,6 +763,7 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
     case 7: return run<EPI, 64, 128, 64, 3, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
     case 8: if constexpr (kPlain) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 9: if constexpr (kPlain) return run<EPI, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
+    case 10: if constexpr (EPI == kEpiSwiglu) return run<EPI, 256, 192, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     default: break;
   }
   return run<EPI, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
@@ -779,7 +789,7 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   double best_t = 0;
   for (int c = 0; c < kNumCfg; ++c) {
     const int ncols = (epi == kEpiSwiglu) ? kCfg[c].bn / 2 : kCfg[c].bn;
-    if (N % ncols != 0 || K % kCfg[c].bk != 0 || (kCfg[c].quad && K % 128 != 0) || (kCfg[c].plain_only && !plain)) continue;
+    if (N % ncols != 0 || K % kCfg[c].bk != 0 || (kCfg[c].quad && K % 128 != 0) || (kCfg[c].plain_only && !plain) || (kCfg[c].swiglu_only && epi != kEpiSwiglu)) continue;
     if (forced == c) return c;
     if (kCfg[c].eff <= 0.0) continue;
     const int64_t tiles = (int64_t)((M + kCfg[c].bm - 1) / kCfg[c].bm) * (N / ncols);
@@ -833,24 +843,38 @@ splitk_finalize_kernel(const float *__restrict__ partial, int splits, int M, int
 
 constexpr int kSplitMaxRows = 640;   // launches with more rows have enough tiles without splitting K
 
-// Tile shape and number of splits of a split-K launch; splits = 0: not possible.  The estimate is rounds of
-// workgroups over the chip x (k stages per workgroup + ~8 stages' worth of prologue and epilogue).
-// Up to 384 rows the tiles are as tall as the launch (64x128, 192x128, 320x128: all rows in one or two row
-// tiles).  From there to 640 rows (one 512-token canvas) 128x128 tiles, and only where they would leave half
-// the chip idle (the O and down projections: 128 tiles).
-void splitk_plan(int M, int Nw, int K, size_t ws_floats, int *tile, int *splits) {
-  *tile = M <= 64 ? 7 : M <= 192 ? 8 : M <= 384 ? 5 : 3;
-  const int bm = M <= 64 ? 64 : M <= 192 ? 192 : M <= 384 ? 320 : 128;
-  const int slots = M <= 64 ? 512 : 256;                     // the 4-wave shape runs two workgroups per CU
-  const int tiles = ((M + bm - 1) / bm) * (Nw / 128), nk = K / 64;
+// Tile shape and number of splits of a split-K launch; splits = 0: not possible.
+//  up to 64 rows     64 x 128, two workgroups per CU: bound by the bytes in flight, as many workgroups as fit twice
+//  65-192            192 x 128
+//  193-384, 385-640  the shapes below by estimated time: rounds of workgroups over the chip x (k stages per workgroup + ~8
+//                    stages' worth of prologue and epilogue) x the tile's area over its relative efficiency, plus what the
+//                    partial sums cost, 4 bytes written and read per split and element.  193-384 rows are two (three) tile rows
+//                    of 160: as many tiles as with 320 x 128 and room for a third stage, which these latency-bound launches want
+//                    more than they mind fetching each weight tile twice from L2.  385-640 rows split only where tiles of
+//                    128 x 128 would leave half the chip idle (the O and down projections: 128 tiles).
+enum SplitTile { kS64x128, kS192x128, kS320x128, kS160x256, kS160x192, kS160x128, kS128x128, kS128x256 };
+struct SplitShape { SplitTile tile; int bm, bn; double eff; };
+void splitk_plan(int M, int Nw, int K, size_t ws_floats, SplitTile *tile, int *splits) {
+  constexpr SplitShape k64[] = {{kS64x128, 64, 128, 1}}, k192[] = {{kS192x128, 192, 128, 1}};
+  constexpr SplitShape k384[] = {{kS160x256, 160, 256, 0.85}, {kS160x192, 160, 192, 0.80}, {kS160x128, 160, 128, 0.65},
+                                  {kS192x128, 192, 128, 0.72}, {kS320x128, 320, 128, 0.70}};
+  constexpr SplitShape k640[] = {{kS128x128, 128, 128, 0.70}, {kS128x256, 128, 256, 0.89}};
+  const SplitShape *shapes = M <= 64 ? k64 : M <= 192 ? k192 : M <= 384 ? k384 : k640;
+  const int n_shapes = M <= 192 ? 1 : M <= 384 ? 5 : 2, nk = K / 64;
+  *tile = shapes[0].tile;
   *splits = 0;
-  if (M > 384 && tiles > 128) return;
-  int best = 0;
-  for (int sp = 1; sp <= 8; sp <<= 1) {
-    if (nk % sp != 0 || nk / sp < 8 || (size_t)sp * M * Nw > ws_floats) continue;
-    // 64-row tiles do little arithmetic per stage and are bound by the bytes in flight: as many workgroups as fit twice
-    const int cost = M <= 64 ? (tiles * sp <= 2 * slots ? -sp : 1) : ((tiles * sp + slots - 1) / slots) * (nk / sp + 8);
-    if (*splits == 0 || cost < best) { *splits = sp; best = cost; }
+  if (M > 384 && (M + 127) / 128 * (Nw / 128) > 128) return;
+  double best = 0;
+  for (const SplitShape *c = shapes; c < shapes + n_shapes; ++c) {
+    if (Nw % c->bn != 0) continue;
+    const int64_t tiles = (int64_t)((M + c->bm - 1) / c->bm) * (Nw / c->bn);
+    for (int sp = 1; sp <= 8; sp <<= 1) {
+      if (nk % sp != 0 || nk / sp < 8 || (size_t)sp * M * Nw > ws_floats) continue;
+      // a stage of 160 x 256 takes about 1 us; 5 TB/s for the partial sums
+      const double us = M <= 64 ? (tiles * sp <= 1024 ? -sp : 1)
+                                : (double)((tiles * sp + 255) / 256) * (nk / sp + 8) * (c->bm * c->bn) / c->eff * 2.1e-5 + sp * (double)M * Nw * 1.6e-6;
+      if (*splits == 0 || us < best) { *tile = c->tile; *splits = sp; best = us; }
+    }
   }
 }
 
@@ -867,10 +891,12 @@ bool gemm_mfma_splitk_supported(int dtype, GemmEpilogue epi, int M, int N, int K
   if (epi == kEpiQkvRope || epi == kEpiPartial || !gemm_mfma_supported(dtype, epi, M, N, K)) return false;
   const int Nw = epi == kEpiSwiglu ? 2 * N : N;
   if (M > kSplitMaxRows || Nw % 128 != 0 || N % 8 != 0 || Nw > 32768) return false;
-  int tile, splits;
+  SplitTile tile;
+  int splits;
   splitk_plan(M, Nw, K, ws_floats, &tile, &splits);
-  // one split only for SwiGLU, whose fused epilogue the tall tiles (wave tiles 32 columns wide) do not have
-  return splits >= 2 || (splits == 1 && epi == kEpiSwiglu && M > 128 && M <= 384);
+  // one split where a launch of its own takes the 64 x 128 tiles (SwiGLU, whose fused epilogue the tall tiles do not have, and
+  // wide plain stores)
+  return splits >= 2 || (splits == 1 && epi != kEpiResidual && M > 128 && M <= 384);
 }
 
 // The split-K launch alone: float32 partial tiles ws[split][M][Nw] (Nw = weight rows: 2 N for SwiGLU); *splits_out
@@ -879,18 +905,23 @@ pvf_status launch_gemm_mfma_splitk_partial(pvf_ctx *ctx, hipStream_t s, const vo
                                            float *ws, size_t ws_floats, int *splits_out) {
   const uintptr_t al = (uintptr_t)A | (uintptr_t)W | (uintptr_t)ws;
   PVF_REQUIRE(ctx, (al & 15u) == 0, PVF_EINVAL, "gemm_mfma: operands must be 16-byte aligned");
-  int tile, splits;
+  SplitTile tile;
+  int splits;
   splitk_plan(M, Nw, K, ws_floats, &tile, &splits);
   PVF_REQUIRE(ctx, splits >= 1 && ws != nullptr, PVF_ESHAPE, "gemm_mfma: no split-K plan for M=%d N=%d K=%d", M, Nw, K);
   const SplitK sk{ws, K / 64 / splits};
   *splits_out = splits;
-  // 193-384 rows: two (three) tile rows of 160 x 256 where the width allows it -- as many tiles as 320 x 128 and room for
-  // a third stage, which these latency-bound launches want more than they mind fetching each weight tile twice from L2
-  if (tile == 5 && Nw % 256 == 0) return run<kEpiPartial, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
-  if (tile == 3) return run<kEpiPartial, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
-  if (tile == 7) return run<kEpiPartial, 64, 128, 64, 3, 2, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
-  if (tile == 8) return run<kEpiPartial, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
-  return run<kEpiPartial, 320, 128, 64, 2, 4, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+  switch (tile) {
+    case kS64x128: return run<kEpiPartial, 64, 128, 64, 3, 2, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS192x128: return run<kEpiPartial, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS320x128: return run<kEpiPartial, 320, 128, 64, 2, 4, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS160x256: return run<kEpiPartial, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS160x192: return run<kEpiPartial, 160, 192, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS160x128: return run<kEpiPartial, 160, 128, 64, 4, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS128x128: return run<kEpiPartial, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS128x256: return run<kEpiPartial, 128, 256, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+  }
+  return PVF_EINVAL;
 }
 
 pvf_status launch_splitk_finalize(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const float *partial, int splits,

@@ -1,4 +1,4 @@
-"""The two GEMM tile shapes with a ring of two stages (256 x 256 and 192 x 256) take the 64-k stages in pairs: the smallest
+"""The GEMM tile shapes with a ring of two stages (256 x 256, 192 x 256 and, for SwiGLU, 256 x 192) take the 64-k stages in pairs: the smallest
 number of stages (only the first and the last pass), one pair in the loop, and odd numbers, which another shape takes."""
 import os
 import subprocess
@@ -17,7 +17,7 @@ sys.path.insert(0, %r)
 from paper_2601_12247_amd import binding as B
 g = torch.Generator(device="cuda").manual_seed(5)
 for K in (64, 128, 192, 256, 384, 448):
-    for M, N in ((1, 256), (193, 512), (257, 256), (511, 768)):
+    for M, N in ((1, 256), (193, 512), (257, 256), (511, 768), (449, 384)):
         A = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
         W = torch.randn(2 * N, K, device="cuda", generator=g).to(torch.bfloat16)
         R = torch.randn(M, N, device="cuda", generator=g).to(torch.bfloat16)
@@ -32,7 +32,7 @@ print("ok")
 """ % ROOT
 
 
-@pytest.mark.parametrize("tile", ["0", "4"])
+@pytest.mark.parametrize("tile", ["0", "4", "10"])
 def test_stage_counts(tile):
     env = dict(os.environ, PVF_GEMM_TILE=tile)
     r = subprocess.run([sys.executable, "-c", CHILD], capture_output=True, text=True, env=env, timeout=110)
