@@ -50,7 +50,7 @@ struct WinArgs {
   int32_t slots_per_group, prompt_len, block_len, R, Rv;
 };
 
-// SPLIT (window mode with at most 64 query rows per canvas): the 64 queries need only two of the four waves, and
+// SPLIT (window mode, launches that leave CUs idle): a workgroup takes 64 queries, which need only two of the four waves, and
 // the loop over the key tiles is a chain of dependent steps of ~2 us each, so the waves work as two pairs: pair
 // 0 takes the even key tiles, pair 1 the odd ones (two tiles are staged per step), and at the end pair 0 merges
 // pair 1's running maximum, sum and O into its own.  Half as many steps for the same work.
@@ -64,13 +64,13 @@ template <bool WIN, bool SPLIT, bool RAG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ vt,
                       bf16_t *__restrict__ out, int T, int H, int vt_stride, WinArgs wa) {
-  static_assert(!SPLIT || WIN, "the key split exists in window mode only");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[(SPLIT ? 4 : 2) * kStage];
+  static_assert(!SPLIT || WIN, "the key split exists in window mode only");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int pair = SPLIT ? wave >> 1 : 0;                    // which half of the key tiles this wave takes
   const int qwave = SPLIT ? wave & 1 : wave;                 // which 32 queries
   const int fr = lane & 31, fh = lane >> 5;
-  const int q0 = blockIdx.x * TQ, head = blockIdx.y, seq = blockIdx.z;
+  const int q0 = blockIdx.x * (SPLIT ? TQ / 2 : TQ), head = blockIdx.y, seq = blockIdx.z;
   const int d = H * DH;
   const int TQrows = WIN ? wa.R : T;                       // query rows per canvas in qkv / out
   const int64_t row0 = (int64_t)seq * TQrows;
@@ -318,69 +318,55 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
 // hold them) are then one 16-byte chunk.
 __device__ __forceinline__ int vt_pos(int t) { return (t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1); }
 
-// Rotary embedding of q and k in place (pair (i, i + 64) of each head) and the key-contiguous copy of v, one 256-thread
-// workgroup per 64 canvas positions of one (canvas, head), with 16-byte accesses throughout.
-//   whole canvases: positions [64 bx, 64 bx + 64) of T;  vt[canvas][head][d][vt_pos(t)] = v[canvas * T + t][head * 128 + d]
-//   window rows (WIN): positions from the 16-key boundary at or below the window's first row; row r of the window is
-//   position w0 + r (rows past the canvas end are padding, rotated like position T - 1).  vt row d, keys counted from that
-//   boundary; positions of a boundary group that lie outside the window come from the cache.
-template <bool WIN>
+// Rotation of 8 pairs (i, i + 64) of a head: lo / hi hold elements i.. and i + 64.. in bf16, cs their (cos, sin).
+__device__ __forceinline__ void rotate8(const uint4 &lo, const uint4 &hi, const float2 *cs, uint4 *ro, uint4 *rh) {
+  const float4 *cs4 = reinterpret_cast<const float4 *>(cs);
+  const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
+  uint32_t ol[4], oh[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float4 c4 = cs4[e];                                // (cos, sin) of pairs 2e, 2e + 1
+    const float a0 = __uint_as_float(lw[e] << 16), a1 = __uint_as_float(lw[e] & 0xffff0000u);
+    const float b0 = __uint_as_float(hw[e] << 16), b1 = __uint_as_float(hw[e] & 0xffff0000u);
+    const bf16_t l0 = (bf16_t)(a0 * c4.x - b0 * c4.y), l1 = (bf16_t)(a1 * c4.z - b1 * c4.w);
+    const bf16_t h0 = (bf16_t)(b0 * c4.x + a0 * c4.y), h1 = (bf16_t)(b1 * c4.z + a1 * c4.w);
+    ol[e] = (uint32_t)__builtin_bit_cast(uint16_t, l0) | ((uint32_t)__builtin_bit_cast(uint16_t, l1) << 16);
+    oh[e] = (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
+  }
+  *ro = make_uint4(ol[0], ol[1], ol[2], ol[3]);
+  *rh = make_uint4(oh[0], oh[1], oh[2], oh[3]);
+}
+
+// Rotary embedding of q and k in place and the key-contiguous copy of v for whole canvases, one 256-thread workgroup per
+// 64 canvas positions of one (canvas, head), with 16-byte accesses throughout:
+// vt[canvas][head][d][vt_pos(t)] = v[canvas * T + t][head * 128 + d].
 __global__ void __launch_bounds__(256)
 rope_vt_kernel(bf16_t *__restrict__ qkv, bf16_t *__restrict__ vt, int T, int H, int vt_stride,
-               const float2 *__restrict__ cos_sin, WinArgs wa) {
+               const float2 *__restrict__ cos_sin) {
   __shared__ bf16_t tile[DH][64 + 2];
   const int tid = threadIdx.x, head = blockIdx.y, seq = blockIdx.z;
-  const int d = H * DH, n_rows = WIN ? wa.R : T;
-  int p0 = blockIdx.x * 64, w0 = 0, w1 = T;                  // first position of the workgroup; positions that have rows
-  const bf16_t *vtcb = nullptr;
-  if (WIN) {
-    const int g = wa.seq_slot[seq] / wa.slots_per_group;
-    w0 = wa.prompt_len + wa.k_active[g] * wa.block_len;
-    w1 = w0 + min(wa.R, T - w0);
-    p0 += w0 & ~15;
-    vtcb = wa.vtc + g * wa.group_stride + (int64_t)head * DH * vt_stride;
-  }
-  const int r0 = p0 - w0;                                    // row of position p0 (WIN: negative in front of the window)
-  bf16_t *base = qkv + (int64_t)seq * n_rows * 3 * d + (int64_t)head * DH;
+  const int d = H * DH, p0 = blockIdx.x * 64;
+  bf16_t *base = qkv + ((int64_t)seq * T + p0) * 3 * d + (int64_t)head * DH;
   // rotate q and k: 64 rows x 2 tensors x 8 chunks of 8 pairs
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int idx = it * 256 + tid;
-    const int ch = idx & 7, which = (idx >> 3) & 1, r = r0 + (idx >> 4);
-    if (r < 0 || r >= n_rows) continue;
+    const int ch = idx & 7, which = (idx >> 3) & 1, r = idx >> 4;
+    if (p0 + r >= T) continue;
     bf16_t *p = base + (int64_t)r * 3 * d + which * d + ch * 8;
-    const float4 *cs4 = reinterpret_cast<const float4 *>(cos_sin + (int64_t)min(w0 + r, T - 1) * 64 + ch * 8);
     const uint4 lo = *reinterpret_cast<const uint4 *>(p), hi = *reinterpret_cast<const uint4 *>(p + 64);
-    const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
-    uint32_t ol[4], oh[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float4 c4 = cs4[e];                              // (cos, sin) of pairs 2e, 2e + 1 of the chunk
-      const float a0 = __uint_as_float(lw[e] << 16), a1 = __uint_as_float(lw[e] & 0xffff0000u);
-      const float b0 = __uint_as_float(hw[e] << 16), b1 = __uint_as_float(hw[e] & 0xffff0000u);
-      const bf16_t l0 = (bf16_t)(a0 * c4.x - b0 * c4.y), l1 = (bf16_t)(a1 * c4.z - b1 * c4.w);
-      const bf16_t h0 = (bf16_t)(b0 * c4.x + a0 * c4.y), h1 = (bf16_t)(b1 * c4.z + a1 * c4.w);
-      ol[e] = (uint32_t)__builtin_bit_cast(uint16_t, l0) | ((uint32_t)__builtin_bit_cast(uint16_t, l1) << 16);
-      oh[e] = (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
-    }
-    *reinterpret_cast<uint4 *>(p) = make_uint4(ol[0], ol[1], ol[2], ol[3]);
-    *reinterpret_cast<uint4 *>(p + 64) = make_uint4(oh[0], oh[1], oh[2], oh[3]);
+    uint4 ro, rh;
+    rotate8(lo, hi, cos_sin + (int64_t)(p0 + r) * 64 + ch * 8, &ro, &rh);
+    *reinterpret_cast<uint4 *>(p) = ro;
+    *reinterpret_cast<uint4 *>(p + 64) = rh;
   }
   // transpose v through LDS: a thread reads 8 d of one row, then writes the 8 keys of one 16-byte vt chunk
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int idx = it * 256 + tid;
     const int rr = idx & 63, ch = idx >> 6;                  // consecutive lanes = consecutive rows: no bank conflicts
-    const int pos = p0 + rr;
     uint4 v8 = make_uint4(0, 0, 0, 0);
-    if (pos >= w0 && pos < w1) {
-      v8 = *reinterpret_cast<const uint4 *>(base + (int64_t)(r0 + rr) * 3 * d + 2 * d + ch * 8);
-    } else if (WIN && pos < T && pos < ((w1 + 15) & ~15)) {
-      uint16_t x[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = __builtin_bit_cast(uint16_t, vtcb[(int64_t)(ch * 8 + e) * vt_stride + vt_pos(pos)]);
-      v8 = make_uint4(x[0] | ((uint32_t)x[1] << 16), x[2] | ((uint32_t)x[3] << 16), x[4] | ((uint32_t)x[5] << 16), x[6] | ((uint32_t)x[7] << 16));
-    }
+    if (p0 + rr < T) v8 = *reinterpret_cast<const uint4 *>(base + (int64_t)rr * 3 * d + 2 * d + ch * 8);
     const uint32_t w[4] = {v8.x, v8.y, v8.z, v8.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -389,8 +375,7 @@ rope_vt_kernel(bf16_t *__restrict__ qkv, bf16_t *__restrict__ vt, int T, int H, 
     }
   }
   __syncthreads();
-  const int out_stride = WIN ? wa.Rv : vt_stride;
-  bf16_t *vb = vt + ((int64_t)seq * H + head) * DH * out_stride + blockIdx.x * 64;
+  bf16_t *vb = vt + ((int64_t)seq * H + head) * DH * vt_stride + p0;
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int idx = it * 256 + tid;
@@ -402,22 +387,113 @@ rope_vt_kernel(bf16_t *__restrict__ qkv, bf16_t *__restrict__ vt, int T, int H, 
       const int kr = k0 + (e & 1) * 2 + (e >> 1) * 8;
       w[e] = (uint32_t)__builtin_bit_cast(uint16_t, tile[dd][kr]) | ((uint32_t)__builtin_bit_cast(uint16_t, tile[dd][kr + 1]) << 16);
     }
-    *reinterpret_cast<uint4 *>(vb + (int64_t)dd * out_stride + g * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+    *reinterpret_cast<uint4 *>(vb + (int64_t)dd * vt_stride + g * 8) = make_uint4(w[0], w[1], w[2], w[3]);
   }
+}
+
+// The same for the window rows of a K/V-cached round, one workgroup per 16-key group of one (canvas, head): every thread has
+// one chunk of each step.  Groups are counted from the 16-key boundary at or below the window's first row; row r of the
+// window is position w0 + r (rows past the canvas end are padding, rotated like position T - 1).  vt row d, keys counted from
+// that boundary; positions of a boundary group that lie outside the window come from the cache.
+// PART: q, k and v come as the float32 partial sums of the split-K projection, part[split][row][3 d], added in split order and
+// rounded to bf16 here; the v third of qkv is then not written (only the attention reads these rows).  Bound by latency:
+// 64 rows, 8 splits: 9.4 us, where a reduction of its own and 64-row workgroups took 5.4 + 6.4; 320 rows, 2 splits: 11.4, 7.1 + 7.7.
+template <bool PART>
+__global__ void __launch_bounds__(256)
+rope_vt_rows_kernel(bf16_t *__restrict__ qkv, const float *__restrict__ part, int splits, int M, bf16_t *__restrict__ vt, int T, int H,
+                    int vt_stride, const float2 *__restrict__ cos_sin, WinArgs wa) {
+  __shared__ bf16_t tile[DH][16 + 2];
+  const int tid = threadIdx.x, head = blockIdx.y, seq = blockIdx.z;
+  const int d = H * DH;
+  const int g = wa.seq_slot[seq] / wa.slots_per_group;
+  const int w0 = wa.prompt_len + wa.k_active[g] * wa.block_len, w1 = w0 + min(wa.R, T - w0);
+  const int p0 = (w0 & ~15) + blockIdx.x * 16;               // first position of the group
+  const int64_t row0 = (int64_t)seq * wa.R;
+  auto load8 = [&](int64_t row, int col) -> uint4 {          // 8 elements of a row of the projection, in bf16
+    if constexpr (!PART) return *reinterpret_cast<const uint4 *>(qkv + row * 3 * d + col);
+    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int z0 = 0; z0 < splits; z0 += 4) {                 // 4 splits in flight at a time
+      float4 x[4], y[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float4 *p = reinterpret_cast<const float4 *>(part + ((int64_t)min(z0 + j, splits - 1) * M + row) * 3 * d + col);
+        x[j] = p[0]; y[j] = p[1];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (z0 + j < splits) {
+          a[0] += x[j].x; a[1] += x[j].y; a[2] += x[j].z; a[3] += x[j].w;
+          a[4] += y[j].x; a[5] += y[j].y; a[6] += y[j].z; a[7] += y[j].w;
+        }
+    }
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      w[e] = (uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)a[2 * e]) | ((uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)a[2 * e + 1]) << 16);
+    return make_uint4(w[0], w[1], w[2], w[3]);
+  };
+  {                                                          // rotate q and k: 16 rows x 2 tensors x 8 chunks of 8 pairs
+    const int ch = tid & 7, which = (tid >> 3) & 1, r = p0 - w0 + (tid >> 4);
+    if (r >= 0 && r < wa.R) {
+      const int col = which * d + head * DH + ch * 8;
+      uint4 ro, rh;
+      rotate8(load8(row0 + r, col), load8(row0 + r, col + 64), cos_sin + (int64_t)min(w0 + r, T - 1) * 64 + ch * 8, &ro, &rh);
+      bf16_t *p = qkv + (row0 + r) * 3 * d + col;
+      *reinterpret_cast<uint4 *>(p) = ro;
+      *reinterpret_cast<uint4 *>(p + 64) = rh;
+    }
+  }
+  {                                                          // v through LDS: 16 rows x 16 chunks of 8 d
+    const int rr = tid & 15, ch = tid >> 4, pos = p0 + rr;
+    uint4 v8 = make_uint4(0, 0, 0, 0);
+    if (pos >= w0 && pos < w1) {
+      v8 = load8(row0 + pos - w0, 2 * d + head * DH + ch * 8);
+    } else if (pos < T && pos < ((w1 + 15) & ~15)) {
+      const bf16_t *vtcb = wa.vtc + g * wa.group_stride + ((int64_t)head * DH + ch * 8) * vt_stride + vt_pos(pos);
+      uint16_t x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = __builtin_bit_cast(uint16_t, vtcb[(int64_t)e * vt_stride]);
+      v8 = make_uint4(x[0] | ((uint32_t)x[1] << 16), x[2] | ((uint32_t)x[3] << 16), x[4] | ((uint32_t)x[5] << 16), x[6] | ((uint32_t)x[7] << 16));
+    }
+    const uint32_t w[4] = {v8.x, v8.y, v8.z, v8.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      tile[ch * 8 + 2 * e][rr] = __builtin_bit_cast(bf16_t, (uint16_t)(w[e] & 0xffffu));
+      tile[ch * 8 + 2 * e + 1][rr] = __builtin_bit_cast(bf16_t, (uint16_t)(w[e] >> 16));
+    }
+  }
+  __syncthreads();
+  const int h8 = tid & 1, dd = tid >> 1;                     // chunk h8 of vt row dd: keys 4 h8 + {0-3, 8-11} of the group
+  uint32_t w[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int kr = 4 * h8 + (e & 1) * 2 + (e >> 1) * 8;
+    w[e] = (uint32_t)__builtin_bit_cast(uint16_t, tile[dd][kr]) | ((uint32_t)__builtin_bit_cast(uint16_t, tile[dd][kr + 1]) << 16);
+  }
+  bf16_t *vb = vt + (((int64_t)seq * H + head) * DH + dd) * wa.Rv + blockIdx.x * 16 + h8 * 8;
+  *reinterpret_cast<uint4 *>(vb) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 }  // namespace
 
 bool attention_mfma_supported(int dtype, int d_head) { return dtype == PVF_BF16 && d_head == DH; }
 
-// Keys per row of the window rows' value buffer: whole 64-position workgroups from the 16-key boundary below the window.
+// Keys per row of the window rows' value buffer: whole key tiles from the 16-key boundary below the window.
 static int window_vt_stride(int R, int block_len, int prompt_len) {
   const int before = block_len % 16 == 0 && prompt_len % 16 == 0 ? 0 : 15;
   return (before + R + 63) / 64 * 64;
 }
 
-pvf_status launch_window_attention_mfma(pvf_ctx *ctx, hipStream_t s, void *qkv_w, void *vt_w, const void *kc, const void *vtc,
-                                        int64_t group_stride, const int32_t *seq_slot, const int32_t *k_active,
+// 64-query workgroups whose wave pairs share the key tiles, where they do not outnumber the CUs (one per CU, by LDS): four
+// windows of 128 rows over 715 keys 30.7 -> 25.6 us a layer (whole canvases gain nothing: 1 x 512 tokens 16.0 -> 17.2).  Up to
+// 640 rows, like the splitting of K: above, a canvas's logits do not depend on what rides along.
+static bool split_pays(int S, int rows, int n_heads) {
+  return (int64_t)S * rows <= 640 && (int64_t)S * n_heads * ((rows + TQ / 2 - 1) / (TQ / 2)) <= 256;
+}
+
+// part: NULL, or the float32 partial sums of the split-K QKV projection [splits][S * R][3 d] that qkv_w is to be made from.
+pvf_status launch_window_attention_mfma(pvf_ctx *ctx, hipStream_t s, void *qkv_w, const float *part, int splits, void *vt_w, const void *kc,
+                                        const void *vtc, int64_t group_stride, const int32_t *seq_slot, const int32_t *k_active,
                                         const pvf_decode_cfg &cfg, int S, int n_heads, const float2 *cos_sin, void *out) {
   if (S == 0) return PVF_OK;
   const int T = cfg.prompt_len + cfg.gen_len, R = window_rows(cfg), vts = vt_keys(T);
@@ -426,15 +502,20 @@ pvf_status launch_window_attention_mfma(pvf_ctx *ctx, hipStream_t s, void *qkv_w
   wa.seq_slot = seq_slot; wa.k_active = k_active; wa.slots_per_group = 1 + cfg.K;
   wa.prompt_len = cfg.prompt_len; wa.block_len = cfg.block_len; wa.R = R;
   wa.Rv = window_vt_stride(R, cfg.block_len, cfg.prompt_len);
-  rope_vt_kernel<true><<<dim3(wa.Rv / 64, n_heads, S), 256, 0, s>>>((bf16_t *)qkv_w, (bf16_t *)vt_w, T, n_heads, vts, cos_sin, wa);
+  // groups up to the end of the last key tile: the rest of the buffer's row (nothing, or groups behind the window) holds zeros
+  const dim3 rgrid(wa.Rv / 16, n_heads, S);
+  if (part) rope_vt_rows_kernel<true><<<rgrid, 256, 0, s>>>((bf16_t *)qkv_w, part, splits, S * R, (bf16_t *)vt_w, T, n_heads, vts, cos_sin, wa);
+  else rope_vt_rows_kernel<false><<<rgrid, 256, 0, s>>>((bf16_t *)qkv_w, nullptr, 0, S * R, (bf16_t *)vt_w, T, n_heads, vts, cos_sin, wa);
   PVF_LAUNCH_CHECK(ctx, "rope_vt_rows");
   // even: whole key tiles, whole 64-row blocks of window rows, windows that begin and end with a 16-key group
   const bool even = T % TK == 0 && R % 64 == 0 && cfg.block_len % 16 == 0 && cfg.prompt_len % 16 == 0;
-  const dim3 grid((R + TQ - 1) / TQ, n_heads, S);
+  const bool split = R <= 64 || split_pays(S, R, n_heads);
+  const int tq = split ? TQ / 2 : TQ;
+  const dim3 grid((R + tq - 1) / tq, n_heads, S);
   const bf16_t *q = (const bf16_t *)qkv_w, *v = (const bf16_t *)vt_w;
   bf16_t *o = (bf16_t *)out;
-  if (R <= 64 && even) attention_mfma_kernel<true, true, false><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
-  else if (R <= 64) attention_mfma_kernel<true, true, true><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
+  if (split && even) attention_mfma_kernel<true, true, false><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
+  else if (split) attention_mfma_kernel<true, true, true><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
   else if (even) attention_mfma_kernel<true, false, false><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
   else attention_mfma_kernel<true, false, true><<<grid, 256, 0, s>>>(q, v, o, T, n_heads, vts, wa);
   PVF_LAUNCH_CHECK(ctx, "attention_window_mfma");
@@ -457,7 +538,7 @@ pvf_status launch_attention_mfma(pvf_ctx *ctx, hipStream_t s, const void *qkv, c
 pvf_status launch_rope_vt(pvf_ctx *ctx, hipStream_t s, void *qkv, void *vt, int S, int T,
                           int n_heads, const float2 *cos_sin) {
   if (S == 0) return PVF_OK;
-  rope_vt_kernel<false><<<dim3(vt_keys(T) / 64, n_heads, S), 256, 0, s>>>((bf16_t *)qkv, (bf16_t *)vt, T, n_heads, vt_keys(T), cos_sin, WinArgs{});
+  rope_vt_kernel<<<dim3(vt_keys(T) / 64, n_heads, S), 256, 0, s>>>((bf16_t *)qkv, (bf16_t *)vt, T, n_heads, vt_keys(T), cos_sin);
   PVF_LAUNCH_CHECK(ctx, "rope_vt");
   return PVF_OK;
 }

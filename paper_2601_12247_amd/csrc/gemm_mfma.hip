@@ -194,6 +194,11 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   Ab += k_shift;
   Wb += k_shift;
   constexpr int kLoadsPerStage = LA + LW;
+  const int nk = EPI == kEpiPartial ? sk.nk_per : K / BK;
+  // Split-K launches are bound by the weight stream, and with all workgroups at the same k their loads of a moment lie
+  // K * 2 bytes apart, on few memory channels: each XCD starts an eighth of its k range further on and wraps around (the
+  // workgroups of one XCD stay together, they share the activations in its L2).  Cached rounds 2.0 and 2.6 % faster.
+  const int turn = EPI == kEpiPartial ? nk / 8 * (int)(blockIdx.x & 7) : 0;
   // The quadrant schedule loads through buffer descriptors: base + 32-bit lane offset + scalar offset, where the compiler
   // turns the global form into a 64-bit address per load and lane (16 registers that are not there).
   const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;
@@ -203,14 +208,15 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
 #endif
   auto issue_one = [&](int kt, int i) {                      // load i (A loads first, then W) of stage kt
     unsigned char *dst = lds + (kt % kStages) * kStage + wave * 1024;
+    const int kr = EPI != kEpiPartial || kt + turn < nk ? kt + turn : kt + turn - nk;
     if constexpr (kQuad) {
 #ifdef __HIP_DEVICE_COMPILE__
-      if (i < LA) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lptr_t *)(dst + i * kInstrBytes), 16, a_off[i], kt * (BK * 2), 0, 0);
-      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, w_off[kStepW ? 0 : i - LA], (kStepW ? w_step[i - LA] : 0u) + kt * (BK * 2), 0, 0);
+      if (i < LA) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lptr_t *)(dst + i * kInstrBytes), 16, a_off[i], kr * (BK * 2), 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lptr_t *)(dst + kATile + (i - LA) * kInstrBytes), 16, w_off[kStepW ? 0 : i - LA], (kStepW ? w_step[i - LA] : 0u) + kr * (BK * 2), 0, 0);
 #endif
       return;
     }
-    const size_t koff = (size_t)kt * (BK * 2);
+    const size_t koff = (size_t)kr * (BK * 2);
     if (i < LA) {
       const int ia = (kHalfA && i == LA - 1 && wave >= WM * WN / 2) ? i - 1 : i;      // uniform
       __builtin_amdgcn_global_load_lds((gptr_t *)(Ab + koff + a_off[ia]), (lptr_t *)(dst + ia * kInstrBytes), 16, 0, 0);
@@ -235,7 +241,6 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[nt][mt][e] = 0.f;
 
-  const int nk = EPI == kEpiPartial ? sk.nk_per : K / BK;
   // Quadrant schedule: a stage's loads in the order in which their LDS rows are freed.  Group 1: the loads that lie in the
   // lower halves; group 2: the loads across the halves of an operand (192 rows) first, then the upper halves, W's before A's.
   constexpr int kLoA = (BM / 2) / RPI, kLoW = (BN / 2) / RPI;
