@@ -42,10 +42,39 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t z) {
 }
 constexpr int kMaxWinBlocks = 4;
 
+// Sums over a wave; every lane gets the result.
+template <typename V> __device__ __forceinline__ V wave_add(V v) {
+  for (int m = 32; m; m >>= 1) v += __shfl_xor(v, m);
+  return v;
+}
+
+// One thread of every wave adds the number of its lanes that say yes.  Called by whole waves.
+__device__ __forceinline__ void wave_count(int32_t *counter, bool yes) {
+  const int n = __popcll(__ballot(yes));
+  if (n && (threadIdx.x & 63) == 0) atomicAdd(counter, n);
+}
+
+// Ranks the candidates (s_cand == 3) by (-confidence, position) and lists the K first.  The confidences of the others
+// become NaN, above which and equal to which nothing is, so that the counting loop has no branches and its LDS reads
+// overlap.  cw is not used again.  Called by the whole workgroup.
+__device__ __forceinline__ void rank_candidates(const int32_t *s_cand, float *cw, const int32_t *tw, int plen, int K, int pos0,
+                                                int32_t *s_npos, int32_t *s_ntok) {
+  for (int i = threadIdx.x; i < plen; i += kStage2Threads) if (s_cand[i] != 3) cw[i] = __builtin_nanf("");
+  __syncthreads();
+  for (int i = threadIdx.x; i < plen; i += kStage2Threads) {
+    if (s_cand[i] != 3) continue;
+    const float c = cw[i];
+    int rank = 0;
+#pragma unroll 8
+    for (int i2 = 0; i2 < plen; ++i2) rank += (cw[i2] > c) | ((cw[i2] == c) & (i2 < i));
+    if (rank < K) { s_npos[rank] = pos0 + i; s_ntok[rank] = tw[i]; }
+  }
+}
+
 // Dynamic LDS layout: conf[(1+K)*R] | tok[(1+K)*R] | x[R] | flag[2*block_len]
 __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   extern __shared__ unsigned char smem[];
-  const int tid = threadIdx.x, nth = kStage2Threads;
+  const int tid = threadIdx.x, nth = kStage2Threads, lane = tid & 63, wave = tid >> 6;
   const int g = blockIdx.x;
   const int K = a.cfg.K, bl = a.cfg.block_len, R = a.R, T = a.T, MASK = a.mask_id;
   const int slots = 1 + K;
@@ -62,8 +91,9 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
 
   uint8_t *accept = a.st.accept + (int64_t)g * K;
   int32_t *ncommit = a.st.n_commit + (int64_t)g * 3;
-  const int ka = a.st.k_active[g];
-  if (a.st.done[g] || ka < 0 || ka >= a.n_blocks) {   // finished (or invalid) group: report an empty round
+  const int ka = a.st.k_active[g], done = a.st.done[g];      // five loads on the way together
+  const int n_drafts = a.st.n_drafts[g], draft_route = a.st.draft_route[g], n_ws = a.st.n_ws_blocks[g];
+  if (done || ka < 0 || ka >= a.n_blocks) {   // finished (or invalid) group: report an empty round
     for (int j = tid; j < K; j += nth) accept[j] = 0;
     if (tid == 0) {
       a.st.winner[g] = 0; ncommit[0] = ncommit[1] = ncommit[2] = 0; a.st.n_drafts[g] = 0; a.st.done[g] = 1;
@@ -71,16 +101,16 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
     return;
   }
 
-  int Kt = a.st.n_drafts[g];
-  Kt = Kt < 0 ? 0 : (Kt > K ? K : Kt);
-  const int route = Kt ? a.st.draft_route[g] : PVF_ROUTE_NONE;
+  const int Kt = n_drafts < 0 ? 0 : (n_drafts > K ? K : n_drafts);
+  const int route = Kt ? draft_route : PVF_ROUTE_NONE;
   // working set this batch was formed on: 1 block, or 2 with early cross-block revelation
-  int ws = (a.cfg.n_sparse > 0 && a.st.n_ws_blocks[g] == 2 && ka + 1 < a.n_blocks) ? 2 : 1;
+  int ws = (a.cfg.n_sparse > 0 && n_ws == 2 && ka + 1 < a.n_blocks) ? 2 : 1;
   const int wlen = ws * bl;
   const int w0 = a.cfg.prompt_len + ka * bl;
   const int nwb = min(R / bl, a.n_blocks - ka);          // window blocks that exist
   int32_t *canvas0 = a.st.canvas + (int64_t)g * slots * T;
 
+#pragma unroll 4
   for (int i = tid; i < (1 + Kt) * R; i += nth) {
     s_conf[i] = a.st.conf[(int64_t)g * slots * R + i];
     s_tok[i] = a.st.tok[(int64_t)g * slots * R + i];
@@ -102,40 +132,48 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   // ---------------- verify ----------------
   if (route == PVF_ROUTE_PLAN) {
     // impact set: masked in the base branch and confident under the base branch
-    for (int i = tid; i < wlen; i += nth) {
-      const int imp = (s_x[i] == MASK) && (s_conf[i] >= a.cfg.tau_high);
-      s_flag[i] = imp;
-      if (imp) atomicAdd(&s_cnt[0], 1);
+    for (int i0 = 0; i0 < wlen; i0 += nth) {
+      const int i = i0 + tid;
+      const bool imp = i < wlen && (s_x[i] == MASK) && (s_conf[i] >= a.cfg.tau_high);
+      if (i < wlen) s_flag[i] = imp;
+      wave_count(&s_cnt[0], imp);
     }
     __syncthreads();
-    if (tid >= 1 && tid <= Kt) {          // one thread per draft
-      const int j = tid, fp = s_fpos[j - 1];
+    for (int j = 1 + wave; j <= Kt; j += nth / 64) {          // one wave per draft
+      const int fp = s_fpos[j - 1];
       bool ok = (s_cnt[0] > 0) && (fp >= 0);
       double C = 0.0;
-      for (int i = 0; i < wlen; ++i) {
+      for (int i = lane; i < wlen; i += 64) {
         if (s_flag[i] && s_tok[j * R + i] != s_tok[i]) ok = false;
         if (s_x[i] == MASK && i != fp) C += (double)s_conf[j * R + i];
       }
-      s_ok[j - 1] = ok;
-      s_C[j - 1] = C;
+      ok = __all(ok);
+      C = wave_add(C);
+      if (lane == 0) { s_ok[j - 1] = ok; s_C[j - 1] = C; }
     }
   } else if (route == PVF_ROUTE_CAL) {
-    for (int i = tid; i < wlen; i += nth) {
-      const int imp = (s_x[i] == MASK) && (s_conf[i] >= a.cfg.tau_high);
-      s_flag[i] = imp;
-      if (imp) atomicAdd(&s_cnt[0], 1);
+    for (int i0 = 0; i0 < wlen; i0 += nth) {
+      const int i = i0 + tid;
+      const bool imp = i < wlen && (s_x[i] == MASK) && (s_conf[i] >= a.cfg.tau_high);
+      if (i < wlen) s_flag[i] = imp;
+      wave_count(&s_cnt[0], imp);
     }
     __syncthreads();
-    if (tid >= 1 && tid <= Kt) {          // one thread per measured draft
-      const int j = tid, fp = s_fpos[j - 1], v = s_ftok[j - 1];
+    for (int j = 1 + wave; j <= Kt; j += nth / 64) {          // one wave per measured draft
+      const int fp = s_fpos[j - 1], v = s_ftok[j - 1];
       bool ok = (s_cnt[0] > 0) && (fp >= 0);
       const float *ent0 = a.st.ent + (int64_t)g * slots * R, *entj = ent0 + (int64_t)j * R;
       double sum = 0.0;
       int cnt = 0;
-      for (int i = 0; i < wlen; ++i) {
+      for (int i = lane; i < wlen; i += 64) {
+        const float e0 = ent0[i], ej = entj[i];      // requested before the tests, which wait for LDS
         if (s_flag[i] && s_tok[j * R + i] != s_tok[i]) ok = false;
-        if (s_x[i] == MASK && i != fp) { sum += (double)ent0[i] - (double)entj[i]; ++cnt; }
+        if (s_x[i] == MASK && i != fp) { sum += (double)e0 - (double)ej; ++cnt; }
       }
+      ok = __all(ok);
+      sum = wave_add(sum);
+      cnt = wave_add(cnt);
+      if (lane) continue;
       const double dH = cnt ? sum / cnt : 0.0;
       s_ok[j - 1] = ok;
       a.st.dh[(int64_t)g * K + j - 1] = dH;
@@ -201,25 +239,38 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
 
   if (!s_done && in_window) {
     // ---------------- propose from the winner's own predictions ----------------
-    const float *cw = s_conf + winner * R + off;
+    float *cw = s_conf + winner * R + off;
     const int32_t *tw = s_tok + winner * R + off;
     int32_t *xb = s_x + off;
     // flag: 0 known, 1 masked (stays), 2 masked and committed by the threshold
-    for (int i = tid; i < plen; i += nth) {
+    for (int i0 = 0; i0 < plen; i0 += nth) {
+      const int i = i0 + tid;
       int f = 0;
-      if (xb[i] == MASK) {
-        f = (cw[i] >= a.cfg.tau_high) ? 2 : 1;
-        atomicAdd(&s_cnt[3], 1);
-        if (f == 2) atomicAdd(&s_cnt[1], 1);
+      if (i < plen) {
+        if (xb[i] == MASK) f = (cw[i] >= a.cfg.tau_high) ? 2 : 1;
+        s_flag[i] = f;
       }
-      s_flag[i] = f;
+      wave_count(&s_cnt[3], f != 0);
+      wave_count(&s_cnt[1], f == 2);
     }
     __syncthreads();
-    if (tid == 0 && s_cnt[1] == 0) {             // progress rule: the single most confident mask
-      int best = -1;
-      for (int i = 0; i < plen; ++i)
-        if (s_flag[i] == 1 && (best < 0 || cw[i] > cw[best])) best = i;
-      if (best >= 0) { s_flag[best] = 2; s_cnt[1] = 1; }
+    // progress rule: the single most confident mask, the first of equals; NaN only where the first mask has it
+    if (wave == 0 && s_cnt[1] == 0) {
+      int best = -1, first = plen;
+      float c = 0.f;
+      for (int i = lane; i < plen; i += 64) {
+        if (s_flag[i] != 1) continue;
+        first = min(first, i);
+        if (cw[i] == cw[i] && (best < 0 || cw[i] > c)) { best = i; c = cw[i]; }
+      }
+      for (int m = 1; m < 64; m <<= 1) {
+        first = min(first, __shfl_xor(first, m));
+        const int ob = __shfl_xor(best, m);
+        const float oc = __shfl_xor(c, m);
+        if (ob >= 0 && (best < 0 || oc > c || (oc == c && ob < best))) { best = ob; c = oc; }
+      }
+      if (first < plen && cw[first] != cw[first]) best = first;
+      if (lane == 0 && best >= 0) { s_flag[best] = 2; s_cnt[1] = 1; }
     }
     __syncthreads();
     for (int i = tid; i < plen; i += nth) if (s_flag[i] == 2) xb[i] = tw[i];
@@ -275,13 +326,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
         if (s_cnt[2] > 0) {
           route_next = PVF_ROUTE_PLAN;
           K_next = min(K, s_cnt[2]);
-          for (int i = tid; i < plen; i += nth) {  // rank by (-confidence, position)
-            if (s_cand[i] != 3) continue;
-            int rank = 0;
-            for (int i2 = 0; i2 < plen; ++i2)
-              if (s_cand[i2] == 3 && (cw[i2] > cw[i] || (cw[i2] == cw[i] && i2 < i))) ++rank;
-            if (rank < K) { s_npos[rank] = w0 + off + i; s_ntok[rank] = tw[i]; }
-          }
+          rank_candidates(s_cand, cw, tw, plen, K, w0 + off, s_npos, s_ntok);
         }
       }
       if (a.cfg.routes & PVF_ROUTES_CAL) {
@@ -293,13 +338,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
         if (s_cnt[2] > 0) {
           route_next = PVF_ROUTE_CAL;
           K_next = min(K, s_cnt[2]);
-          for (int i = tid; i < plen; i += nth) {  // rank by (-confidence, position)
-            if (s_cand[i] != 3) continue;
-            int rank = 0;
-            for (int i2 = 0; i2 < plen; ++i2)
-              if (s_cand[i2] == 3 && (cw[i2] > cw[i] || (cw[i2] == cw[i] && i2 < i))) ++rank;
-            if (rank < K) { s_npos[rank] = w0 + off + i; s_ntok[rank] = tw[i]; }
-          }
+          rank_candidates(s_cand, cw, tw, plen, K, w0 + off, s_npos, s_ntok);
         }
       }
       if (route_next == PVF_ROUTE_NONE && (a.cfg.routes & PVF_ROUTES_AR)) {
@@ -312,7 +351,8 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
           for (int i = tid; i < plen; i += nth) {  // leftmost first
             if (s_cand[i] != 4) continue;
             int rank = 0;
-            for (int i2 = 0; i2 < i; ++i2) if (s_cand[i2] == 4) ++rank;
+#pragma unroll 8
+            for (int i2 = 0; i2 < i; ++i2) rank += s_cand[i2] == 4;
             if (rank < K) { s_npos[rank] = w0 + off + i; s_ntok[rank] = tw[i]; }
           }
         }
@@ -372,15 +412,28 @@ __global__ void state_init_kernel(const int32_t *__restrict__ prompt, int G, int
 __global__ void build_batch_kernel(int G, int K, int n_seq, int R, int T, int prompt_len, int bl,
                                    pvf_state st, int32_t *__restrict__ seq_slot,
                                    int32_t *__restrict__ row_pos) {
-  if (threadIdx.x == 0) {
-    int n = 0;
-    for (int g = 0; g < G; ++g) {
-      if (st.done[g]) continue;
-      int kt = st.n_drafts[g]; kt = kt < 0 ? 0 : (kt > K ? K : kt);
-      for (int j = 0; j <= kt && n < n_seq; ++j) seq_slot[n++] = g * (1 + K) + j;
+  if (threadIdx.x < 64) {                          // one wave, 64 groups at a time, a prefix sum over their live slots
+    const int lane = threadIdx.x;
+    int n = 0, first = -1;
+    for (int g0 = 0; g0 < G && n < n_seq; g0 += 64) {
+      const int g = g0 + lane;
+      int live = 0;
+      if (g < G) {
+        const int done = st.done[g], kt = st.n_drafts[g];
+        live = done ? 0 : 1 + (kt < 0 ? 0 : (kt > K ? K : kt));
+      }
+      int end = live;
+      for (int m = 1; m < 64; m <<= 1) {
+        const int v = __shfl_up(end, m);
+        if (lane >= m) end += v;
+      }
+      const int at = n + end - live;
+      for (int j = 0; j < live && at + j < n_seq; ++j) seq_slot[at + j] = g * (1 + K) + j;
+      const unsigned long long any = __ballot(live > 0);
+      if (first < 0 && any) first = (g0 + __ffsll(any) - 1) * (1 + K);
+      n += __shfl(end, 63);
     }
-    const int first = n ? seq_slot[0] : 0;
-    while (n < n_seq) seq_slot[n++] = first;       // padding: repeats a live canvas
+    for (int i = n + lane; i < n_seq; i += 64) seq_slot[i] = first < 0 ? 0 : first;      // padding: repeats a live canvas
   }
   __syncthreads();
   for (int idx = threadIdx.x; idx < n_seq * R; idx += blockDim.x) {
