@@ -85,7 +85,9 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   __shared__ int32_t s_fpos[PVF_MAX_K], s_ftok[PVF_MAX_K], s_ok[PVF_MAX_K];
   __shared__ int32_t s_npos[PVF_MAX_K], s_ntok[PVF_MAX_K];
   __shared__ double s_C[PVF_MAX_K];
-  __shared__ int32_t s_cnt[4];     // 0: impact size, 1: base commits, 2: candidates, 3: masks in the proposing set
+  // 0: impact size, 1: base commits, 2: planning or calibration candidates, 3: masks in the proposing set, 4: AR candidates
+  // (a counter of their own: all waves read s_cnt[2] behind the barrier that ends its counting, and AR counts with none between)
+  __shared__ int32_t s_cnt[5];
   __shared__ int32_t s_blk[kMaxWinBlocks];   // masks per window block after the commit
   __shared__ int32_t s_winner, s_knew, s_done, s_wsnew;
 
@@ -125,7 +127,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
     }
     s_fpos[tid] = fp; s_ftok[tid] = ft; s_ok[tid] = 0;
   }
-  if (tid < 4) s_cnt[tid] = 0;
+  if (tid < 5) s_cnt[tid] = 0;
   if (tid < kMaxWinBlocks) s_blk[tid] = 0;
   __syncthreads();
 
@@ -343,11 +345,11 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
       }
       if (route_next == PVF_ROUTE_NONE && (a.cfg.routes & PVF_ROUTES_AR)) {
         for (int i = tid; i < plen; i += nth)
-          if (s_flag[i] == 1 && cw[i] >= a.cfg.tau_ar_lo) { s_cand[i] = 4; atomicAdd(&s_cnt[2], 1); }
+          if (s_flag[i] == 1 && cw[i] >= a.cfg.tau_ar_lo) { s_cand[i] = 4; atomicAdd(&s_cnt[4], 1); }
         __syncthreads();
-        if (s_cnt[2] > 0) {
+        if (s_cnt[4] > 0) {
           route_next = PVF_ROUTE_AR;
-          K_next = min(K, s_cnt[2]);
+          K_next = min(K, s_cnt[4]);
           for (int i = tid; i < plen; i += nth) {  // leftmost first
             if (s_cand[i] != 4) continue;
             int rank = 0;
