@@ -196,9 +196,11 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   constexpr int kLoadsPerStage = LA + LW;
   const int nk = EPI == kEpiPartial ? sk.nk_per : K / BK;
   // Split-K launches are bound by the weight stream, and with all workgroups at the same k their loads of a moment lie
-  // K * 2 bytes apart, on few memory channels: each XCD starts an eighth of its k range further on and wraps around (the
-  // workgroups of one XCD stay together, they share the activations in its L2).  Cached rounds 2.0 and 2.6 % faster.
-  const int turn = EPI == kEpiPartial ? nk / 8 * (int)(blockIdx.x & 7) : 0;
+  // K * 2 bytes apart, on few memory channels: each eighth of the tile columns starts an eighth of its k range further on and
+  // wraps around.  An eighth of the columns is what one XCD has (up to the remainder where they are no multiple of 8), whose
+  // workgroups share the activations in its L2.  By the column and not by the XCD itself: all tiles of a column, so all rows
+  // of a launch, add their k in the same order, and equal rows stay equal.  Cached rounds 2.0 and 2.6 % faster.
+  const int turn = EPI == kEpiPartial ? nk / 8 * (tile_n * 8 / tiles_n) : 0;
   // The quadrant schedule loads through buffer descriptors: base + 32-bit lane offset + scalar offset, where the compiler
   // turns the global form into a 64-bit address per load and lane (16 registers that are not there).
   const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;

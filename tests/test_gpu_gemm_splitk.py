@@ -65,3 +65,16 @@ def test_context_gemm_in_place_residual_and_other_paths_agree(ctx):
     assert torch.equal(h2, want)
     d = (want.float() - tiled.float()).abs()
     assert bool((d <= 2.0 ** -7 * tiled.float().abs() + 1e-3).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(320, 1280, 1280), (384, 1536, 4096), (320, 3584, 3584), (512, 2560, 2560), (640, 1408, 1024),
+                                   (320, 4096, 4096)])
+def test_equal_rows_stay_equal(ctx, M, N, K):
+    """A batch padded with copies of a canvas has them in other tile rows: their sums are the same bits, also where the tile
+    columns are no multiple of the 8 XCDs (a round writes the summaries of all copies to one place)."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    a = torch.randn(M // 2, K, device="cuda", generator=g).to(torch.bfloat16)
+    A = torch.cat([a, a])
+    W = torch.randn(N, K, device="cuda", generator=g).to(torch.bfloat16)
+    for out in (ctx.gemm(A, W), ctx.gemm(A, W, residual=torch.zeros(M, N, dtype=torch.bfloat16, device="cuda")), ctx.gemm_swiglu(A, W)):
+        assert torch.equal(out[:M // 2], out[M // 2:])
