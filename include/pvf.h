@@ -324,7 +324,7 @@ pvf_status pvf_rope_attention_noalloc(void *stream, int32_t dtype, void *qkv, vo
  * rotary embedding of q and k, out[S*T, d] = attention.  On return qkv holds rotated q | rotated k
  * | v.  With bf16, d_head = 128 and T % 64 == 0 the rotation and the key-contiguous copy of v that
  * the attention kernel reads are fused into the projection's epilogue; the results equal
- * pvf_gemm followed by pvf_rope_attention up to the rounding of one fused multiply-add.
+ * pvf_gemm followed by pvf_rope_attention bit for bit.
  * vt: dev [S, n_heads, 128, T] in dtype, or NULL.  On the fused path (bf16, d_head = 128, T % 64 == 0)
  * it receives the key-contiguous copy of v the attention kernel reads: vt[s][h][c][t'] = v[s*T + t][h*128 + c]
  * with t' = t with bits 2 and 3 exchanged (each 16 keys stored as 0-3, 8-11, 4-7, 12-15); on the other

@@ -328,8 +328,8 @@ __device__ __forceinline__ void rotate8(const uint4 &lo, const uint4 &hi, const 
     const float4 c4 = cs4[e];                                // (cos, sin) of pairs 2e, 2e + 1
     const float a0 = __uint_as_float(lw[e] << 16), a1 = __uint_as_float(lw[e] & 0xffff0000u);
     const float b0 = __uint_as_float(hw[e] << 16), b1 = __uint_as_float(hw[e] & 0xffff0000u);
-    const bf16_t l0 = (bf16_t)(a0 * c4.x - b0 * c4.y), l1 = (bf16_t)(a1 * c4.z - b1 * c4.w);
-    const bf16_t h0 = (bf16_t)(b0 * c4.x + a0 * c4.y), h1 = (bf16_t)(b1 * c4.z + a1 * c4.w);
+    const float2 r0 = rotate_pair(a0, b0, c4.x, c4.y), r1 = rotate_pair(a1, b1, c4.z, c4.w);
+    const bf16_t l0 = (bf16_t)r0.x, l1 = (bf16_t)r1.x, h0 = (bf16_t)r0.y, h1 = (bf16_t)r1.y;
     ol[e] = (uint32_t)__builtin_bit_cast(uint16_t, l0) | ((uint32_t)__builtin_bit_cast(uint16_t, l1) << 16);
     oh[e] = (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
   }

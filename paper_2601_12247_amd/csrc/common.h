@@ -161,6 +161,14 @@ struct NormArgs {
   int32_t n_slots_in = 0, ld = 0; // slots to add up; rows per slot
   float inv_d = 0.f, eps = 0.f;
 };
+// Rotary embedding of one pair: a = element i of a head, b = element i + d_head / 2 -> (a cos - b sin, b cos + a sin).  Written
+// out as one rounded product and one fused multiply-add each, so that every kernel that rotates bf16 rows of 128-wide heads (the
+// QKV projection's epilogue, the passes of their own) gives the same bits: which of them a launch takes depends on its size,
+// and left to itself the compiler contracted the sum differently from place to place (6e-6 of the elements differed).
+__device__ __forceinline__ float2 rotate_pair(float a, float b, float cos, float sin) {
+#pragma clang fp contract(off)
+  return make_float2(__builtin_fmaf(a, cos, -(b * sin)), __builtin_fmaf(a, sin, b * cos));
+}
 // Rotary embedding in the epilogue of a float32 QKV projection: row m is canvas position m % T, or row_pos[m] (negative:
 // a padding row, rotated like position T - 1); cos_sin [T][half].
 struct RopeF32 {

@@ -558,8 +558,9 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
             const float4 c4 = csr[EPI == kEpiQkvRope ? mt & 1 : 0][h][nt][e];
             const float a0 = __uint_as_float(aw[e] << 16), a1 = __uint_as_float(aw[e] & 0xffff0000u);
             const float b0 = __uint_as_float(bw[e] << 16), b1 = __uint_as_float(bw[e] & 0xffff0000u);
-            lo[e] = pack_bf16x2(a0 * c4.x - b0 * c4.y, a1 * c4.z - b1 * c4.w);
-            up[e] = pack_bf16x2(b0 * c4.x + a0 * c4.y, b1 * c4.z + a1 * c4.w);
+            const float2 r0 = rotate_pair(a0, b0, c4.x, c4.y), r1 = rotate_pair(a1, b1, c4.z, c4.w);
+            lo[e] = pack_bf16x2(r0.x, r1.x);
+            up[e] = pack_bf16x2(r0.y, r1.y);
           }
           *reinterpret_cast<uint2 *>(wrow + (nt * 16 + 4 * fq) * 2) = make_uint2(lo[0], lo[1]);
           *reinterpret_cast<uint2 *>(wrow + (32 + nt * 16 + 4 * fq) * 2) = make_uint2(up[0], up[1]);
