@@ -492,7 +492,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
   RUN(project_residual_norm(c, s, c->xn, c->wo[l], Mr, d, c->hrows, c->ffn_norm[l], c->att, split_ok));
   RUN(project(c, s, kEpiSwiglu, c->att, c->w_gate_up[l], c->act, nullptr, Mr, ff, d, split_ok));
   RUN(project_residual_norm(c, s, c->act, c->w_down[l], Mr, ff, c->hrows, c->w.final_norm, c->xn, split_ok));
-  RUN(project(c, s, kEpiStore, c->xn, c->w.out_head, logits, nullptr, Mr, m.vocab, d));
+  RUN(project(c, s, kEpiStore, c->xn, c->w.out_head, logits, nullptr, Mr, m.vocab, d, split_ok));
 #undef RUN
   return PVF_OK;
 }

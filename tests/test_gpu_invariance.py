@@ -44,6 +44,12 @@ def test_ragged_canvases(weights, T):
     assert batches_unlike_the_largest(weights, T, T) == []
 
 
+@pytest.mark.parametrize("T,R", [(229, 64), (437, 32), (715, 100)])
+def test_few_rows_behind_a_large_forward(weights, T, R):
+    """At most 640 rows reach the last layer's projections and the head: they too take no share of K there."""
+    assert batches_unlike_the_largest(weights, T, R) == []
+
+
 @pytest.mark.parametrize("S_,T,H", [(5, 512, 32), (3, 512, 32), (9, 1280, 32), (1, 64, 2), (2, 320, 4), (7, 192, 8)])
 def test_rotation_in_the_projection_is_the_separate_pass(S_, T, H):
     d = H * 128
