@@ -151,7 +151,7 @@ pvf_status launch_rope(pvf_ctx *ctx, hipStream_t s, int dtype, void *qkv, int M,
                        int n_heads, int d_head, const float2 *cos_sin);
 enum GemmEpilogue { kEpiStore = 0, kEpiResidual = 1, kEpiSwiglu = 2, kEpiQkvRope = 3, kEpiPartial = 4 };
 // RMSNorm folded into the projections around it (bf16 MFMA GEMMs of launches above the split-K range):
-// the projection that writes the residual stream also writes, per output tile column `slot`, the sum of
+// the projection that writes the residual stream also writes, per `slot` of 256 (or 64) columns, the sum of
 // squares of each row's (rounded) values, ss[slot * ld + m]; the projection that reads the stream takes h
 // itself as its operand, with the gain folded into its weights, and multiplies row m of its accumulators by
 // rsqrt(sum over slots of ss / d + eps) in its epilogue.
@@ -159,6 +159,7 @@ struct NormArgs {
   float *ss_out = nullptr;        // kEpiResidual: where the row sums of squares of this launch go
   const float *ss_in = nullptr;   // kEpiSwiglu / kEpiQkvRope: row sums of squares of the operand rows
   int32_t n_slots_in = 0, ld = 0; // slots to add up; rows per slot
+  int32_t group_in = 1;           // 4: slots of 64 columns, four are added up first
   float inv_d = 0.f, eps = 0.f;
 };
 // Rotary embedding of one pair: a = element i of a head, b = element i + d_head / 2 -> (a cos - b sin, b cos + a sin).  Written

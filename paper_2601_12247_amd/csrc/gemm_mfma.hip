@@ -275,7 +275,10 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = s0 + j < na.n_slots_in ? src[(int64_t)(s0 + j) * na.ld] : 0.f;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) t += v[j];
+      for (int j = 0; j < 8; j += 4) {
+        if (na.group_in == 4) t += ((v[j] + v[j + 1]) + v[j + 2]) + v[j + 3];      // uniform
+        else t = (((t + v[j]) + v[j + 1]) + v[j + 2]) + v[j + 3];
+      }
     }
     my_rnorm = rsqrtf(t * na.inv_d + na.eps);
   }
@@ -700,13 +703,24 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
       }
     }
   }
-  if (norm_out) {                                                        // add the WN column parts in a fixed order
+  if (norm_out) {
+    // The sums of 64 columns, from left to right: a slot of 256, or slots of 64 where the tile is narrower (its reader adds four
+    // of them first), so that a row's sum is the same bits whatever tile shape the launch took.
+    constexpr int kPerSlot = BN == 256 ? 256 : 64, kSlots = BN / kPerSlot, kWaves64 = WTN < 64 ? 64 / WTN : 1;
+    static_assert(EPI != kEpiResidual || WTN == 64 || WTN == 32, "64 columns are whole waves");
     __syncthreads();
     for (int row = tid; row < BM; row += kThreads) {
-      float t = 0.f;
+      if (m0 + row >= M) continue;
 #pragma unroll
-      for (int w = 0; w < WN; ++w) t += norm_x[w * BM + row];
-      if (m0 + row < M) na.ss_out[(int64_t)tile_n * na.ld + m0 + row] = t;
+      for (int sl = 0; sl < kSlots; ++sl) {
+        float t = 0.f;
+#pragma unroll
+        for (int c = 0; c < kPerSlot / 64; ++c) {
+          const float *x = norm_x + (sl * (kPerSlot / 64) + c) * kWaves64 * BM + row;
+          t += kWaves64 == 2 ? x[0] + x[BM] : x[0];
+        }
+        na.ss_out[((int64_t)tile_n * kSlots + sl) * na.ld + m0 + row] = t;
+      }
     }
   }
 }
@@ -998,13 +1012,14 @@ bool gemm_mfma_supported(int dtype, GemmEpilogue epi, int M, int N, int K) {
 // Tile shapes with room for the folded-norm exchange (every 8-wave shape).
 bool gemm_mfma_norm_capable(int cfg) { return cfg >= 0 && cfg != 6 && cfg != 7; }
 
-// Output tile columns (= slots of row sums of squares a kEpiResidual launch writes); 0: no folded norm for this launch.
+// Slots of row sums of squares a kEpiResidual launch writes, 256 columns each or (tiles 128 wide) 64; 0: no folded norm for
+// this launch.
 int gemm_mfma_norm_slots(GemmEpilogue epi, int M, int N, int K) {
   if (!gemm_mfma_supported(PVF_BF16, epi, M, N, K)) return 0;
   const int cfg = pick_config(epi, M, N, K);
   if (!gemm_mfma_norm_capable(cfg)) return 0;
   const int c = cfg == 3 || cfg >= kNumCfg ? 3 : cfg;
-  return N / (epi == kEpiSwiglu ? kCfg[c].bn / 2 : kCfg[c].bn);
+  return N / (kCfg[c].bn == 256 ? 256 : 64);
 }
 
 pvf_status launch_gemm_mfma(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const void *A,

@@ -23,7 +23,7 @@ struct pvf_ctx {
   float *splitk_ws = nullptr;          // float32 partial sums of the split-K GEMMs (bf16 contexts)
   size_t splitk_floats = 0;
   // RMSNorm folded into the projections (bf16, launches above the split-K range): row sums of squares
-  // [d / 128 slots][max rows], and wqkv / w_gate_up with the norm gain folded in (the caller's matrices
+  // [d / 64 slots at most][max rows], and wqkv / w_gate_up with the norm gain folded in (the caller's matrices
   // themselves where every gain is 1)
   float *row_ss = nullptr;
   std::vector<const void *> wqkv_f, w_gate_up_f;
@@ -265,7 +265,7 @@ extern "C" pvf_status pvf_create(pvf_ctx **out, const pvf_model_cfg *m, const pv
       // partial sums of the few-row GEMMs: rows x splits x row length, at most 384 x 49152 floats (up to 384 rows
       // every layer GEMM may split, from there to 640 rows only those with rows of 4096 or less)
       {(void **)&c->splitk_ws, m->dtype == PVF_BF16 ? (int64_t)384 * 49152 * 4 : 0},
-      {(void **)&c->row_ss, m->dtype == PVF_BF16 && d % 128 == 0 ? (d / 128) * M * 4 : 0}};
+      {(void **)&c->row_ss, m->dtype == PVF_BF16 && d % 128 == 0 ? (d / 64) * M * 4 : 0}};
   for (auto &r : req) {
     if (r.bytes == 0) continue;
     hipError_t e = hipMalloc(r.p, (size_t)r.bytes);
@@ -395,7 +395,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
   // (2.20e-2 against 2.18e-2), and canvases of other lengths never had it; there the norms cost 12 us of ~650 a layer.
   const int slots_o = gemm_mfma_norm_slots(kEpiResidual, M, d, d), slots_down = gemm_mfma_norm_slots(kEpiResidual, M, d, ff);
   const bool fold_norm = !force_simple() && fold_norm_enabled() && fused_rope && whole_tiles && c->row_ss && M > 640 && slots_o > 0 && slots_down > 0 &&
-                         slots_o <= d / 128 && slots_down <= d / 128 &&
+                         slots_o <= d / 64 && slots_down <= d / 64 &&
                          gemm_mfma_norm_slots(kEpiQkvRope, M, 3 * d, d) > 0 && gemm_mfma_norm_slots(kEpiSwiglu, M, ff, d) > 0;
   // Logits are wanted for R rows of each canvas, so behind the attention of the last layer only those rows go on (compact,
   // [S * R]): 3 of 4 of that layer's projections shrink to R / T of their rows.  Above 640 rows a canvas's logits do not
@@ -429,7 +429,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
         ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)d * d, (double)c->esize * ((double)M * d + (double)d * d + 2.0 * M * d));
         RUN(launch_gemm_mfma(c, s, kEpiResidual, c->att, c->wo[l], c->h, c->h, M, d, d, &n_out));
       }
-      n_in.n_slots_in = slots_o;
+      n_in.n_slots_in = slots_o; n_in.group_in = slots_o == d / 64 ? 4 : 1;
       {
         ProfScope ps(c, s, PVF_PROF_GEMM, 4.0 * M * (double)ff * d, (double)c->esize * ((double)M * d + 2.0 * ff * d + (double)M * ff));
         RUN(launch_gemm_mfma(c, s, kEpiSwiglu, c->h, c->w_gate_up_f[l], c->act, nullptr, M, ff, d, &n_in));
@@ -438,7 +438,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
         ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * M * (double)d * ff, (double)c->esize * ((double)M * ff + (double)d * ff + 2.0 * M * d));
         RUN(launch_gemm_mfma(c, s, kEpiResidual, c->act, c->w_down[l], c->h, c->h, M, d, ff, &n_out));
       }
-      n_in.n_slots_in = slots_down;
+      n_in.n_slots_in = slots_down; n_in.group_in = slots_down == d / 64 ? 4 : 1;
       continue;
     }
     if (!xn_ready) RUN(launch_rmsnorm(c, s, dt, c->h, c->attn_norm[l], c->xn, M, d, m.rms_eps));

@@ -44,6 +44,12 @@ def test_ragged_canvases(weights, T):
     assert batches_unlike_the_largest(weights, T, T) == []
 
 
+@pytest.mark.parametrize("T,R", [(704, 704), (704, 64), (1280, 128), (832, 832), (192, 64)])
+def test_canvases_of_whole_tiles(weights, T, R):
+    """The norm folded into the projections: the tile shapes of the launches that write the rows' sums of squares differ."""
+    assert batches_unlike_the_largest(weights, T, R) == []
+
+
 @pytest.mark.parametrize("T,R", [(229, 64), (437, 32), (715, 100)])
 def test_few_rows_behind_a_large_forward(weights, T, R):
     """At most 640 rows reach the last layer's projections and the head: they too take no share of K there."""
