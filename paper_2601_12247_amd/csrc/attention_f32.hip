@@ -118,7 +118,11 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
     float vb[2][4];
     auto fetch_v = [&](int buf, int kt) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) vb[buf][e] = v_row(kt * 16 + 4 * fq + e)[dt * 16 + fr];
+      for (int e = 0; e < 4; ++e) {
+        const int key = kt * 16 + 4 * fq + e;
+        const float v = v_row(key)[dt * 16 + fr];
+        vb[buf][e] = key < T ? v : 0.f;        // the weight of a padding column is 0, and 0 * inf would not be
+      }
     };
     auto mul = [&](int buf, int kt) {
       const float4 p = *reinterpret_cast<const float4 *>(s_p + fr * stride + kt * 16 + 4 * fq);

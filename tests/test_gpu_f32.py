@@ -47,3 +47,18 @@ def test_attention_f32(S, T, H, dh):
         # |score| <= 20 rounded to float32 moves a weight by 20 * 2^-24 relative, the weight's own chain
         # (exp, sum, product) by a few 2^-24 more: 4e-6 of max |v| = 5
         assert np.abs(got[s * T:(s + 1) * T] - want).max() <= 2e-5
+
+
+# the last tile of 16 keys whole, with one key, with 15; values that are read again for the padding keys are infinite
+@pytest.mark.parametrize("T,dh", [(16, 64), (17, 32), (31, 128), (229, 64)])
+def test_attention_f32_of_infinite_values(T, dh):
+    """Every weight is above zero, so an infinite value of any key gives that infinity and no other column is touched."""
+    rng = np.random.default_rng(T)
+    H, d = 2, 2 * dh
+    qkv = rng.standard_normal((T, 3 * d), dtype=np.float32)
+    qkv[T - 1, 2 * d + 3], qkv[T - 1, 2 * d + dh + 5], qkv[0, 2 * d + 9] = np.inf, -np.inf, np.inf
+    got = B.rope_attention(dev(qkv), 1, T, H, dh, 1e4).cpu().numpy()
+    q, k, v = (qkv[:, i * d:(i + 1) * d].astype(np.float64).reshape(T, H, dh) for i in range(3))
+    want = O.attention(O.rope(q, 1e4), O.rope(k, 1e4), v).reshape(T, d)
+    inf = np.isinf(want)
+    assert inf.sum() == 3 * T and np.array_equal(got[inf], want[inf]) and np.abs(got[~inf] - want[~inf]).max() <= 2e-5
