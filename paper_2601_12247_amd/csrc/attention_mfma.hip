@@ -35,6 +35,28 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Eight values p >= 0 as p = x[0] + x[1] + x[2] in bf16, cut and not rounded: 8 bits each, so all 24 of a float32.  The two
+// lower parts are at least 2^-126, which no sum shows, because a part of 0 would make a NaN of an infinite value.
+__device__ __forceinline__ void split3(const float *p, bf16x8 *x) {
+  typedef short short2v __attribute__((ext_vector_type(2)));
+  constexpr short2v kTiny = {0x0080, 0x0080};
+  uint32_t w[3][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float a = p[2 * e], b = p[2 * e + 1];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+      w[i][e] = __builtin_amdgcn_perm(ub, ua, 0x07060302);   // the upper halves
+      if (i) w[i][e] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(short2v, w[i][e]), kTiny));
+      a -= __uint_as_float(ua & 0xffff0000u);
+      b -= __uint_as_float(ub & 0xffff0000u);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) x[i] = __builtin_bit_cast(bf16x8, make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]));
+}
+
 // Rows of the key-contiguous value buffers hold T rounded up to a whole tile of keys (vt_stride); what lies beyond T is
 // never written and never used.
 //
@@ -57,9 +79,9 @@ struct WinArgs {
 //
 // RAG: any canvas length and window alignment.  Keys beyond T in the last tile are read as key T - 1, get a score of
 // -inf, and their value columns are cleared in LDS.  These shapes used to take a vector-ALU kernel that kept the
-// probabilities in float32, so P goes into the second product as hi + lo bf16 (2^-17 relative instead of 2^-9): against
-// float64 the outputs are as close as that kernel's (1.661531e-3 against 1.661530e-3, bf16 rounding alone 1.661530e-3).  Per
-// layer: 3 canvases x 437 tokens 1196 -> 34 us, four windows of 128 rows over 715 tokens 1496 -> 32 us.  The even shapes keep the single bf16 P they always had.
+// probabilities in float32, so P goes into the second product as three bf16 parts (split3): all 24 bits of it, and an infinite
+// value gives an infinity as it does there.  The even shapes keep the single bf16 P they always had.  Rotary pass and attention
+// of 3 canvases x 437 tokens, 32 heads: 1236 us on that kernel, 47.5 with P in two parts (its last bits lost), 52.5 in three.
 template <bool WIN, bool SPLIT, bool RAG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ vt,
@@ -228,7 +250,8 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
     const float m_new = upd ? mx : m_run;
     const float alpha = upd ? fast_exp2((m_run - m_new) * c) : 1.0f;   // first tile: exp2(-inf) = 0
     const float nmc = -m_new * c;
-    bf16x8 pf[4], pl[RAG ? 4 : 1];                           // "B" operand of the 4 key k-steps; RAG: and what its rounding left
+    bf16x8 pf[4];                                            // "B" operand of the 4 key k-steps
+    float pr[RAG ? 4 : 1][8];                                // RAG: P, taken apart where it is multiplied
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -236,8 +259,8 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float p = fast_exp2(fmaf(s[t][8 * u + e], c, nmc));
-          pf[2 * t + u][e] = (bf16_t)p;
-          if (RAG) pl[RAG ? 2 * t + u : 0][e] = (bf16_t)(p - (float)pf[2 * t + u][e]);
+          if constexpr (RAG) pr[2 * t + u][e] = p;
+          else pf[2 * t + u][e] = (bf16_t)p;
         }
     m_run = m_new;
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
@@ -251,16 +274,19 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
     //      16*ks2 + 4*fh + e (e < 4) or 16*ks2 + 8 + 4*fh + (e - 4): the order P came out in ----
 #pragma unroll
     for (int ks2 = 0; ks2 < 4; ++ks2) {
+      bf16x8 p3[3];
+      if constexpr (RAG) split3(pr[ks2], p3);
+      else p3[0] = pf[ks2];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         // d row t*32 + fr; vt stores each group of 16 keys as {0-3, 8-11 | 4-7, 12-15}: chunk 2*ks2 + fh is this lane's 8 keys
         const bf16x8 vf = *reinterpret_cast<const bf16x8 *>(vs_ + t * 32 * 128 + v_rd[ks2]);
-        o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks2], o[t], 0, 0, 0);
-        if (RAG) o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl[RAG ? ks2 : 0], o[t], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < (RAG ? 3 : 1); ++i) o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, p3[i], o[t], 0, 0, 0);
       }
       // row sums of P on the matrix pipe (a "V^T" row of ones): the vector ALU is the busier unit here
-      ol = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf[ks2], ol, 0, 0, 0);
-      if (RAG) ol = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pl[RAG ? ks2 : 0], ol, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < (RAG ? 3 : 1); ++i) ol = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, p3[i], ol, 0, 0, 0);
     }
   };
   for (int st = 0; st + 1 < n_steps; st += 2) {

@@ -40,6 +40,39 @@ def test_attention_of_any_length(T):
     assert ((out - want).abs() <= tol).all(), float(((out - want).abs() / tol).max())
 
 
+@pytest.mark.parametrize("T", [65, 127, 437])
+def test_probabilities_keep_24_bits(T):
+    """Values of +1 and -1 under weights p and p (1 + delta), delta = 8.6e-5: what is left is 1e4 times smaller than the weights, so
+    it shows their last bits.  An exponent below 4 rounds to 2^-22 / 2 (x ln 2), the hardware exponential to 2^-23, together 2.9e-7 a
+    weight and 0.7 % of delta for two; the output's own rounding is 2^-9.  Weights of 16 bits (2^-18) are up to 12 % off here."""
+    dh = 128
+    qkv = torch.zeros(T, 3 * dh, dtype=torch.bfloat16)
+    j = torch.arange(T)
+    qkv[:, 60], qkv[:, 61] = 2.0 ** -3, 8 * (1 + (j % 64) / 64)           # a theta of 1e30 leaves these columns as they are
+    qkv[:, dh + 60] = 1 + (j % 2) / 128
+    qkv[:, 2 * dh:] = (2.0 * (j % 2) - 1)[:, None]
+    qkv[0, dh + 61], qkv[0, dh + 60], qkv[0, 2 * dh:] = 2, 0, 0            # this key has the largest weight, and no value
+    out = B.rope_attention(qkv.cuda(), 1, T, 1, dh, 1e30).double().cpu()
+    q, k, v = qkv.double().split(dh, -1)
+    want = torch.softmax(q @ k.T / dh ** 0.5, -1) @ v
+    assert want.abs().max() <= 1e-3 and float(((out - want).abs() / want.abs()).max()) <= 0.009
+
+
+@pytest.mark.parametrize("T", [1, 17, 65, 127, 437])
+def test_infinite_values(T):
+    """Every weight is above zero, so an infinite value of any key gives that infinity and no other column is touched."""
+    H, dh = 2, 128
+    d = H * dh
+    g = torch.Generator(device="cuda").manual_seed(T)
+    qkv = torch.randn(T, 3 * d, device="cuda", generator=g).to(torch.bfloat16)
+    qkv[T - 1, 2 * d + 3], qkv[T - 1, 2 * d + dh + 5], qkv[0, 2 * d + 9] = float("inf"), float("-inf"), float("inf")
+    got = B.rope_attention(qkv, 1, T, H, dh, 5e5)
+    want = torch.zeros(d, device="cuda")
+    want[3], want[dh + 5], want[9] = float("inf"), float("-inf"), float("inf")
+    inf = torch.isinf(want)
+    assert torch.equal(got[:, inf].float(), want[inf].expand(T, 3)) and bool(torch.isfinite(got[:, ~inf]).all())
+
+
 @pytest.mark.parametrize("S_,T", [(3, 100), (2, 81), (3, 208), (5, 150), (1, 40), (1, 1)])
 def test_forward_of_ragged_canvases(model, S_, T):
     """Also: what an earlier, longer call left in the workspace must not show."""
