@@ -18,7 +18,6 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -INFINITY;
 constexpr float kLog2eLo = 1.9259629911266174e-08f;     // log2 e - kLog2e
-constexpr float kLn2 = 0.6931471805599453f;
 
 __device__ __forceinline__ float mul_rn(float a, float b) {
 #pragma clang fp contract(off)
@@ -127,33 +126,43 @@ template <> struct Running<false> {
   __device__ __forceinline__ float sum_for(float M) const { return z * fast_exp2(-delta) * fast_exp2((m - M) * c); }
 };
 
-// Entropy sums of one thread (calibration), relative to its own running max m of the scaled logits x:
-// S = sum e^t, U = sum t e^t, t = fl32(x - m), both in float64.  e^t = 2^(t log2 e) by the hardware exponential; the
-// rounding error of the product is put back to first order, so a term is off by about an ulp of float32 besides what
-// rounding t costs, and not by |t| ulps.  A float64 exponential per element and a pass of its own took 5x as long
-// (2112 bf16 rows of 126464: 751 us behind stage 1's 83; this pass does both in 144).  Bound by the vector ALU, about 17
-// slots an element; its entropies are as far from float64 as the ones with float64 exponentials (2e-8 to 3e-8, the rounding of t).
+// e^t for -700 <= t <= 0 in float64: 2^n 2^f, n = rint(t log2 e), |f| <= 1/2, 2^f = 1 + f Q(f) with Q of degree 6 through the
+// Chebyshev nodes of [-1/2, 1/2].  At most 1.1e-10 off relative, in proportion to |f|, so that e^0 is 1; NaN for a NaN.
+__device__ __forceinline__ double exp_f64(double t) {
+  constexpr double kLog2eD = 1.4426950408889634074, kRound = 0x1.8p52;       // adding kRound leaves n in the low bits
+  constexpr double q[7] = {0.6931471805599453, 0.24022650922288757, 0.05550410883909618, 0.009618056678524627,
+                           0.001333350238616314, 0.00015461444698573144, 1.529732376059561e-05};
+  const double k = fma(t, kLog2eD, kRound);
+  const double f = fma(t, kLog2eD, -(k - kRound));
+  double p = q[6];
+#pragma unroll
+  for (int i = 5; i >= 0; --i) p = fma(p, f, q[i]);
+  p = fma(p, f, 1.0);
+  return __hiloint2double(__double2hiint(p) + (__double2loint(k) << 20), __double2loint(p));     // p 2^n
+}
+
+// Entropy sums of one thread (calibration), relative to its own running max m of the scaled logits x: S = sum e^t,
+// U = sum t e^t, t = x - m, all in float64, as the entropy of short rows has them.  Bound by the vector ALU: 13 float64
+// instructions an element, which take twice the slots of float32 ones here.  2112 rows of 126464: bf16 240 us, float32 265; the
+// same pass over a float32 exponential with its argument corrected 165 and 205, but 1-3 % of its bf16 entropies were an ulp off
+// where these are all the exact value rounded once; a float64 exponential of the library in a pass of its own 737 and 786.  Four
+// chains side by side, and workgroups of 256 threads, measured alike.
 struct EntropySums {
-  double S = 0.0, U = 0.0;
-  float m = kNegInf;
+  double S = 0.0, U = 0.0, m = (double)kNegInf;
   __device__ __forceinline__ void raise(float x) {
-    if (m > kNegInf) {
-      const double d = (double)m - (double)x, f = exp(d);
+    if (m > (double)kNegInf) {
+      const double d = m - (double)x, f = exp(d);
       U = (U + d * S) * f;
       S *= f;
     }
-    m = x;
+    m = (double)x;
   }
   template <bool kGuard> __device__ __forceinline__ void add(float x) {
-#pragma clang fp contract(off)
-    const float t = x - m;
-    if (kGuard && (x == kNegInf || t < -1000.f)) return;           // e^t = 0; a NaN goes through to the sums
-    const float y = t * kLog2e;
-    const float lo = fmaf(t, kLog2e, -y) * kLn2;                     // what rounding y took off, as a difference of t
-    const float e0 = fast_exp2(y);
-    const double e = (double)fmaf(e0, fmaf(t, kLog2eLo * kLn2, lo), e0);
+    const double t = (double)x - m;
+    if (kGuard && (x == kNegInf || t < -700.0)) return;            // e^t < 1e-304; a NaN goes through to the sums
+    const double e = exp_f64(t);
     S += e;
-    U = fma((double)t, e, U);
+    U = fma(t, e, U);
   }
 };
 
@@ -232,7 +241,7 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
       for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int i = 0; i < N; ++i) lo = fminf(lo, f[u][i]);
-      if ((kRaw ? lo * scale : lo) - es.m > -1000.f) {
+      if ((double)(kRaw ? lo * scale : lo) - es.m > -700.0) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -328,28 +337,7 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
     double St = 0.0, Ut = 0.0;
 #pragma unroll
     for (int i = 0; i < BLOCK / kWave; ++i) { St += s_d[2 * i]; Ut += s_d[2 * i + 1]; }
-    double H = log(St) - Ut / St;
-    // One-hot to 20 digits: what is left of H are terms below the range of the float32 exponential.  All threads
-    // hold the same sums, so the block takes this path as one.
-    if (H < 1e-20 && M > kNegInf) {
-      __syncthreads();
-      const float mx = kRaw ? mul_rn(M, scale) : M;
-      double S = 0.0, U2 = 0.0;
-      for (int w = tid; w < vocab; w += BLOCK) {
-        if (w == mask_id) continue;
-        const float t = mul_rn(scale, to_float(row[w])) - mx;
-        const double e = exp((double)t);
-        S += e;
-        if (t > kNegInf) U2 += (double)t * e;
-      }
-      wave_sum2(S, U2);
-      if (lane == 0) { s_d[2 * wid] = S; s_d[2 * wid + 1] = U2; }
-      __syncthreads();
-      St = Ut = 0.0;
-#pragma unroll
-      for (int i = 0; i < BLOCK / kWave; ++i) { St += s_d[2 * i]; Ut += s_d[2 * i + 1]; }
-      H = log(St) - Ut / St;
-    }
+    const double H = log(St) - Ut / St;
     if (tid == 0) {
       ent[out_row] = (float)H;
       if (conf) {

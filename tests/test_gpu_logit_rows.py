@@ -58,3 +58,20 @@ def test_entropy_of_rows_without_numbers():
     x[2, 2049] = float("nan")
     got = B.entropy(x.cuda(), 7, 1.0).cpu()
     assert torch.isnan(got[:3]).all() and abs(got[3].item() - np.log(2049)) < 1e-5
+
+
+@pytest.mark.parametrize("V", [2056, 4101, 126464])
+def test_entropies_are_rounded_once(V):
+    """One id far above the rest, which alternate between two values: every term but one then has the same error, and it shows.
+    Exponentials of 1.1e-10 and float64 sums leave the final rounding to float32 as the only one, but where the exact value lies
+    within 0.4 % of the middle between two floats (float32 exponentials: every third row)."""
+    rows, mask_id = 400, 11
+    rng = np.random.default_rng(V)
+    low, step = rng.uniform(2, 9, size=rows).astype(np.float32), rng.uniform(0.1, 6, size=rows).astype(np.float32)
+    x = torch.from_numpy(np.where(np.arange(V)[None] % 2, -low[:, None], -(low + step)[:, None])).to(torch.bfloat16)
+    x[torch.arange(rows), torch.from_numpy(rng.integers(12, V, size=rows))] = float(np.log(V))
+    x[:, mask_id] = 60.0
+    want = reference(x.float().numpy(), 1.0, mask_id)[2].astype(np.float32)
+    got = B.entropy(x.cuda(), mask_id, 1.0).cpu().numpy()
+    np.testing.assert_allclose(got, want, rtol=1.2e-7, atol=0)
+    assert (got == want).mean() >= 0.97
