@@ -112,7 +112,7 @@ struct SplitK {
   int32_t nk_per;                                    // k stages per split
 };
 
-template <int EPI, int BM, int BN, int BK, int kStages, int WM, int WN>
+template <int EPI, int BM, int BN, int BK, int kStages, int WM, int WN, bool kPairs>
 __global__ void __launch_bounds__(64 * WM * WN)
 __attribute__((amdgpu_waves_per_eu(waves_per_simd(kStages * (BM + BN) * BK * 2, WM * WN),
                                    waves_per_simd(kStages * (BM + BN) * BK * 2, WM * WN))))
@@ -133,13 +133,15 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   constexpr int LA = (BM + RPI - 1) / RPI, LW = BN / RPI;        // direct loads per thread per stage
   constexpr int KS = BK / 32;                        // MFMA k-steps per stage
   constexpr int kRowBytes = BK * 2;
-  // With a ring of only two stages (and wave tiles that the quadrant schedule cannot take) the refill of a slot is issued as soon as the slot is free (right
+  // With a ring of only two stages (where the quadrant schedule cannot be taken) the refill of a slot is issued as soon as the slot is free (right
   // after the barrier in the last k-step of the stage that was read from it), all of it in that one
   // k-step: the loads of stage kt + 2 then have a whole stage to land.  Deeper rings spread the refill
   // of the slot freed one stage ago over the first k-steps of a stage.
   constexpr bool kLate = kStages == 2;
-  // Rings of two stages whose wave tiles split into four equal quadrants run the quadrant schedule (quad_stage below).
-  constexpr bool kQuad = kLate && MT16 % 2 == 0 && NT16 % 2 == 0;
+  // Rings of two stages whose wave tiles split into four equal quadrants run the quadrant schedule (quad_stage below).  It takes
+  // the stages in pairs; an odd number of them (K % 128 == 64) has an instance of its own (kPairs = false) on the k-step
+  // schedule.  With a tail for odd numbers beside the other one in one kernel the compiler spilled 100-400 registers.
+  constexpr bool kQuad = kPairs && kLate && MT16 % 2 == 0 && NT16 % 2 == 0;
   // With whole load instructions per half of the W tile the W row of a lane is that of lane 0 plus a distance that is the
   // same for all loads, and one offset register does.
   constexpr bool kStepW = kQuad && (BN / 2) % RPI == 0;
@@ -355,7 +357,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
       quad_stage(kt, k0, k0);
       quad_stage(kt + 1, k0, k1);
     }
-    quad_stage(nk - 2, k1, k0);                              // nk is even (pick_config)
+    quad_stage(nk - 2, k1, k0);                              // nk is even (run_cfg)
     quad_stage(nk - 1, k2, k1);
   } else {
   // Waits until at most n whole stages of this wave's direct loads are still in flight.
@@ -725,7 +727,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   }
 }
 
-template <int EPI, int BM, int BN, int BK, int ST, int WM, int WN>
+template <int EPI, int BM, int BN, int BK, int ST, int WM, int WN, bool kPairs = true>
 pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *C, const void *Res,
                int M, int N_out, int K, const RopeArgs &ra, const SplitK &sk = SplitK{nullptr, 0}, int splits = 1,
                const NormArgs &na = NormArgs{}) {
@@ -733,7 +735,7 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   static_assert(kLdsBytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a CU");
   // once per kernel instance; a function-local static is initialised exactly once even with concurrent callers
   static const hipError_t configured = hipFuncSetAttribute(
-      reinterpret_cast<const void *>(gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN>),
+      reinterpret_cast<const void *>(gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN, kPairs>),
       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
   PVF_HIP_CHECK(ctx, configured);
   const int tiles_m = (M + BM - 1) / BM;
@@ -746,13 +748,13 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   constexpr int kBand = BM > BN ? 4 : 8;
   const int n_bands = (tiles_m + kBand - 1) / kBand;
   const int group_m = (tiles_m + n_bands - 1) / n_bands;
-  gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN><<<dim3(grid, splits), 64 * WM * WN, kLdsBytes, s>>>(
+  gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN, kPairs><<<dim3(grid, splits), 64 * WM * WN, kLdsBytes, s>>>(
       (const bf16_t *)A, (const bf16_t *)W, (bf16_t *)C, (const bf16_t *)Res, M, N_out, K, tiles_m, tiles_n, group_m, ra, sk, na);
   PVF_LAUNCH_CHECK(ctx, "gemm_mfma");
   return PVF_OK;
 }
 
-struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only, quad, swiglu_only = false; };   // quad: runs the quadrant schedule, which takes stages in pairs
+struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only, pairs_only = false; };   // pairs_only: SwiGLU with K % 128 == 0 (the quadrant schedule)
 constexpr int kNumCfg = 11;
 // Every shape for many rows runs 8 waves, two per SIMD (the two small ones 4 waves, two workgroups per CU):
 // with one wave per SIMD the 256 x 256 tile (wave tiles of 128 x 128, a third fewer LDS reads) measured 2-4 %
@@ -760,21 +762,23 @@ constexpr int kNumCfg = 11;
 // plain_only: wave tiles 32 columns wide, which the SwiGLU and rotary epilogues cannot pair up, or 80 rows high
 // (a last epilogue pass of 16 rows, which only the plain epilogues handle).
 constexpr TileCfg kCfg[kNumCfg] = {
-    {256, 256, 64, 2, 1.00, false, true},   // the wide layers
-    {128, 256, 64, 3, 0.89, false, false}, {256, 128, 64, 3, 0.885, false, false},
-    {128, 128, 64, 5, 0.70, false, false},   // launches of a single round of tiles: the smallest area finishes first
-    {192, 256, 64, 2, 0.93, false, true},   // fills the chip when M / 256 leaves many CUs idle
-    {320, 128, 64, 2, 0.78, true, false},    // 2560 rows = 8 tile rows: with N = 4096 exactly one tile per CU (wave tiles 80 x 64)
-    {64, 64, 64, 5, 0.0, true, false},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights,
-    {64, 128, 64, 3, 0.0, false, false},     // so many small workgroups with deep rings; chosen by pick_config for M <= 384
-    {192, 128, 64, 3, 0.86, true, false},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU
-    {160, 256, 64, 3, 0.85, true, false},   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
-    {256, 192, 64, 2, 0.97, false, true, true}};   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
+    {256, 256, 64, 2, 1.00, false},   // the wide layers
+    {128, 256, 64, 3, 0.89, false}, {256, 128, 64, 3, 0.885, false},
+    {128, 128, 64, 5, 0.70, false},   // launches of a single round of tiles: the smallest area finishes first
+    {192, 256, 64, 2, 0.93, false},   // fills the chip when M / 256 leaves many CUs idle
+    {320, 128, 64, 2, 0.78, true},    // 2560 rows = 8 tile rows: with N = 4096 exactly one tile per CU (wave tiles 80 x 64)
+    {64, 64, 64, 5, 0.0, true},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights,
+    {64, 128, 64, 3, 0.0, false},     // so many small workgroups with deep rings; chosen by pick_config for M <= 384
+    {192, 128, 64, 3, 0.86, true},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU
+    {160, 256, 64, 3, 0.85, true},   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
+    {256, 192, 64, 2, 0.97, false, true}};   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
 
 template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
                    const void *Res, int M, int N, int K, const RopeArgs &ra = RopeArgs{}, const NormArgs &na = NormArgs{}) {
   constexpr bool kPlain = EPI != kEpiSwiglu && EPI != kEpiQkvRope;
+  if (K % 128 != 0 && cfg == 0) return run<EPI, 256, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
+  if (K % 128 != 0 && cfg == 4) return run<EPI, 192, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
   switch (cfg) {
     case 0: return run<EPI, 256, 256, 64, 2, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
     case 1: return run<EPI, 128, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
@@ -811,7 +815,7 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   double best_t = 0;
   for (int c = 0; c < kNumCfg; ++c) {
     const int ncols = (epi == kEpiSwiglu) ? kCfg[c].bn / 2 : kCfg[c].bn;
-    if (N % ncols != 0 || K % kCfg[c].bk != 0 || (kCfg[c].quad && K % 128 != 0) || (kCfg[c].plain_only && !plain) || (kCfg[c].swiglu_only && epi != kEpiSwiglu)) continue;
+    if (N % ncols != 0 || K % kCfg[c].bk != 0 || (kCfg[c].plain_only && !plain) || (kCfg[c].pairs_only && (epi != kEpiSwiglu || K % 128 != 0))) continue;
     if (forced == c) return c;
     if (kCfg[c].eff <= 0.0) continue;
     const int64_t tiles = (int64_t)((M + kCfg[c].bm - 1) / kCfg[c].bm) * (N / ncols);

@@ -1,5 +1,6 @@
 """The GEMM tile shapes with a ring of two stages (256 x 256, 192 x 256 and, for SwiGLU, 256 x 192) take the 64-k stages in pairs: the smallest
-number of stages (only the first and the last pass), one pair in the loop, and odd numbers, which another shape takes."""
+number of stages (only the first and the last pass), one pair in the loop, and odd numbers, which the first two run on another
+schedule and the last leaves to another shape."""
 import os
 import subprocess
 import sys
