@@ -59,3 +59,74 @@ def test_planning_without_candidates_hands_over_to_ar(bl, gen, n_sparse, K):
                 ar += new.drafts.route == 2
             ost[g] = new
     assert checked >= 1.5 * G and ar >= G
+
+
+@pytest.mark.parametrize("bl", [64, 256, 400])
+def test_progress_rule_of_equal_and_nan_confidences(bl):
+    """No confidence reaches the threshold: the most confident mask is committed, the first of equals, a NaN only where the first
+    mask has it (nothing compares above it, and it compares above nothing).  Masks of one lane, of neighbouring lanes, of the last pass."""
+    hi, nan = 4.0, float("nan")
+    cases = [({}, []), ({5: hi, 37: hi, bl - 1: hi}, []), ({bl - 2: hi, bl // 2: hi}, []), ({0: nan, bl // 3: hi}, []),
+             ({3: nan, bl // 3: hi, bl // 3 + 20: hi}, []), ({i: nan for i in range(bl)}, []), ({10: nan, 20: hi}, range(10)),
+             ({bl - 2: hi, bl - 1: hi}, range(bl - 2)), ({bl // 2 + 1: nan, bl - 1: hi}, range(bl // 2)), ({bl - 1: nan}, range(bl - 1))]
+    G = len(cases)
+    cfg = B.DecodeCfg(block_len=bl, prompt_len=0, gen_len=bl, K=0, tau_high=0.9)
+    ocfg = oracle_decode_cfg(cfg)
+    logits = np.zeros((G, 1, bl, V), np.float32)
+    canvas = np.full((G, bl), MASK, np.int32)
+    for g, (level, known) in enumerate(cases):
+        logits[g, 0, np.arange(bl), np.arange(bl) % 400 + g] = 3.0
+        for i, x in level.items():
+            logits[g, 0, i, i % 400 + g] = x
+        canvas[g, list(known)] = 7
+    st = fresh_state(G, cfg)
+    st.canvas.copy_(dev(canvas)[:, None])
+    B.epilogue(dev(logits, torch.float32), st, dev(np.zeros((V + 31) // 32)), V, MASK)
+    conf, tok = st.conf.cpu().numpy(), st.tok.cpu().numpy()
+    for g, (level, _) in enumerate(cases):
+        old = O.State(canvas[g], O.Drafts(0, []), 0, False)
+        assert np.array_equal(np.isnan(conf[g, 0]), [np.isnan(level.get(i, 0.0)) for i in range(bl)])
+        new, info = O.decide(old, conf[g], tok[g], ocfg, MASK, [])
+        assert info.n_base == 1
+        assert_state_equals(st, g, new, info, cfg, where=f"group {g}")
+
+
+TINY = S.ModelShape(n_layers=1, d_model=64, n_heads=2, d_ff=96, vocab=V, mask_id=MASK, logit_scale=20.0)
+
+
+@pytest.mark.parametrize("G,first_live", [(63, 0), (65, 64), (70, 0), (130, 66), (130, 128)])
+def test_batches_of_more_than_64_groups(G, first_live):
+    """The list of live canvases is made 64 groups at a time: groups before first_live and every fifth one are done, the others have
+    no, one or two drafts.  Every live slot's summary is that of its canvas, with a compact list, a padded one and one for the
+    first half of the live canvases only, which leaves the others' summaries alone; finished groups stay as they are."""
+    K = 2
+    cfg = B.DecodeCfg(block_len=8, prompt_len=3, gen_len=16, K=K, tau_high=0.9, logit_scale=TINY.logit_scale)
+    ctx = make_context(TINY, to_device(S.make_weights(TINY, seed=2)), max_seqs=G * (1 + K), max_T=cfg.T, max_rows=cfg.R)
+    rng = np.random.default_rng(G + first_live)
+    done = (np.arange(G) < first_live) | (np.arange(G) % 5 == 4) & (np.arange(G) != first_live)
+    n_drafts = np.where(done, 0, rng.integers(0, K + 1, size=G))
+    canvas = rng.integers(0, MASK, size=(G, 1 + K, cfg.T))
+    canvas[:, :, 5:] = MASK                            # two known positions of the first block
+    canvas[:, 1:, 5] = 9
+    rows = torch.arange(cfg.prompt_len, cfg.T, dtype=torch.int32, device="cuda")[None].repeat(G * (1 + K), 1).contiguous()
+    logits = ctx.forward(dev(canvas.reshape(-1, cfg.T)), rows)
+    want_conf, want_tok = B.stage1(logits.view(-1, V), MASK, TINY.logit_scale)
+    want_conf, want_tok = want_conf.view(G, 1 + K, cfg.R), want_tok.view(G, 1 + K, cfg.R)
+    live = [(g, j) for g in range(G) if not done[g] for j in range(1 + n_drafts[g])]
+    bitmap = dev(np.zeros((V + 31) // 32))
+    for n_seq in (len(live), 0, len(live) // 2):
+        st = fresh_state(G, cfg)
+        st.canvas.copy_(dev(canvas)); st.done.copy_(dev(done)); st.n_drafts.copy_(dev(n_drafts))
+        st.draft_route.fill_(B.PVF_ROUTE_PLAN); st.fill_pos.fill_(5); st.fill_tok.fill_(9); st.n_ws_blocks.fill_(1)
+        st.conf.fill_(-1.0); st.tok.fill_(-2)
+        ctx.round(st, bitmap, n_seq)
+        torch.cuda.synchronize()
+        seen = live[:n_seq] if n_seq else live
+        at = tuple(np.array(seen).T)
+        conf, tok = st.conf.cpu().numpy(), st.tok.cpu().numpy()
+        assert np.array_equal(conf[at], want_conf.cpu().numpy()[at]) and np.array_equal(tok[at], want_tok.cpu().numpy()[at]), n_seq
+        if n_seq:
+            rest = np.ones((G, 1 + K), bool)
+            rest[at] = False
+            assert (conf[rest] == -1.0).all(), n_seq
+        assert np.array_equal(st.canvas.cpu().numpy()[done], canvas[done]) and bool(st.done[torch.from_numpy(done).cuda()].all())
