@@ -162,17 +162,17 @@ def test_bf16_cached_decode_completes_and_agrees_on_refresh_rounds():
     assert np.array_equal(first[0][0], first[1][0]) and np.array_equal(first[0][1], first[1][1])
 
 
-@pytest.mark.parametrize("bl,pl,gl", [(32, 64, 128), (24, 48, 144)], ids=["mfma-window", "row-major-v-cache"])
-def test_bf16_window_attention_on_matrix_cores_matches_oracle(bl, pl, gl):
-    """d_head = 128, bf16, 64-row window: the cached round takes the MFMA window-attention path.
-    With blocks of 24 the window kernel does not apply: the cache keeps V row-major, which the fused
-    QKV projection of the refresh round then has to write (it otherwise writes only the key-contiguous copy).
+@pytest.mark.parametrize("bl,pl,gl,heads", [(32, 64, 128, 2), (24, 48, 144, 2), (24, 48, 144, 4)],
+                         ids=["mfma-window", "mfma-window-of-48", "row-major-v-cache"])
+def test_bf16_window_attention_on_matrix_cores_matches_oracle(bl, pl, gl, heads):
+    """d_head = 128, bf16, windows of 64 and of 48 rows: the cached round takes the MFMA window-attention path.
+    With d_head = 64 that kernel does not apply: the cache keeps V row-major and the plain window attention reads it.
     Round 1 (refresh) and round 2 (cached) are run on the GPU; the oracle repeats round 2 from the
     GPU's own state after round 1, on the bf16-rounded weights.  bf16 activations move a
     confidence by a few 1e-3 at this temperature, so confidences are compared within 2e-2 absolute
     / 4e-3 on average, and top-1 tokens wherever the oracle's confidence is not tiny."""
     from tests.gpu_util import oracle_state
-    shape = S.ModelShape(n_layers=2, d_model=256, n_heads=2, d_ff=512, vocab=4096, mask_id=4095, logit_scale=6.0)
+    shape = S.ModelShape(n_layers=2, d_model=256, n_heads=heads, d_ff=512, vocab=4096, mask_id=4095, logit_scale=6.0)
     w = S.make_weights(shape, seed=5)
     wb = {k: (S.bf16_round(v) if k != "layers" else [{kk: S.bf16_round(vv) for kk, vv in lw.items()} for lw in v])
           for k, v in w.items()}
