@@ -80,8 +80,9 @@ struct WinArgs {
 // RAG: any canvas length and window alignment.  Keys beyond T in the last tile are read as key T - 1, get a score of
 // -inf, and their value columns are cleared in LDS.  These shapes used to take a vector-ALU kernel that kept the
 // probabilities in float32, so P goes into the second product as three bf16 parts (split3): all 24 bits of it, and an infinite
-// value gives an infinity as it does there.  The even shapes keep the single bf16 P they always had.  Rotary pass and attention
-// of 3 canvases x 437 tokens, 32 heads: 1236 us on that kernel, 47.5 with P in two parts (its last bits lost), 52.5 in three.
+// value gives an infinity as it does there.  The even shapes keep the single bf16 P they always had.  Per layer, 32 heads:
+// 3 canvases x 437 tokens 1196 us on that kernel, 34 with P in two parts (its last bits lost), 40 in three; four windows of 128
+// rows over 715 tokens 1496, 25.6 and 27.6.
 template <bool WIN, bool SPLIT, bool RAG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ vt,

@@ -418,11 +418,15 @@ static bool launch_vec(hipStream_t s, const T *logits, int64_t n_rows, int vocab
                        float *conf, int32_t *tok, float *ent) {
   constexpr int N = Vec16<T>::N;
   const int nvec = vocab / N;
-  const bool aligned = vocab % N == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0;
   const dim3 grid((unsigned)n_rows);
   constexpr int kWide = kEnt ? 512 : 1024;
-  if (nvec >= 4096 && aligned && !kEnt) stage1_vec_kernel<T, kWide, 2, kEnt, false><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
-  else if (nvec >= 4096) stage1_vec_kernel<T, kWide, 2, kEnt, true><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
+  if constexpr (!kEnt) {
+    if (nvec >= 4096 && vocab % N == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0) {
+      stage1_vec_kernel<T, kWide, 2, false, false><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
+      return true;
+    }
+  }
+  if (nvec >= 4096) stage1_vec_kernel<T, kWide, 2, kEnt, true><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
   else if (nvec >= 256) stage1_vec_kernel<T, 256, 2, kEnt, true><<<grid, 256, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
   else return false;
   return true;

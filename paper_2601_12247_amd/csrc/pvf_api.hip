@@ -420,9 +420,8 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
       }
       if (capture_spg > 0) {
         const int64_t layer_off = (int64_t)l * vt_keys(T) * d * c->esize, gstride = (int64_t)m.n_layers * vt_keys(T) * d;
-        void *vl = (char *)c->vcache + layer_off;
         RUN(launch_kv_store(c, s, dt, c->qkv, c->vt, seq_slot, capture_spg, S, T, d, (char *)c->kcache + layer_off,
-                            c->cache_vt ? nullptr : vl, c->cache_vt ? vl : nullptr, gstride));
+                            nullptr, (char *)c->vcache + layer_off, gstride));        // the matrix-core kernels' cache: values key-contiguous
       }
       if (cut) break;
       {
@@ -535,8 +534,8 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
           RUN(launch_attention_window_f32(c, s, c->qkv, (const char *)c->kcache + layer_off, (const char *)c->vcache + layer_off,
                                           gstride, cfg, state, seq_slot, S, H, dh, c->att));
         else
-        RUN(launch_attention_window(c, s, dt, c->qkv, (const char *)c->kcache + layer_off, (const char *)c->vcache + layer_off,
-                                    gstride, cfg, state, seq_slot, S, H, dh, c->att));
+          RUN(launch_attention_window(c, s, dt, c->qkv, (const char *)c->kcache + layer_off, (const char *)c->vcache + layer_off,
+                                      gstride, cfg, state, seq_slot, S, H, dh, c->att));
       }
     }
     RUN(project_residual_norm(c, s, c->att, c->wo[l], M, d, c->h, c->ffn_norm[l], c->xn));

@@ -64,7 +64,7 @@ def test_entropy_of_rows_without_numbers():
 def test_entropies_are_rounded_once(V):
     """One id far above the rest, which alternate between two values: every term but one then has the same error, and it shows.
     Exponentials of 1.1e-10 and float64 sums leave the final rounding to float32 as the only one, but where the exact value lies
-    within 0.4 % of the middle between two floats (float32 exponentials: every third row)."""
+    within 0.4 % of the middle between two floats (float32 exponentials: more than 3 % of the rows)."""
     rows, mask_id = 400, 11
     rng = np.random.default_rng(V)
     low, step = rng.uniform(2, 9, size=rows).astype(np.float32), rng.uniform(0.1, 6, size=rows).astype(np.float32)
