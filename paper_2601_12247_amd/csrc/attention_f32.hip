@@ -118,10 +118,10 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
     float vb[2][4];
     auto fetch_v = [&](int buf, int kt) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int key = kt * 16 + 4 * fq + e;
-        const float v = v_row(key)[dt * 16 + fr];
-        vb[buf][e] = key < T ? v : 0.f;        // the weight of a padding column is 0, and 0 * inf would not be
+      for (int e = 0; e < 4; ++e) vb[buf][e] = v_row(kt * 16 + 4 * fq + e)[dt * 16 + fr];
+      if (kt * 16 + 16 > T) {                    // the weight of a padding column is 0, and 0 * inf would not be
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vb[buf][e] = kt * 16 + 4 * fq + e < T ? vb[buf][e] : 0.f;
       }
     };
     auto mul = [&](int buf, int kt) {
