@@ -11,8 +11,8 @@
 //   * O^T = V^T P^T: the probabilities a lane just produced are already the "B" operand of
 //     the second product (the contraction index is permuted identically on both operands), and
 //     every O^T accumulator of a lane belongs to that lane's query, so rescaling is lane-local;
-//   * V is read key-contiguous, from a [canvas, head, d_head, T] copy written by the rotary
-//     kernel; K and V^T tiles go global -> LDS directly, XOR-swizzled against bank conflicts,
+//   * V is read key-contiguous, from a [canvas, head, d_head, T rounded up to 64] copy written by the
+//     rotary kernel or the QKV projection's epilogue; K and V^T tiles go global -> LDS directly, XOR-swizzled against bank conflicts,
 //     double-buffered.
 #include "common.h"
 
@@ -81,7 +81,7 @@ struct WinArgs {
 // -inf, and their value columns are cleared in LDS.  These shapes used to take a vector-ALU kernel that kept the
 // probabilities in float32, so P goes into the second product as three bf16 parts (split3): all 24 bits of it, and an infinite
 // value gives an infinity as it does there.  The even shapes keep the single bf16 P they always had.  Per layer, 32 heads:
-// 3 canvases x 437 tokens 1196 us on that kernel, 34 with P in two parts (its last bits lost), 40 in three; four windows of 128
+// 3 canvases x 437 tokens 1196 us on that kernel, 34 with P in two parts (its last bits lost), 38 in three; four windows of 128
 // rows over 715 tokens 1496, 25.6 and 27.6.
 template <bool WIN, bool SPLIT, bool RAG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -162,6 +162,7 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[t][e] = 0.f;
   float m_run = -INFINITY;
+  float l_rag = 0.f;                                         // RAG: running sum of P over this lane's keys
   floatx16 ol;                                               // ol[0] in lanes 0..31: running sum of P for query lane
 #pragma unroll
   for (int e = 0; e < 16; ++e) ol[e] = 0.f;
@@ -269,7 +270,15 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
       for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[t][e] *= alpha;
-      ol[0] *= alpha;
+      if (RAG) l_rag *= alpha; else ol[0] *= alpha;
+    }
+    if (RAG) {
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part[i] += pr[RAG ? i : 0][e];
+      l_rag += (part[0] + part[1]) + (part[2] + part[3]);
     }
     // ---- O^T += V^T P^T : 4 d tiles x 4 key k-steps.  k slot (fh, e) of k-step ks2 is key
     //      16*ks2 + 4*fh + e (e < 4) or 16*ks2 + 8 + 4*fh + (e - 4): the order P came out in ----
@@ -285,9 +294,8 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
 #pragma unroll
         for (int i = 0; i < (RAG ? 3 : 1); ++i) o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, p3[i], o[t], 0, 0, 0);
       }
-      // row sums of P on the matrix pipe (a "V^T" row of ones): the vector ALU is the busier unit here
-#pragma unroll
-      for (int i = 0; i < (RAG ? 3 : 1); ++i) ol = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, p3[i], ol, 0, 0, 0);
+      // row sums of P on the matrix pipe (a "V^T" row of ones): the vector ALU is the busier unit here, but not with three parts
+      if (!RAG) ol = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, p3[0], ol, 0, 0, 0);
     }
   };
   for (int st = 0; st + 1 < n_steps; st += 2) {
@@ -295,7 +303,8 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
     tile(st + 1, std::integral_constant<int, 1>{});
   }
   if (n_steps & 1) tile(n_steps - 1, std::integral_constant<int, 0>{});
-  float l_run = __shfl(ol[0], fr, 64);                       // row 0 of that product: lane q % 32, register 0
+  // row 0 of that product: lane q % 32, register 0; RAG: the keys of this lane and of lane ^ 32
+  float l_run = RAG ? l_rag + __shfl_xor(l_rag, 32, 64) : __shfl(ol[0], fr, 64);
 
   if (SPLIT) {
     // pair 1 hands (O, running maximum, running sum) of its key tiles to the wave of pair 0 with the same queries;
