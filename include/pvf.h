@@ -23,7 +23,7 @@
  *     the last failing call on that context (or on the calling thread if ctx is NULL).
  *   - Matrices are row-major.  Weight matrices are [out_features, in_features], i.e.
  *     y = x * W^T.  dtype 0 = float32, 1 = bfloat16 (storage of weights, activations and
- *     logits; accumulation is always float32).
+ *     logits; sums are kept in float32 or, for float32 data, in float64).
  *   - Canvas positions: [0, prompt_len) prompt, then gen_len generated tokens split into
  *     gen_len / block_len blocks (App. A.1).  T = prompt_len + gen_len.
  *   - Window: the R = min(c*block_len, gen_len) canvas positions starting at the first
@@ -226,7 +226,8 @@ pvf_status pvf_epilogue(pvf_ctx *ctx, void *stream, const void *logits, int32_t 
  * made for (states are told apart by their canvas buffer; a caller who rewrites a canvas in place
  * between rounds must call pvf_state_init or run one round with kv_cache = 0).  Such a round first reads done / n_drafts / k_active back
  * (one stream synchronisation) to split the groups into refreshing and cached ones; the
- * cache memory (2 * n_layers * T * d_model elements per group) is allocated on first use.
+ * cache memory (2 * n_layers * T' * d_model elements per group, T' = T rounded up to a multiple of 64) is
+ * allocated on first use.
  *
  * forward + epilogue on the same stream, no synchronisation in between.  n_seq_host: if
  * > 0, the caller's count of live canvases sum_g (done[g] ? 0 : 1 + n_drafts[g]) as read

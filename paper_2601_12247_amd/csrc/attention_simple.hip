@@ -1,8 +1,8 @@
 // Non-causal multi-head attention, plain version: out = softmax(q k^T / sqrt(dh)) v over all
 // T keys of the same canvas, no mask of any kind (the denoiser sees the whole canvas, Sec. 2).
 // One block = 8 queries of one (canvas, head); the full score rows live in LDS.  Any d_head,
-// any dtype; this is the float32 path (dot products and sums in float64) and the fallback of
-// the MFMA kernel (float32 accumulation).
+// any dtype: the fallback of the two matrix-core kernels, for bf16 with d_head other than 128 (float32
+// accumulation) and float32 with d_head other than 16, 32, 64, 128 (dot products and sums in float64).
 #include "common.h"
 
 #include <type_traits>

@@ -6,7 +6,7 @@
 //           This kernel takes short rows (below 256 vectors of 16 bytes): one workgroup per row,
 //           two passes over it (max, then the sums), float64 exponentials and sums.  Longer rows
 //           get their entropy from stage 1's pass (epilogue.hip).
-//           x_w is rounded to float32 once (fl32(scale * logit)) like in stage 1.
+//           x_w is rounded to float32 once (fl32(scale * logit)) like in stage 1, and here t_w too.
 // select    the filtering rule: one thread per 32 vocabulary ids builds one bitmap word.
 #include "common.h"
 

@@ -3,7 +3,7 @@
 // stage 1  one pass over every live logits row: top-1 token (lowest id on ties, the [MASK]
 //          column excluded) and its softmax probability (Sec. 3, definitions of y-hat and p).
 //          The row is streamed once from HBM with 16-byte loads; the softmax itself is never
-//          written anywhere.
+//          written anywhere.  Calibration takes the row's entropy in the same pass (float64 sums).
 // stage 2 (the decisions on those summaries) lives in decision.hip.
 #include "common.h"
 

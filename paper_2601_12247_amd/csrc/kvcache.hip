@@ -7,7 +7,8 @@
 //
 // Kernels here: storing a full forward's K/V into the cache, token embedding / rotary embedding
 // of window rows at their own canvas positions, and the window attention (plain version: any
-// dtype and head size; float32 rows accumulate in float64 like the plain full attention).
+// dtype and head size; float32 rows accumulate in float64 like the plain full attention), which runs where
+// neither of the matrix-core attention kernels covers the head size.
 #include "common.h"
 
 #include <type_traits>
