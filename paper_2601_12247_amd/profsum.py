@@ -3,7 +3,7 @@
     python -m paper_2601_12247_amd.profsum <output dir> [--top N]
 
 * ``*_kernel_trace.csv``       -> calls, total, mean, min, max duration and share per kernel;
-  stage-1 launches are also split by grid size (one workgroup of 1024 threads per logits row).
+  stage-1 launches are also split by their rows (one workgroup per logits row).
 * ``*_counter_collection.csv`` -> mean counter value per dispatch, per kernel.  FETCH_SIZE and
   WRITE_SIZE are in KiB; the plain device-to-device copy that ``bench.py --pmc-reference``
   issues (256 MiB read, 256 MiB written) shows what the counters read for a known size.
@@ -37,7 +37,8 @@ def kernel_trace(path: str, top: int) -> None:
         k = short(r["Kernel_Name"])
         acc[k].append(d)
         if "stage1_vec" in k:
-            s1[int(r.get("Grid_Size", r.get("Grid_Size_X", 0)))].append(d)
+            wg = int(r.get("Workgroup_Size", r.get("Workgroup_Size_X", 1024)))
+            s1[int(r.get("Grid_Size", r.get("Grid_Size_X", 0))) // wg].append(d)
     tot = sum(sum(v) for v in acc.values())
     print(f"{'kernel':70s} {'calls':>6s} {'total_ms':>9s} {'avg_us':>9s} {'min_us':>8s} {'max_us':>8s} {'%':>6s}")
     for k, v in sorted(acc.items(), key=lambda kv: -sum(kv[1]))[:top]:
@@ -47,9 +48,8 @@ def kernel_trace(path: str, top: int) -> None:
     if g:
         n, t = sum(len(v) for v in g), sum(sum(v) for v in g)
         print(f"\nall gemm_bf16_mfma_kernel launches: {n} calls, mean {t / n / 1e3:.2f} us")
-    for grid, v in sorted(s1.items()):
-        print(f"stage1_vec_kernel grid {grid:8d} ({grid // 1024:5d} rows): calls {len(v):4d} mean {sum(v) / len(v) / 1e3:8.2f} us "
-              f"min {min(v) / 1e3:8.2f} us")
+    for rows, v in sorted(s1.items()):
+        print(f"stage1_vec_kernel {rows:5d} rows: calls {len(v):4d} mean {sum(v) / len(v) / 1e3:8.2f} us min {min(v) / 1e3:8.2f} us")
 
 
 def counters(path: str) -> None:
