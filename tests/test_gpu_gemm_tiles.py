@@ -18,12 +18,14 @@ import hashlib, sys, torch
 sys.path.insert(0, %r)
 from paper_2601_12247_amd import binding as B
 g = torch.Generator(device="cuda").manual_seed(11)
-M, N, K = 700, 1536, 512                       # ragged last row tile for every tile height
-A = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
-W = (torch.randn(N, K, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
-W2 = (torch.randn(2 * N, K, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
-R = torch.randn(M, N, device="cuda", generator=g).to(torch.bfloat16)
-outs = [B.gemm(A, W), B.gemm(A, W, residual=R), B.gemm_swiglu(A, W2)]
+M, N = 700, 1536                               # ragged last row tile for every tile height
+outs = []
+for K in (512, 576):                           # an even and an odd number of 64-k stages
+    A = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
+    W = (torch.randn(N, K, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    W2 = (torch.randn(2 * N, K, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    R = torch.randn(M, N, device="cuda", generator=g).to(torch.bfloat16)
+    outs += [B.gemm(A, W), B.gemm(A, W, residual=R), B.gemm_swiglu(A, W2)]
 torch.cuda.synchronize()
 print(" ".join(hashlib.sha256(o.view(torch.int16).cpu().numpy().tobytes()).hexdigest() for o in outs))
 """ % ROOT
@@ -39,7 +41,7 @@ def run_child(tile):
 
 def test_all_tile_shapes_agree_bit_for_bit():
     want = run_child("")                           # the shapes the cost model picks
-    assert len(want) == 3
-    for tile in range(10):
+    assert len(want) == 6
+    for tile in range(11):
         got = run_child(str(tile))
         assert got == want, f"tile shape {tile} differs from the default choice"
