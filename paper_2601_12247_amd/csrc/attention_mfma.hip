@@ -58,7 +58,7 @@ __device__ __forceinline__ void split3(const float *p, bf16x8 *x) {
 }
 
 // Rows of the key-contiguous value buffers hold T rounded up to a whole tile of keys (vt_stride); what lies beyond T is
-// never written and never used.
+// never used.
 //
 // Window mode (K/V-cached rounds): the queries are the R window rows of a canvas (qkv holds only
 // those rows); keys in the window [w0, w0 + n_valid) are read from there, every other key from the cache of the
