@@ -30,7 +30,7 @@ struct WinF32 {
 template <int KC, bool WIN>            // KC = d_head / 16
 __global__ void __launch_bounds__(256)
 attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int n_rows, int T, int n_heads,
-                     float inv_sqrt_dh, WinF32 wa) {
+                     float inv_sqrt_dh, const int32_t *__restrict__ n_live, WinF32 wa) {
   constexpr int dh = KC * 16;
   extern __shared__ float s_p[];       // [TQ][T16 + 4]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -38,6 +38,7 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
   const int q0 = blockIdx.x * TQ, head = blockIdx.y, seq = blockIdx.z;
   const int d = n_heads * dh;
   const int64_t ld = 3 * (int64_t)d;
+  if (n_live && seq >= *n_live) return;
   const float *fresh = qkv + (int64_t)seq * n_rows * ld + (int64_t)head * dh;      // q; k at + d, v at + 2 d
   const int n_tiles = (T + 15) / 16, stride = n_tiles * 16 + 4;
   int w0 = 0, w1 = T;                  // keys [w0, w1) are rows of this launch
@@ -151,7 +152,7 @@ size_t lds_bytes(int T) { return (size_t)TQ * ((T + 15) / 16 * 16 + 4) * sizeof(
 
 template <bool WIN>
 pvf_status launch(pvf_ctx *ctx, hipStream_t s, const float *qkv, float *out, int S, int n_rows, int T, int n_heads, int d_head,
-                  const WinF32 &wa) {
+                  const WinF32 &wa, const int32_t *n_live = nullptr) {
   const size_t lds = lds_bytes(T);
   const dim3 grid((n_rows + TQ - 1) / TQ, n_heads, S);
   const float isd = 1.0f / sqrtf((float)d_head);
@@ -160,7 +161,7 @@ pvf_status launch(pvf_ctx *ctx, hipStream_t s, const float *qkv, float *out, int
     static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(attention_f32_kernel<KC, WIN>), \
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
     PVF_HIP_CHECK(ctx, configured);                                                                                  \
-    attention_f32_kernel<KC, WIN><<<grid, 256, lds, s>>>(qkv, out, n_rows, T, n_heads, isd, wa);                     \
+    attention_f32_kernel<KC, WIN><<<grid, 256, lds, s>>>(qkv, out, n_rows, T, n_heads, isd, n_live, wa);             \
     break;                                                                                                           \
   }
   switch (d_head / 16) {
@@ -179,9 +180,11 @@ bool attention_f32_supported(int dtype, int T, int d_head) {
 }
 
 // qkv must already be rotated.
-pvf_status launch_attention_f32(pvf_ctx *ctx, hipStream_t s, const void *qkv, void *out, int S, int T, int n_heads, int d_head) {
+// n_live (may be NULL): device count of the canvases that are there, at most S.
+pvf_status launch_attention_f32(pvf_ctx *ctx, hipStream_t s, const void *qkv, void *out, int S, int T, int n_heads, int d_head,
+                                const int32_t *n_live) {
   if (S == 0) return PVF_OK;
-  return launch<false>(ctx, s, (const float *)qkv, (float *)out, S, T, T, n_heads, d_head, WinF32{});
+  return launch<false>(ctx, s, (const float *)qkv, (float *)out, S, T, T, n_heads, d_head, WinF32{}, n_live);
 }
 
 pvf_status launch_attention_window_f32(pvf_ctx *ctx, hipStream_t s, const void *qkv_w, const void *kc, const void *vc,

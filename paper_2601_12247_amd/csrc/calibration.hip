@@ -25,7 +25,7 @@ entropy_kernel(const T *__restrict__ logits, int vocab, int mask_id, float scale
   const int tid = threadIdx.x;
   int64_t out_row;
   if (!row_target(rf, blockIdx.x, &out_row)) {
-    if (tid == 0) ent[out_row] = 0.f;
+    if (tid == 0 && out_row >= 0) ent[out_row] = 0.f;
     return;
   }
   const T *__restrict__ p = logits + (int64_t)blockIdx.x * vocab;

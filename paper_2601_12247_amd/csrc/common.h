@@ -64,15 +64,17 @@ struct RowFilter {
   const int32_t *done;      // [G]
   const int32_t *k_active;  // [G]
   const int32_t *seq_slot;  // [n_seq] compact sequence -> slot g*(1+K)+j, or NULL (identity)
+  const int32_t *n_live;    // device count of compact sequences, or NULL: those behind it do not exist
   int32_t slots_per_group;  // 1+K
   int32_t R, prompt_len, block_len, T;
 };
 
-// Where a logits row's summary goes and whether the row exists at all.
+// Where a logits row's summary goes (-1: nowhere) and whether the row exists at all.
 __device__ __forceinline__ bool row_target(const RowFilter &rf, int64_t row, int64_t *out_row) {
   *out_row = row;
   if (rf.n_drafts == nullptr) return true;
   const int s = (int)(row / rf.R), r = (int)(row % rf.R);
+  if (rf.n_live && s >= *rf.n_live) { *out_row = -1; return false; }
   const int slot = rf.seq_slot ? rf.seq_slot[s] : s;
   const int g = slot / rf.slots_per_group, j = slot % rf.slots_per_group;
   *out_row = (int64_t)slot * rf.R + r;
@@ -102,9 +104,15 @@ pvf_status launch_plan_vocab_select(pvf_ctx *ctx, hipStream_t s, const uint32_t 
                                     uint32_t m_min, float rho_ver, float gamma_vig,
                                     uint32_t *plan_bitmap);
 
+// status (NULL: none; may be pinned host memory): status[5 g ..] = done, n_drafts, n_commit[0..2] of group g after the round.
+// skip_if_zero (NULL: never): device word; where it holds 0 the state stays as it is.
+struct Stage2Out {
+  int32_t *status = nullptr;
+  const int32_t *skip_if_zero = nullptr;
+};
 pvf_status launch_stage2(pvf_ctx *ctx, hipStream_t s, int G, int vocab, int mask_id,
                          const uint32_t *plan_bitmap, const pvf_decode_cfg &cfg,
-                         const pvf_state &st);
+                         const pvf_state &st, const Stage2Out &out = Stage2Out{});
 
 pvf_status launch_state_init(pvf_ctx *ctx, hipStream_t s, const int32_t *prompt, int G,
                              int mask_id, const pvf_decode_cfg &cfg, const pvf_state &st);
@@ -113,6 +121,11 @@ pvf_status launch_state_init(pvf_ctx *ctx, hipStream_t s, const int32_t *prompt,
 pvf_status launch_build_batch(pvf_ctx *ctx, hipStream_t s, int G, int n_seq,
                               const pvf_decode_cfg &cfg, const pvf_state &st,
                               int32_t *seq_slot, int32_t *row_pos);
+
+// the same, n_seq being an upper bound: *n_live = number of live slots, at most n_seq, whose entries alone are written (pad:
+// slot 0 where none is); and the embedding of their canvases (float32), h[s * T + t]
+pvf_status launch_embed_batch(pvf_ctx *ctx, hipStream_t s, int G, int n_seq, const pvf_decode_cfg &cfg, const pvf_state &st,
+                              const float *embed, int d, int vocab, bool pad, int32_t *seq_slot, int32_t *row_pos, int32_t *n_live, float *h);
 
 // block-level K/V cache (kvcache.hip)
 pvf_status launch_fill_row_pos(pvf_ctx *ctx, hipStream_t s, const pvf_decode_cfg &cfg, const pvf_state &st,
@@ -129,9 +142,6 @@ pvf_status launch_attention_window(pvf_ctx *ctx, hipStream_t s, int dtype, const
                                    const void *vc, int64_t group_stride, const pvf_decode_cfg &cfg,
                                    const pvf_state &st, const int32_t *seq_slot, int n_seq, int n_heads,
                                    int d_head, void *out);
-
-// out[5 g ..] = done, n_drafts, n_commit[0..2] of group g
-pvf_status launch_pack_status(pvf_ctx *ctx, hipStream_t s, int G, const pvf_state &st, int32_t *out);
 
 pvf_status launch_copy_out(pvf_ctx *ctx, hipStream_t s, int G, int K, int T,
                            const int32_t *canvas, int32_t *out_tokens);
@@ -176,6 +186,15 @@ struct RopeF32 {
   const float2 *cos_sin;
   const int32_t *row_pos;         // NULL: whole canvases
   int32_t T, half;
+};
+// Rows of a float32 projection.
+struct RowsF32 {
+  const float *gain = nullptr;    // the operand is RMSNorm(A) * gain
+  float eps = 0.f;
+  const int32_t *map = nullptr;   // row s * R + r is row s * T + map[s * R + r] of A and of the residual (zeros outside [0, T))
+  int32_t T = 0, R = 0;
+  const int32_t *n_live = nullptr;   // device: only the first *n_live * per_seq rows are computed
+  int32_t per_seq = 0;
 };
 // C[M,N] = A[M,K] W[N,K]^T; kEpiResidual adds residual[M,N]; kEpiSwiglu: W is [2N,K] (gate|up),
 // C[M,N] = silu(gate) * up.

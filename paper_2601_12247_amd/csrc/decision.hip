@@ -28,6 +28,7 @@ struct Stage2Args {
   pvf_state st;
   pvf_decode_cfg cfg;
   const uint32_t *plan_bitmap;
+  Stage2Out out;
   int32_t vocab, mask_id, R, T, n_blocks;
 };
 
@@ -91,6 +92,13 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   __shared__ int32_t s_blk[kMaxWinBlocks];   // masks per window block after the commit
   __shared__ int32_t s_winner, s_knew, s_done, s_wsnew;
 
+  if (a.out.skip_if_zero && *a.out.skip_if_zero == 0) return;
+  int32_t nc0 = 0, nc1 = 0, nc2 = 0;           // thread 0: n_commit of the group
+  auto report = [&](int is_done, int n_next) {
+    if (a.out.status == nullptr) return;
+    int32_t *w = a.out.status + 5 * (int64_t)g;
+    w[0] = is_done; w[1] = n_next; w[2] = nc0; w[3] = nc1; w[4] = nc2;
+  };
   uint8_t *accept = a.st.accept + (int64_t)g * K;
   int32_t *ncommit = a.st.n_commit + (int64_t)g * 3;
   const int ka = a.st.k_active[g], done = a.st.done[g];      // five loads on the way together
@@ -99,6 +107,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
     for (int j = tid; j < K; j += nth) accept[j] = 0;
     if (tid == 0) {
       a.st.winner[g] = 0; ncommit[0] = ncommit[1] = ncommit[2] = 0; a.st.n_drafts[g] = 0; a.st.done[g] = 1;
+      report(1, 0);
     }
     return;
   }
@@ -213,7 +222,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
       if (route == PVF_ROUTE_PLAN) { s_x[s_fpos[w - 1]] = s_ftok[w - 1]; n_plan = 1; }
       else { for (int r = 0; r < w; ++r) s_x[s_fpos[r]] = s_ftok[r]; n_ar = w; }
     }
-    ncommit[1] = n_plan; ncommit[2] = n_ar;
+    ncommit[1] = nc1 = n_plan; ncommit[2] = nc2 = n_ar;
     a.st.winner[g] = w;
   }
   __syncthreads();
@@ -277,7 +286,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
     __syncthreads();
     for (int i = tid; i < plen; i += nth) if (s_flag[i] == 2) xb[i] = tw[i];
     if (tid == 0) {
-      ncommit[0] = s_cnt[1];
+      ncommit[0] = nc0 = s_cnt[1];
       int total = masks_beyond;                  // masked positions of the whole canvas before this step's commits
       for (int b = 0; b < nwb; ++b) total += s_blk[b];
       int extra = 0;
@@ -303,7 +312,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
             if (pick-- == 0) { s_flag[i] = 2; xb[i] = t; extra = 1; break; }
           }
         }
-        ncommit[1] = extra;                      // reported in the planning slot of n_commit
+        ncommit[1] = nc1 = extra;                // reported in the planning slot of n_commit
       }
       s_cnt[1] += extra;
       if (total - s_cnt[1] == 0) s_done = 1;     // nothing left anywhere: no further forward
@@ -386,6 +395,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
     a.st.k_active[g] = k_new;
     a.st.n_ws_blocks[g] = ws_new;
     a.st.done[g] = s_done;
+    report(s_done, s_done ? 0 : K_next);
   }
 }
 
@@ -446,6 +456,56 @@ __global__ void build_batch_kernel(int G, int K, int n_seq, int R, int T, int pr
   }
 }
 
+// The batch and the embedding of its canvases in one launch, one wave per canvas position: every wave finds the slot behind
+// its compact sequence by the same prefix sum over the groups (64 at a time).  n_seq bounds the number of live slots, which
+// only the device knows; waves behind it end at once, and the launches that follow read *n_live.
+__global__ void __launch_bounds__(256)
+embed_batch_kernel(int G, int K, int n_seq, int R, int T, int prompt_len, int bl, pvf_state st, const float *__restrict__ embed,
+                   int d, int vocab, bool pad, int32_t *__restrict__ seq_slot, int32_t *__restrict__ row_pos,
+                   int32_t *__restrict__ n_live, float *__restrict__ h) {
+  const int64_t m = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (m >= (int64_t)n_seq * T) return;
+  const int s = (int)(m / T), t = (int)(m % T);
+  int n = 0, slot = -1;
+  for (int g0 = 0; g0 < G && n < n_seq; g0 += 64) {
+    const int g = g0 + lane;
+    int live = 0;
+    if (g < G) {
+      const int done = st.done[g], kt = st.n_drafts[g];
+      live = done ? 0 : 1 + (kt < 0 ? 0 : (kt > K ? K : kt));
+    }
+    int end = live;
+    for (int m2 = 1; m2 < 64; m2 <<= 1) {
+      const int v = __shfl_up(end, m2);
+      if (lane >= m2) end += v;
+    }
+    const int first = n + end - live;                // compact index of the group's backbone
+    const unsigned long long mine = __ballot(s >= first && s < first + live);
+    if (mine) {
+      const int at = __ffsll(mine) - 1;
+      slot = (g0 + at) * (1 + K) + s - __shfl(first, at);
+    }
+    n += __shfl(end, 63);
+  }
+  if (pad && n == 0) {                               // nothing is live: slot 0 stands in, as build_batch_kernel pads
+    n = 1;
+    if (s == 0) slot = 0;
+  }
+  if (m == 0 && lane == 0) *n_live = min(n, n_seq);
+  if (slot < 0) return;
+  if (t == 0) {
+    if (lane == 0) seq_slot[s] = slot;
+    const int w0 = prompt_len + st.k_active[slot / (1 + K)] * bl;
+    for (int r = lane; r < R; r += 64) row_pos[(int64_t)s * R + r] = w0 + r >= 0 && w0 + r < T ? w0 + r : -1;
+  }
+  int id = st.canvas[(int64_t)slot * T + t];
+  id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);  // ids are validated on the host; stay in bounds regardless
+  const float4 *src = reinterpret_cast<const float4 *>(embed + (int64_t)id * d);
+  float4 *dst = reinterpret_cast<float4 *>(h + m * d);
+  for (int i = lane; i < d / 4; i += 64) dst[i] = src[i];
+}
+
 __global__ void copy_out_kernel(int K, int T, const int32_t *__restrict__ canvas,
                                 int32_t *__restrict__ out) {
   const int g = blockIdx.x;
@@ -462,9 +522,9 @@ int window_rows(const pvf_decode_cfg &c) {
 
 pvf_status launch_stage2(pvf_ctx *ctx, hipStream_t s, int G, int vocab, int mask_id,
                          const uint32_t *plan_bitmap, const pvf_decode_cfg &cfg,
-                         const pvf_state &st) {
+                         const pvf_state &st, const Stage2Out &out) {
   Stage2Args a;
-  a.st = st; a.cfg = cfg; a.plan_bitmap = plan_bitmap; a.vocab = vocab; a.mask_id = mask_id;
+  a.st = st; a.cfg = cfg; a.out = out; a.plan_bitmap = plan_bitmap; a.vocab = vocab; a.mask_id = mask_id;
   a.T = cfg.prompt_len + cfg.gen_len;
   a.R = window_rows(cfg);
   a.n_blocks = cfg.gen_len / cfg.block_len;
@@ -493,19 +553,15 @@ pvf_status launch_build_batch(pvf_ctx *ctx, hipStream_t s, int G, int n_seq,
   return PVF_OK;
 }
 
-__global__ void pack_status_kernel(int G, pvf_state st, int32_t *__restrict__ out) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= G) return;
-  out[5 * g + 0] = st.done[g];
-  out[5 * g + 1] = st.n_drafts[g];
-  out[5 * g + 2] = st.n_commit[3 * g + 0];
-  out[5 * g + 3] = st.n_commit[3 * g + 1];
-  out[5 * g + 4] = st.n_commit[3 * g + 2];
-}
-
-pvf_status launch_pack_status(pvf_ctx *ctx, hipStream_t s, int G, const pvf_state &st, int32_t *out) {
-  pack_status_kernel<<<(G + 255) / 256, 256, 0, s>>>(G, st, out);
-  PVF_LAUNCH_CHECK(ctx, "pack_status");
+pvf_status launch_embed_batch(pvf_ctx *ctx, hipStream_t s, int G, int n_seq, const pvf_decode_cfg &cfg, const pvf_state &st,
+                              const float *embed, int d, int vocab, bool pad, int32_t *seq_slot, int32_t *row_pos, int32_t *n_live,
+                              float *h) {
+  const int T = cfg.prompt_len + cfg.gen_len;
+  const int64_t blocks = ((int64_t)n_seq * T + 3) / 4;
+  PVF_REQUIRE(ctx, blocks > 0 && blocks < (1ll << 31), PVF_ESHAPE, "embed_batch: %d canvases of %d", n_seq, T);
+  embed_batch_kernel<<<(unsigned)blocks, 256, 0, s>>>(G, cfg.K, n_seq, window_rows(cfg), T, cfg.prompt_len, cfg.block_len, st, embed, d,
+                                                      vocab, pad, seq_slot, row_pos, n_live, h);
+  PVF_LAUNCH_CHECK(ctx, "embed_batch");
   return PVF_OK;
 }
 

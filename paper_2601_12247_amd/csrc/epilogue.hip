@@ -176,7 +176,7 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
   const int tid = threadIdx.x;
   int64_t out_row;
   if (!row_target(rf, blockIdx.x, &out_row)) {
-    if (tid == 0) {
+    if (tid == 0 && out_row >= 0) {
       if (!kEnt || conf) { conf[out_row] = 0.f; tok[out_row] = -1; }
       if (kEnt) ent[out_row] = 0.f;
     }
@@ -366,7 +366,7 @@ stage1_scalar_kernel(const T *__restrict__ logits, int vocab, int mask_id, float
   const int tid = threadIdx.x;
   int64_t out_row;
   if (!row_target(rf, blockIdx.x, &out_row)) {
-    if (tid == 0) { conf[out_row] = 0.f; tok[out_row] = -1; }
+    if (tid == 0 && out_row >= 0) { conf[out_row] = 0.f; tok[out_row] = -1; }
     return;
   }
   const T *__restrict__ p = logits + (int64_t)blockIdx.x * vocab;

@@ -7,15 +7,20 @@
 // matrix rate (78 TFLOP/s in float64) -- and from a few thousand rows on that rate.  So
 //   * operands go from global memory straight into registers in operand layout, with no LDS and no barrier
 //     in the loop: a lane holds four consecutive k of its row (one 16-byte load) and feeds them to four MFMAs,
-//     the contraction index being permuted alike on both operands.  Two 16-k chunks are in flight per wave;
-//   * a workgroup computes a 32 x 32 tile (SwiGLU: 32 gate and the same 32 up columns); its four waves share K, each
-//     taking every fourth chunk, and their tiles are added through LDS in wave order.  Small launches get short
-//     loops that way, and large ones many equal workgroups: 64 x 64 tiles with a quarter per wave and K undivided
-//     were 0-30 % slower at 4 580 - 9 160 rows (they leave the last wave of workgroups emptier) and 5 % faster only
-//     where N = 4096.
-// Measured on the small model's shapes (us per launch, plain kernel -> this one): QKV of 384 rows 42 -> 10, gate/up
-// 62 -> 17, down 81 -> 12; gate/up of 9 160 rows 148 (44 TFLOP/s), output head 395 (49 TFLOP/s).
+//     the contraction index being permuted alike on both operands;
+//   * the four waves of a workgroup share K, each taking every fourth 16-k chunk, and their tiles are added through LDS in wave
+//     order.  Small launches get short loops that way, and large ones many equal workgroups.  The order in which an
+//     element's k are added is the same for every tile shape, so a row's bits do not depend on the launch's size;
+//   * tiles of 32 x 32 with one chunk ahead, at most 128 registers: four workgroups a CU instead of three cover each other's
+//     prologue and epilogue, which are half of a loop over 256 k (6 236 rows: QKV 60 -> 52 us, down projection 57 -> 52).  SwiGLU
+//     takes 32 rows x 16 gate and the same 16 up columns for the same reason (32 + 32 columns need 230 registers: 108 -> 89 us);
+//   * launches of at most 512 such tiles (two a CU) take 16 x 32 with two chunks ahead instead: twice as many workgroups with
+//     half the work each (384 rows: QKV 9.7 -> 8.2 us, down 12.1 -> 7.9; above, the bigger tile reads less: 52 against 62 us).
+// Measured on the small model's shapes (us per launch, plain vector-ALU kernel -> this one): QKV of 384 rows 42 -> 8, gate/up
+// 62 -> 11, down 81 -> 8; gate/up of 6 236 rows 89 (50 TFLOP/s), output head of 1 743 rows 75 (49 TFLOP/s).
 #include "common.h"
+
+#include <type_traits>
 
 namespace pvf {
 namespace {
@@ -24,33 +29,72 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double silu_f64(double g) { return g / (1.0 + exp(-g)); }
 
+// 1 / rms of a row that eight neighbouring threads share (j = 0..7), from float64 sums; every one of them gets it.  The fused
+// norm and the pass of its own take it from here, so that which of them a launch takes does not show in a bit.
+__device__ __forceinline__ float row_rnorm(const float *x, int j, int K, float eps) {
+  double ss = 0.0;
+  for (int k = 4 * j; k < K; k += 32) {
+    const float4 v = *reinterpret_cast<const float4 *>(x + k);
+    ss += ((double)v.x * v.x + (double)v.y * v.y) + ((double)v.z * v.z + (double)v.w * v.w);
+  }
+  ss += __shfl_xor(ss, 1); ss += __shfl_xor(ss, 2); ss += __shfl_xor(ss, 4);
+  return (float)(1.0 / sqrt(ss / K + (double)eps));
+}
+
+// out = RMSNorm(x) * gain, eight threads a row
+__global__ void __launch_bounds__(256)
+rmsnorm_f32_kernel(const float *__restrict__ x, const float *__restrict__ gain, float *__restrict__ out, int M, int K, float eps,
+                   const int32_t *__restrict__ n_live, int per_seq) {
+  const int m = blockIdx.x * 32 + (threadIdx.x >> 3), j = threadIdx.x & 7;
+  if (n_live) M = min(M, *n_live * per_seq);
+  if (m >= M) return;                                               // whole rows, so whole groups of eight
+  const float *xr = x + (int64_t)m * K;
+  const float r = row_rnorm(xr, j, K, eps);
+  for (int k = 4 * j; k < K; k += 32) {
+    const float4 v = *reinterpret_cast<const float4 *>(xr + k), g = *reinterpret_cast<const float4 *>(gain + k);
+    *reinterpret_cast<float4 *>(out + (int64_t)m * K + k) = make_float4(v.x * r * g.x, v.y * r * g.y, v.z * r * g.z, v.w * r * g.w);
+  }
+}
+
 // W row behind column c (0..31) of a 32-column wave tile: with the rotary epilogue the second 16 columns are the
 // rotation partners (+ d_head / 2) of the first 16, so that a pair meets in one lane.
-template <int EPI>
+template <int EPI, int TN>
 __device__ __forceinline__ int tile_col(int tile, int c, int half) {
-  if (EPI != kEpiQkvRope) return tile * 32 + c;
+  if (EPI != kEpiQkvRope) return tile * TN + c;
   const int per_head = half / 16;                                   // wave tiles per head
   const int head = tile / per_head, j = tile % per_head;
   return head * 2 * half + j * 16 + (c >= 16 ? half : 0) + (c & 15);
 }
 
-template <int EPI, bool VEC>
-__global__ void __launch_bounds__(256)
+// NORM: the operand is RMSNorm(A) * gain, each row's 1 / rms from float64 sums taken by the workgroup itself while its first
+// chunks are on the way, the elements rounded to float32 as the norm's own pass rounds them.  MAP: rows through RowsF32::map.
+template <int EPI, bool VEC, bool NORM, bool MAP, int MT, int NT, int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float *__restrict__ C,
-                const float *__restrict__ Res, int M, int N, int K, RopeF32 ra) {
-  constexpr int MT = 2, NT = 2, WK = 4;                             // 16 x 16 tiles in each direction; waves that share K
+                const float *__restrict__ Res, int M, int N, int K, RopeF32 ra, RowsF32 rw) {
+  constexpr int WK = 4;                                             // waves that share K
+  constexpr int TM = 16 * MT, TN = 16 * NT;
+  static_assert(EPI != kEpiQkvRope || NT == 2, "a rotation pair is two tiles wide");
   constexpr int NB = EPI == kEpiSwiglu ? 2 * NT : NT;               // SwiGLU: gate tiles, then up tiles
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int fr = lane & 15, fq = lane >> 4;
-  const int tiles_n = (N + 31) / 32;
-  const int tile_n = blockIdx.x % tiles_n, m0 = blockIdx.x / tiles_n * 32;
+  const int tiles_n = (N + TN - 1) / TN;
+  const int tile_n = blockIdx.x % tiles_n, m0 = blockIdx.x / tiles_n * TM;
 
-  const float *ap[MT], *wp[NB];
+  auto src_row = [&](int m, bool *ok) -> int64_t {                  // row of A and Res behind row m
+    *ok = true;
+    if constexpr (!MAP) return m;
+    const int s = m / rw.R, pos = rw.map[m];
+    *ok = pos >= 0 && pos < rw.T;
+    return (int64_t)s * rw.T + (*ok ? pos : 0);
+  };
+  const float *ap[MT], *wp[NB], *gp = rw.gain;
+  bool a_ok[MT];
 #pragma unroll
-  for (int t = 0; t < MT; ++t) ap[t] = A + (int64_t)min(m0 + t * 16 + fr, M - 1) * K;   // ragged edge: a valid row again
+  for (int t = 0; t < MT; ++t) ap[t] = A + src_row(min(m0 + t * 16 + fr, M - 1), &a_ok[t]) * K;   // ragged edge: a valid row again
 #pragma unroll
   for (int t = 0; t < NB; ++t) {
-    const int n = min(tile_col<EPI>(tile_n, (t % NT) * 16 + fr, ra.half), N - 1);
+    const int n = min(tile_col<EPI, TN>(tile_n, (t % NT) * 16 + fr, ra.half), N - 1);
     wp[t] = W + (int64_t)(t >= NT ? N + n : n) * K;
   }
   doublex4 acc[MT][NB];
@@ -59,7 +103,7 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
 
-  struct Chunk { float a[MT][4], w[NB][4]; };
+  struct Chunk { float a[MT][4], w[NB][4], g[NORM ? 4 : 1]; };
   const int n_chunks = (K + 15) / 16;
   auto fetch = [&](Chunk &c, int ch) {                              // 16 k from ch * 16; lanes past K hold zeros
     const int k = ch * 16 + 4 * fq;
@@ -76,26 +120,45 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
     for (int t = 0; t < MT; ++t) one(ap[t], c.a[t]);
 #pragma unroll
     for (int t = 0; t < NB; ++t) one(wp[t], c.w[t]);
+    if constexpr (NORM) one(gp, c.g);
   };
+  float rnorm[MT];
   auto multiply = [&](const Chunk &c) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+      for (int i = 0; i < MT; ++i) {
+        float a = c.a[i][e];
+        if constexpr (NORM) a = a * rnorm[i] * c.g[NORM ? e : 0];
+        if (MAP && !a_ok[i]) a = 0.f;
 #pragma unroll
         for (int j = 0; j < NB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)c.a[i][e], (double)c.w[j][e], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)c.w[j][e], acc[i][j], 0, 0, 0);
+      }
   };
-  // this wave's chunks wave, wave + 4, ...: two in registers ahead of the one being multiplied.  (One call of multiply: with
+  // this wave's chunks wave, wave + 4, ...: D - 1 in registers ahead of the one being multiplied.  (One call of multiply: with
   // the loop unrolled over the buffers the accumulators were copied between register files at every turn.)
-  Chunk c0, c1, c2;
-  fetch(c0, wave);
-  fetch(c1, wave + WK);
+  Chunk c[D];
+#pragma unroll
+  for (int i = 0; i + 1 < D; ++i) fetch(c[i], wave + i * WK);
+  if (rw.n_live && m0 >= *rw.n_live * rw.per_seq) return;           // uniform
+  if constexpr (NORM) {
+    __shared__ float s_r[TM];
+    const int row = threadIdx.x >> 3, j = threadIdx.x & 7;          // eight threads a row
+    if (row < TM) {
+      const float r = row_rnorm(A + (int64_t)min(m0 + row, M - 1) * K, j, K, rw.eps);
+      if (j == 0) s_r[row] = r;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < MT; ++t) rnorm[t] = s_r[t * 16 + fr];
+  }
 #pragma unroll 1
   for (int ch = wave; ch < n_chunks; ch += WK) {
-    fetch(c2, ch + 2 * WK);
-    multiply(c0);
-    c0 = c1; c1 = c2;
+    fetch(c[D - 1], ch + (D - 1) * WK);
+    multiply(c[0]);
+#pragma unroll
+    for (int i = 0; i + 1 < D; ++i) c[i] = c[i + 1];
   }
 
   // ---- wave w adds up register w of every tile (rows 4 w + lane / 16) over the four waves, in wave order ----
@@ -121,8 +184,10 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
     const int m = m0 + i * 16 + 4 * wave + fq;
     if (m >= M) continue;
     float *row = C + (int64_t)m * N;
+    bool r_ok = true;
+    const float *rrow = EPI == kEpiResidual ? Res + src_row(m, &r_ok) * N : nullptr;
     if (EPI == kEpiQkvRope) {
-      const int n = tile_col<EPI>(tile_n, fr, ra.half);           // and its partner n + half; N = 3 d is a whole number of heads
+      const int n = tile_col<EPI, TN>(tile_n, fr, ra.half);           // and its partner n + half; N = 3 d is a whole number of heads
       if (n >= N) continue;
       const float a = (float)v[i][0], b = (float)v[i][1];
       if (n < 2 * (N / 3)) {
@@ -138,50 +203,76 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
     }
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      const int n = tile_n * 32 + j * 16 + fr;
+      const int n = tile_n * TN + j * 16 + fr;
       if (n >= N) continue;
       double x = v[i][j];
-      if (EPI == kEpiResidual) x += (double)Res[(int64_t)m * N + n];
+      if (EPI == kEpiResidual && r_ok) x += (double)rrow[n];
       if (EPI == kEpiSwiglu) x = silu_f64(x) * v[i][NT + j];
       row[n] = (float)x;
     }
   }
 }
 
-template <int EPI>
+template <int EPI, bool NORM = false, bool MAP = false>
 pvf_status run_epi(pvf_ctx *ctx, hipStream_t s, const float *A, const float *W, float *C, const float *res, int M, int N, int K,
-                   const RopeF32 &ra) {
-  const bool vec = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15u) == 0;
-  const int64_t tiles = (int64_t)((N + 31) / 32) * ((M + 31) / 32);
-  PVF_REQUIRE(ctx, tiles < (1ll << 31), PVF_ESHAPE, "gemm_f32: M=%d N=%d", M, N);
-  const unsigned grid = (unsigned)tiles;
-  if (vec) gemm_f32_kernel<EPI, true><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra);
-  else gemm_f32_kernel<EPI, false><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra);
-  PVF_LAUNCH_CHECK(ctx, "gemm_f32");
-  return PVF_OK;
+                   const RopeF32 &ra, const RowsF32 &rw = RowsF32{}) {
+  const bool vec = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)rw.gain) & 15u) == 0;
+  auto launch = [&](auto mt, auto nt, auto depth) -> pvf_status {
+    constexpr int MT = decltype(mt)::value, NT = decltype(nt)::value, D = decltype(depth)::value;
+    const int64_t tiles = (int64_t)((N + 16 * NT - 1) / (16 * NT)) * ((M + 16 * MT - 1) / (16 * MT));
+    PVF_REQUIRE(ctx, tiles < (1ll << 31), PVF_ESHAPE, "gemm_f32: M=%d N=%d", M, N);
+    const unsigned grid = (unsigned)tiles;
+    if (vec) gemm_f32_kernel<EPI, true, NORM, MAP, MT, NT, D><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
+    else if constexpr (!NORM) gemm_f32_kernel<EPI, false, NORM, MAP, MT, NT, D><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
+    else PVF_REQUIRE(ctx, false, PVF_ESHAPE, "gemm_f32: the fused norm takes 16-byte aligned rows");
+    PVF_LAUNCH_CHECK(ctx, "gemm_f32");
+    return PVF_OK;
+  };
+  using std::integral_constant;
+  constexpr integral_constant<int, 1> k1{};
+  constexpr integral_constant<int, 2> k2{};
+  constexpr integral_constant<int, 3> k3{};
+  const int64_t tiles32 = (int64_t)((N + 31) / 32) * ((M + 31) / 32);
+  if constexpr (EPI == kEpiSwiglu) return launch(k2, k1, k2);
+  else return tiles32 <= 512 ? launch(k1, k2, k3) : launch(k2, k2, k2);
 }
 
 }  // namespace
 
 pvf_status launch_gemm_f32(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const float *A, const float *W, float *C,
-                           const float *res, int M, int N, int K) {
+                           const float *res, int M, int N, int K, const RowsF32 *rows) {
   if (M == 0 || N == 0) return PVF_OK;
   const RopeF32 none{};
+  const RowsF32 rw = rows ? *rows : RowsF32{};
   switch (epi) {
-    case kEpiStore: return run_epi<kEpiStore>(ctx, s, A, W, C, res, M, N, K, none);
-    case kEpiResidual: return run_epi<kEpiResidual>(ctx, s, A, W, C, res, M, N, K, none);
-    case kEpiSwiglu: return run_epi<kEpiSwiglu>(ctx, s, A, W, C, res, M, N, K, none);
+    case kEpiStore: return rw.gain ? run_epi<kEpiStore, true>(ctx, s, A, W, C, res, M, N, K, none, rw) : run_epi<kEpiStore>(ctx, s, A, W, C, res, M, N, K, none, rw);
+    case kEpiResidual: return rw.map ? run_epi<kEpiResidual, false, true>(ctx, s, A, W, C, res, M, N, K, none, rw) : run_epi<kEpiResidual>(ctx, s, A, W, C, res, M, N, K, none, rw);
+    case kEpiSwiglu: return rw.gain ? run_epi<kEpiSwiglu, true>(ctx, s, A, W, C, res, M, N, K, none, rw) : run_epi<kEpiSwiglu>(ctx, s, A, W, C, res, M, N, K, none, rw);
     default: PVF_REQUIRE(ctx, false, PVF_ENOTIMPL, "gemm_f32: epilogue %d has its own entry", (int)epi);
   }
+}
+
+// Whether the projections that read a normed stream of rows d long take the norm along.  Every workgroup of a row of tiles
+// norms the same rows again, half as many bytes once more as its main loop reads, which costs less than a launch and a pass
+// where rows and launches are short (1-3 canvases x 128 tokens, 256 wide: a round with five norms 157 -> 136 us) and more where
+// there are many rows (8 canvases x 229 with drafts: 565 -> 612): fused up to 1280 rows (forward_f32_impl).
+bool gemm_f32_norm_supported(int d) { return d <= 1024 && d % 4 == 0; }
+
+pvf_status launch_rmsnorm_f32(pvf_ctx *ctx, hipStream_t s, const float *x, float *out, int M, int K, const RowsF32 &rows) {
+  if (M == 0) return PVF_OK;
+  rmsnorm_f32_kernel<<<(M + 31) / 32, 256, 0, s>>>(x, rows.gain, out, M, K, rows.eps, rows.n_live, rows.per_seq);
+  PVF_LAUNCH_CHECK(ctx, "rmsnorm_f32");
+  return PVF_OK;
 }
 
 // QKV projection whose epilogue rotates q and k: qkv[M, 3 d] with d_head % 32 == 0.
 bool gemm_f32_qkv_rope_supported(int d_head) { return d_head % 32 == 0; }
 
 pvf_status launch_gemm_f32_qkv_rope(pvf_ctx *ctx, hipStream_t s, const float *A, const float *W, float *qkv, int M, int d, int K,
-                                    const RopeF32 &ra) {
+                                    const RopeF32 &ra, const RowsF32 *rows) {
   if (M == 0) return PVF_OK;
-  return run_epi<kEpiQkvRope>(ctx, s, A, W, qkv, nullptr, M, 3 * d, K, ra);
+  if (rows && rows->gain) return run_epi<kEpiQkvRope, true>(ctx, s, A, W, qkv, nullptr, M, 3 * d, K, ra, *rows);
+  return run_epi<kEpiQkvRope>(ctx, s, A, W, qkv, nullptr, M, 3 * d, K, ra, rows ? *rows : RowsF32{});
 }
 
 }  // namespace pvf

@@ -30,9 +30,12 @@ struct pvf_ctx {
   std::vector<void *> folded_owned;
   int32_t *seq_slot = nullptr, *row_pos = nullptr;
   float2 *cos_sin = nullptr;           // [max_T, d_head/2]
-  int32_t *status_host = nullptr;      // pinned, 5*G words per round: done, n_drafts, n_commit[3] of each group
-  int32_t *status_dev = nullptr;       // the same words, packed on the device by one small kernel
+  // pinned, written by stage 2 itself: 5*G words (done, n_drafts, n_commit[3] of each group) for each of the two rounds that
+  // pvf_decode may have under way, and the event behind each
+  int32_t *status_host = nullptr;
   int status_cap = 0;
+  hipEvent_t round_ev[2] = {nullptr, nullptr};
+  int32_t *n_live = nullptr;           // device: number of live canvases of the batch (float32 rounds)
   // block-level K/V cache (decode_cfg.kv_cache): [G][n_layers][vt_keys(T)][d] each, row-major like the
   // k / v thirds of the qkv buffer; cache_block[g] = active block the cache of group g is for
   void *kcache = nullptr, *vcache = nullptr;
@@ -88,11 +91,15 @@ struct ProfScope {
 // ---- dispatch between the MFMA kernels and the plain ones -------------------------------
 pvf_status launch_gemm_simple(pvf_ctx *, hipStream_t, GemmEpilogue, const bf16_t *, const bf16_t *, bf16_t *, const bf16_t *,
                               int, int, int);
-pvf_status launch_gemm_f32(pvf_ctx *, hipStream_t, GemmEpilogue, const float *, const float *, float *, const float *, int, int, int);
+pvf_status launch_gemm_f32(pvf_ctx *, hipStream_t, GemmEpilogue, const float *, const float *, float *, const float *, int, int, int,
+                           const RowsF32 *rows = nullptr);
+bool gemm_f32_norm_supported(int d);
+pvf_status launch_rmsnorm_f32(pvf_ctx *, hipStream_t, const float *, float *, int M, int K, const RowsF32 &);
 bool gemm_f32_qkv_rope_supported(int d_head);
-pvf_status launch_gemm_f32_qkv_rope(pvf_ctx *, hipStream_t, const float *, const float *, float *, int M, int d, int K, const RopeF32 &);
+pvf_status launch_gemm_f32_qkv_rope(pvf_ctx *, hipStream_t, const float *, const float *, float *, int M, int d, int K, const RopeF32 &,
+                                    const RowsF32 *rows = nullptr);
 bool attention_f32_supported(int dtype, int T, int d_head);
-pvf_status launch_attention_f32(pvf_ctx *, hipStream_t, const void *, void *, int, int, int, int);
+pvf_status launch_attention_f32(pvf_ctx *, hipStream_t, const void *, void *, int, int, int, int, const int32_t *n_live = nullptr);
 pvf_status launch_attention_window_f32(pvf_ctx *, hipStream_t, const void *, const void *, const void *, int64_t, const pvf_decode_cfg &,
                                        const pvf_state &, const int32_t *, int, int, int, void *);
 pvf_status launch_attention_simple(pvf_ctx *, hipStream_t, int, const void *, void *, int, int, int, int);
@@ -208,11 +215,12 @@ static void free_ws(pvf_ctx *c) {
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   c->ev_pool.clear();
   void *ptrs[] = {c->h, c->xn, c->qkv, c->att, c->act, c->vt, c->hrows, c->logits, c->seq_slot, c->row_pos, c->cos_sin,
-                  c->kcache, c->vcache, c->splitk_ws, c->status_dev, c->row_ss};
+                  c->kcache, c->vcache, c->splitk_ws, c->n_live, c->row_ss};
   for (void *p : ptrs) if (p) (void)hipFree(p);
   for (void *p : c->folded_owned) if (p) (void)hipFree(p);
   c->folded_owned.clear();
   if (c->status_host) (void)hipHostFree(c->status_host);
+  for (hipEvent_t e : c->round_ev) if (e) (void)hipEventDestroy(e);
   if (c->seq_host) (void)hipHostFree(c->seq_host);
 }
 
@@ -261,6 +269,7 @@ extern "C" pvf_status pvf_create(pvf_ctx **out, const pvf_model_cfg *m, const pv
       {&c->act, M * ff * (int64_t)c->esize},    {&c->hrows, rows * d * (int64_t)c->esize},
       {&c->logits, rows * (int64_t)m->vocab * (int64_t)c->esize},
       {(void **)&c->seq_slot, (int64_t)max_seqs * 4}, {(void **)&c->row_pos, rows * 4},
+      {(void **)&c->n_live, 4},
       {(void **)&c->cos_sin, (int64_t)max_T * half * 8},
       // partial sums of the few-row GEMMs: rows x splits x row length, at most 384 x 49152 floats (up to 384 rows
       // every layer GEMM may split, from there to 640 rows only those with rows of 4096 or less)
@@ -373,6 +382,88 @@ static pvf_status project_residual_norm(pvf_ctx *c, hipStream_t s, const void *A
   return launch_rmsnorm(c, s, dt, h, gain, out, M, d, c->model.rms_eps);
 }
 
+// Whether a float32 forward runs with the norms inside the projections (forward_f32_impl).
+static bool f32_fused(const pvf_ctx *c, int T) {
+  const pvf_model_cfg &m = c->model;
+  const int dh = m.d_model / m.n_heads;
+  if (m.dtype != PVF_F32 || !gemm_f32_qkv_rope_supported(dh) || !attention_f32_supported(PVF_F32, T, dh) || !gemm_f32_norm_supported(m.d_model)) return false;
+  uintptr_t al = (uintptr_t)c->w.out_head | (uintptr_t)c->w.final_norm;
+  for (int l = 0; l < m.n_layers; ++l)
+    al |= (uintptr_t)c->attn_norm[l] | (uintptr_t)c->wqkv[l] | (uintptr_t)c->ffn_norm[l] | (uintptr_t)c->w_gate_up[l];
+  return (al & 15u) == 0;
+}
+
+// The float32 forward of small models, in five launches a layer: the norms are taken by the projections that read them, and
+// behind the attention of the last layer the O projection picks the rows that logits are wanted for.  embedded: h holds the
+// embeddings already.  n_live (may be NULL): device count of the canvases that are there, at most S.
+// Small launches are bound by their number: a round of 1-3 canvases x 128 tokens has 14 launches where it had 23, and takes
+// 131 us where it took 182 (with the tile shapes of the projections and the attention's softmax as they are now).
+static pvf_status forward_f32_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens, const int32_t *seq_slot, int S, int T,
+                                   const int32_t *row_pos, int R, float *logits, int capture_spg, bool embedded, const int32_t *n_live) {
+  const pvf_model_cfg &m = c->model;
+  const int d = m.d_model, H = m.n_heads, dh = d / H, ff = m.d_ff, M = S * T, Mr = S * R;
+  float *h = (float *)c->h, *qkv = (float *)c->qkv, *att = (float *)c->att, *act = (float *)c->act, *hrows = (float *)c->hrows;
+  pvf_status st;
+#define RUN(x) do { st = (x); if (st != PVF_OK) return st; } while (0)
+  if (!embedded) RUN(launch_embed(c, s, PVF_F32, c->w.embed, tokens, seq_slot, S, T, d, m.vocab, h));
+  auto gemm = [&](GemmEpilogue epi, const float *A, const void *W, float *C, const float *res, int rows, int N, int K, const RowsF32 &rw) {
+    const double mats = epi == kEpiSwiglu ? 2 : 1;
+    ProfScope ps(c, s, PVF_PROF_GEMM, 2.0 * rows * (double)N * K * mats,
+                 4.0 * ((double)rows * K + (double)N * K * mats + (double)rows * N * (epi == kEpiResidual ? 2 : 1)));
+    return launch_gemm_f32(c, s, epi, A, (const float *)W, C, res, rows, N, K, &rw);
+  };
+  auto rows_of = [&](const void *gain, int per_seq) {
+    RowsF32 rw;
+    rw.gain = (const float *)gain; rw.eps = m.rms_eps; rw.n_live = n_live; rw.per_seq = per_seq;
+    return rw;
+  };
+  // x normed by a pass of its own into xn where the launch has many rows (see gemm_f32_norm_supported); rw then loses its gain
+  auto normed = [&](const float **x, int rows, RowsF32 *rw) -> pvf_status {
+    if (rows <= 1280) return PVF_OK;
+    pvf_status e = launch_rmsnorm_f32(c, s, *x, (float *)c->xn, rows, d, *rw);
+    *x = (const float *)c->xn;
+    rw->gain = nullptr;
+    return e;
+  };
+  const bool few_last = R < T;
+  for (int l = 0; l < m.n_layers; ++l) {
+    {
+      RowsF32 rw = rows_of(c->attn_norm[l], T);
+      const float *in = h;
+      RUN(normed(&in, M, &rw));
+      ProfScope ps(c, s, PVF_PROF_GEMM, 6.0 * M * (double)d * d, 4.0 * (4.0 * M * d + 3.0 * d * d));
+      RUN(launch_gemm_f32_qkv_rope(c, s, in, (const float *)c->wqkv[l], qkv, M, d, d, RopeF32{c->cos_sin, nullptr, T, dh / 2}, &rw));
+    }
+    {
+      ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)T * T * d, 0.0);
+      RUN(launch_attention_f32(c, s, qkv, att, S, T, H, dh, n_live));
+    }
+    if (capture_spg > 0) {
+      const int64_t layer_off = (int64_t)l * vt_keys(T) * d * 4, gstride = (int64_t)m.n_layers * vt_keys(T) * d;
+      RUN(launch_kv_store(c, s, PVF_F32, qkv, nullptr, seq_slot, capture_spg, S, T, d, (char *)c->kcache + layer_off,
+                          (char *)c->vcache + layer_off, nullptr, gstride));
+    }
+    const bool cut = few_last && l + 1 == m.n_layers;
+    const int rows = cut ? Mr : M, per_seq = cut ? R : T;
+    float *x = cut ? hrows : h;
+    RowsF32 ro = rows_of(nullptr, per_seq);
+    if (cut) { ro.map = row_pos; ro.T = T; ro.R = R; }
+    RUN(gemm(kEpiResidual, att, c->wo[l], x, h, rows, d, d, ro));
+    RowsF32 rg = rows_of(c->ffn_norm[l], per_seq);
+    const float *in = x;
+    RUN(normed(&in, rows, &rg));
+    RUN(gemm(kEpiSwiglu, in, c->w_gate_up[l], act, nullptr, rows, ff, d, rg));
+    RUN(gemm(kEpiResidual, act, c->w_down[l], x, x, rows, d, ff, rows_of(nullptr, per_seq)));
+  }
+  if (!few_last) RUN(launch_gather_rows(c, s, PVF_F32, h, row_pos, S, T, R, d, hrows));
+  RowsF32 rh = rows_of(c->w.final_norm, R);
+  const float *in = hrows;
+  RUN(normed(&in, Mr, &rh));
+  RUN(gemm(kEpiStore, in, c->w.out_head, logits, nullptr, Mr, m.vocab, d, rh));
+#undef RUN
+  return PVF_OK;
+}
+
 // tokens: [*, T] rows addressed through seq_slot (NULL = identity).  Writes logits [S, R, V].
 // capture_spg > 0: the rotated keys and the values of every backbone canvas of the batch (slot
 // index divisible by capture_spg) are stored into the context's K/V cache after each layer.
@@ -383,6 +474,7 @@ static pvf_status forward_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens,
   const int d = m.d_model, H = m.n_heads, dh = d / H, ff = m.d_ff, dt = m.dtype;
   const int M = S * T;
   pvf_status st;
+  if (f32_fused(c, T)) return forward_f32_impl(c, s, tokens, seq_slot, S, T, row_pos, R, (float *)logits, capture_spg, false, nullptr);
 #define RUN(x) do { st = (x); if (st != PVF_OK) return st; } while (0)
   const bool f32_rope = dt == PVF_F32 && gemm_f32_qkv_rope_supported(dh);
   const bool whole_tiles = T % 64 == 0;
@@ -599,7 +691,7 @@ extern "C" pvf_status pvf_plan_vocab_select(void *stream, const uint32_t *cal_n,
 
 static RowFilter make_filter(const pvf_decode_cfg &cfg, const pvf_state &st, const int32_t *seq_slot) {
   RowFilter rf;
-  rf.n_drafts = st.n_drafts; rf.done = st.done; rf.k_active = st.k_active; rf.seq_slot = seq_slot;
+  rf.n_drafts = st.n_drafts; rf.done = st.done; rf.k_active = st.k_active; rf.seq_slot = seq_slot; rf.n_live = nullptr;
   rf.slots_per_group = 1 + cfg.K; rf.R = window_rows(cfg);
   rf.prompt_len = cfg.prompt_len; rf.block_len = cfg.block_len; rf.T = cfg.prompt_len + cfg.gen_len;
   return rf;
@@ -647,22 +739,29 @@ static pvf_status check_round(pvf_ctx *ctx, int G, const uint32_t *plan_bitmap, 
 }
 
 static pvf_status round_cached_impl(pvf_ctx *ctx, hipStream_t s, int G, const uint32_t *plan_bitmap,
-                                    const pvf_decode_cfg &cfg, const pvf_state &state);
+                                    const pvf_decode_cfg &cfg, const pvf_state &state, int32_t *status);
 
+// status (may be NULL): where stage 2 reports.  ahead: the round may find every group done and then changes nothing (float32
+// rounds, whose launches read the number of live canvases from the device: n_seq is an upper bound of it).
 static pvf_status round_impl(pvf_ctx *ctx, hipStream_t s, int G, const uint32_t *plan_bitmap,
-                             const pvf_decode_cfg &cfg, const pvf_state &state, int n_seq) {
-  if (cfg.kv_cache) return round_cached_impl(ctx, s, G, plan_bitmap, cfg, state);
+                             const pvf_decode_cfg &cfg, const pvf_state &state, int n_seq, int32_t *status = nullptr, bool ahead = false) {
+  if (cfg.kv_cache) return round_cached_impl(ctx, s, G, plan_bitmap, cfg, state, status);
   const int T = cfg.prompt_len + cfg.gen_len, R = window_rows(cfg);
   const int all = G * (1 + cfg.K);
   if (n_seq <= 0 || n_seq > all) n_seq = all;
-  pvf_status st = launch_build_batch(ctx, s, G, n_seq, cfg, state, ctx->seq_slot, ctx->row_pos);
+  const bool fused = f32_fused(ctx, T);
+  pvf_status st = fused ? launch_embed_batch(ctx, s, G, n_seq, cfg, state, (const float *)ctx->w.embed, ctx->model.d_model, ctx->model.vocab,
+                                             !ahead, ctx->seq_slot, ctx->row_pos, ctx->n_live, (float *)ctx->h)
+                        : launch_build_batch(ctx, s, G, n_seq, cfg, state, ctx->seq_slot, ctx->row_pos);
   if (st != PVF_OK) return st;
   {
     ProfScope ps(ctx, s, PVF_PROF_FORWARD, 0.0, 0.0);
-    st = forward_impl(ctx, s, state.canvas, ctx->seq_slot, n_seq, T, ctx->row_pos, R, ctx->logits);
+    st = fused ? forward_f32_impl(ctx, s, state.canvas, ctx->seq_slot, n_seq, T, ctx->row_pos, R, (float *)ctx->logits, 0, true, ctx->n_live)
+               : forward_impl(ctx, s, state.canvas, ctx->seq_slot, n_seq, T, ctx->row_pos, R, ctx->logits);
   }
   if (st != PVF_OK) return st;
-  const RowFilter rf = make_filter(cfg, state, ctx->seq_slot);
+  RowFilter rf = make_filter(cfg, state, ctx->seq_slot);
+  if (fused) rf.n_live = ctx->n_live;
   {
     ProfScope ps(ctx, s, PVF_PROF_STAGE1, 0.0, (double)n_seq * R * ctx->model.vocab * (double)ctx->esize);
     st = launch_stage1(ctx, s, ctx->logits, ctx->model.dtype, (int64_t)n_seq * R, ctx->model.vocab,
@@ -671,14 +770,15 @@ static pvf_status round_impl(pvf_ctx *ctx, hipStream_t s, int G, const uint32_t 
   }
   if (st != PVF_OK) return st;
   ProfScope ps(ctx, s, PVF_PROF_STAGE2, 0.0, 0.0);
-  return launch_stage2(ctx, s, G, ctx->model.vocab, ctx->model.mask_id, plan_bitmap, cfg, state);
+  return launch_stage2(ctx, s, G, ctx->model.vocab, ctx->model.mask_id, plan_bitmap, cfg, state,
+                       Stage2Out{status, ahead && fused ? ctx->n_live : nullptr});
 }
 
 // kv_cache round: the backbone of a group whose active block differs from the block its cache was
 // made for (or that has no cache yet) gets the full forward, which also refills the cache; every
 // other canvas runs the window forward (after the full one, so it sees the fresh cache).  The sequence list is built on the host from a read-back of the state.
 static pvf_status round_cached_impl(pvf_ctx *ctx, hipStream_t s, int G, const uint32_t *plan_bitmap,
-                                    const pvf_decode_cfg &cfg, const pvf_state &state) {
+                                    const pvf_decode_cfg &cfg, const pvf_state &state, int32_t *status) {
   const pvf_model_cfg &m = ctx->model;
   const int T = cfg.prompt_len + cfg.gen_len, R = window_rows(cfg), spg = 1 + cfg.K;
   // cache memory
@@ -726,7 +826,7 @@ static pvf_status round_cached_impl(pvf_ctx *ctx, hipStream_t s, int G, const ui
   n_win = (int)win.size();
   for (int i = 0; i < n_win; ++i) h_seq[n_full + i] = win[i];
   const int n_seq = n_full + n_win;
-  if (n_seq == 0) return launch_stage2(ctx, s, G, m.vocab, m.mask_id, plan_bitmap, cfg, state);   // all done: reports an empty round
+  if (n_seq == 0) return launch_stage2(ctx, s, G, m.vocab, m.mask_id, plan_bitmap, cfg, state, Stage2Out{status, nullptr});   // all done: reports an empty round
   PVF_HIP_CHECK(ctx, hipMemcpyAsync(ctx->seq_slot, h_seq, n_seq * sizeof(int32_t), hipMemcpyHostToDevice, s));
   pvf_status st = launch_fill_row_pos(ctx, s, cfg, state, ctx->seq_slot, n_seq, ctx->row_pos);
   if (st != PVF_OK) return st;
@@ -751,25 +851,26 @@ static pvf_status round_cached_impl(pvf_ctx *ctx, hipStream_t s, int G, const ui
   }
   if (st != PVF_OK) return st;
   ProfScope ps(ctx, s, PVF_PROF_STAGE2, 0.0, 0.0);
-  return launch_stage2(ctx, s, G, m.vocab, m.mask_id, plan_bitmap, cfg, state);
+  return launch_stage2(ctx, s, G, m.vocab, m.mask_id, plan_bitmap, cfg, state, Stage2Out{status, nullptr});
 }
 
-// One round, then the 5 status words of every group (done, n_drafts, n_commit[3]) packed by one small
-// kernel, copied to the context's pinned buffer with one copy, and the stream synchronised.
+// Pinned room for the status words of two rounds of G groups.
+static pvf_status reserve_status(pvf_ctx *ctx, int G) {
+  if (ctx->status_cap >= 10 * G) return PVF_OK;
+  if (ctx->status_host) (void)hipHostFree(ctx->status_host);
+  ctx->status_host = nullptr; ctx->status_cap = 0;
+  PVF_HIP_CHECK(ctx, hipHostMalloc((void **)&ctx->status_host, (size_t)10 * G * sizeof(int32_t), hipHostMallocDefault));
+  ctx->status_cap = 10 * G;
+  return PVF_OK;
+}
+
+// One round whose stage 2 writes the 5 status words of every group (done, n_drafts, n_commit[3]) to the context's pinned
+// buffer, and the stream synchronised.
 static pvf_status round_status_impl(pvf_ctx *ctx, hipStream_t s, int G, const uint32_t *plan_bitmap,
                                     const pvf_decode_cfg &cfg, const pvf_state &state, int n_seq) {
-  if (ctx->status_cap < 5 * G) {
-    if (ctx->status_host) (void)hipHostFree(ctx->status_host);
-    if (ctx->status_dev) (void)hipFree(ctx->status_dev);
-    ctx->status_host = ctx->status_dev = nullptr; ctx->status_cap = 0;
-    PVF_HIP_CHECK(ctx, hipHostMalloc((void **)&ctx->status_host, (size_t)5 * G * sizeof(int32_t), hipHostMallocDefault));
-    PVF_HIP_CHECK(ctx, hipMalloc((void **)&ctx->status_dev, (size_t)5 * G * sizeof(int32_t)));
-    ctx->status_cap = 5 * G;
-  }
-  pvf_status st = round_impl(ctx, s, G, plan_bitmap, cfg, state, n_seq);
+  pvf_status st = reserve_status(ctx, G);
   if (st != PVF_OK) return st;
-  if ((st = launch_pack_status(ctx, s, G, state, ctx->status_dev)) != PVF_OK) return st;
-  PVF_HIP_CHECK(ctx, hipMemcpyAsync(ctx->status_host, ctx->status_dev, (size_t)5 * G * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  if ((st = round_impl(ctx, s, G, plan_bitmap, cfg, state, n_seq, ctx->status_host)) != PVF_OK) return st;
   PVF_HIP_CHECK(ctx, hipStreamSynchronize(s));
   return PVF_OK;
 }
@@ -817,17 +918,41 @@ extern "C" pvf_status pvf_decode(pvf_ctx *ctx, void *stream, const int32_t *prom
   if ((st = launch_state_init(ctx, s, prompt, G, ctx->model.mask_id, *cfg, *state)) != PVF_OK) return st;
   int n_seq = G;                                  // first round: backbones only
   const int max_rounds = cfg->gen_len + 2;        // every round commits at least one token per live group
+  // Rounds whose launches do not depend on the number of live canvases (float32) are enqueued one ahead: round r + 1 is on the
+  // stream before the host waits for the status of round r, so that the device never waits for the host.  The round behind the
+  // last one finds no live canvas and changes nothing.
+  const bool ahead = !cfg->kv_cache && !ctx->prof_on && f32_fused(ctx, cfg->prompt_len + cfg->gen_len);
+  if ((st = reserve_status(ctx, G)) != PVF_OK) return st;
+  if (ahead)
+    for (hipEvent_t &e : ctx->round_ev) if (!e) PVF_HIP_CHECK(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  auto enqueue = [&](int r, int bound) -> pvf_status {
+    pvf_status e = round_impl(ctx, s, G, plan_bitmap, *cfg, *state, bound, ctx->status_host + (r & 1) * 5 * G, true);
+    if (e != PVF_OK) return e;
+    PVF_HIP_CHECK(ctx, hipEventRecord(ctx->round_ev[r & 1], s));
+    return PVF_OK;
+  };
+  if (ahead && (st = enqueue(0, G)) != PVF_OK) { (void)hipStreamSynchronize(s); return st; }
+  int live_groups = G;
   while (n_seq > 0) {
     PVF_REQUIRE(ctx, acc.rounds < max_rounds, PVF_EINVAL, "pvf_decode: no progress after %d rounds", acc.rounds);
-    if ((st = round_status_impl(ctx, s, G, plan_bitmap, *cfg, *state, n_seq)) != PVF_OK) return st;
+    const int32_t *status = ctx->status_host;
+    if (ahead) {
+      const int r = acc.rounds;
+      // the last round allowed has none behind it
+      if (r + 1 < max_rounds && (st = enqueue(r + 1, live_groups * (1 + cfg->K))) != PVF_OK) { (void)hipStreamSynchronize(s); return st; }
+      PVF_HIP_CHECK(ctx, hipEventSynchronize(ctx->round_ev[r & 1]));
+      status += (r & 1) * 5 * G;
+    } else if ((st = round_status_impl(ctx, s, G, plan_bitmap, *cfg, *state, n_seq)) != PVF_OK) {
+      return st;
+    }
     acc.rounds += 1;
     acc.seq_forwards += n_seq;
-    n_seq = 0;
+    n_seq = live_groups = 0;
     for (int g = 0; g < G; ++g) {
-      const int32_t *w = ctx->status_host + 5 * g;            // done, n_drafts, n_commit[3]
+      const int32_t *w = status + 5 * g;                      // done, n_drafts, n_commit[3]
       acc.n_base += w[2]; acc.n_plan += w[3]; acc.n_ar += w[4];
       acc.drafts_accepted += (w[3] > 0) + w[4];
-      if (!w[0]) { n_seq += 1 + w[1]; acc.drafts_proposed += w[1]; }
+      if (!w[0]) { n_seq += 1 + w[1]; acc.drafts_proposed += w[1]; ++live_groups; }
     }
   }
   if ((st = launch_copy_out(ctx, s, G, cfg->K, cfg->prompt_len + cfg->gen_len, state->canvas, out_tokens)) != PVF_OK) return st;
