@@ -8,10 +8,12 @@
 //   * scores: the waves take every fourth tile of 16 keys; operands come from global memory in operand layout
 //     (16 bytes per lane = four consecutive d, the contraction permuted alike in q and k), the next tile's while
 //     this one's are multiplied; scores are rounded to float32 into LDS, rows padded against bank conflicts;
-//   * softmax in float32 like the plain kernel: four rows per wave;
+//   * softmax in float32 like the plain kernel: four rows per wave side by side, divided by their sum where they are read;
 //   * out: the waves take every fourth 16 columns of the head, all keys, so that nothing is added across waves;
-//     two accumulators alternate because a float64 MFMA that waits for the previous one idles the pipe.
-// Measured (per layer): 1-3 canvases x 128 tokens 28 -> 12 us, 8-40 canvases x 229 tokens 199 -> 58 us on average.
+//     two accumulators alternate because a float64 MFMA that waits for the previous one idles the pipe; values are
+//     fetched four tiles ahead, the first ones before the softmax (a tile is 256 cycles of MFMA, a load 1500).
+// Measured (per layer; plain kernel, one row at a time with values one tile ahead, now): 1-3 canvases x 128 tokens 28, 11, 9 us;
+// 8-40 canvases x 229 tokens 199, 53, 41 us on average.
 #include "common.h"
 
 namespace pvf {
@@ -33,6 +35,7 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
                      float inv_sqrt_dh, const int32_t *__restrict__ n_live, WinF32 wa) {
   constexpr int dh = KC * 16;
   extern __shared__ float s_p[];       // [TQ][T16 + 4]
+  __shared__ float s_inv[TQ];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int fr = lane & 15, fq = lane >> 4;
   const int q0 = blockIdx.x * TQ, head = blockIdx.y, seq = blockIdx.z;
@@ -94,51 +97,85 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
     if (kt + 8 < n_tiles) fetch_k(0, kt + 8);
     score(1, kt + 4);
   }
-  __syncthreads();
-
-  // ---- softmax over each row (the padding columns hold -inf, so their weight is 0) ----
-  for (int r = wave * 4; r < wave * 4 + 4; ++r) {
-    float *pr = s_p + r * stride;
-    float m = -INFINITY;
-    for (int k = lane; k < n_tiles * 16; k += kWave) m = fmaxf(m, pr[k]);
-    m = wave_max(m);
-    float z = 0.f;
-    for (int k = lane; k < n_tiles * 16; k += kWave) {
-      const float e = expf(pr[k] - m);
-      pr[k] = e; z += e;
+  // values of the first kVRing tiles: on the way while the softmax runs
+  constexpr int kVRing = 4;
+  float vb[kVRing][4];
+  auto fetch_v = [&](float *v, int dt, int kt) {
+    if (kt >= n_tiles) return;
+    if (!WIN && kt * 16 + 16 <= T) {             // rows of this launch at a fixed distance
+      const float *p = fresh + 2 * d + (int64_t)(kt * 16 + 4 * fq) * ld + dt * 16 + fr;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = p[e * ld];
+      return;
     }
-    z = wave_sum(z);
-    const float inv = 1.0f / z;
-    for (int k = lane; k < n_tiles * 16; k += kWave) pr[k] *= inv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = v_row(kt * 16 + 4 * fq + e)[dt * 16 + fr];
+    if (kt * 16 + 16 > T) {                      // the weight of a padding column is 0, and 0 * inf would not be
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = kt * 16 + 4 * fq + e < T ? v[e] : 0.f;
+    }
+  };
+  if (wave < KC) {
+#pragma unroll
+    for (int i = 0; i < kVRing; ++i) fetch_v(vb[i], wave, i);
   }
   __syncthreads();
+
+  // ---- softmax over each row (the padding columns hold -inf, so their weight is 0): the wave's four rows side by side,
+  // sixteen lanes each, because one row after the other is a chain of 12 shuffles a row.  A row is summed up as if its lanes
+  // were a whole wave (keys k, k + 64, .. in one sum, then halves, quarters, ..). ----
+  float *pr = s_p + (wave * 4 + fq) * stride;
+  {
+    float m = -INFINITY;
+#pragma unroll 4
+    for (int kt = 0; kt < n_tiles; ++kt) m = fmaxf(m, pr[kt * 16 + fr]);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    float z[4] = {0.f, 0.f, 0.f, 0.f};
+    int kt = 0;
+    for (; kt + 4 <= n_tiles; kt += 4) {
+      float e[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) e[i] = expf(pr[(kt + i) * 16 + fr] - m);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { pr[(kt + i) * 16 + fr] = e[i]; z[i] += e[i]; }
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (kt + i < n_tiles) {
+        const float e = expf(pr[(kt + i) * 16 + fr] - m);
+        pr[(kt + i) * 16 + fr] = e; z[i] += e;
+      }
+    float t = (z[0] + z[2]) + (z[1] + z[3]);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o);
+    if (fr == 0) s_inv[wave * 4 + fq] = 1.0f / t;
+  }
+  __syncthreads();
+  const float inv = s_inv[fr];         // of the query whose weights this lane reads
 
   // ---- out: row = query, column = lane % 16 of the wave's 16 columns ----
   for (int dt = wave; dt < KC; dt += 4) {
     doublex4 o0 = {0.0, 0.0, 0.0, 0.0}, o1 = o0;
-    float vb[2][4];
-    auto fetch_v = [&](int buf, int kt) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) vb[buf][e] = v_row(kt * 16 + 4 * fq + e)[dt * 16 + fr];
-      if (kt * 16 + 16 > T) {                    // the weight of a padding column is 0, and 0 * inf would not be
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vb[buf][e] = kt * 16 + 4 * fq + e < T ? vb[buf][e] : 0.f;
-      }
-    };
     auto mul = [&](int buf, int kt) {
       const float4 p = *reinterpret_cast<const float4 *>(s_p + fr * stride + kt * 16 + 4 * fq);
-      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.x, (double)vb[buf][0], o0, 0, 0, 0);
-      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.y, (double)vb[buf][1], o1, 0, 0, 0);
-      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.z, (double)vb[buf][2], o0, 0, 0, 0);
-      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.w, (double)vb[buf][3], o1, 0, 0, 0);
+      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.x * inv), (double)vb[buf][0], o0, 0, 0, 0);
+      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.y * inv), (double)vb[buf][1], o1, 0, 0, 0);
+      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.z * inv), (double)vb[buf][2], o0, 0, 0, 0);
+      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.w * inv), (double)vb[buf][3], o1, 0, 0, 0);
     };
-    fetch_v(0, 0);
-    for (int kt = 0; kt < n_tiles; kt += 2) {
-      if (kt + 1 < n_tiles) fetch_v(1, kt + 1);
-      mul(0, kt);
-      if (kt + 1 >= n_tiles) break;
-      if (kt + 2 < n_tiles) fetch_v(0, kt + 2);
-      mul(1, kt + 1);
+    if (dt != wave) {
+#pragma unroll
+      for (int i = 0; i < kVRing; ++i) fetch_v(vb[i], dt, i);
+    }
+    for (int kt = 0; kt < n_tiles; kt += kVRing) {
+#pragma unroll
+      for (int i = 0; i < kVRing; ++i) {
+        if (kt + i < n_tiles) {
+          mul(i, kt + i);
+          fetch_v(vb[i], dt, kt + i + kVRing);
+        }
+      }
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -159,7 +196,7 @@ pvf_status launch(pvf_ctx *ctx, hipStream_t s, const float *qkv, float *out, int
 #define PVF_ATT_CASE(KC)                                                                                             \
   case KC: {                                                                                                         \
     static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void *>(attention_f32_kernel<KC, WIN>), \
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 64); \
     PVF_HIP_CHECK(ctx, configured);                                                                                  \
     attention_f32_kernel<KC, WIN><<<grid, 256, lds, s>>>(qkv, out, n_rows, T, n_heads, isd, n_live, wa);             \
     break;                                                                                                           \
@@ -176,7 +213,7 @@ pvf_status launch(pvf_ctx *ctx, hipStream_t s, const float *qkv, float *out, int
 }  // namespace
 
 bool attention_f32_supported(int dtype, int T, int d_head) {
-  return dtype == PVF_F32 && (d_head == 16 || d_head == 32 || d_head == 64 || d_head == 128) && lds_bytes(T) <= 160 * 1024;
+  return dtype == PVF_F32 && (d_head == 16 || d_head == 32 || d_head == 64 || d_head == 128) && lds_bytes(T) <= 160 * 1024 - 64;
 }
 
 // qkv must already be rotated.
