@@ -142,7 +142,8 @@ __device__ __forceinline__ double exp_f64(double t) {
 }
 
 // Entropy sums of one thread (calibration), relative to its own running max m of the scaled logits x: S = sum e^t,
-// U = sum t e^t, t = x - m, all in float64, as the entropy of short rows has them.  Bound by the vector ALU: 13 float64
+// U = sum t e^t, t = x - m, all in float64, as the entropy of short rows has them (float32 rows, and the bf16 rows that
+// stage1_hist_kernel leaves).  Bound by the vector ALU: 13 float64
 // instructions an element, which take twice the slots of float32 ones here.  2112 rows of 126464: bf16 240 us, float32 265; the
 // same pass over a float32 exponential with its argument corrected 165 and 205, but 1-3 % of its bf16 entropies were an ulp off
 // where these are all the exact value rounded once; a float64 exponential of the library in a pass of its own 737 and 786.  Four
@@ -167,7 +168,10 @@ struct EntropySums {
 };
 
 // kEnt: the row's entropy too, and conf from its sums (conf, tok may then be NULL).
-template <typename T, int BLOCK, int U, bool kEnt, bool kFine>
+// kMarked: only rows whose entropy is kRereadRow.
+constexpr uint32_t kRereadRow = 0x7fc0cafeu;     // a NaN that no computation makes
+
+template <typename T, int BLOCK, int U, bool kEnt, bool kFine, bool kMarked = false>
 __global__ void __launch_bounds__(BLOCK)
 stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float scale,
                   RowFilter rf, float *__restrict__ conf, int32_t *__restrict__ tok, float *__restrict__ ent) {
@@ -182,6 +186,7 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
     }
     return;
   }
+  if (kMarked && __float_as_uint(ent[out_row]) != kRereadRow) return;
   constexpr bool kAnywhere = kEnt || kFine;      // the plain terms are for aligned rows
   // Rows of a vocabulary that is no multiple of N begin anywhere: up to N - 1 elements in front of the first whole vector and
   // behind the last one are taken by single threads.
@@ -358,6 +363,217 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
   }
 }
 
+// Entropy, confidence and top-1 token of long bf16 rows (calibration) from a histogram: a bf16 row holds few distinct values,
+// so the row is counted into LDS, 8192 counters for both signs of 32 exponents, and the float64 exponential is taken once
+// per value that occurs instead of once per element -- the same terms as EntropySums adds, each weighted by its count.  The
+// range ends four exponents above the largest one among the row's first 4096 elements; what lies outside goes to a list (1024
+// entries) or, from -1.7e38 down, adds nothing beside any larger value.  Rows of which this does not hold (more such elements,
+// NaN, a maximum as low as that) are left to stage1_vec_kernel in a launch behind this one (3 us where there are none); so are
+// rows of few values, told by equal neighbours in that sample: equal values of a wave wait for each other at their counter, and
+// from a chance of 1 / 32 for two elements to be equal on an exponential for each is the quicker way (2112 rows of 126464:
+// one value 170 against 970 us, 11 values 230 against 720).
+// Bound by HBM and the LDS atomics together (2112 rows of 126464 210 -> 108 us, 5 TB/s): per two elements 4 packed instructions for the counters' addresses, 3 for the
+// maximum, 4 more, and 2 atomics.
+constexpr int kHistBlock = 512, kHistBins = 8192, kHistList = 1024;
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+
+// y = bits - low of an element (16 bits): in range where bits 12..14 are 0; its counter is y ^ (y >> 3), 13 bits of it, which
+// brings the sign down to bit 12 and permutes the other 12.
+__device__ __forceinline__ float hist_value(int bin, uint32_t low) {
+  uint32_t t = (uint32_t)bin & 0xfffu;
+  t ^= t >> 3;
+  t ^= t >> 6;
+  return __uint_as_float((t + low + (((uint32_t)bin & 0x1000u) << 3)) << 16);
+}
+
+__global__ void __launch_bounds__(kHistBlock) __attribute__((amdgpu_waves_per_eu(8, 8)))
+stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, float scale, RowFilter rf, float *__restrict__ conf,
+                   int32_t *__restrict__ tok, float *__restrict__ ent) {
+  constexpr int N = 8, U = 2, kStride = kHistBlock * U;
+  __shared__ uint32_t s_hist[kHistBins];
+  __shared__ uint16_t s_list[kHistList];
+  __shared__ int s_n, s_low, s_nan;                      // list entries; whether an element below -1.7e38, a NaN occurred
+  __shared__ int s_match, s_top;                         // of the sample: equal neighbours, largest exponent
+  __shared__ float s_f[kHistBlock / kWave];
+  __shared__ int s_i[kHistBlock / kWave];
+  __shared__ double s_d[2 * (kHistBlock / kWave)];
+  const int tid = threadIdx.x, lane = tid % kWave, wid = tid / kWave;
+  int64_t out_row;
+  if (!row_target(rf, blockIdx.x, &out_row)) {
+    if (tid == 0 && out_row >= 0) {
+      if (conf) { conf[out_row] = 0.f; tok[out_row] = -1; }
+      ent[out_row] = 0.f;
+    }
+    return;
+  }
+  const bf16_t *__restrict__ row = logits + (int64_t)blockIdx.x * vocab;
+  const int head = (int)((16u - ((uint32_t)reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) / 2;
+  const uint4 *__restrict__ p = reinterpret_cast<const uint4 *>(row + head);
+  const int nvec = (vocab - head) / N;
+  const int mask_vec = mask_id >= head ? (mask_id - head) / N : INT_MAX, mask_lane = mask_id >= head ? (mask_id - head) % N : 0;
+  const uint4 sample = p[tid];                           // nvec >= 2500
+  for (int i = tid; i < kHistBins / 4; i += kHistBlock) reinterpret_cast<uint4 *>(s_hist)[i] = make_uint4(0, 0, 0, 0);
+  if (tid == 0) s_n = s_low = s_nan = s_match = s_top = 0;
+  __syncthreads();
+  {
+    const uint32_t w[4] = {sample.x, sample.y, sample.z, sample.w};
+    int match = 0, top = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t o = __shfl(w[i], (lane + 1) & (kWave - 1));
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t a = h ? w[i] >> 16 : w[i] & 0xffffu, b = h ? o >> 16 : o & 0xffffu;
+        match += __popcll(__ballot(a == b && a < 0xff00u));
+        const int e = (int)(a >> 7) & 0xff;
+        if (e < 254 && !(tid == mask_vec && 2 * i + h == mask_lane)) top = max(top, e);
+      }
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, kWave));
+    if (lane == 0) { atomicAdd(&s_match, match); atomicMax(&s_top, top); }
+  }
+  __syncthreads();
+  if (s_match > kHistBlock * N / 32) {                   // uniform
+    if (tid == 0) ent[out_row] = __uint_as_float(kRereadRow);
+    return;
+  }
+  const uint32_t low = (uint32_t)max((s_top ? s_top : 127) - 27, 0) << 7;      // bits of the smallest value counted
+
+  float m = kNegInf;
+  int first = INT_MAX, cnt = 0;                          // vectors first, first + BLOCK, .. (cnt of them) raised m; cnt = 0: element first
+  auto count_one = [&](uint32_t u) {                     // 16 bits of one element, whatever it is
+    const uint32_t y = (u - low) & 0xffffu;
+    if (!(y & 0x7000u)) { atomicAdd(&s_hist[(y ^ (y >> 3)) & 0x1fffu], 1u); return; }
+    if (u == 0xff80u) return;                            // -inf
+    if (u >= 0xff00u && u < 0xff80u) { s_low = 1; return; }
+    if ((u & 0x7fffu) > 0x7f80u) { s_nan = 1; return; }
+    if (s_n > kHistList) return;                         // full: the row is read again
+    const int at = atomicAdd(&s_n, 1);
+    if (at < kHistList) s_list[at] = (uint16_t)u;
+  };
+  auto single = [&](int id) {
+    if (id == mask_id) return;
+    const float v = to_float(row[id]);
+    if (v > m) { m = v; first = id; cnt = 0; }
+    count_one(__float_as_uint(v) >> 16);
+  };
+  // UV vectors of this thread from `base`, BLOCK apart
+  auto vectors = [&](int base, auto uv, auto check_mask) {
+    constexpr int UV = decltype(uv)::value;
+    uint4 w[UV];
+#pragma unroll
+    for (int u = 0; u < UV; ++u) w[u] = load_stream(p + base + u * kHistBlock);
+    __builtin_amdgcn_sched_barrier(0);                   // issue all loads before touching any result
+    uint32_t b[UV][4];
+#pragma unroll
+    for (int u = 0; u < UV; ++u) {
+      b[u][0] = w[u].x; b[u][1] = w[u].y; b[u][2] = w[u].z; b[u][3] = w[u].w;
+      if (decltype(check_mask)::value && base + u * kHistBlock == mask_vec) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+          if (i == mask_lane) b[u][i / 2] = i & 1 ? (b[u][i / 2] & 0xffffu) | 0xff800000u : (b[u][i / 2] & 0xffff0000u) | 0xff80u;
+      }
+    }
+    float gm = kNegInf;
+    uint32_t bad = 0;
+    const ushort2v low2 = {(unsigned short)low, (unsigned short)low};
+#pragma unroll
+    for (int u = 0; u < UV; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        gm = fmaxf(fmaxf(gm, __uint_as_float(b[u][i] << 16)), __uint_as_float(b[u][i] & 0xffff0000u));
+        const ushort2v y = __builtin_bit_cast(ushort2v, b[u][i]) - low2;
+        bad |= __builtin_bit_cast(uint32_t, y);
+      }
+    if (gm > m) { m = gm; first = base; cnt = UV; }
+    if ((bad & 0x70007000u) == 0) {
+#pragma unroll
+      for (int u = 0; u < UV; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          constexpr ushort2v k3 = {3, 3}, k2 = {2, 2};
+          const ushort2v y = __builtin_bit_cast(ushort2v, b[u][i]) - low2;
+          const ushort2v z = (y ^ (y >> k3)) << k2;      // byte address, bit 15 apart
+          const uint32_t zz = __builtin_bit_cast(uint32_t, z);
+          atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(s_hist) + (zz & 0x7fffu)), 1u);
+          atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(s_hist) + ((zz >> 16) & 0x7fffu)), 1u);
+        }
+    } else {
+#pragma unroll 1
+      for (int i = 0; i < UV * 4; ++i) {
+        uint32_t x = b[0][0];
+#pragma unroll
+        for (int q = 1; q < UV * 4; ++q) x = i == q ? b[q / 4][q % 4] : x;
+        count_one(x & 0xffffu);
+        count_one(x >> 16);
+      }
+    }
+  };
+  if (tid < head) single(tid);
+  const int nfull = nvec / kStride, it_mask = mask_vec / kStride;
+  const std::integral_constant<int, U> all{};
+  const int split = it_mask < nfull ? it_mask : nfull;
+  for (int it = 0; it < split; ++it) vectors(it * kStride + tid, all, std::false_type{});
+  if (it_mask < nfull) vectors(it_mask * kStride + tid, all, std::true_type{});
+  for (int it = split + 1; it < nfull; ++it) vectors(it * kStride + tid, all, std::false_type{});
+  for (int idx = nfull * kStride + tid; idx < nvec; idx += kHistBlock) vectors(idx, std::integral_constant<int, 1>{}, std::true_type{});
+  if (tid < vocab - head - nvec * N) single(head + nvec * N + tid);
+  float M = wave_max(m);
+  if (lane == 0) s_f[wid] = M;
+  __syncthreads();                                       // and every element is counted
+  M = s_f[0];
+#pragma unroll
+  for (int i = 1; i < kHistBlock / kWave; ++i) M = fmaxf(M, s_f[i]);
+  if (s_n > kHistList || s_nan || (s_low && !(M > -1e38f))) {           // uniform
+    if (tid == 0) ent[out_row] = __uint_as_float(kRereadRow);
+    return;
+  }
+  // S = sum e^t, T = sum t e^t, t = x - max x, over the values that occur
+  const double xm = (double)mul_rn(M, scale);
+  double S = 0.0, T = 0.0;
+  auto add = [&](float v, double n) {
+    const float x = mul_rn(v, scale);
+    const double t = (double)x - xm;
+    if (x == kNegInf || t < -700.0) return;              // e^t < 1e-304; a NaN goes through to the sums
+    const double e = exp_f64(t);
+    S = fma(n, e, S);
+    T = fma(n * t, e, T);
+  };
+  for (int i = tid; i < kHistBins; i += kHistBlock) {
+    const uint32_t n = s_hist[i];
+    if (n) add(hist_value(i, low), (double)n);
+  }
+  for (int i = tid; i < s_n; i += kHistBlock) add(__uint_as_float((uint32_t)s_list[i] << 16), 1.0);
+  wave_sum2(S, T);
+  if (lane == 0) { s_d[2 * wid] = S; s_d[2 * wid + 1] = T; }
+  // ---- arg-max: lowest id attaining M; a thread whose own maximum is M reads the vectors in which it first met it again ----
+  int cand = INT_MAX;
+  if (m == M && cnt == 0) cand = first;
+  else if (m == M) {
+    for (int u = 0; u < cnt && cand == INT_MAX; ++u) {
+      const int idx = first + u * kHistBlock;
+      float f[N];
+      Vec16<bf16_t>::unpack(p[idx], f);
+#pragma unroll
+      for (int i = N - 1; i >= 0; --i)
+        if (head + idx * N + i != mask_id && f[i] == M) cand = head + idx * N + i;
+    }
+  }
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) cand = min(cand, __shfl_xor(cand, o, kWave));
+  if (lane == 0) s_i[wid] = cand;
+  __syncthreads();
+  if (tid == 0) {
+    double St = 0.0, Tt = 0.0;
+    int best = INT_MAX;
+#pragma unroll
+    for (int i = 0; i < kHistBlock / kWave; ++i) { St += s_d[2 * i]; Tt += s_d[2 * i + 1]; best = min(best, s_i[i]); }
+    ent[out_row] = (float)(log(St) - Tt / St);
+    if (conf) { conf[out_row] = (float)(1.0 / St); tok[out_row] = best; }
+  }
+}
+
 // Short rows (fewer than 256 vectors): one element per load.
 template <typename T, int BLOCK>
 __global__ void __launch_bounds__(BLOCK)
@@ -423,6 +639,14 @@ static bool launch_vec(hipStream_t s, const T *logits, int64_t n_rows, int vocab
   if constexpr (!kEnt) {
     if (nvec >= 4096 && vocab % N == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0) {
       stage1_vec_kernel<T, kWide, 2, false, false><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
+      return true;
+    }
+  }
+  // Counting pays from 20000 elements a row on (2112 rows: 16384 34.7 us either way, 20000 44 -> 40, 32768 61 -> 46).
+  if constexpr (kEnt && sizeof(T) == 2) {
+    if (nvec >= 2500) {
+      stage1_hist_kernel<<<grid, kHistBlock, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
+      stage1_vec_kernel<T, kWide, 2, true, true, true><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
       return true;
     }
   }
