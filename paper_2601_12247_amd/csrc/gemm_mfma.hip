@@ -112,6 +112,7 @@ struct RopeArgs {
 struct SplitK {
   float *partial;
   int32_t nk_per;                                    // k stages per split
+  int32_t turn = 0;                                  // undivided launches: columns of tiles may start anywhere in K
 };
 
 template <int EPI, int BM, int BN, int BK, int kStages, int WM, int WN, bool kPairs>
@@ -199,16 +200,15 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   Wb += k_shift;
   constexpr int kLoadsPerStage = LA + LW;
   const int nk = EPI == kEpiPartial ? sk.nk_per : K / BK;
-  // Split-K launches are bound by the weight stream, and with all workgroups at the same k their loads of a moment lie
-  // K * 2 bytes apart, on few memory channels: each eighth of the tile columns starts an eighth of its k range further on and
-  // wraps around.  An eighth of the columns is what one XCD has (up to the remainder where they are no multiple of 8), whose
-  // workgroups share the activations in its L2.  By the column and not by the XCD itself: all tiles of a column, so all rows
-  // of a launch, add their k in the same order, and equal rows stay equal.  Cached rounds 2.0 and 2.6 % faster.
-  const int turn = EPI == kEpiPartial ? nk / 8 * (tile_n * 8 / tiles_n) : 0;
+  // So do launches of few rows that do not split K, every column of tiles from a place of its own: the 64-row tiles read the
+  // activations from L2 wherever they are (64 rows: gate/up of 24576 weight rows 42.5 -> 35.5 us, QKV 24.5 -> 22.9).
+  constexpr bool kWhole = EPI != kEpiPartial && ((EPI == kEpiSwiglu && BM == 128 && BN == 128) || (BM == 64 && BN == 128 && kStages == 6) ||
+                                                 (BM == 64 && BN == 64) || (BM == 128 && BN == 64));
+  const int turn = EPI == kEpiPartial ? nk / 8 * (tile_n * 8 / tiles_n) : kWhole && sk.turn ? (int)((int64_t)tile_n * nk / tiles_n) : 0;
   // Weights that at most two rows of tiles read are loaded with the non-temporal hint, so that they do not push the activations
   // and the partial sums out of L2 (cached rounds of 64 and 320 rows 4.4 and 2.5 % faster; with more rows of tiles they are gone
   // before the last one reads them: 256 x 192 tiles at 1311 rows 1 % slower).
-  constexpr int kWAux = (EPI == kEpiPartial && BM != 128) || (EPI == kEpiStore && (BM == 64 || BM == 160)) ? 2 : 0;
+  constexpr int kWAux = (EPI == kEpiPartial && BM != 128) || (kWhole && !(BM == 128 && BN == 128)) || (EPI == kEpiStore && BM == 160) ? 2 : 0;
   // The quadrant schedule loads through buffer descriptors: base + 32-bit lane offset + scalar offset, where the compiler
   // turns the global form into a 64-bit address per load and lane (16 registers that are not there).
   const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;
@@ -218,7 +218,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
 #endif
   auto issue_one = [&](int kt, int i) {                      // load i (A loads first, then W) of stage kt
     unsigned char *dst = lds + (kt % kStages) * kStage + wave * 1024;
-    const int kr = EPI != kEpiPartial || kt + turn < nk ? kt + turn : kt + turn - nk;
+    const int kr = !(EPI == kEpiPartial || kWhole) || kt + turn < nk ? kt + turn : kt + turn - nk;
     if constexpr (kQuad) {
 #ifdef __HIP_DEVICE_COMPILE__
       if (i < LA) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lptr_t *)(dst + i * kInstrBytes), 16, a_off[i], kr * (BK * 2), 0, 0);
@@ -761,7 +761,7 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
 }
 
 struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only, pairs_only = false; };   // pairs_only: SwiGLU with K % 128 == 0 (the quadrant schedule)
-constexpr int kNumCfg = 11;
+constexpr int kNumCfg = 13;
 // Every shape for many rows runs 8 waves, two per SIMD (the two small ones 4 waves, two workgroups per CU):
 // with one wave per SIMD the 256 x 256 tile (wave tiles of 128 x 128, a third fewer LDS reads) measured 2-4 %
 // slower, smaller wave tiles far slower.
@@ -777,11 +777,13 @@ constexpr TileCfg kCfg[kNumCfg] = {
     {64, 128, 64, 3, 0.0, false},     // so many small workgroups with deep rings; chosen by pick_config for M <= 384
     {192, 128, 64, 3, 0.86, true},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU
     {160, 256, 64, 3, 0.85, true},   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
-    {256, 192, 64, 2, 0.97, false, true}};   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
+    {256, 192, 64, 2, 0.97, false, true},
+    {64, 128, 64, 6, 0.0, false}, {128, 64, 64, 6, 0.0, true}};   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
 
 template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
-                   const void *Res, int M, int N, int K, const RopeArgs &ra = RopeArgs{}, const NormArgs &na = NormArgs{}) {
+                   const void *Res, int M, int N, int K, const RopeArgs &ra = RopeArgs{}, const NormArgs &na = NormArgs{}, bool turn = false) {
+  const SplitK whole{nullptr, 0, turn && M <= 128};
   constexpr bool kPlain = EPI != kEpiSwiglu && EPI != kEpiQkvRope;
   if (K % 128 != 0 && cfg == 0) return run<EPI, 256, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
   if (K % 128 != 0 && cfg == 4) return run<EPI, 192, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
@@ -791,14 +793,27 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
     case 2: return run<EPI, 256, 128, 64, 3, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
     case 4: return run<EPI, 192, 256, 64, 2, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
     case 5: if constexpr (kPlain) return run<EPI, 320, 128, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
-    case 6: if constexpr (kPlain) return run<EPI, 64, 64, 64, 5, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
+    case 6: if constexpr (kPlain) return run<EPI, 64, 64, 64, 5, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     case 7: return run<EPI, 64, 128, 64, 3, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
     case 8: if constexpr (kPlain) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 9: if constexpr (kPlain) return run<EPI, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 10: if constexpr (EPI == kEpiSwiglu) return run<EPI, 256, 192, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
+    case 11: return run<EPI, 64, 128, 64, 6, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);
+    case 12: if constexpr (kPlain) return run<EPI, 128, 64, 64, 6, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     default: break;
   }
-  return run<EPI, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
+  return run<EPI, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);
+}
+
+// Launches of up to 128 rows whose columns make enough tiles take the whole of K: with deep rings (5-6 stages, 64-120 KB of
+// weights on the way per CU) they stream the weights as fast as a launch that divides K, and write bf16 once instead of float32
+// partial sums that another launch adds up.  At K = 4096, with that launch counted: 64 rows, QKV of 12288 columns 33.5 -> 22.9 us,
+// gate/up of 2 x 12288 46.8 -> 35.5; 96 rows 32 -> 28 and 57 -> 43.  Limits: 64 rows x 4096 columns 12 us either way, gate/up of
+// 2 x 6144 21 -> 18, of 2 x 4096 16 against 18.
+constexpr int kWholeCols = 6144;
+bool takes_whole_k(GemmEpilogue epi, int M, int N) {
+  if (epi == kEpiSwiglu) return M <= 64 ? N >= kWholeCols : M <= 128 && N >= 4096;
+  return epi == kEpiStore && M <= 128 && N >= kWholeCols && N % 64 == 0;
 }
 
 // Tile shape: the one with the least estimated time = rounds of workgroups over the 256 CUs
@@ -814,7 +829,10 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   // The output head (N = vocabulary) has enough tiles to fill the chip at any M > 64 and goes by the
   // cost model below.
   if (forced < 0 && M <= 384 && (M <= 64 || N <= 32768)) {
+    if (epi == kEpiStore && M > 64 && M <= 128 && N > 8192 && N % 64 == 0) return 12;       // 64 x 64 tiles would be more than one a CU
     if (plain && M <= 128 && N % 64 == 0) return 6;
+    if (epi == kEpiSwiglu && M <= 64 && N >= kWholeCols) return 11;
+    if (epi == kEpiSwiglu && M > 64 && M <= 128 && N >= 8192) return 3;
     if (N % (epi == kEpiSwiglu ? 64 : 128) == 0) return 7;
   }
   int best = -1;
@@ -876,7 +894,8 @@ splitk_finalize_kernel(const float *__restrict__ partial, int splits, int M, int
 constexpr int kSplitMaxRows = 640;   // launches with more rows have enough tiles without splitting K
 
 // Tile shape and number of splits of a split-K launch; splits = 0: not possible.
-//  up to 64 rows     64 x 128, two workgroups per CU: bound by the bytes in flight, as many workgroups as fit twice
+//  up to 64 rows     64 x 64 with five stages, up to one workgroup per CU: fewer partial sums than 64 x 128 with two workgroups a CU
+//                    (O projection with its reduction 16.4 -> 13.0 us, down 26.5 -> 24.5)
 //  65-192            192 x 128
 //  193-384, 385-640  the shapes below by estimated time: rounds of workgroups over the chip x (k stages per workgroup + ~8
 //                    stages' worth of prologue and epilogue) x the tile's area over its relative efficiency, plus what the
@@ -884,10 +903,10 @@ constexpr int kSplitMaxRows = 640;   // launches with more rows have enough tile
 //                    of 160: as many tiles as with 320 x 128 and room for a third stage, which these latency-bound launches want
 //                    more than they mind fetching each weight tile twice from L2.  385-640 rows split only where tiles of
 //                    128 x 128 would leave half the chip idle (the O and down projections: 128 tiles).
-enum SplitTile { kS64x128, kS192x128, kS320x128, kS160x256, kS160x192, kS160x128, kS128x128, kS128x256 };
+enum SplitTile { kS64x64, kS192x128, kS320x128, kS160x256, kS160x192, kS160x128, kS128x128, kS128x256 };
 struct SplitShape { SplitTile tile; int bm, bn; double eff; };
 void splitk_plan(int M, int Nw, int K, size_t ws_floats, SplitTile *tile, int *splits) {
-  constexpr SplitShape k64[] = {{kS64x128, 64, 128, 1}}, k192[] = {{kS192x128, 192, 128, 1}};
+  constexpr SplitShape k64[] = {{kS64x64, 64, 64, 1}}, k192[] = {{kS192x128, 192, 128, 1}};
   constexpr SplitShape k384[] = {{kS160x256, 160, 256, 0.85}, {kS160x192, 160, 192, 0.80}, {kS160x128, 160, 128, 0.65},
                                   {kS192x128, 192, 128, 0.72}, {kS320x128, 320, 128, 0.70}};
   constexpr SplitShape k640[] = {{kS128x128, 128, 128, 0.70}, {kS128x256, 128, 256, 0.89}};
@@ -903,7 +922,7 @@ void splitk_plan(int M, int Nw, int K, size_t ws_floats, SplitTile *tile, int *s
     for (int sp = 1; sp <= 8; sp <<= 1) {
       if (nk % sp != 0 || nk / sp < 8 || (size_t)sp * M * Nw > ws_floats) continue;
       // a stage of 160 x 256 takes about 1 us; 5 TB/s for the partial sums
-      const double us = M <= 64 ? (tiles * sp <= 1024 ? -sp : 1)
+      const double us = M <= 64 ? (tiles * sp <= 256 ? -sp : 1)
                                 : (double)((tiles * sp + 255) / 256) * (nk / sp + 8) * (c->bm * c->bn) / c->eff * 2.1e-5 + sp * (double)M * Nw * 1.6e-6;
       if (*splits == 0 || us < best) { *tile = c->tile; *splits = sp; best = us; }
     }
@@ -922,7 +941,7 @@ bool gemm_mfma_norm_capable(int cfg);
 bool gemm_mfma_splitk_supported(int dtype, GemmEpilogue epi, int M, int N, int K, size_t ws_floats) {
   if (epi == kEpiQkvRope || epi == kEpiPartial || !gemm_mfma_supported(dtype, epi, M, N, K)) return false;
   const int Nw = epi == kEpiSwiglu ? 2 * N : N;
-  if (M > kSplitMaxRows || Nw % 128 != 0 || N % 8 != 0 || Nw > 32768) return false;
+  if (M > kSplitMaxRows || Nw % 128 != 0 || N % 8 != 0 || Nw > 32768 || takes_whole_k(epi, M, N)) return false;
   SplitTile tile;
   int splits;
   splitk_plan(M, Nw, K, ws_floats, &tile, &splits);
@@ -944,7 +963,7 @@ pvf_status launch_gemm_mfma_splitk_partial(pvf_ctx *ctx, hipStream_t s, const vo
   const SplitK sk{ws, K / 64 / splits};
   *splits_out = splits;
   switch (tile) {
-    case kS64x128: return run<kEpiPartial, 64, 128, 64, 3, 2, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS64x64: return run<kEpiPartial, 64, 64, 64, 5, 2, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
     case kS192x128: return run<kEpiPartial, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
     case kS320x128: return run<kEpiPartial, 320, 128, 64, 2, 4, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
     case kS160x256: return run<kEpiPartial, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
@@ -1032,8 +1051,9 @@ int gemm_mfma_norm_slots(GemmEpilogue epi, int M, int N, int K) {
   return N / (kCfg[c].bn == 256 ? 256 : 64);
 }
 
+// turn: the order in which an element's k are added may depend on the launch (few rows, see kWhole).
 pvf_status launch_gemm_mfma(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const void *A,
-                            const void *W, void *C, const void *residual, int M, int N, int K, const NormArgs *na) {
+                            const void *W, void *C, const void *residual, int M, int N, int K, const NormArgs *na, bool turn) {
   const uintptr_t al = (uintptr_t)A | (uintptr_t)W | (uintptr_t)C | (uintptr_t)residual;
   PVF_REQUIRE(ctx, (al & 15u) == 0, PVF_EINVAL, "gemm_mfma: operands must be 16-byte aligned");
   const int cfg = pick_config(epi, M, N, K);
@@ -1041,9 +1061,9 @@ pvf_status launch_gemm_mfma(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const
   const NormArgs nrm = na ? *na : NormArgs{};
   PVF_REQUIRE(ctx, !(nrm.ss_in || nrm.ss_out) || gemm_mfma_norm_capable(cfg), PVF_ESHAPE, "gemm_mfma: tile shape %d cannot fold the norm", cfg);
   switch (epi) {
-    case kEpiStore: return run_cfg<kEpiStore>(ctx, s, cfg, A, W, C, residual, M, N, K);
+    case kEpiStore: return run_cfg<kEpiStore>(ctx, s, cfg, A, W, C, residual, M, N, K, RopeArgs{}, NormArgs{}, turn);
     case kEpiResidual: return run_cfg<kEpiResidual>(ctx, s, cfg, A, W, C, residual, M, N, K, RopeArgs{}, nrm);
-    case kEpiSwiglu: return run_cfg<kEpiSwiglu>(ctx, s, cfg, A, W, C, residual, M, N, K, RopeArgs{}, nrm);
+    case kEpiSwiglu: return run_cfg<kEpiSwiglu>(ctx, s, cfg, A, W, C, residual, M, N, K, RopeArgs{}, nrm, turn);
     case kEpiQkvRope: break;                     // has its own entry (launch_gemm_mfma_qkv_rope)
     case kEpiPartial: break;                     // launch_gemm_mfma_splitk
   }

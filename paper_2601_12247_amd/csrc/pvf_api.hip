@@ -105,7 +105,7 @@ pvf_status launch_attention_window_f32(pvf_ctx *, hipStream_t, const void *, con
 pvf_status launch_attention_simple(pvf_ctx *, hipStream_t, int, const void *, void *, int, int, int, int);
 bool gemm_mfma_supported(int dtype, GemmEpilogue epi, int M, int N, int K);
 pvf_status launch_gemm_mfma(pvf_ctx *, hipStream_t, GemmEpilogue, const void *, const void *, void *,
-                            const void *, int, int, int, const NormArgs *na = nullptr);
+                            const void *, int, int, int, const NormArgs *na = nullptr, bool turn = false);
 int gemm_mfma_norm_slots(GemmEpilogue epi, int M, int N, int K);
 bool gemm_mfma_splitk_supported(int dtype, GemmEpilogue epi, int M, int N, int K, size_t ws_floats);
 pvf_status launch_gemm_mfma_splitk(pvf_ctx *, hipStream_t, GemmEpilogue, const void *, const void *, void *, const void *,
@@ -139,7 +139,7 @@ pvf_status launch_gemm(pvf_ctx *ctx, hipStream_t s, int dtype, GemmEpilogue epi,
   if (split_ok && !force_simple() && ctx && ctx->splitk_ws && gemm_mfma_splitk_supported(dtype, epi, M, N, K, ctx->splitk_floats))
     return launch_gemm_mfma_splitk(ctx, s, epi, A, W, C, residual, M, N, K, ctx->splitk_ws, ctx->splitk_floats);
   if (!force_simple() && gemm_mfma_supported(dtype, epi, M, N, K))
-    return launch_gemm_mfma(ctx, s, epi, A, W, C, residual, M, N, K);
+    return launch_gemm_mfma(ctx, s, epi, A, W, C, residual, M, N, K, nullptr, ctx && split_ok);
   return launch_gemm_simple(ctx, s, epi, (const bf16_t *)A, (const bf16_t *)W, (bf16_t *)C, (const bf16_t *)residual, M, N, K);
 }
 

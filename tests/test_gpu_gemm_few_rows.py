@@ -1,0 +1,40 @@
+"""Launches of up to 128 rows that take the whole of K (context GEMMs of wide projections): every element against float64
+products of the same bf16 inputs, on both sides of the limits in rows and columns, with fewer stages than the ring holds, with
+columns of tiles that start inside K, and last tiles with few rows."""
+import pytest
+import torch
+
+from synth import inputs as S
+from tests.gpu_util import make_context, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    shape = S.ModelShape(n_layers=1, d_model=256, n_heads=2, d_ff=512, vocab=512, mask_id=511)
+    return make_context(shape, to_device(S.make_weights(shape, seed=3, round_to_bf16=True), torch.bfloat16), max_seqs=1, max_T=64, max_rows=64)
+
+
+@pytest.mark.parametrize("M", [1, 16, 63, 64, 65, 96, 127, 128, 129])
+@pytest.mark.parametrize("N,K", [(6144, 64), (6144, 320), (6144, 448), (8192, 1024), (8320, 704), (12288, 4096), (4096, 832), (6016, 512)])
+def test_every_element(ctx, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
+    W = (torch.randn(2 * N, K, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    full = A.double() @ W.double().T
+    gate, up = full[:, :N], full[:, N:]
+    # one bf16 rounding of a float32 sum of K products, whose own error is below K^0.5 2^-24 of its terms' size
+    slack = K ** 0.5 * 2.0 ** -22
+    for got, want in ((ctx.gemm(A, W[:N]), gate), (ctx.gemm_swiglu(A, W), torch.nn.functional.silu(gate) * up)):
+        bound = 2.0 ** -8 * want.abs() + slack * (1 + gate.abs() + up.abs())
+        assert bool(((got.double() - want).abs() <= bound).all()), (M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 6144, 512), (128, 6144, 512), (128, 12288, 1024), (2, 8192, 2048)])
+def test_equal_rows_stay_equal(ctx, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    a = torch.randn(M // 2, K, device="cuda", generator=g).to(torch.bfloat16)
+    W = torch.randn(2 * N, K, device="cuda", generator=g).to(torch.bfloat16)
+    for out in (ctx.gemm(torch.cat([a, a]), W[:N]), ctx.gemm_swiglu(torch.cat([a, a]), W)):
+        assert torch.equal(out[:M // 2], out[M // 2:])
