@@ -208,7 +208,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   // Weights that at most two rows of tiles read are loaded with the non-temporal hint, so that they do not push the activations
   // and the partial sums out of L2 (cached rounds of 64 and 320 rows 4.4 and 2.5 % faster; with more rows of tiles they are gone
   // before the last one reads them: 256 x 192 tiles at 1311 rows 1 % slower).
-  constexpr int kWAux = (EPI == kEpiPartial && BM != 128) || (kWhole && !(BM == 128 && BN == 128)) || (EPI == kEpiStore && BM == 160) ? 2 : 0;
+  constexpr int kWAux = (EPI == kEpiPartial && (BM == 64 || BN == 192)) || (kWhole && !(BM == 128 && BN == 128)) || (EPI == kEpiStore && BM == 160) ? 2 : 0;
   // The quadrant schedule loads through buffer descriptors: base + 32-bit lane offset + scalar offset, where the compiler
   // turns the global form into a 64-bit address per load and lane (16 registers that are not there).
   const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;
@@ -775,7 +775,7 @@ constexpr TileCfg kCfg[kNumCfg] = {
     {320, 128, 64, 2, 0.78, true},    // 2560 rows = 8 tile rows: with N = 4096 exactly one tile per CU (wave tiles 80 x 64)
     {64, 64, 64, 5, 0.0, true},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights,
     {64, 128, 64, 3, 0.0, false},     // so many small workgroups with deep rings; chosen by pick_config for M <= 384
-    {192, 128, 64, 3, 0.86, true},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU
+    {192, 128, 64, 3, 0.86, true},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU; SwiGLU of 129-192 rows (pick_config)
     {160, 256, 64, 3, 0.85, true},   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
     {256, 192, 64, 2, 0.97, false, true},
     {64, 128, 64, 6, 0.0, false}, {128, 64, 64, 6, 0.0, true}};   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
@@ -795,7 +795,7 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
     case 5: if constexpr (kPlain) return run<EPI, 320, 128, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 6: if constexpr (kPlain) return run<EPI, 64, 64, 64, 5, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     case 7: return run<EPI, 64, 128, 64, 3, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
-    case 8: if constexpr (kPlain) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
+    case 8: if constexpr (EPI != kEpiQkvRope) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 9: if constexpr (kPlain) return run<EPI, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 10: if constexpr (EPI == kEpiSwiglu) return run<EPI, 256, 192, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 11: return run<EPI, 64, 128, 64, 6, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);
@@ -809,11 +809,22 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
 // weights on the way per CU) they stream the weights as fast as a launch that divides K, and write bf16 once instead of float32
 // partial sums that another launch adds up.  At K = 4096, with that launch counted: 64 rows, QKV of 12288 columns 33.5 -> 22.9 us,
 // gate/up of 2 x 12288 46.8 -> 35.5; 96 rows 32 -> 28 and 57 -> 43.  Limits: 64 rows x 4096 columns 12 us either way, gate/up of
-// 2 x 6144 21 -> 18, of 2 x 4096 16 against 18.
+// 2 x 7168, K = 3584, 28 against 31 and, of 96 rows, 30 against 32.
 constexpr int kWholeCols = 6144;
+// SwiGLU of 129-384 rows on tiles as tall as the launch or half of it, where they fill half of the chip or more in one round: no
+// partial sums either.  Gate/up of 2 x 12288, K = 4096, with the launch that adds up: 160 rows 63 -> 56 us, 256 rows 67 -> 63,
+// 384 rows 103 (three rows of 160-row tiles) -> 78; 257-320 rows are as fast as 160 x 192 tiles and their sums (71 us).
+// QKV of 321-384 rows on two rows of 192 x 128 tiles: 55 -> 49 us, where 160-row tiles make three rows.
+bool store_one_round(int M, int N) { return M > 320 && M <= 384 && N >= 8192 && N <= 16384 && N % 128 == 0; }
+int swiglu_one_round(int M, int N) {
+  if (N < 8192 || N > 16384 || N % 128 != 0) return -1;
+  if (M > 128 && M <= 192) return 8;
+  if (M > 192 && M <= 256) return 2;
+  return M > 320 && M <= 384 ? 4 : -1;
+}
 bool takes_whole_k(GemmEpilogue epi, int M, int N) {
-  if (epi == kEpiSwiglu) return M <= 64 ? N >= kWholeCols : M <= 128 && N >= 4096;
-  return epi == kEpiStore && M <= 128 && N >= kWholeCols && N % 64 == 0;
+  if (epi == kEpiSwiglu) return M <= 64 ? N >= 9216 : M <= 128 ? N >= 8192 : swiglu_one_round(M, N) >= 0;
+  return epi == kEpiStore && ((M <= 128 && N >= kWholeCols && N % 64 == 0) || store_one_round(M, N));
 }
 
 // Tile shape: the one with the least estimated time = rounds of workgroups over the 256 CUs
@@ -831,8 +842,10 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   if (forced < 0 && M <= 384 && (M <= 64 || N <= 32768)) {
     if (epi == kEpiStore && M > 64 && M <= 128 && N > 8192 && N % 64 == 0) return 12;       // 64 x 64 tiles would be more than one a CU
     if (plain && M <= 128 && N % 64 == 0) return 6;
-    if (epi == kEpiSwiglu && M <= 64 && N >= kWholeCols) return 11;
+    if (epi == kEpiStore && store_one_round(M, N)) return 8;
+    if (epi == kEpiSwiglu && M <= 64 && takes_whole_k(epi, M, N)) return 11;
     if (epi == kEpiSwiglu && M > 64 && M <= 128 && N >= 8192) return 3;
+    if (epi == kEpiSwiglu && swiglu_one_round(M, N) >= 0) return swiglu_one_round(M, N);
     if (N % (epi == kEpiSwiglu ? 64 : 128) == 0) return 7;
   }
   int best = -1;
@@ -843,7 +856,10 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
     if (forced == c) return c;
     if (kCfg[c].eff <= 0.0) continue;
     const int64_t tiles = (int64_t)((M + kCfg[c].bm - 1) / kCfg[c].bm) * (N / ncols);
-    const double t = (double)((tiles + 255) / 256) * kCfg[c].bm * kCfg[c].bn / kCfg[c].eff;
+    // two rows of tiles at most: what counts is by how many rows of tiles the weights are read (512 rows, QKV of 12288 columns:
+    // 128 x 256 60.5 us, 256 x 128 54.6)
+    const double eff = c == 2 && M <= 512 ? 0.95 : kCfg[c].eff;
+    const double t = (double)((tiles + 255) / 256) * kCfg[c].bm * kCfg[c].bn / eff;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
   if (cost) *cost = best_t;
@@ -894,27 +910,33 @@ splitk_finalize_kernel(const float *__restrict__ partial, int splits, int M, int
 constexpr int kSplitMaxRows = 640;   // launches with more rows have enough tiles without splitting K
 
 // Tile shape and number of splits of a split-K launch; splits = 0: not possible.
-//  up to 64 rows     64 x 64 with five stages, up to one workgroup per CU: fewer partial sums than 64 x 128 with two workgroups a CU
-//                    (O projection with its reduction 16.4 -> 13.0 us, down 26.5 -> 24.5)
-//  65-192            192 x 128
-//  193-384, 385-640  the shapes below by estimated time: rounds of workgroups over the chip x (k stages per workgroup + ~8
-//                    stages' worth of prologue and epilogue) x the tile's area over its relative efficiency, plus what the
-//                    partial sums cost, 4 bytes written and read per split and element.  193-384 rows are two (three) tile rows
-//                    of 160: as many tiles as with 320 x 128 and room for a third stage, which these latency-bound launches want
-//                    more than they mind fetching each weight tile twice from L2.  385-640 rows split only where tiles of
-//                    128 x 128 would leave half the chip idle (the O and down projections: 128 tiles).
-enum SplitTile { kS64x64, kS192x128, kS320x128, kS160x256, kS160x192, kS160x128, kS128x128, kS128x256 };
+//  up to 64 rows  64 x 64 with five stages, up to one workgroup per CU, two where K is divided in two: fewer partial sums than 64 x 128 with two workgroups a CU
+//                 (O projection with its reduction 16.4 -> 13.0 us, down 26.5 -> 24.5)
+//  above          the shapes below by estimated time: rounds of workgroups over the chip x (k stages per workgroup + ~8
+//                 stages' worth of prologue and epilogue) x the tile's area over its relative efficiency, plus what the
+//                 partial sums cost, 4 bytes written and read per split and element.  Which shapes stand against each other in a
+//                 range of rows, and their efficiencies, follow the times of the O (K = 4096) and down (12288) projections of 4096
+//                 columns.  96 rows: O 64 x 64 in 2 15.1 us, 128 x 128 in 8 17.6; down 33 (64 x 64), 28.6.  192 rows: O 128 x 128
+//                 in 4 19.9, 192 x 128 in 8 23.6; down 36.9, 34.3.  256 rows: O 128 x 128 in 4 22.2, 256 x 128 in 8 26.0; down 42.1,
+//                 39.6.  512 rows: O 128 x 128 in 2 29.3; down 67.6, 256 x 128 in 4 57.9.  640 rows: O 160 x 128 in 2 32.8, undivided
+//                 35.4; down 160 x 256 in 4 67.8, undivided 108.
+enum SplitTile { kS64x64, kS192x128, kS320x128, kS160x256, kS160x192, kS160x128, kS128x128, kS128x256, kS256x128 };
 struct SplitShape { SplitTile tile; int bm, bn; double eff; };
 void splitk_plan(int M, int Nw, int K, size_t ws_floats, SplitTile *tile, int *splits) {
-  constexpr SplitShape k64[] = {{kS64x64, 64, 64, 1}}, k192[] = {{kS192x128, 192, 128, 1}};
+  constexpr SplitShape k64[] = {{kS64x64, 64, 64, 1}}, k128[] = {{kS64x64, 64, 64, 0.3}, {kS128x128, 128, 128, 0.66}};
+  constexpr SplitShape k192[] = {{kS128x128, 128, 128, 0.66}, {kS192x128, 192, 128, 0.72}};
+  constexpr SplitShape k256[] = {{kS128x128, 128, 128, 0.66}, {kS256x128, 256, 128, 1.0}, {kS160x192, 160, 192, 0.80}};
   constexpr SplitShape k384[] = {{kS160x256, 160, 256, 0.85}, {kS160x192, 160, 192, 0.80}, {kS160x128, 160, 128, 0.65},
                                   {kS192x128, 192, 128, 0.72}, {kS320x128, 320, 128, 0.70}};
-  constexpr SplitShape k640[] = {{kS128x128, 128, 128, 0.70}, {kS128x256, 128, 256, 0.89}};
-  const SplitShape *shapes = M <= 64 ? k64 : M <= 192 ? k192 : M <= 384 ? k384 : k640;
-  const int n_shapes = M <= 192 ? 1 : M <= 384 ? 5 : 2, nk = K / 64;
+  constexpr SplitShape k640[] = {{kS128x128, 128, 128, 0.70}, {kS128x256, 128, 256, 0.89}, {kS256x128, 256, 128, 0.93},
+                                 {kS160x256, 160, 256, 0.85}, {kS160x128, 160, 128, 0.65}};
+  const SplitShape *shapes = M <= 64 ? k64 : M <= 128 ? k128 : M <= 192 ? k192 : M <= 256 ? k256 : M <= 384 ? k384 : k640;
+  const int n_shapes = M <= 64 ? 1 : M <= 192 ? 2 : M <= 256 ? 3 : 5, nk = K / 64;
   *tile = shapes[0].tile;
   *splits = 0;
-  if (M > 384 && (M + 127) / 128 * (Nw / 128) > 128) return;
+  // 385-640 rows split only where tiles of 128 x 128 would leave half the chip idle or make a second round for a few (the O and
+  // down projections: 128-160 tiles)
+  if (M > 384 && (M + 127) / 128 * (Nw / 128) > 160) return;
   double best = 0;
   for (const SplitShape *c = shapes; c < shapes + n_shapes; ++c) {
     if (Nw % c->bn != 0) continue;
@@ -922,7 +944,7 @@ void splitk_plan(int M, int Nw, int K, size_t ws_floats, SplitTile *tile, int *s
     for (int sp = 1; sp <= 8; sp <<= 1) {
       if (nk % sp != 0 || nk / sp < 8 || (size_t)sp * M * Nw > ws_floats) continue;
       // a stage of 160 x 256 takes about 1 us; 5 TB/s for the partial sums
-      const double us = M <= 64 ? (tiles * sp <= 256 ? -sp : 1)
+      const double us = M <= 64 ? (tiles * sp <= (sp == 2 ? 512 : 256) ? -sp : 1)
                                 : (double)((tiles * sp + 255) / 256) * (nk / sp + 8) * (c->bm * c->bn) / c->eff * 2.1e-5 + sp * (double)M * Nw * 1.6e-6;
       if (*splits == 0 || us < best) { *tile = c->tile; *splits = sp; best = us; }
     }
@@ -969,6 +991,7 @@ pvf_status launch_gemm_mfma_splitk_partial(pvf_ctx *ctx, hipStream_t s, const vo
     case kS160x256: return run<kEpiPartial, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
     case kS160x192: return run<kEpiPartial, 160, 192, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
     case kS160x128: return run<kEpiPartial, 160, 128, 64, 4, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
+    case kS256x128: return run<kEpiPartial, 256, 128, 64, 3, 4, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
     case kS128x128: return run<kEpiPartial, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
     case kS128x256: return run<kEpiPartial, 128, 256, 64, 3, 2, 4>(ctx, s, A, W, nullptr, nullptr, M, Nw, K, RopeArgs{}, sk, splits);
   }

@@ -1,4 +1,5 @@
-"""Launches of up to 128 rows that take the whole of K (context GEMMs of wide projections): every element against float64
+"""Launches of few rows that take the whole of K (context GEMMs of wide projections), and the ones that divide it where the tile
+shapes change: every element against float64
 products of the same bf16 inputs, on both sides of the limits in rows and columns, with fewer stages than the ring holds, with
 columns of tiles that start inside K, and last tiles with few rows."""
 import pytest
@@ -31,7 +32,24 @@ def test_every_element(ctx, M, N, K):
         assert bool(((got.double() - want).abs() <= bound).all()), (M, N, K)
 
 
-@pytest.mark.parametrize("M,N,K", [(64, 6144, 512), (128, 6144, 512), (128, 12288, 1024), (2, 8192, 2048)])
+@pytest.mark.parametrize("M", [130, 160, 192, 193, 256, 257, 320, 321, 384, 385, 512, 513, 640, 641])
+@pytest.mark.parametrize("N,K,kind", [(8192, 192, "swiglu"), (12288, 512, "swiglu"), (12288, 512, "store"), (8320, 1024, "store"),
+                                      (4096, 4096, "residual"), (4096, 2048, "residual"), (1280, 6144, "residual")])
+def test_every_element_of_more_rows(ctx, M, N, K, kind):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
+    W = (torch.randn(N * (2 if kind == "swiglu" else 1), K, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    R = torch.randn(M, N, device="cuda", generator=g).to(torch.bfloat16) if kind == "residual" else None
+    full = A.double() @ W.double().T
+    size = 1 + full.abs()
+    if kind == "swiglu":
+        got, want, size = ctx.gemm_swiglu(A, W), torch.nn.functional.silu(full[:, :N]) * full[:, N:], size[:, :N] + size[:, N:]
+    else:
+        got, want = ctx.gemm(A, W, residual=R), full + (R.double() if R is not None else 0)
+    assert bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + K ** 0.5 * 2.0 ** -22 * size).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 6144, 512), (128, 6144, 512), (128, 12288, 1024), (2, 8192, 2048), (384, 8192, 512), (256, 4096, 8192), (640, 4096, 4096)])
 def test_equal_rows_stay_equal(ctx, M, N, K):
     g = torch.Generator(device="cuda").manual_seed(N)
     a = torch.randn(M // 2, K, device="cuda", generator=g).to(torch.bfloat16)
