@@ -36,7 +36,7 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
   constexpr int dh = KC * 16;
   extern __shared__ float s_p[];       // [TQ][T16 + 4]
   __shared__ float s_inv[TQ];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 15, fq = lane >> 4;
   const int q0 = blockIdx.x * TQ, head = blockIdx.y, seq = blockIdx.z;
   const int d = n_heads * dh;
@@ -89,31 +89,23 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
     for (int e = 0; e < 4; ++e)        // row 4 e + lane / 16 = query, column lane % 16 = key
       s_p[(4 * e + fq) * stride + key] = key < T ? (float)((s0[e] + s1[e]) * (double)inv_sqrt_dh) : -INFINITY;
   };
-  if (wave < n_tiles) fetch_k(0, wave);
+  // tiles past the end are the last one again: loads behind a condition would be waited for with the tile before them
+  fetch_k(0, min(wave, n_tiles - 1));
+  fetch_k(1, min(wave + 4, n_tiles - 1));
+#pragma unroll 1
   for (int kt = wave; kt < n_tiles; kt += 8) {
-    if (kt + 4 < n_tiles) fetch_k(1, kt + 4);
     score(0, kt);
-    if (kt + 4 >= n_tiles) break;
-    if (kt + 8 < n_tiles) fetch_k(0, kt + 8);
-    score(1, kt + 4);
+    fetch_k(0, min(kt + 8, n_tiles - 1));
+    if (kt + 4 < n_tiles) score(1, kt + 4);
+    fetch_k(1, min(kt + 12, n_tiles - 1));
   }
   // values of the first kVRing tiles: on the way while the softmax runs
   constexpr int kVRing = 4;
   float vb[kVRing][4];
   auto fetch_v = [&](float *v, int dt, int kt) {
-    if (kt >= n_tiles) return;
-    if (!WIN && kt * 16 + 16 <= T) {             // rows of this launch at a fixed distance
-      const float *p = fresh + 2 * d + (int64_t)(kt * 16 + 4 * fq) * ld + dt * 16 + fr;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = p[e * ld];
-      return;
-    }
+    kt = min(kt, n_tiles - 1);
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = v_row(kt * 16 + 4 * fq + e)[dt * 16 + fr];
-    if (kt * 16 + 16 > T) {                      // the weight of a padding column is 0, and 0 * inf would not be
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = kt * 16 + 4 * fq + e < T ? v[e] : 0.f;
-    }
   };
   if (wave < KC) {
 #pragma unroll
@@ -158,6 +150,10 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
   for (int dt = wave; dt < KC; dt += 4) {
     doublex4 o0 = {0.0, 0.0, 0.0, 0.0}, o1 = o0;
     auto mul = [&](int buf, int kt) {
+      if (kt * 16 + 16 > T) {                    // uniform: the weight of a padding column is 0, and 0 * inf would not be
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vb[buf][e] = kt * 16 + 4 * fq + e < T ? vb[buf][e] : 0.f;
+      }
       const float4 p = *reinterpret_cast<const float4 *>(s_p + fr * stride + kt * 16 + 4 * fq);
       o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.x * inv), (double)vb[buf][0], o0, 0, 0, 0);
       o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.y * inv), (double)vb[buf][1], o1, 0, 0, 0);
@@ -171,10 +167,8 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
     for (int kt = 0; kt < n_tiles; kt += kVRing) {
 #pragma unroll
       for (int i = 0; i < kVRing; ++i) {
-        if (kt + i < n_tiles) {
-          mul(i, kt + i);
-          fetch_v(vb[i], dt, kt + i + kVRing);
-        }
+        if (kt + i < n_tiles) mul(i, kt + i);
+        fetch_v(vb[i], dt, kt + i + kVRing);
       }
     }
 #pragma unroll

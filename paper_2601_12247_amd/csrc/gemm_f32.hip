@@ -11,11 +11,14 @@
 //   * the four waves of a workgroup share K, each taking every fourth 16-k chunk, and their tiles are added through LDS in wave
 //     order.  Small launches get short loops that way, and large ones many equal workgroups.  The order in which an
 //     element's k are added is the same for every tile shape, so a row's bits do not depend on the launch's size;
-//   * tiles of 32 x 32 with one chunk ahead, at most 128 registers: four workgroups a CU instead of three cover each other's
+//   * tiles of 32 x 32, at most 128 registers: four workgroups a CU instead of three cover each other's
 //     prologue and epilogue, which are half of a loop over 256 k (6 236 rows: QKV 60 -> 52 us, down projection 57 -> 52).  SwiGLU
 //     takes 32 rows x 16 gate and the same 16 up columns for the same reason (32 + 32 columns need 230 registers: 108 -> 89 us);
-//   * launches of at most 512 such tiles (two a CU) take 16 x 32 with two chunks ahead instead: twice as many workgroups with
-//     half the work each (384 rows: QKV 9.7 -> 8.2 us, down 12.1 -> 7.9; above, the bigger tile reads less: 52 against 62 us).
+//   * launches of at most 512 such tiles (two a CU) take 16 x 32 instead: twice as many workgroups with
+//     half the work each (384 rows: QKV 9.7 -> 8.2 us, down 12.1 -> 7.9; above, the bigger tile reads less: 52 against 62 us);
+//   * one or two chunks are on their way while another is multiplied (one chunk ahead, fetched under a condition, every chunk was
+//     waited for whole; with that and the rows of the fused norm read eight loads at a time, rounds of 1-3 canvases x 128
+//     tokens 131 -> 120 us, of 8-40 canvases x 229 539 -> 525).
 // Measured on the small model's shapes (us per launch, plain vector-ALU kernel -> this one): QKV of 384 rows 42 -> 8, gate/up
 // 62 -> 11, down 81 -> 8; gate/up of 6 236 rows 89 (50 TFLOP/s), output head of 1 743 rows 75 (49 TFLOP/s).
 #include "common.h"
@@ -33,9 +36,14 @@ __device__ __forceinline__ double silu_f64(double g) { return g / (1.0 + exp(-g)
 // norm and the pass of its own take it from here, so that which of them a launch takes does not show in a bit.
 __device__ __forceinline__ float row_rnorm(const float *x, int j, int K, float eps) {
   double ss = 0.0;
-  for (int k = 4 * j; k < K; k += 32) {
-    const float4 v = *reinterpret_cast<const float4 *>(x + k);
-    ss += ((double)v.x * v.x + (double)v.y * v.y) + ((double)v.z * v.z + (double)v.w * v.w);
+  for (int k0 = 4 * j; k0 < K; k0 += 256) {                         // eight loads on their way together
+    float4 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const float4 *>(x + min(k0 + 32 * i, K - 4));
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (k0 + 32 * i < K)
+        ss += ((double)v[i].x * v[i].x + (double)v[i].y * v[i].y) + ((double)v[i].z * v[i].z + (double)v[i].w * v[i].w);
   }
   ss += __shfl_xor(ss, 1); ss += __shfl_xor(ss, 2); ss += __shfl_xor(ss, 4);
   return (float)(1.0 / sqrt(ss / K + (double)eps));
@@ -50,6 +58,7 @@ rmsnorm_f32_kernel(const float *__restrict__ x, const float *__restrict__ gain, 
   if (m >= M) return;                                               // whole rows, so whole groups of eight
   const float *xr = x + (int64_t)m * K;
   const float r = row_rnorm(xr, j, K, eps);
+#pragma unroll 4
   for (int k = 4 * j; k < K; k += 32) {
     const float4 v = *reinterpret_cast<const float4 *>(xr + k), g = *reinterpret_cast<const float4 *>(gain + k);
     *reinterpret_cast<float4 *>(out + (int64_t)m * K + k) = make_float4(v.x * r * g.x, v.y * r * g.y, v.z * r * g.z, v.w * r * g.w);
@@ -68,7 +77,7 @@ __device__ __forceinline__ int tile_col(int tile, int c, int half) {
 
 // NORM: the operand is RMSNorm(A) * gain, each row's 1 / rms from float64 sums taken by the workgroup itself while its first
 // chunks are on the way, the elements rounded to float32 as the norm's own pass rounds them.  MAP: rows through RowsF32::map.
-template <int EPI, bool VEC, bool NORM, bool MAP, int MT, int NT, int D>
+template <int EPI, bool VEC, bool NORM, bool MAP, int MT, int NT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float *__restrict__ C,
                 const float *__restrict__ Res, int M, int N, int K, RopeF32 ra, RowsF32 rw) {
@@ -76,7 +85,7 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
   constexpr int TM = 16 * MT, TN = 16 * NT;
   static_assert(EPI != kEpiQkvRope || NT == 2, "a rotation pair is two tiles wide");
   constexpr int NB = EPI == kEpiSwiglu ? 2 * NT : NT;               // SwiGLU: gate tiles, then up tiles
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 15, fq = lane >> 4;
   const int tiles_n = (N + TN - 1) / TN;
   const int tile_n = blockIdx.x % tiles_n, m0 = blockIdx.x / tiles_n * TM;
@@ -105,11 +114,14 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
 
   struct Chunk { float a[MT][4], w[NB][4], g[NORM ? 4 : 1]; };
   const int n_chunks = (K + 15) / 16;
-  auto fetch = [&](Chunk &c, int ch) {                              // 16 k from ch * 16; lanes past K hold zeros
-    const int k = ch * 16 + 4 * fq;
+  // 16 k from ch * 16.  The loads are unconditional (a chunk past the end is the last one again, and never multiplied), so that
+  // the wait for a chunk lets the loads of the next one stay in flight; with the fetch behind a condition it waited for them all.
+  auto fetch = [&](Chunk &c, int ch) {
+    const int k = min(ch, n_chunks - 1) * 16 + 4 * fq;
+    const int kv = VEC ? min(k, K - 4) : k;
     auto one = [&](const float *p, float *v) {
       if (VEC) {
-        const float4 x = k < K ? *reinterpret_cast<const float4 *>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 x = *reinterpret_cast<const float4 *>(p + kv);
         v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
       } else {
 #pragma unroll
@@ -123,7 +135,17 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
     if constexpr (NORM) one(gp, c.g);
   };
   float rnorm[MT];
-  auto multiply = [&](const Chunk &c) {
+  auto multiply = [&](Chunk &c, int ch) {
+    if (VEC && K % 16 != 0 && ch == n_chunks - 1) {                 // uniform: lanes past K bring nothing
+      const bool in = ch * 16 + 4 * fq < K;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) c.a[t][e] = in ? c.a[t][e] : 0.f;
+#pragma unroll
+        for (int t = 0; t < NB; ++t) c.w[t][e] = in ? c.w[t][e] : 0.f;
+      }
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -136,11 +158,10 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
           acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)c.w[j][e], acc[i][j], 0, 0, 0);
       }
   };
-  // this wave's chunks wave, wave + 4, ...: D - 1 in registers ahead of the one being multiplied.  (One call of multiply: with
-  // the loop unrolled over the buffers the accumulators were copied between register files at every turn.)
-  Chunk c[D];
-#pragma unroll
-  for (int i = 0; i + 1 < D; ++i) fetch(c[i], wave + i * WK);
+  // this wave's chunks wave, wave + 4, ...: one or two on their way while another is multiplied
+  Chunk c0, c1;
+  fetch(c0, wave);
+  fetch(c1, wave + WK);
   if (rw.n_live && m0 >= *rw.n_live * rw.per_seq) return;           // uniform
   if constexpr (NORM) {
     __shared__ float s_r[TM];
@@ -154,11 +175,11 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
     for (int t = 0; t < MT; ++t) rnorm[t] = s_r[t * 16 + fr];
   }
 #pragma unroll 1
-  for (int ch = wave; ch < n_chunks; ch += WK) {
-    fetch(c[D - 1], ch + (D - 1) * WK);
-    multiply(c[0]);
-#pragma unroll
-    for (int i = 0; i + 1 < D; ++i) c[i] = c[i + 1];
+  for (int ch = wave; ch < n_chunks; ch += 2 * WK) {
+    multiply(c0, ch);
+    fetch(c0, ch + 2 * WK);
+    if (ch + WK < n_chunks) multiply(c1, ch + WK);
+    fetch(c1, ch + 3 * WK);
   }
 
   // ---- wave w adds up register w of every tile (rows 4 w + lane / 16) over the four waves, in wave order ----
@@ -217,13 +238,13 @@ template <int EPI, bool NORM = false, bool MAP = false>
 pvf_status run_epi(pvf_ctx *ctx, hipStream_t s, const float *A, const float *W, float *C, const float *res, int M, int N, int K,
                    const RopeF32 &ra, const RowsF32 &rw = RowsF32{}) {
   const bool vec = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)rw.gain) & 15u) == 0;
-  auto launch = [&](auto mt, auto nt, auto depth) -> pvf_status {
-    constexpr int MT = decltype(mt)::value, NT = decltype(nt)::value, D = decltype(depth)::value;
+  auto launch = [&](auto mt, auto nt) -> pvf_status {
+    constexpr int MT = decltype(mt)::value, NT = decltype(nt)::value;
     const int64_t tiles = (int64_t)((N + 16 * NT - 1) / (16 * NT)) * ((M + 16 * MT - 1) / (16 * MT));
     PVF_REQUIRE(ctx, tiles < (1ll << 31), PVF_ESHAPE, "gemm_f32: M=%d N=%d", M, N);
     const unsigned grid = (unsigned)tiles;
-    if (vec) gemm_f32_kernel<EPI, true, NORM, MAP, MT, NT, D><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
-    else if constexpr (!NORM) gemm_f32_kernel<EPI, false, NORM, MAP, MT, NT, D><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
+    if (vec) gemm_f32_kernel<EPI, true, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
+    else if constexpr (!NORM) gemm_f32_kernel<EPI, false, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
     else PVF_REQUIRE(ctx, false, PVF_ESHAPE, "gemm_f32: the fused norm takes 16-byte aligned rows");
     PVF_LAUNCH_CHECK(ctx, "gemm_f32");
     return PVF_OK;
@@ -231,10 +252,9 @@ pvf_status run_epi(pvf_ctx *ctx, hipStream_t s, const float *A, const float *W, 
   using std::integral_constant;
   constexpr integral_constant<int, 1> k1{};
   constexpr integral_constant<int, 2> k2{};
-  constexpr integral_constant<int, 3> k3{};
   const int64_t tiles32 = (int64_t)((N + 31) / 32) * ((M + 31) / 32);
-  if constexpr (EPI == kEpiSwiglu) return launch(k2, k1, k2);
-  else return tiles32 <= 512 ? launch(k1, k2, k3) : launch(k2, k2, k2);
+  if constexpr (EPI == kEpiSwiglu) return launch(k2, k1);
+  else return tiles32 <= 512 ? launch(k1, k2) : launch(k2, k2);
 }
 
 }  // namespace

@@ -397,7 +397,7 @@ static bool f32_fused(const pvf_ctx *c, int T) {
 // behind the attention of the last layer the O projection picks the rows that logits are wanted for.  embedded: h holds the
 // embeddings already.  n_live (may be NULL): device count of the canvases that are there, at most S.
 // Small launches are bound by their number: a round of 1-3 canvases x 128 tokens has 14 launches where it had 23, and takes
-// 131 us where it took 182 (with the tile shapes of the projections and the attention's softmax as they are now).
+// 120 us where it took 182 (with the projections and the attention as they are now).
 static pvf_status forward_f32_impl(pvf_ctx *c, hipStream_t s, const int32_t *tokens, const int32_t *seq_slot, int S, int T,
                                    const int32_t *row_pos, int R, float *logits, int capture_spg, bool embedded, const int32_t *n_live) {
   const pvf_model_cfg &m = c->model;
