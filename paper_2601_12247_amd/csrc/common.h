@@ -63,8 +63,7 @@ struct RowFilter {
   const int32_t *n_drafts;  // [G] or NULL (NULL: every row is live, out row = in row)
   const int32_t *done;      // [G]
   const int32_t *k_active;  // [G]
-  const int32_t *seq_slot;  // [n_seq] compact sequence -> slot g*(1+K)+j, or NULL (identity)
-  const int32_t *n_live;    // device count of compact sequences, or NULL: those behind it do not exist
+  const int32_t *seq_slot;  // [n_seq] compact sequence -> slot g*(1+K)+j (negative: no sequence), or NULL (identity)
   int32_t slots_per_group;  // 1+K
   int32_t R, prompt_len, block_len, T;
 };
@@ -74,8 +73,8 @@ __device__ __forceinline__ bool row_target(const RowFilter &rf, int64_t row, int
   *out_row = row;
   if (rf.n_drafts == nullptr) return true;
   const int s = (int)(row / rf.R), r = (int)(row % rf.R);
-  if (rf.n_live && s >= *rf.n_live) { *out_row = -1; return false; }
   const int slot = rf.seq_slot ? rf.seq_slot[s] : s;
+  if (slot < 0) { *out_row = -1; return false; }
   const int g = slot / rf.slots_per_group, j = slot % rf.slots_per_group;
   *out_row = (int64_t)slot * rf.R + r;
   if (rf.done[g] || j > rf.n_drafts[g]) return false;
@@ -122,8 +121,8 @@ pvf_status launch_build_batch(pvf_ctx *ctx, hipStream_t s, int G, int n_seq,
                               const pvf_decode_cfg &cfg, const pvf_state &st,
                               int32_t *seq_slot, int32_t *row_pos);
 
-// the same, n_seq being an upper bound: *n_live = number of live slots, at most n_seq, whose entries alone are written (pad:
-// slot 0 where none is); and the embedding of their canvases (float32), h[s * T + t]
+// the same, n_seq being an upper bound: *n_live = number of live slots, at most n_seq (pad: slot 0 where none is); entries behind
+// them are -1, without window rows; and the embedding of their canvases (float32), h[s * T + t]
 pvf_status launch_embed_batch(pvf_ctx *ctx, hipStream_t s, int G, int n_seq, const pvf_decode_cfg &cfg, const pvf_state &st,
                               const float *embed, int d, int vocab, bool pad, int32_t *seq_slot, int32_t *row_pos, int32_t *n_live, float *h);
 
@@ -191,6 +190,7 @@ struct RopeF32 {
 struct RowsF32 {
   const float *gain = nullptr;    // the operand is RMSNorm(A) * gain
   float eps = 0.f;
+  double inv_k = 0.0;             // 1 / row length
   const int32_t *map = nullptr;   // row s * R + r is row s * T + map[s * R + r] of A and of the residual (zeros outside [0, T))
   int32_t T = 0, R = 0;
   const int32_t *n_live = nullptr;   // device: only the first *n_live * per_seq rows are computed

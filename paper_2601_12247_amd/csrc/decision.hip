@@ -92,7 +92,6 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   __shared__ int32_t s_blk[kMaxWinBlocks];   // masks per window block after the commit
   __shared__ int32_t s_winner, s_knew, s_done, s_wsnew;
 
-  if (a.out.skip_if_zero && *a.out.skip_if_zero == 0) return;
   int32_t nc0 = 0, nc1 = 0, nc2 = 0;           // thread 0: n_commit of the group
   auto report = [&](int is_done, int n_next) {
     if (a.out.status == nullptr) return;
@@ -103,6 +102,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   int32_t *ncommit = a.st.n_commit + (int64_t)g * 3;
   const int ka = a.st.k_active[g], done = a.st.done[g];      // five loads on the way together
   const int n_drafts = a.st.n_drafts[g], draft_route = a.st.draft_route[g], n_ws = a.st.n_ws_blocks[g];
+  if (a.out.skip_if_zero && *a.out.skip_if_zero == 0) return;
   if (done || ka < 0 || ka >= a.n_blocks) {   // finished (or invalid) group: report an empty round
     for (int j = tid; j < K; j += nth) accept[j] = 0;
     if (tid == 0) {
@@ -493,7 +493,10 @@ embed_batch_kernel(int G, int K, int n_seq, int R, int T, int prompt_len, int bl
     if (s == 0) slot = 0;
   }
   if (m == 0 && lane == 0) *n_live = min(n, n_seq);
-  if (slot < 0) return;
+  if (slot < 0) {
+    if (t == 0 && lane == 0) seq_slot[s] = -1;
+    return;
+  }
   if (t == 0) {
     if (lane == 0) seq_slot[s] = slot;
     const int w0 = prompt_len + st.k_active[slot / (1 + K)] * bl;

@@ -34,7 +34,7 @@ __device__ __forceinline__ double silu_f64(double g) { return g / (1.0 + exp(-g)
 
 // 1 / rms of a row that eight neighbouring threads share (j = 0..7), from float64 sums; every one of them gets it.  The fused
 // norm and the pass of its own take it from here, so that which of them a launch takes does not show in a bit.
-__device__ __forceinline__ float row_rnorm(const float *x, int j, int K, float eps) {
+__device__ __forceinline__ float row_rnorm(const float *x, int j, int K, double inv_k, float eps) {
   double ss = 0.0;
   for (int k0 = 4 * j; k0 < K; k0 += 256) {                         // eight loads on their way together
     float4 v[8];
@@ -46,18 +46,20 @@ __device__ __forceinline__ float row_rnorm(const float *x, int j, int K, float e
         ss += ((double)v[i].x * v[i].x + (double)v[i].y * v[i].y) + ((double)v[i].z * v[i].z + (double)v[i].w * v[i].w);
   }
   ss += __shfl_xor(ss, 1); ss += __shfl_xor(ss, 2); ss += __shfl_xor(ss, 4);
-  return (float)(1.0 / sqrt(ss / K + (double)eps));
+  // the hardware's estimate of 1 / sqrt (2^-26) and one Newton step: 2^-51, in a tenth of the instructions of sqrt and divide
+  const double v = ss * inv_k + (double)eps, r = __builtin_amdgcn_rsq(v);
+  return (float)(r * fma(-0.5 * v * r, r, 1.5));
 }
 
 // out = RMSNorm(x) * gain, eight threads a row
 __global__ void __launch_bounds__(256)
-rmsnorm_f32_kernel(const float *__restrict__ x, const float *__restrict__ gain, float *__restrict__ out, int M, int K, float eps,
+rmsnorm_f32_kernel(const float *__restrict__ x, const float *__restrict__ gain, float *__restrict__ out, int M, int K, double inv_k, float eps,
                    const int32_t *__restrict__ n_live, int per_seq) {
   const int m = blockIdx.x * 32 + (threadIdx.x >> 3), j = threadIdx.x & 7;
   if (n_live) M = min(M, *n_live * per_seq);
   if (m >= M) return;                                               // whole rows, so whole groups of eight
   const float *xr = x + (int64_t)m * K;
-  const float r = row_rnorm(xr, j, K, eps);
+  const float r = row_rnorm(xr, j, K, inv_k, eps);
 #pragma unroll 4
   for (int k = 4 * j; k < K; k += 32) {
     const float4 v = *reinterpret_cast<const float4 *>(xr + k), g = *reinterpret_cast<const float4 *>(gain + k);
@@ -167,7 +169,7 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
     __shared__ float s_r[TM];
     const int row = threadIdx.x >> 3, j = threadIdx.x & 7;          // eight threads a row
     if (row < TM) {
-      const float r = row_rnorm(A + (int64_t)min(m0 + row, M - 1) * K, j, K, rw.eps);
+      const float r = row_rnorm(A + (int64_t)min(m0 + row, M - 1) * K, j, K, rw.inv_k, rw.eps);
       if (j == 0) s_r[row] = r;
     }
     __syncthreads();
@@ -280,7 +282,7 @@ bool gemm_f32_norm_supported(int d) { return d <= 1024 && d % 4 == 0; }
 
 pvf_status launch_rmsnorm_f32(pvf_ctx *ctx, hipStream_t s, const float *x, float *out, int M, int K, const RowsF32 &rows) {
   if (M == 0) return PVF_OK;
-  rmsnorm_f32_kernel<<<(M + 31) / 32, 256, 0, s>>>(x, rows.gain, out, M, K, rows.eps, rows.n_live, rows.per_seq);
+  rmsnorm_f32_kernel<<<(M + 31) / 32, 256, 0, s>>>(x, rows.gain, out, M, K, rows.inv_k, rows.eps, rows.n_live, rows.per_seq);
   PVF_LAUNCH_CHECK(ctx, "rmsnorm_f32");
   return PVF_OK;
 }

@@ -414,7 +414,7 @@ static pvf_status forward_f32_impl(pvf_ctx *c, hipStream_t s, const int32_t *tok
   };
   auto rows_of = [&](const void *gain, int per_seq) {
     RowsF32 rw;
-    rw.gain = (const float *)gain; rw.eps = m.rms_eps; rw.n_live = n_live; rw.per_seq = per_seq;
+    rw.gain = (const float *)gain; rw.eps = m.rms_eps; rw.inv_k = 1.0 / d; rw.n_live = n_live; rw.per_seq = per_seq;
     return rw;
   };
   // x normed by a pass of its own into xn where the launch has many rows (see gemm_f32_norm_supported); rw then loses its gain
@@ -691,7 +691,7 @@ extern "C" pvf_status pvf_plan_vocab_select(void *stream, const uint32_t *cal_n,
 
 static RowFilter make_filter(const pvf_decode_cfg &cfg, const pvf_state &st, const int32_t *seq_slot) {
   RowFilter rf;
-  rf.n_drafts = st.n_drafts; rf.done = st.done; rf.k_active = st.k_active; rf.seq_slot = seq_slot; rf.n_live = nullptr;
+  rf.n_drafts = st.n_drafts; rf.done = st.done; rf.k_active = st.k_active; rf.seq_slot = seq_slot;
   rf.slots_per_group = 1 + cfg.K; rf.R = window_rows(cfg);
   rf.prompt_len = cfg.prompt_len; rf.block_len = cfg.block_len; rf.T = cfg.prompt_len + cfg.gen_len;
   return rf;
@@ -760,8 +760,7 @@ static pvf_status round_impl(pvf_ctx *ctx, hipStream_t s, int G, const uint32_t 
                : forward_impl(ctx, s, state.canvas, ctx->seq_slot, n_seq, T, ctx->row_pos, R, ctx->logits);
   }
   if (st != PVF_OK) return st;
-  RowFilter rf = make_filter(cfg, state, ctx->seq_slot);
-  if (fused) rf.n_live = ctx->n_live;
+  const RowFilter rf = make_filter(cfg, state, ctx->seq_slot);
   {
     ProfScope ps(ctx, s, PVF_PROF_STAGE1, 0.0, (double)n_seq * R * ctx->model.vocab * (double)ctx->esize);
     st = launch_stage1(ctx, s, ctx->logits, ctx->model.dtype, (int64_t)n_seq * R, ctx->model.vocab,
