@@ -829,7 +829,10 @@ bool takes_whole_k(GemmEpilogue epi, int M, int N) {
 
 // Tile shape: the one with the least estimated time = rounds of workgroups over the 256 CUs
 // x tile area / relative efficiency of the shape (measured on the forward's GEMM shapes: the
-// smaller tiles re-read operands more often but quantise better when there are few tiles).
+// smaller tiles re-read operands more often but quantise better when there are few tiles).  A round that is not full costs more
+// than its share of the chip and less than a whole one (the CUs that work clock higher): 0.6 of a round and 0.4 of the share.  By
+// whole rounds alone, timed in turn: gate/up of 1311 rows 220 us (256 x 192, 3.0 rounds) against 215 (192 x 256, 2.6), of 1600 rows
+// 276 (256 x 192, 3.5) against 265 (256 x 256, 2.6); QKV of 2048 rows 166 (128 x 256) against 160 (256 x 128).
 // PVF_GEMM_TILE=<n> in the environment forces shape n (for tuning runs).
 int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   static const int forced = [] { const char *e = getenv("PVF_GEMM_TILE"); return (e && e[0]) ? atoi(e) : -1; }();
@@ -858,8 +861,11 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
     const int64_t tiles = (int64_t)((M + kCfg[c].bm - 1) / kCfg[c].bm) * (N / ncols);
     // two rows of tiles at most: what counts is by how many rows of tiles the weights are read (512 rows, QKV of 12288 columns:
     // 128 x 256 60.5 us, 256 x 128 54.6)
-    const double eff = c == 2 && M <= 512 ? 0.95 : kCfg[c].eff;
-    const double t = (double)((tiles + 255) / 256) * kCfg[c].bm * kCfg[c].bn / eff;
+    // Above, a residual projection also writes the rows' sums of squares, four times as many from 128 columns as from 256, and the
+    // projection behind it reads them: 256 x 128 before 128 x 256 there gains 5-9 % of the down projection and loses more (5 x 320
+    // tokens 22.0 -> 22.5 ms).
+    const double eff = c == 2 && M <= 512 ? 0.95 : c == 2 && epi != kEpiResidual ? 0.92 : kCfg[c].eff;
+    const double t = (0.6 * (double)((tiles + 255) / 256) + 0.4 * (double)tiles / 256) * kCfg[c].bm * kCfg[c].bn / eff;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
   if (cost) *cost = best_t;
