@@ -10,7 +10,7 @@ before the timed region, so every input is resident in HBM when timing starts; t
 decode eight seeded prompts one after the other (a finished canvas is followed by the next prompt).
 
 Prints ONE JSON line.  `value` = tokens committed during the timed rounds / wall time, measured in a
-pass WITHOUT per-launch events (one packed status read per round, like pvf_decode).  A second pass
+pass WITHOUT per-launch events (one wait for the status words per round, like pvf_decode).  A second pass
 replays the same rounds with a pair of HIP events around every launch for the roofline.
 Extra objects:
   roofline            dominant kernel (bf16 MFMA GEMM): algorithmic FLOPs / HIP-event time summed over
@@ -81,7 +81,7 @@ def run_rounds(ctx, B, cfg, prompts, bitmap, steps, warmup, torch, profile):
     def one_round():
         nonlocal n_seq, which
         used = n_seq
-        (done, nd, c0, c1, c2), = ctx.round_sync(st, bitmap, n_seq)   # the round + one packed status read
+        (done, nd, c0, c1, c2), = ctx.round_sync(st, bitmap, n_seq)   # the round + its status words
         if done:
             which = (which + 1) % len(prompts)
             ctx.state_init(st, prompts[which])

@@ -236,7 +236,7 @@ pvf_status pvf_epilogue(pvf_ctx *ctx, void *stream, const void *logits, int32_t 
 pvf_status pvf_round(pvf_ctx *ctx, void *stream, int32_t G, const uint32_t *plan_bitmap,
                      const pvf_decode_cfg *cfg, const pvf_state *state, int32_t n_seq_host);
 
-/* pvf_round, then the per-group status words read back with ONE copy and the stream synchronised:
+/* pvf_round, whose last kernel writes the per-group status words to host memory, then the stream synchronised:
  * status_host (host, 5*G int32) = { done, n_drafts, n_commit[0..2] } of every group after the round.
  * sum over live groups of 1 + n_drafts is the next round's n_seq_host.  pvf_decode loops over this. */
 pvf_status pvf_round_sync(pvf_ctx *ctx, void *stream, int32_t G, const uint32_t *plan_bitmap,
@@ -249,7 +249,8 @@ pvf_status pvf_state_init(pvf_ctx *ctx, void *stream, const int32_t *prompt, int
                           const pvf_decode_cfg *cfg, const pvf_state *state);
 
 /* Algorithm 1 to completion for G groups: pvf_state_init, then pvf_round until every group
- * is done.  Synchronises the stream once per round to read 5*G status words (one copy).
+ * is done.  Waits once per round for 5*G status words, which the round's last kernel writes to host memory; a float32
+ * decode without the K/V cache waits for the round before the one it enqueued last.
  *   out_tokens dev int32 [G, T]; stats host (may be NULL). */
 pvf_status pvf_decode(pvf_ctx *ctx, void *stream, const int32_t *prompt, int32_t G,
                       const uint32_t *plan_bitmap, const pvf_decode_cfg *cfg,

@@ -10,9 +10,9 @@
 //     MFMAs runs both at the same rate).  The shapes in use: 256 x 256 with 8 waves (2 x 4) for the
 //     wide layers; 192 x 256, 128 x 256, 256 x 128, 160 x 256, 320 x 128, 192 x 128, 128 x 128 and (SwiGLU)
 //     256 x 192, also with 8 waves, where they put (nearly) one tile on every CU; 64 x 64 and 64 x 128 with
-//     4 waves for launches with few rows, which stream the weights and want many workgroups with deep rings
-//     (pick_config); launches of up to 640 rows may also split K over several workgroups per tile, as eight
-//     shapes of which 160 x 192 and 160 x 128 exist only there (splitk_plan);
+//     4 waves and 128 x 64 with 8 for launches with few rows, which stream the weights and want many bytes on
+//     the way (pick_config); launches of up to 640 rows may also split K over several workgroups per tile, as
+//     nine shapes of which 160 x 192 and 160 x 128 exist only there (splitk_plan);
 //   * both operands are K-contiguous in memory, so a 16-byte chunk is 8 consecutive k of one
 //     row.  K advances in stages of BK = 64 (whole 128-byte lines per row: half the L2 requests
 //     of 64-byte pieces) through a ring of LDS buffers; tiles go from
@@ -773,12 +773,12 @@ constexpr TileCfg kCfg[kNumCfg] = {
     {128, 128, 64, 5, 0.70, false},   // launches of a single round of tiles: the smallest area finishes first
     {192, 256, 64, 2, 0.93, false},   // fills the chip when M / 256 leaves many CUs idle
     {320, 128, 64, 2, 0.78, true},    // 2560 rows = 8 tile rows: with N = 4096 exactly one tile per CU (wave tiles 80 x 64)
-    {64, 64, 64, 5, 0.0, true},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights,
-    {64, 128, 64, 3, 0.0, false},     // so many small workgroups with deep rings; chosen by pick_config for M <= 384
+    {64, 64, 64, 5, 0.0, true},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights;
+    {64, 128, 64, 3, 0.0, false},     // these two and the last two are chosen by pick_config for M <= 384
     {192, 128, 64, 3, 0.86, true},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU; SwiGLU of 129-192 rows (pick_config)
     {160, 256, 64, 3, 0.85, true},   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
-    {256, 192, 64, 2, 0.97, false, true},
-    {64, 128, 64, 6, 0.0, false}, {128, 64, 64, 6, 0.0, true}};   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
+    {256, 192, 64, 2, 0.97, false, true},   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
+    {64, 128, 64, 6, 0.0, false}, {128, 64, 64, 6, 0.0, true}};   // the whole of K behind one workgroup a CU: rings of 144 KB
 
 template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
@@ -962,10 +962,9 @@ void splitk_plan(int M, int Nw, int K, size_t ws_floats, SplitTile *tile, int *s
 bool gemm_mfma_supported(int dtype, GemmEpilogue epi, int M, int N, int K);
 bool gemm_mfma_norm_capable(int cfg);
 
-// Few rows (window forward of the K/V-cached rounds, full forward of one short canvas): tiles as tall as
-// the launch up to 384 rows, so that every weight row goes from L2 to a CU once, and K split over 2-8
-// workgroups per tile to fill the chip and to shorten the serial k loop; a second small kernel adds the
-// partial sums.  ws: float32 scratch.
+// Few rows (window forward of the K/V-cached rounds, full forward of one short canvas): tiles of which one or two
+// rows cover the launch, so that every weight row goes from L2 to few CUs, and K split over 2-8 workgroups per tile
+// to fill the chip and to shorten the serial k loop; a second small kernel adds the partial sums.  ws: float32 scratch.
 bool gemm_mfma_splitk_supported(int dtype, GemmEpilogue epi, int M, int N, int K, size_t ws_floats) {
   if (epi == kEpiQkvRope || epi == kEpiPartial || !gemm_mfma_supported(dtype, epi, M, N, K)) return false;
   const int Nw = epi == kEpiSwiglu ? 2 * N : N;
@@ -1068,7 +1067,7 @@ bool gemm_mfma_supported(int dtype, GemmEpilogue epi, int M, int N, int K) {
 }
 
 // Tile shapes with room for the folded-norm exchange (every 8-wave shape).
-bool gemm_mfma_norm_capable(int cfg) { return cfg >= 0 && cfg != 6 && cfg != 7; }
+bool gemm_mfma_norm_capable(int cfg) { return cfg >= 0 && cfg != 6 && cfg != 7 && cfg != 11; }
 
 // Slots of row sums of squares a kEpiResidual launch writes, 256 columns each or (tiles 128 wide) 64; 0: no folded norm for
 // this launch.
