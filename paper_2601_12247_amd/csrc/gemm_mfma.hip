@@ -200,6 +200,11 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   Wb += k_shift;
   constexpr int kLoadsPerStage = LA + LW;
   const int nk = EPI == kEpiPartial ? sk.nk_per : K / BK;
+  // Split-K launches are bound by the weight stream, and with all workgroups at the same k their loads of a moment lie
+  // K * 2 bytes apart, on few memory channels: each eighth of the tile columns starts an eighth of its k range further on and
+  // wraps around.  An eighth of the columns is what one XCD has (up to the remainder where they are no multiple of 8), whose
+  // workgroups share the activations in its L2.  By the column and not by the XCD itself: all tiles of a column, so all rows
+  // of a launch, add their k in the same order, and equal rows stay equal.  Cached rounds 2.0 and 2.6 % faster.
   // So do launches of few rows that do not split K, every column of tiles from a place of its own: the 64-row tiles read the
   // activations from L2 wherever they are (64 rows: gate/up of 24576 weight rows 42.5 -> 35.5 us, QKV 24.5 -> 22.9).
   constexpr bool kWhole = EPI != kEpiPartial && ((EPI == kEpiSwiglu && BM == 128 && BN == 128) || (BM == 64 && BN == 128 && kStages == 6) ||
