@@ -102,8 +102,9 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   int32_t *ncommit = a.st.n_commit + (int64_t)g * 3;
   const int ka = a.st.k_active[g], done = a.st.done[g];      // five loads on the way together
   const int n_drafts = a.st.n_drafts[g], draft_route = a.st.draft_route[g], n_ws = a.st.n_ws_blocks[g];
-  if (a.out.skip_if_zero && *a.out.skip_if_zero == 0) return;
   if (done || ka < 0 || ka >= a.n_blocks) {   // finished (or invalid) group: report an empty round
+    // No live canvas means that every group is done, so the word is looked at here and live groups do not wait for it.
+    if (a.out.skip_if_zero && *a.out.skip_if_zero == 0) return;
     for (int j = tid; j < K; j += nth) accept[j] = 0;
     if (tid == 0) {
       a.st.winner[g] = 0; ncommit[0] = ncommit[1] = ncommit[2] = 0; a.st.n_drafts[g] = 0; a.st.done[g] = 1;
