@@ -367,8 +367,9 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
 // so the row is counted into LDS, 8192 counters for both signs of 32 exponents, and the float64 exponential is taken once
 // per value that occurs instead of once per element -- the same terms as EntropySums adds, each weighted by its count.  The
 // range ends four exponents above the largest one among the row's first 4096 elements; what lies outside goes to a list (1024
-// entries) or, from -1.7e38 down, adds nothing beside any larger value.  Rows of which this does not hold (more such elements,
-// NaN, a maximum as low as that) are left to stage1_vec_kernel in a launch behind this one (3 us where there are none); so are
+// entries) or, from -1.7e38 down, adds nothing beside any value above -1e38 (they are 700 apart at scales from 1e-35 on).  Rows of
+// which this does not hold (more such elements, NaN, a maximum as low as that, a smaller scale) are left to stage1_vec_kernel in a
+// launch behind this one (4.5 us where there are none); so are
 // rows of few values, told by equal neighbours in that sample: equal values of a wave wait for each other at their counter, and
 // from a chance of 1 / 32 for two elements to be equal on an exponential for each is the quicker way (2112 rows of 126464:
 // one value 170 against 970 us, 11 values 230 against 720).
@@ -525,7 +526,7 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
   M = s_f[0];
 #pragma unroll
   for (int i = 1; i < kHistBlock / kWave; ++i) M = fmaxf(M, s_f[i]);
-  if (s_n > kHistList || s_nan || (s_low && !(M > -1e38f))) {           // uniform
+  if (s_n > kHistList || s_nan || (s_low && !(M > -1e38f && scale >= 1e-35f))) {           // uniform
     if (tid == 0) ent[out_row] = __uint_as_float(kRereadRow);
     return;
   }

@@ -43,6 +43,17 @@ def test_every_route(scale):
             assert (np.isnan(w) and np.isnan(g)) or abs(g - w) <= 2e-6 * abs(w) + 1e-38, (name, mask_id, g, w)
 
 
+def test_scales_so_small_that_no_value_is_negligible():
+    """At 2e-38 the type's lowest value lies 7 below the row's maximum."""
+    rows = rows_of(4)
+    x = torch.from_numpy(np.stack(list(rows.values()))).to(torch.bfloat16)
+    for scale in (2e-38, 1e-37, 1e-36):
+        _, _, ent = reference(x.float().numpy(), scale, 7)
+        got = B.entropy(x.cuda(), 7, scale).cpu().numpy()
+        for name, g, w in zip(rows, got, ent):
+            assert abs(g - w) <= 2e-6 * abs(w) + 1e-38, (name, scale, g, w)
+
+
 def test_rows_without_numbers():
     x = torch.from_numpy(np.stack([rows_of(5)["normal"]] * 5)).to(torch.bfloat16)
     x[0], x[1, 77], x[2, V - 1], x[3, 9] = float("-inf"), float("inf"), float("nan"), float("nan")
