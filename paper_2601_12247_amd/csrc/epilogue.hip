@@ -392,7 +392,7 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
                    int32_t *__restrict__ tok, float *__restrict__ ent) {
   constexpr int N = 8, U = 2, kStride = kHistBlock * U;
   __shared__ uint32_t s_hist[kHistBins];
-  __shared__ uint16_t s_list[kHistList];
+  __shared__ alignas(16) uint16_t s_list[kHistList];
   __shared__ int s_n, s_low, s_nan;                      // list entries; whether an element below -1.7e38, a NaN occurred
   __shared__ int s_match, s_top;                         // of the sample: equal neighbours, largest exponent
   __shared__ float s_f[kHistBlock / kWave];
@@ -529,6 +529,30 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
   if (s_n > kHistList || s_nan || (s_low && !(M > -1e38f && scale >= 1e-35f))) {           // uniform
     if (tid == 0) ent[out_row] = __uint_as_float(kRereadRow);
     return;
+  }
+  // The list is in the order of the atomics; by value it is the same for every run, and with it which thread adds what.  An
+  // element's place is the number of elements before it (1024 of them: 2 x 128 reads of eight, the same for a whole wave).
+  if (s_n > 1) {                                         // uniform
+    constexpr int kEach = kHistList / kHistBlock;
+    uint16_t v[kEach];
+    int at[kEach];
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) { v[q] = s_list[tid + q * kHistBlock]; at[q] = 0; }
+    for (int i = 0; i < s_n; i += 8) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(s_list + i);
+      const uint32_t xw[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t o = e & 1 ? xw[e / 2] >> 16 : xw[e / 2] & 0xffffu;
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) at[q] += i + e < s_n && (o < v[q] || (o == v[q] && i + e < tid + q * kHistBlock));
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kEach; ++q)
+      if (tid + q * kHistBlock < s_n) s_list[at[q]] = v[q];
+    __syncthreads();
   }
   // S = sum e^t, T = sum t e^t, t = x - max x, over the values that occur
   const double xm = (double)mul_rn(M, scale);

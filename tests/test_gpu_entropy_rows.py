@@ -54,6 +54,25 @@ def test_scales_so_small_that_no_value_is_negligible():
             assert abs(g - w) <= 2e-6 * abs(w) + 1e-38, (name, scale, g, w)
 
 
+def test_listed_elements_are_added_in_one_order():
+    """Equal rows, whose elements beyond the counters' range reach the list in any order: one value above them, the others 30-33
+    below it, so that the order of the sums shows in the entropy."""
+    n = 20_032
+    rng = np.random.default_rng(6)
+    x = 0.1 * rng.standard_normal(n).astype(np.float32)
+    at = np.arange(4096, n)
+    at = rng.permutation(at[(at // 8 % 39 >= 12) & (at // 8 % 39 < 34)])[:900]      # between the places that the range is taken from
+    x[at] = 40 + rng.integers(0, 13, 900) / 4
+    x[at[450]] = 73
+    rows = torch.from_numpy(x).to(torch.bfloat16).cuda()[None].repeat(512, 1)
+    first = B.entropy(rows, 3, 1.0)
+    for _ in range(8):
+        assert torch.equal(B.entropy(rows, 3, 1.0), first)
+    assert (first == first[0]).all()
+    _, _, ent = reference(rows[:1].float().cpu().numpy(), 1.0, 3)
+    assert abs(first[0].item() - ent[0]) <= 1e-5 * ent[0]    # S is 1 and a few 1e-11, rounded at 2^-53
+
+
 def test_rows_without_numbers():
     x = torch.from_numpy(np.stack([rows_of(5)["normal"]] * 5)).to(torch.bfloat16)
     x[0], x[1, 77], x[2, V - 1], x[3, 9] = float("-inf"), float("inf"), float("nan"), float("nan")
