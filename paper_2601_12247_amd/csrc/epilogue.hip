@@ -366,15 +366,18 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
 // Entropy, confidence and top-1 token of long bf16 rows (calibration) from a histogram: a bf16 row holds few distinct values,
 // so the row is counted into LDS, 8192 counters for both signs of 32 exponents, and the float64 exponential is taken once
 // per value that occurs instead of once per element -- the same terms as EntropySums adds, each weighted by its count.  The
-// range ends four exponents above the largest one among the row's first 4096 elements; what lies outside goes to a list (1024
-// entries) or, from -1.7e38 down, adds nothing beside any value above -1e38 (they are 700 apart at scales from 1e-35 on).  Rows of
-// which this does not hold (more such elements, NaN, a maximum as low as that, a smaller scale) are left to stage1_vec_kernel in a
-// launch behind this one (4.5 us where there are none); so are
-// rows of few values, told by equal neighbours in that sample: equal values of a wave wait for each other at their counter, and
-// from a chance of 1 / 32 for two elements to be equal on an exponential for each is the quicker way (2112 rows of 126464:
-// one value 170 against 970 us, 11 values 230 against 720).
-// Bound by HBM and the LDS atomics together (2112 rows of 126464 210 -> 108 us, 5 TB/s): per two elements 4 packed instructions for the counters' addresses, 3 for the
-// maximum, 4 more, and 2 atomics.
+// range ends four exponents above the largest one of a sample, 4096 elements at equal distances over the row; what lies outside
+// goes to a list (1024 entries, counted afterwards range by range) or, from -1.7e38 down, adds nothing beside any value above
+// -1e38 (they are 700 apart at scales from 1e-35 on).  Rows of which this does not hold (more such elements, NaN, a maximum as low
+// as that, a smaller scale) are left to stage1_vec_kernel in a launch behind this one (4.5 us where there are none), at once where
+// the sample holds more than 1024 / vocab of them; so are rows of few values, told by equal elements of the sample: equal values
+// of a wave wait for each other at their counter, and from a chance of 1 / 16 for two elements to be equal on an exponential for
+// each is the quicker way (2112 rows of 126464: one value 170 against 970 us, 11 values 230 against 720, the last tenth of a row
+// of one value 195 against 190).
+// Bound by HBM and the LDS atomics together (2112 rows of 126464 of normal distribution 205-230 -> 108-115 us, 5 TB/s): per two
+// elements 4 packed instructions for the counters' addresses, 3 for the maximum, 4 more, and 2 atomics.  Elements outside the range
+// send their thread's 16 through a slower loop: 0.2 % of zeros 162 us, 0.5 % 210 (185-195 without counting); rows that are left at once
+// take 5-15 us longer than without the attempt, and where the list just overflows, 40 % longer (1 % of zeros).
 constexpr int kHistBlock = 512, kHistBins = 8192, kHistList = 1024;
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
@@ -392,9 +395,9 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
                    int32_t *__restrict__ tok, float *__restrict__ ent) {
   constexpr int N = 8, U = 2, kStride = kHistBlock * U;
   __shared__ uint32_t s_hist[kHistBins];
-  __shared__ alignas(16) uint16_t s_list[kHistList];
-  __shared__ int s_n, s_low, s_nan;                      // list entries; whether an element below -1.7e38, a NaN occurred
-  __shared__ int s_match, s_top;                         // of the sample: equal neighbours, largest exponent
+  __shared__ uint16_t s_list[kHistList];
+  __shared__ int s_n, s_low, s_nan, s_ranges;            // list entries; whether an element below -1.7e38, a NaN occurred; ranges listed
+  __shared__ int s_match, s_top, s_out;                  // of the sample: equal neighbours, largest exponent, elements for the list
   __shared__ float s_f[kHistBlock / kWave];
   __shared__ int s_i[kHistBlock / kWave];
   __shared__ double s_d[2 * (kHistBlock / kWave)];
@@ -412,16 +415,17 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
   const uint4 *__restrict__ p = reinterpret_cast<const uint4 *>(row + head);
   const int nvec = (vocab - head) / N;
   const int mask_vec = mask_id >= head ? (mask_id - head) / N : INT_MAX, mask_lane = mask_id >= head ? (mask_id - head) % N : 0;
-  const uint4 sample = p[tid];                           // nvec >= 2500
+  // 64 pieces of 64 elements (whole lines), at equal distances over the row: nvec >= 2499
+  const uint4 sample = p[tid / 8 * ((nvec - 8) / 63) + tid % 8];
   for (int i = tid; i < kHistBins / 4; i += kHistBlock) reinterpret_cast<uint4 *>(s_hist)[i] = make_uint4(0, 0, 0, 0);
-  if (tid == 0) s_n = s_low = s_nan = s_match = s_top = 0;
+  if (tid == 0) s_n = s_low = s_nan = s_ranges = s_match = s_top = s_out = 0;
   __syncthreads();
   {
     const uint32_t w[4] = {sample.x, sample.y, sample.z, sample.w};
     int match = 0, top = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t o = __shfl(w[i], (lane + 1) & (kWave - 1));
+      const uint32_t o = __shfl(w[i], (lane + 8) & (kWave - 1));      // of the next piece
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const uint32_t a = h ? w[i] >> 16 : w[i] & 0xffffu, b = h ? o >> 16 : o & 0xffffu;
@@ -435,14 +439,26 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
     if (lane == 0) { atomicAdd(&s_match, match); atomicMax(&s_top, top); }
   }
   __syncthreads();
-  if (s_match > kHistBlock * N / 32) {                   // uniform
+  const uint32_t low = (uint32_t)max((s_top ? s_top : 127) - 27, 0) << 7;      // bits of the smallest value counted
+  {
+    const uint32_t w[4] = {sample.x, sample.y, sample.z, sample.w};
+    int out = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t a = i & 1 ? w[i / 2] >> 16 : w[i / 2] & 0xffffu;
+      out += __popcll(__ballot(((a - low) & 0x7000u) != 0 && !(a >= 0xff00u && a <= 0xff80u)));
+    }
+    if (lane == 0 && out) atomicAdd(&s_out, out);
+  }
+  __syncthreads();
+  if (s_match > kHistBlock * N / 16 || (int64_t)s_out * (vocab / (kHistBlock * N)) > kHistList) {      // uniform
     if (tid == 0) ent[out_row] = __uint_as_float(kRereadRow);
     return;
   }
-  const uint32_t low = (uint32_t)max((s_top ? s_top : 127) - 27, 0) << 7;      // bits of the smallest value counted
 
   float m = kNegInf;
   int first = INT_MAX, cnt = 0;                          // vectors first, first + BLOCK, .. (cnt of them) raised m; cnt = 0: element first
+  bool full = false;                                     // the list is: the row is read again, and this thread need not go on
   auto count_one = [&](uint32_t u) {                     // 16 bits of one element, whatever it is
     const uint32_t y = (u - low) & 0xffffu;
     if (!(y & 0x7000u)) { atomicAdd(&s_hist[(y ^ (y >> 3)) & 0x1fffu], 1u); return; }
@@ -500,24 +516,42 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
           atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(s_hist) + (zz & 0x7fffu)), 1u);
           atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(s_hist) + ((zz >> 16) & 0x7fffu)), 1u);
         }
-    } else {
-#pragma unroll 1
+      return;
+    }
+    uint32_t every = b[0][0], some = b[0][0];
+#pragma unroll
+    for (int i = 1; i < UV * 4; ++i) { every &= b[i / 4][i % 4]; some |= b[i / 4][i % 4]; }
+    if (every != 0xff80ff80u || some != 0xff80ff80u) {   // all -inf brings nothing
+      uint32_t outside = 0;                              // bit 2 i + h: half h of word i
+#pragma unroll
       for (int i = 0; i < UV * 4; ++i) {
+        const uint32_t y = __builtin_bit_cast(uint32_t, __builtin_bit_cast(ushort2v, b[i / 4][i % 4]) - low2);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t z = h ? y >> 16 : y & 0xffffu, u = h ? b[i / 4][i % 4] >> 16 : b[i / 4][i % 4] & 0xffffu;
+          if (!(z & 0x7000u)) atomicAdd(&s_hist[(z ^ (z >> 3)) & 0x1fffu], 1u);
+          else if (u - 0xff00u > 0x80u) outside |= 1u << (2 * i + h);
+          else if (u != 0xff80u) s_low = 1;              // -inf brings nothing
+        }
+      }
+      while (outside) {
+        const int k = __ffs(outside) - 1;
+        outside &= outside - 1;
         uint32_t x = b[0][0];
 #pragma unroll
-        for (int q = 1; q < UV * 4; ++q) x = i == q ? b[q / 4][q % 4] : x;
-        count_one(x & 0xffffu);
-        count_one(x >> 16);
+        for (int q = 1; q < UV * 4; ++q) x = k / 2 == q ? b[q / 4][q % 4] : x;
+        count_one(k & 1 ? x >> 16 : x & 0xffffu);
       }
+      full = *(volatile int *)&s_n > kHistList;
     }
   };
   if (tid < head) single(tid);
   const int nfull = nvec / kStride, it_mask = mask_vec / kStride;
   const std::integral_constant<int, U> all{};
   const int split = it_mask < nfull ? it_mask : nfull;
-  for (int it = 0; it < split; ++it) vectors(it * kStride + tid, all, std::false_type{});
-  if (it_mask < nfull) vectors(it_mask * kStride + tid, all, std::true_type{});
-  for (int it = split + 1; it < nfull; ++it) vectors(it * kStride + tid, all, std::false_type{});
+  for (int it = 0; it < split && !full; ++it) vectors(it * kStride + tid, all, std::false_type{});
+  if (it_mask < nfull && !full) vectors(it_mask * kStride + tid, all, std::true_type{});
+  for (int it = split + 1; it < nfull && !full; ++it) vectors(it * kStride + tid, all, std::false_type{});
   for (int idx = nfull * kStride + tid; idx < nvec; idx += kHistBlock) vectors(idx, std::integral_constant<int, 1>{}, std::true_type{});
   if (tid < vocab - head - nvec * N) single(head + nvec * N + tid);
   float M = wave_max(m);
@@ -530,30 +564,6 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
     if (tid == 0) ent[out_row] = __uint_as_float(kRereadRow);
     return;
   }
-  // The list is in the order of the atomics; by value it is the same for every run, and with it which thread adds what.  An
-  // element's place is the number of elements before it (1024 of them: 2 x 128 reads of eight, the same for a whole wave).
-  if (s_n > 1) {                                         // uniform
-    constexpr int kEach = kHistList / kHistBlock;
-    uint16_t v[kEach];
-    int at[kEach];
-#pragma unroll
-    for (int q = 0; q < kEach; ++q) { v[q] = s_list[tid + q * kHistBlock]; at[q] = 0; }
-    for (int i = 0; i < s_n; i += 8) {
-      const uint4 x = *reinterpret_cast<const uint4 *>(s_list + i);
-      const uint32_t xw[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t o = e & 1 ? xw[e / 2] >> 16 : xw[e / 2] & 0xffffu;
-#pragma unroll
-        for (int q = 0; q < kEach; ++q) at[q] += i + e < s_n && (o < v[q] || (o == v[q] && i + e < tid + q * kHistBlock));
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kEach; ++q)
-      if (tid + q * kHistBlock < s_n) s_list[at[q]] = v[q];
-    __syncthreads();
-  }
   // S = sum e^t, T = sum t e^t, t = x - max x, over the values that occur
   const double xm = (double)mul_rn(M, scale);
   double S = 0.0, T = 0.0;
@@ -565,11 +575,32 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
     S = fma(n, e, S);
     T = fma(n * t, e, T);
   };
-  for (int i = tid; i < kHistBins; i += kHistBlock) {
-    const uint32_t n = s_hist[i];
-    if (n) add(hist_value(i, low), (double)n);
+  auto add_counts = [&](uint32_t from) {
+    for (int i = tid; i < kHistBins; i += kHistBlock) {
+      const uint32_t n = s_hist[i];
+      if (n) add(hist_value(i, from), (double)n);
+    }
+  };
+  add_counts(low);
+  // The list is in the order of the atomics, so its elements are counted like the others, 32 exponents after 32: sums of counts
+  // have one order.
+  if (s_n) {                                             // uniform
+    for (int i = tid; i < s_n; i += kHistBlock) atomicOr(&s_ranges, 1 << (((s_list[i] - low) >> 12) & 7));
+    __syncthreads();
+    for (int r = 1; r < 8; ++r) {
+      if (!(s_ranges >> r & 1)) continue;                // uniform
+      const uint32_t from = low + (r << 12);
+      for (int i = tid; i < kHistBins / 4; i += kHistBlock) reinterpret_cast<uint4 *>(s_hist)[i] = make_uint4(0, 0, 0, 0);
+      __syncthreads();
+      for (int i = tid; i < s_n; i += kHistBlock) {
+        const uint32_t y = (s_list[i] - from) & 0xffffu;
+        if (!(y & 0x7000u)) atomicAdd(&s_hist[(y ^ (y >> 3)) & 0x1fffu], 1u);
+      }
+      __syncthreads();
+      add_counts(from);
+      __syncthreads();
+    }
   }
-  for (int i = tid; i < s_n; i += kHistBlock) add(__uint_as_float((uint32_t)s_list[i] << 16), 1.0);
   wave_sum2(S, T);
   if (lane == 0) { s_d[2 * wid] = S; s_d[2 * wid + 1] = T; }
   // ---- arg-max: lowest id attaining M; a thread whose own maximum is M reads the vectors in which it first met it again ----

@@ -73,6 +73,32 @@ def test_listed_elements_are_added_in_one_order():
     assert abs(first[0].item() - ent[0]) <= 1e-5 * ent[0]    # S is 1 and a few 1e-11, rounded at 2^-53
 
 
+@pytest.mark.parametrize("n", [V, 20_032, 126_464])
+def test_rows_that_change_along_the_way(n):
+    """Rows whose front says nothing about what follows, and values in any number of the counters' ranges."""
+    rng = np.random.default_rng(n)
+    f = lambda: rng.standard_normal(n).astype(np.float32)
+    behind, front, tiny, huge, off = f(), f(), f(), f(), f()
+    behind[n // 2:] = -3.25
+    front[:n // 2] = -3.25
+    tiny[5000:] *= 1e-6
+    huge[5000:] *= 1e4
+    off[2000:] = -np.inf
+    zeros = {p: f() for p in (0.002, 0.01, 0.2)}             # listed; about as many as the list holds; left at once
+    for p, x in zeros.items():
+        x[rng.random(n) < p] = 0.0
+    ranges = f()
+    at = rng.permutation(n)[:700]
+    ranges[at] *= np.float32(2.0) ** rng.integers(-110, -27, 700)
+    masked = f()
+    masked[rng.random(n) < 0.3] = -1e9
+    x = torch.from_numpy(np.stack([behind, front, tiny, huge, off, *zeros.values(), ranges, masked])).to(torch.bfloat16)
+    for mask_id in (1, n - 1):
+        _, _, ent = reference(x.float().numpy(), 1.0, mask_id)
+        got = B.entropy(x.cuda(), mask_id, 1.0).cpu().numpy()
+        np.testing.assert_allclose(got, ent, rtol=2e-6, atol=1e-38)      # the bound of the tests above
+
+
 def test_rows_without_numbers():
     x = torch.from_numpy(np.stack([rows_of(5)["normal"]] * 5)).to(torch.bfloat16)
     x[0], x[1, 77], x[2, V - 1], x[3, 9] = float("-inf"), float("inf"), float("nan"), float("nan")
