@@ -196,6 +196,9 @@ struct RowsF32 {
   const int32_t *n_live = nullptr;   // device: only the first *n_live * per_seq rows are computed
   int32_t per_seq = 0;
 };
+// out = RMSNorm(x) * gain by rows.gain, eps, inv_k (and n_live); the norm of every float32 row of up to kNormF32Max elements
+constexpr int kNormF32Max = 1024;
+pvf_status launch_rmsnorm_f32(pvf_ctx *ctx, hipStream_t s, const float *x, float *out, int M, int K, const RowsF32 &rows);
 // C[M,N] = A[M,K] W[N,K]^T; kEpiResidual adds residual[M,N]; kEpiSwiglu: W is [2N,K] (gate|up),
 // C[M,N] = silu(gate) * up.
 pvf_status launch_gemm(pvf_ctx *ctx, hipStream_t s, int dtype, GemmEpilogue epi, const void *A,

@@ -221,6 +221,10 @@ pvf_status launch_rmsnorm(pvf_ctx *ctx, hipStream_t s, int dtype, const void *x,
       rmsnorm_bf16_vec_kernel<2><<<M, 256, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, (bf16_t *)out, d, eps);
     else
       rmsnorm_kernel<bf16_t><<<M, 256, 0, s>>>((const bf16_t *)x, (const bf16_t *)gain, (bf16_t *)out, d, eps);
+  } else if (d <= kNormF32Max) {       // the norm that the projections fuse: a row's bits do not depend on its route
+    RowsF32 rows;
+    rows.gain = (const float *)gain; rows.eps = eps; rows.inv_k = 1.0 / d;
+    return launch_rmsnorm_f32(ctx, s, (const float *)x, (float *)out, M, d, rows);
   } else {
     rmsnorm_kernel<float><<<M, 256, 0, s>>>((const float *)x, (const float *)gain, (float *)out, d, eps);
   }

@@ -32,26 +32,38 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double silu_f64(double g) { return g / (1.0 + exp(-g)); }
 
+// Four consecutive elements from k of a row of K; past its end zeros (VEC: the row's last four, which the caller leaves out).
+template <bool VEC>
+__device__ __forceinline__ float4 four(const float *x, int k, int K) {
+  if constexpr (VEC) return *reinterpret_cast<const float4 *>(x + min(k, K - 4));
+  auto one = [&](int i) { const float v = x[min(i, K - 1)]; return i < K ? v : 0.f; };
+  return make_float4(one(k), one(k + 1), one(k + 2), one(k + 3));
+}
+
 // 1 / rms of a row that eight neighbouring threads share (j = 0..7), from float64 sums; every one of them gets it.  The fused
-// norm and the pass of its own take it from here, so that which of them a launch takes does not show in a bit.
+// norm and the pass of its own take it from here, at any alignment and in window rows too, so that which of them a launch takes
+// does not show in a bit.  (Rows longer than kNormF32Max have one norm as well, rmsnorm_kernel.)
+template <bool VEC = true>
 __device__ __forceinline__ float row_rnorm(const float *x, int j, int K, double inv_k, float eps) {
   double ss = 0.0;
   for (int k0 = 4 * j; k0 < K; k0 += 256) {                         // eight loads on their way together
     float4 v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const float4 *>(x + min(k0 + 32 * i, K - 4));
+    for (int i = 0; i < 8; ++i) v[i] = four<VEC>(x, k0 + 32 * i, K);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       if (k0 + 32 * i < K)
         ss += ((double)v[i].x * v[i].x + (double)v[i].y * v[i].y) + ((double)v[i].z * v[i].z + (double)v[i].w * v[i].w);
   }
   ss += __shfl_xor(ss, 1); ss += __shfl_xor(ss, 2); ss += __shfl_xor(ss, 4);
-  // the hardware's estimate of 1 / sqrt (2^-26) and one Newton step: 2^-51, in a tenth of the instructions of sqrt and divide
+  // the hardware's estimate of 1 / sqrt (relative error below 2^-22) and one Newton step, 1.5 times its square: below 2^-43, in a
+  // tenth of the instructions of sqrt and divide
   const double v = ss * inv_k + (double)eps, r = __builtin_amdgcn_rsq(v);
   return (float)(r * fma(-0.5 * v * r, r, 1.5));
 }
 
-// out = RMSNorm(x) * gain, eight threads a row
+// out = RMSNorm(x) * gain, eight threads a row.  VEC: 16-byte loads, K % 4 == 0.
+template <bool VEC>
 __global__ void __launch_bounds__(256)
 rmsnorm_f32_kernel(const float *__restrict__ x, const float *__restrict__ gain, float *__restrict__ out, int M, int K, double inv_k, float eps,
                    const int32_t *__restrict__ n_live, int per_seq) {
@@ -59,11 +71,16 @@ rmsnorm_f32_kernel(const float *__restrict__ x, const float *__restrict__ gain, 
   if (n_live) M = min(M, *n_live * per_seq);
   if (m >= M) return;                                               // whole rows, so whole groups of eight
   const float *xr = x + (int64_t)m * K;
-  const float r = row_rnorm(xr, j, K, inv_k, eps);
+  const float r = row_rnorm<VEC>(xr, j, K, inv_k, eps);
 #pragma unroll 4
   for (int k = 4 * j; k < K; k += 32) {
-    const float4 v = *reinterpret_cast<const float4 *>(xr + k), g = *reinterpret_cast<const float4 *>(gain + k);
-    *reinterpret_cast<float4 *>(out + (int64_t)m * K + k) = make_float4(v.x * r * g.x, v.y * r * g.y, v.z * r * g.z, v.w * r * g.w);
+    const float4 v = four<VEC>(xr, k, K), g = four<VEC>(gain, k, K);
+    const float4 o = make_float4(v.x * r * g.x, v.y * r * g.y, v.z * r * g.z, v.w * r * g.w);
+    float *to = out + (int64_t)m * K + k;
+    if constexpr (VEC) { *reinterpret_cast<float4 *>(to) = o; continue; }
+    const float e[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) if (k + i < K) to[i] = e[i];
   }
 }
 
@@ -278,11 +295,13 @@ pvf_status launch_gemm_f32(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const 
 // norms the same rows again, half as many bytes once more as its main loop reads, which costs less than a launch and a pass
 // where rows and launches are short (1-3 canvases x 128 tokens, 256 wide: a round with five norms 157 -> 136 us) and more where
 // there are many rows (8 canvases x 229 with drafts: 565 -> 612): fused up to 1280 rows (forward_f32_impl).
-bool gemm_f32_norm_supported(int d) { return d <= 1024 && d % 4 == 0; }
+bool gemm_f32_norm_supported(int d) { return d <= kNormF32Max && d % 4 == 0; }
 
 pvf_status launch_rmsnorm_f32(pvf_ctx *ctx, hipStream_t s, const float *x, float *out, int M, int K, const RowsF32 &rows) {
   if (M == 0) return PVF_OK;
-  rmsnorm_f32_kernel<<<(M + 31) / 32, 256, 0, s>>>(x, rows.gain, out, M, K, rows.inv_k, rows.eps, rows.n_live, rows.per_seq);
+  const bool vec = K % 4 == 0 && (((uintptr_t)x | (uintptr_t)rows.gain | (uintptr_t)out) & 15u) == 0;
+  (vec ? rmsnorm_f32_kernel<true> : rmsnorm_f32_kernel<false>)<<<(M + 31) / 32, 256, 0, s>>>(x, rows.gain, out, M, K, rows.inv_k, rows.eps,
+                                                                                            rows.n_live, rows.per_seq);
   PVF_LAUNCH_CHECK(ctx, "rmsnorm_f32");
   return PVF_OK;
 }

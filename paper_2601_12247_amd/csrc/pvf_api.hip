@@ -94,7 +94,6 @@ pvf_status launch_gemm_simple(pvf_ctx *, hipStream_t, GemmEpilogue, const bf16_t
 pvf_status launch_gemm_f32(pvf_ctx *, hipStream_t, GemmEpilogue, const float *, const float *, float *, const float *, int, int, int,
                            const RowsF32 *rows = nullptr);
 bool gemm_f32_norm_supported(int d);
-pvf_status launch_rmsnorm_f32(pvf_ctx *, hipStream_t, const float *, float *, int M, int K, const RowsF32 &);
 bool gemm_f32_qkv_rope_supported(int d_head);
 pvf_status launch_gemm_f32_qkv_rope(pvf_ctx *, hipStream_t, const float *, const float *, float *, int M, int d, int K, const RopeF32 &,
                                     const RowsF32 *rows = nullptr);
