@@ -115,7 +115,7 @@ struct SplitK {
   int32_t turn = 0;                                  // undivided launches: columns of tiles may start anywhere in K
 };
 
-template <int EPI, int BM, int BN, int BK, int kStages, int WM, int WN, bool kPairs>
+template <int EPI, int BM, int BN, int BK, int kStages, int WM, int WN, bool kPairs, bool kHint>
 __global__ void __launch_bounds__(64 * WM * WN)
 __attribute__((amdgpu_waves_per_eu(waves_per_simd(kStages * (BM + BN) * BK * 2, WM * WN),
                                    waves_per_simd(kStages * (BM + BN) * BK * 2, WM * WN))))
@@ -210,10 +210,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   constexpr bool kWhole = EPI != kEpiPartial && ((EPI == kEpiSwiglu && BM == 128 && BN == 128) || (BM == 64 && BN == 128 && kStages == 6) ||
                                                  (BM == 64 && BN == 64) || (BM == 128 && BN == 64));
   const int turn = EPI == kEpiPartial ? nk / 8 * (tile_n * 8 / tiles_n) : kWhole && sk.turn ? (int)((int64_t)tile_n * nk / tiles_n) : 0;
-  // Weights that at most two rows of tiles read are loaded with the non-temporal hint, so that they do not push the activations
-  // and the partial sums out of L2 (cached rounds of 64 and 320 rows 4.4 and 2.5 % faster; with more rows of tiles they are gone
-  // before the last one reads them: 256 x 192 tiles at 1311 rows 1 % slower).
-  constexpr int kWAux = (EPI == kEpiPartial && (BM == 64 || BN == 192)) || (kWhole && !(BM == 128 && BN == 128)) || (EPI == kEpiStore && BM == 160) ? 2 : 0;
+  constexpr int kWAux = kHint ? 2 : 0;               // weights with the non-temporal hint (run)
   // The quadrant schedule loads through buffer descriptors: base + 32-bit lane offset + scalar offset, where the compiler
   // turns the global form into a 64-bit address per load and lane (16 registers that are not there).
   const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;
@@ -744,11 +741,6 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
                const NormArgs &na = NormArgs{}) {
   constexpr int kLdsBytes = ST * (BM + BN) * BK * 2;
   static_assert(kLdsBytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a CU");
-  // once per kernel instance; a function-local static is initialised exactly once even with concurrent callers
-  static const hipError_t configured = hipFuncSetAttribute(
-      reinterpret_cast<const void *>(gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN, kPairs>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-  PVF_HIP_CHECK(ctx, configured);
   const int tiles_m = (M + BM - 1) / BM;
   const int tiles_n = (EPI == kEpiSwiglu) ? N_out / (BN / 2) : N_out / BN;
   const int total = tiles_m * tiles_n;
@@ -759,10 +751,28 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   constexpr int kBand = BM > BN ? 4 : 8;
   const int n_bands = (tiles_m + kBand - 1) / kBand;
   const int group_m = (tiles_m + n_bands - 1) / n_bands;
-  gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN, kPairs><<<dim3(grid, splits), 64 * WM * WN, kLdsBytes, s>>>(
-      (const bf16_t *)A, (const bf16_t *)W, (bf16_t *)C, (const bf16_t *)Res, M, N_out, K, tiles_m, tiles_n, group_m, ra, sk, na);
-  PVF_LAUNCH_CHECK(ctx, "gemm_mfma");
-  return PVF_OK;
+  auto launch = [&](auto hint) -> pvf_status {
+    const auto kernel = gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN, kPairs, decltype(hint)::value>;
+    // once per kernel instance; a function-local static is initialised exactly once even with concurrent callers
+    static const hipError_t configured =
+        hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    PVF_HIP_CHECK(ctx, configured);
+    kernel<<<dim3(grid, splits), 64 * WM * WN, kLdsBytes, s>>>(
+        (const bf16_t *)A, (const bf16_t *)W, (bf16_t *)C, (const bf16_t *)Res, M, N_out, K, tiles_m, tiles_n, group_m, ra, sk, na);
+    PVF_LAUNCH_CHECK(ctx, "gemm_mfma");
+    return PVF_OK;
+  };
+  // Weights that at most two rows of tiles read are loaded with the non-temporal hint by the shapes that gain, so that they do not
+  // push the activations and the partial sums out of L2 (cached rounds of 64 and 320 rows 4.4 and 2.5 % faster).  With more rows of
+  // tiles they may be gone before the last one reads them: 160 x 256 tiles at 1311 rows of 6144 columns, K = 2048, 40.1 us with the
+  // hint and 34.4 without, K = 8192 132 and 121; 4100 rows of 12288 columns, K = 4096, 352 and 335.
+  constexpr bool kFewRows = EPI == kEpiPartial ? BM == 64 : BN == 64 || ST == 6;                 // shapes for up to 128 rows
+  constexpr bool kTwoRows = (EPI == kEpiPartial && BN == 192) || (EPI == kEpiStore && BM == 160);
+  if constexpr (kFewRows) return launch(std::true_type{});
+  else {
+    if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{});
+    return launch(std::false_type{});
+  }
 }
 
 struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only, pairs_only = false; };   // pairs_only: SwiGLU with K % 128 == 0 (the quadrant schedule)
