@@ -34,6 +34,7 @@
 //     mod 8) cover a patch of 8 x 4 output tiles and share operand tiles through that XCD's L2.
 #include "common.h"
 
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -784,15 +785,15 @@ constexpr int kNumCfg = 13;
 // (a last epilogue pass of 16 rows, which only the plain epilogues handle).
 constexpr TileCfg kCfg[kNumCfg] = {
     {256, 256, 64, 2, 1.00, false},   // the wide layers
-    {128, 256, 64, 3, 0.89, false}, {256, 128, 64, 3, 0.885, false},
+    {128, 256, 64, 3, 0.89, false}, {256, 128, 64, 3, 0.891, false},
     {128, 128, 64, 5, 0.70, false},   // launches of a single round of tiles: the smallest area finishes first
-    {192, 256, 64, 2, 0.93, false},   // fills the chip when M / 256 leaves many CUs idle
+    {192, 256, 64, 2, 0.94, false},   // fills the chip when M / 256 leaves many CUs idle
     {320, 128, 64, 2, 0.78, true},    // 2560 rows = 8 tile rows: with N = 4096 exactly one tile per CU (wave tiles 80 x 64)
     {64, 64, 64, 5, 0.0, true},       // few rows (window forward of the K/V-cached rounds): the GEMM streams the weights;
     {64, 128, 64, 3, 0.0, false},     // these two and the last two are chosen by pick_config for M <= 384
     {192, 128, 64, 3, 0.86, true},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU; SwiGLU of 129-192 rows (pick_config)
     {160, 256, 64, 3, 0.85, true},   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
-    {256, 192, 64, 2, 0.97, false, true},   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
+    {256, 192, 64, 2, 0.965, false, true},   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
     {64, 128, 64, 6, 0.0, false}, {128, 64, 64, 6, 0.0, true}};   // the whole of K behind one workgroup a CU: rings of 144 KB
 
 template <int EPI>
@@ -844,10 +845,13 @@ bool takes_whole_k(GemmEpilogue epi, int M, int N) {
 
 // Tile shape: the one with the least estimated time = rounds of workgroups over the 256 CUs
 // x tile area / relative efficiency of the shape (measured on the forward's GEMM shapes: the
-// smaller tiles re-read operands more often but quantise better when there are few tiles).  A round that is not full costs more
-// than its share of the chip and less than a whole one (the CUs that work clock higher): 0.6 of a round and 0.4 of the share.  By
-// whole rounds alone, timed in turn: gate/up of 1311 rows 220 us (256 x 192, 3.0 rounds) against 215 (192 x 256, 2.6), of 1600 rows
-// 276 (256 x 192, 3.5) against 265 (256 x 256, 2.6); QKV of 2048 rows 166 (128 x 256) against 160 (256 x 128).
+// smaller tiles re-read operands more often but quantise better when there are few tiles).  What a last round leaves idle is lost in
+// launches of one or two rounds and counts for less behind several, whose workgroups no longer end together: a tenth of it is given
+// back per round before it, at most 0.4.  Shares and efficiencies follow the times of every shape on 17 matrices of 2048-24576 columns
+// and K = 2048-13824 at 34 numbers of rows from 385 to 4100.  Whole rounds alone: 0.5 % slower on average (gate/up of 2 x 12288, K =
+// 4096, 1311 rows, 230 against 219 us, 3.0 rounds of 256 x 192 tiles and 2.6 of 192 x 256; 2304 rows of 24576 columns, K = 8192, 819
+// against 687).  0.4 of the idle part given back in every round: 0.2 % on average and up to 11 % (gate/up of 2 x 14336, K = 4096, 640
+// rows, 165 against 149; 1792 rows of 12288 columns, K = 4096, 162 against 146).
 // PVF_GEMM_TILE=<n> in the environment forces shape n (for tuning runs).
 int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   static const int forced = [] { const char *e = getenv("PVF_GEMM_TILE"); return (e && e[0]) ? atoi(e) : -1; }();
@@ -879,8 +883,10 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
     // Above, a residual projection also writes the rows' sums of squares, four times as many from 128 columns as from 256, and the
     // projection behind it reads them: 256 x 128 before 128 x 256 there gains 5-9 % of the down projection and loses more (5 x 320
     // tokens 22.0 -> 22.5 ms).
-    const double eff = c == 2 && M <= 512 ? 0.95 : c == 2 && epi != kEpiResidual ? 0.92 : kCfg[c].eff;
-    const double t = (0.6 * (double)((tiles + 255) / 256) + 0.4 * (double)tiles / 256) * kCfg[c].bm * kCfg[c].bn / eff;
+    const double eff = c == 2 && M <= 512 ? 0.95 : c == 2 && epi == kEpiResidual ? 0.885 : kCfg[c].eff;
+    const double full = (double)tiles / 256, rounds = (double)((tiles + 255) / 256);
+    const double back = std::min(0.02 + 0.1 * (rounds - 1), 0.4);      // 0.02: of equal rounds the fewer tiles
+    const double t = (rounds - back * (rounds - full)) * kCfg[c].bm * kCfg[c].bn / eff;
     if (best < 0 || t < best_t) { best = c; best_t = t; }
   }
   if (cost) *cost = best_t;
