@@ -1056,14 +1056,17 @@ bool gemm_mfma_qkv_rope_supported(int dtype, int M, int N, int K, int T, int H) 
 }
 
 // Whether the fused epilogue is the quicker way where both are open.  It excludes the tile shapes with 32-column or 80-row
-// waves, which often fill the chip better: the QKV projection of 3 x 437 rows takes 177 us in two rounds of 192 x 256 tiles, and
-// 129 us in three of 192 x 128 plus 12 us for the rotary pass.  The pass moves 4 bytes per element of C at ~3.5 TB/s; a
-// unit of the tile estimate is 2 K flop on one CU (~5.9 TFLOP/s).
+// waves, which fill the chip better where they make a single round of tiles: 450 rows of 9216 columns, K = 3072, on 192 x 128 tiles and
+// a rotary pass are 2 % of a forward quicker than fused on 256 x 128.  The pass moves 4 bytes per element of C at ~3.5 TB/s; a unit of
+// the tile estimate is 2 K flop on one CU (~5.9 TFLOP/s).  With more rounds fused is as quick or quicker: 1281-1536 rows of 12288
+// columns, K = 4096, two rounds of 192 x 256 against three of 192 x 128 and the pass, forwards 2-2.7 % quicker (3 x 437 tokens, 8 layers, 4.79
+// -> 4.70 ms); 641-700 rows of 24576, K = 8192, 2 %; 1025-1140 rows of 15360, K = 5120, and 1800-1880 of 9216 within 0.5 %.
 bool gemm_mfma_qkv_rope_pays(int M, int N, int K) {
   if (M <= 384) return true;
   double fused = 0, plain = 0;
   if (pick_config(kEpiQkvRope, M, N, K, &fused) < 0) return false;
-  if (pick_config(kEpiStore, M, N, K, &plain) < 0) return true;
+  const int cfg = pick_config(kEpiStore, M, N, K, &plain);
+  if (cfg < 0 || (int64_t)((M + kCfg[cfg].bm - 1) / kCfg[cfg].bm) * (N / kCfg[cfg].bn) > 256) return true;
   return fused <= plain + 2.5 * M * (double)N / K;
 }
 
