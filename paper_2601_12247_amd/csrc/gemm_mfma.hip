@@ -35,6 +35,7 @@
 #include "common.h"
 
 #include <algorithm>
+#include <climits>
 #include <cstdlib>
 #include <type_traits>
 
@@ -799,7 +800,7 @@ constexpr TileCfg kCfg[kNumCfg] = {
 template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
                    const void *Res, int M, int N, int K, const RopeArgs &ra = RopeArgs{}, const NormArgs &na = NormArgs{}, bool turn = false) {
-  const SplitK whole{nullptr, 0, turn && M <= 128};
+  const SplitK whole{nullptr, 0, turn && M <= 128 && K >= 1024};
   constexpr bool kPlain = EPI != kEpiSwiglu && EPI != kEpiQkvRope;
   if (K % 128 != 0 && cfg == 0) return run<EPI, 256, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
   if (K % 128 != 0 && cfg == 4) return run<EPI, 192, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
@@ -821,26 +822,43 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
   return run<EPI, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);
 }
 
-// Launches of up to 128 rows whose columns make enough tiles take the whole of K: with deep rings (5-6 stages, 64-120 KB of
-// weights on the way per CU) they stream the weights as fast as a launch that divides K, and write bf16 once instead of float32
-// partial sums that another launch adds up.  At K = 4096, with that launch counted: 64 rows, QKV of 12288 columns 33.5 -> 22.9 us,
-// gate/up of 2 x 12288 46.8 -> 35.5; 96 rows 32 -> 28 and 57 -> 43.  Limits: 64 rows x 4096 columns 12 us either way, gate/up of
-// 2 x 7168, K = 3584, 28 against 31 and, of 96 rows, 30 against 32.
-constexpr int kWholeCols = 6144;
-// SwiGLU of 129-384 rows on tiles as tall as the launch or half of it, where they fill half of the chip or more in one round: no
-// partial sums either.  Gate/up of 2 x 12288, K = 4096, with the launch that adds up: 160 rows 63 -> 56 us, 256 rows 67 -> 63,
-// 384 rows 103 (three rows of 160-row tiles) -> 78; 257-320 rows are as fast as 160 x 192 tiles and their sums (71 us).
-// QKV of 321-384 rows on two rows of 192 x 128 tiles: 55 -> 49 us, where 160-row tiles make three rows.
-bool store_one_round(int M, int N) { return M > 320 && M <= 384 && N >= 8192 && N <= 16384 && N % 128 == 0; }
-int swiglu_one_round(int M, int N) {
-  if (N < 8192 || N > 16384 || N % 128 != 0) return -1;
-  if (M > 128 && M <= 192) return 8;
-  if (M > 192 && M <= 256) return 2;
-  return M > 320 && M <= 384 ? 4 : -1;
+// Undivided shapes for few rows; -1: by the estimate.  Up to 128 rows rings of 5-6 stages (64-120 KB of weights on the way per CU) where
+// the tiles, one a CU, make one round or the loop is long: 96 rows of 20480 columns, K = 1024, 17.4 us on 128 x 64 and 14.8 on 64 x 64,
+// two a CU; 32 rows of gate/up 2 x 20480, K = 512, 14.4 on six stages and 11.7 on three.  From there tiles as tall as the launch or
+// half of it.
+int few_rows_shape(GemmEpilogue epi, int M, int N, int K) {
+  if (M > 384) return -1;
+  if (epi == kEpiSwiglu) {
+    if (M <= 64) return N >= 9216 && (N <= 16384 || K >= 2048) ? 11 : 7;
+    if (M <= 128) return N >= 8192 && K >= (N <= 16384 ? 1024 : 2048) ? 3 : 7;
+    if (N < 8192 || N > 16384 || N % 128 != 0 || (M > 256 && M <= 320)) return 7;
+    return M <= 192 ? 8 : M <= 256 ? 2 : 4;
+  }
+  if (epi == kEpiStore && M > 64 && M <= 128 && N > 8192 && N % 64 == 0 && (N <= 16384 || N > 24576 || K >= 4096)) return 12;
+  if (epi != kEpiQkvRope && M <= 128 && N % 64 == 0) return 6;
+  return epi == kEpiStore && M > 320 && N >= 8192 && N <= 16384 && N % 128 == 0 ? 8 : N % 128 == 0 ? 7 : -1;
 }
-bool takes_whole_k(GemmEpilogue epi, int M, int N) {
-  if (epi == kEpiSwiglu) return M <= 64 ? N >= 9216 : M <= 128 ? N >= 8192 : swiglu_one_round(M, N) >= 0;
-  return epi == kEpiStore && ((M <= 128 && N >= kWholeCols && N % 64 == 0) || store_one_round(M, N));
+// Whether a launch of few rows that could divide K takes the whole of it: it then writes bf16 once instead of float32 partial sums
+// that another launch adds up, but has no more workgroups than tiles (wgs), and each of them a longer loop.  By times of both ways
+// at K = 512-12288 and N = 4096-32768: whole where the tiles make most of a round, or the loop is short.  At K = 4096:
+// 64 rows, QKV of 12288 columns 33.5 -> 22.9 us, gate/up of 2 x 12288 46.8 -> 35.5; 160 rows, gate/up 63 -> 56, 384 rows 103 -> 78, QKV
+// 55 -> 49.  The other side of the limits: 64 rows of 6144 columns, K = 8192, 29 us divided and 37 whole; gate/up of 2 x 8192, K = 3072,
+// 160 rows 34.5 and 40.8; 384 rows of 8192 columns, K = 8192, 62 and 86; gate/up of 2 x 9216, K = 8192, 384 rows 130 and 137.
+bool takes_whole_k(GemmEpilogue epi, int M, int N, int K) {
+  const int wgs = N / 64;                          // of every shape below but the 64 x 64 tiles of 65-128 rows
+  if (epi == kEpiSwiglu) {
+    if (M <= 64) return wgs >= 144;
+    if (M <= 128) return wgs >= 144 || (wgs >= 128 && K >= 1024 && K <= 2048);
+    if (M > 384 || (M > 256 && M <= 320) || wgs < 128 || wgs > 256 || N % 128 != 0) return false;
+    if (wgs < 144 || K <= 1024) return K <= 1024;
+    if (M <= 192) return K <= (wgs < 256 ? 8192 : 3072);       // 256: gate and up columns a power of two apart, 6-15 % slower from K = 4096 on
+    if (M <= 256) return K <= (wgs < 160 ? 4096 : wgs < 224 ? 8192 : INT_MAX);
+    return wgs >= 172 || K <= 2048;
+  }
+  if (epi != kEpiStore) return false;
+  if (M <= 64) return N % 64 == 0 && wgs >= 96 && (wgs >= 144 || K <= 2048);
+  if (M <= 128) return N % 64 == 0 && wgs >= 96 && K <= (wgs >= 256 ? 8192 : 4096);
+  return M > 320 && M <= 384 && N % 128 == 0 && wgs >= 128 && wgs <= 256 && (wgs >= 192 || K <= 2048);
 }
 
 // Tile shape: the one with the least estimated time = rounds of workgroups over the 256 CUs
@@ -862,13 +880,8 @@ int pick_config(GemmEpilogue epi, int M, int N, int K, double *cost = nullptr) {
   // The output head (N = vocabulary) has enough tiles to fill the chip at any M > 64 and goes by the
   // cost model below.
   if (forced < 0 && M <= 384 && (M <= 64 || N <= 32768)) {
-    if (epi == kEpiStore && M > 64 && M <= 128 && N > 8192 && N % 64 == 0) return 12;       // 64 x 64 tiles would be more than one a CU
-    if (plain && M <= 128 && N % 64 == 0) return 6;
-    if (epi == kEpiStore && store_one_round(M, N)) return 8;
-    if (epi == kEpiSwiglu && M <= 64 && takes_whole_k(epi, M, N)) return 11;
-    if (epi == kEpiSwiglu && M > 64 && M <= 128 && N >= 8192) return 3;
-    if (epi == kEpiSwiglu && swiglu_one_round(M, N) >= 0) return swiglu_one_round(M, N);
-    if (N % (epi == kEpiSwiglu ? 64 : 128) == 0) return 7;
+    const int c = few_rows_shape(epi, M, N, K);
+    if (c >= 0) return c;
   }
   int best = -1;
   double best_t = 0;
@@ -946,13 +959,14 @@ constexpr int kSplitMaxRows = 640;   // launches with more rows have enough tile
 //                 columns.  96 rows: O 64 x 64 in 2 15.1 us, 128 x 128 in 8 17.6; down 33 (64 x 64), 28.6.  192 rows: O 128 x 128
 //                 in 4 19.9, 192 x 128 in 8 23.6; down 36.9, 34.3.  256 rows: O 128 x 128 in 4 22.2, 256 x 128 in 8 26.0; down 42.1,
 //                 39.6.  512 rows: O 128 x 128 in 2 29.3; down 67.6, 256 x 128 in 4 57.9.  640 rows: O 160 x 128 in 2 32.8, undivided
-//                 35.4; down 160 x 256 in 4 67.8, undivided 108.
+//                 35.4; down 160 x 256 in 4 67.8, undivided 108.  193-256 rows of 9216 columns, K = 4096: 160 x 192 in 2 36 us, 256 x
+//                 128 in 2 38 (as fast as one another at 4096 columns, which 192 does not divide).
 enum SplitTile { kS64x64, kS192x128, kS320x128, kS160x256, kS160x192, kS160x128, kS128x128, kS128x256, kS256x128 };
 struct SplitShape { SplitTile tile; int bm, bn; double eff; };
 void splitk_plan(int M, int Nw, int K, size_t ws_floats, SplitTile *tile, int *splits) {
   constexpr SplitShape k64[] = {{kS64x64, 64, 64, 1}}, k128[] = {{kS64x64, 64, 64, 0.3}, {kS128x128, 128, 128, 0.66}};
   constexpr SplitShape k192[] = {{kS128x128, 128, 128, 0.66}, {kS192x128, 192, 128, 0.72}};
-  constexpr SplitShape k256[] = {{kS128x128, 128, 128, 0.66}, {kS256x128, 256, 128, 1.0}, {kS160x192, 160, 192, 0.80}};
+  constexpr SplitShape k256[] = {{kS128x128, 128, 128, 0.66}, {kS256x128, 256, 128, 1.0}, {kS160x192, 160, 192, 0.97}};
   constexpr SplitShape k384[] = {{kS160x256, 160, 256, 0.85}, {kS160x192, 160, 192, 0.80}, {kS160x128, 160, 128, 0.65},
                                   {kS192x128, 192, 128, 0.72}, {kS320x128, 320, 128, 0.70}};
   constexpr SplitShape k640[] = {{kS128x128, 128, 128, 0.70}, {kS128x256, 128, 256, 0.89}, {kS256x128, 256, 128, 0.93},
@@ -961,9 +975,10 @@ void splitk_plan(int M, int Nw, int K, size_t ws_floats, SplitTile *tile, int *s
   const int n_shapes = M <= 64 ? 1 : M <= 192 ? 2 : M <= 256 ? 3 : 5, nk = K / 64;
   *tile = shapes[0].tile;
   *splits = 0;
-  // 385-640 rows split only where tiles of 128 x 128 would leave half the chip idle or make a second round for a few (the O and
-  // down projections: 128-160 tiles)
-  if (M > 384 && (M + 127) / 128 * (Nw / 128) > 160) return;
+  // 385-640 rows split only where tiles of 128 x 128 would leave half the chip idle or, behind a loop of 64 stages or more, make a
+  // second round for a few (the O and down projections: 128-160 tiles).  576 rows of 4096 columns: K = 2048 19.6 us whole and 24-26
+  // divided, K = 12288 102 and 67.
+  if (M > 384 && (M + 127) / 128 * (Nw / 128) > (K >= 4096 ? 160 : 128)) return;
   double best = 0;
   for (const SplitShape *c = shapes; c < shapes + n_shapes; ++c) {
     if (Nw % c->bn != 0) continue;
@@ -989,7 +1004,7 @@ bool gemm_mfma_norm_capable(int cfg);
 bool gemm_mfma_splitk_supported(int dtype, GemmEpilogue epi, int M, int N, int K, size_t ws_floats) {
   if (epi == kEpiQkvRope || epi == kEpiPartial || !gemm_mfma_supported(dtype, epi, M, N, K)) return false;
   const int Nw = epi == kEpiSwiglu ? 2 * N : N;
-  if (M > kSplitMaxRows || Nw % 128 != 0 || N % 8 != 0 || Nw > 32768 || takes_whole_k(epi, M, N)) return false;
+  if (M > kSplitMaxRows || Nw % 128 != 0 || N % 8 != 0 || Nw > 32768 || takes_whole_k(epi, M, N, K)) return false;
   SplitTile tile;
   int splits;
   splitk_plan(M, Nw, K, ws_floats, &tile, &splits);

@@ -1,6 +1,6 @@
 """Launches of few rows that take the whole of K (context GEMMs of wide projections), and the ones that divide it where the tile
 shapes change: every element against float64
-products of the same bf16 inputs, on both sides of the limits in rows and columns, with fewer stages than the ring holds, with
+products of the same bf16 inputs, on both sides of the limits in rows, columns and K, with fewer stages than the rings hold, with
 columns of tiles that start inside K, and last tiles with few rows."""
 import pytest
 import torch
@@ -47,6 +47,30 @@ def test_every_element_of_more_rows(ctx, M, N, K, kind):
     else:
         got, want = ctx.gemm(A, W, residual=R), full + (R.double() if R is not None else 0)
     assert bool(((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + K ** 0.5 * 2.0 ** -22 * size).all())
+
+
+# rings of six stages with one, three and five of them to fill (128 x 64 store, 64 x 128 SwiGLU), an odd multiple of 64 columns, and
+# the limits in columns and K between whole and divided launches
+@pytest.mark.parametrize("M", [1, 64, 65, 128])
+@pytest.mark.parametrize("N,K", [(12288, 64), (12288, 320), (9280, 192), (9280, 1088), (8320, 64), (8320, 320), (20480, 1024), (20480, 2048), (6144, 2112),
+                                 (9216, 5120), (16384, 1024)])
+def test_short_loops_and_limits(ctx, M, N, K):
+    if N % 128 == 0:
+        test_every_element(ctx, M, N, K)
+        return
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)           # plain products take whole 128 columns
+    A = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
+    W = (torch.randn(2 * N, K, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    full = A.double() @ W.double().T
+    want, size = torch.nn.functional.silu(full[:, :N]) * full[:, N:], 1 + full[:, :N].abs() + full[:, N:].abs()
+    assert bool(((ctx.gemm_swiglu(A, W).double() - want).abs() <= 2.0 ** -8 * want.abs() + K ** 0.5 * 2.0 ** -22 * size).all())
+
+
+@pytest.mark.parametrize("M", [129, 192, 193, 256, 320, 321, 384, 385, 513, 576])
+@pytest.mark.parametrize("N,K,kind", [(8192, 1024, "swiglu"), (8192, 1088, "swiglu"), (9216, 2048, "swiglu"), (9216, 4160, "swiglu"), (11008, 2112, "swiglu"),
+                                      (16384, 3072, "swiglu"), (8192, 2048, "store"), (8192, 3072, "store"), (9216, 3072, "store"), (4096, 2048, "residual")])
+def test_limits_of_more_rows(ctx, M, N, K, kind):
+    test_every_element_of_more_rows(ctx, M, N, K, kind)
 
 
 @pytest.mark.parametrize("M,N,K", [(64, 6144, 512), (128, 6144, 512), (128, 12288, 1024), (2, 8192, 2048), (384, 8192, 512), (256, 4096, 8192), (640, 4096, 4096)])
