@@ -73,6 +73,8 @@ __device__ __forceinline__ void rank_candidates(const int32_t *s_cand, float *cw
 }
 
 // Dynamic LDS layout: conf[(1+K)*R] | tok[(1+K)*R] | x[R] | flag[2*block_len]
+// kOut: a.out is in use (rounds whose status the host waits for); decision steps without it pay nothing for it.
+template <bool kOut>
 __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   extern __shared__ unsigned char smem[];
   const int tid = threadIdx.x, nth = kStage2Threads, lane = tid & 63, wave = tid >> 6;
@@ -94,7 +96,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
 
   int32_t nc0 = 0, nc1 = 0, nc2 = 0;           // thread 0: n_commit of the group
   auto report = [&](int is_done, int n_next) {
-    if (a.out.status == nullptr) return;
+    if (!kOut || a.out.status == nullptr) return;
     int32_t *w = a.out.status + 5 * (int64_t)g;
     w[0] = is_done; w[1] = n_next; w[2] = nc0; w[3] = nc1; w[4] = nc2;
   };
@@ -104,7 +106,7 @@ __global__ void __launch_bounds__(kStage2Threads) stage2_kernel(Stage2Args a) {
   const int n_drafts = a.st.n_drafts[g], draft_route = a.st.draft_route[g], n_ws = a.st.n_ws_blocks[g];
   if (done || ka < 0 || ka >= a.n_blocks) {   // finished (or invalid) group: report an empty round
     // No live canvas means that every group is done, so the word is looked at here and live groups do not wait for it.
-    if (a.out.skip_if_zero && *a.out.skip_if_zero == 0) return;
+    if (kOut && a.out.skip_if_zero && *a.out.skip_if_zero == 0) return;
     for (int j = tid; j < K; j += nth) accept[j] = 0;
     if (tid == 0) {
       a.st.winner[g] = 0; ncommit[0] = ncommit[1] = ncommit[2] = 0; a.st.n_drafts[g] = 0; a.st.done[g] = 1;
@@ -534,7 +536,7 @@ pvf_status launch_stage2(pvf_ctx *ctx, hipStream_t s, int G, int vocab, int mask
   a.n_blocks = cfg.gen_len / cfg.block_len;
   const size_t lds = (size_t)(1 + cfg.K) * a.R * 8 + (size_t)a.R * 4 + (size_t)cfg.block_len * 8;
   PVF_REQUIRE(ctx, lds <= 64 * 1024, PVF_ESHAPE, "stage2: (1+K)*R too large for LDS (%zu bytes)", lds);
-  stage2_kernel<<<G, kStage2Threads, lds, s>>>(a);
+  (out.status || out.skip_if_zero ? stage2_kernel<true> : stage2_kernel<false>)<<<G, kStage2Threads, lds, s>>>(a);
   PVF_LAUNCH_CHECK(ctx, "stage2");
   return PVF_OK;
 }
