@@ -250,7 +250,7 @@ pvf_status pvf_state_init(pvf_ctx *ctx, void *stream, const int32_t *prompt, int
 
 /* Algorithm 1 to completion for G groups: pvf_state_init, then pvf_round until every group
  * is done.  Waits once per round for 5*G status words, which the round's last kernel writes to host memory; a float32
- * decode without the K/V cache waits for the round before the one it enqueued last.
+ * decode without the K/V cache may have enqueued the round behind that one already.
  *   out_tokens dev int32 [G, T]; stats host (may be NULL). */
 pvf_status pvf_decode(pvf_ctx *ctx, void *stream, const int32_t *prompt, int32_t G,
                       const uint32_t *plan_bitmap, const pvf_decode_cfg *cfg,

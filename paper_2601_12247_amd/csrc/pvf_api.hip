@@ -916,9 +916,14 @@ extern "C" pvf_status pvf_decode(pvf_ctx *ctx, void *stream, const int32_t *prom
   if ((st = launch_state_init(ctx, s, prompt, G, ctx->model.mask_id, *cfg, *state)) != PVF_OK) return st;
   int n_seq = G;                                  // first round: backbones only
   const int max_rounds = cfg->gen_len + 2;        // every round commits at least one token per live group
-  // Rounds whose launches do not depend on the number of live canvases (float32) are enqueued one ahead: round r + 1 is on the
-  // stream before the host waits for the status of round r, so that the device never waits for the host.  The round behind the
-  // last one finds no live canvas and changes nothing.
+  // Rounds whose launches do not depend on the number of live canvases (float32) may be enqueued one ahead: round r + 1 is on the
+  // stream before the host waits for the status of round r, so that the device does not wait for the host.  The round behind the
+  // last one finds no live canvas and changes nothing.  Its launches then have workgroups for every draft that round r may propose,
+  // and the ones without a canvas take a microsecond each to find that out, so it is only done while the canvases of round r are
+  // short of that by few rows; otherwise its status is waited for.  2 layers, 256 wide: waiting costs 6-10 us a round (1 x 128
+  // tokens, 2 drafts, 118 -> 127 us), a surplus of 512 rows as much; 4 x 229 tokens with room for 32 drafts and none proposed took 590 us
+  // a round and take 157, 12 x 229 with room for 4, 448 and 302.
+  constexpr int64_t kAheadRows = 512;
   const bool ahead = !cfg->kv_cache && !ctx->prof_on && f32_fused(ctx, cfg->prompt_len + cfg->gen_len);
   if ((st = reserve_status(ctx, G)) != PVF_OK) return st;
   if (ahead)
@@ -929,15 +934,17 @@ extern "C" pvf_status pvf_decode(pvf_ctx *ctx, void *stream, const int32_t *prom
     PVF_HIP_CHECK(ctx, hipEventRecord(ctx->round_ev[r & 1], s));
     return PVF_OK;
   };
-  if (ahead && (st = enqueue(0, G)) != PVF_OK) { (void)hipStreamSynchronize(s); return st; }
   int live_groups = G;
+  bool queued = false;                            // round acc.rounds is on the stream already
   while (n_seq > 0) {
     PVF_REQUIRE(ctx, acc.rounds < max_rounds, PVF_EINVAL, "pvf_decode: no progress after %d rounds", acc.rounds);
     const int32_t *status = ctx->status_host;
     if (ahead) {
-      const int r = acc.rounds;
+      const int r = acc.rounds, most = live_groups * (1 + cfg->K);
+      if (!queued && (st = enqueue(r, n_seq)) != PVF_OK) { (void)hipStreamSynchronize(s); return st; }
       // the last round allowed has none behind it
-      if (r + 1 < max_rounds && (st = enqueue(r + 1, live_groups * (1 + cfg->K))) != PVF_OK) { (void)hipStreamSynchronize(s); return st; }
+      queued = r + 1 < max_rounds && (int64_t)(most - n_seq) * (cfg->prompt_len + cfg->gen_len) <= kAheadRows;
+      if (queued && (st = enqueue(r + 1, most)) != PVF_OK) { (void)hipStreamSynchronize(s); return st; }
       PVF_HIP_CHECK(ctx, hipEventSynchronize(ctx->round_ev[r & 1]));
       status += (r & 1) * 5 * G;
     } else if ((st = round_status_impl(ctx, s, G, plan_bitmap, *cfg, *state, n_seq)) != PVF_OK) {

@@ -49,7 +49,8 @@ def test_rows_do_not_depend_on_the_batch(T, R, few, many):
     assert torch.equal(plain, all_)
 
 
-@pytest.mark.parametrize("G,prompt,gen,block,K,routes", [(1, 20, 32, 16, 0, 3), (5, 33, 64, 16, 4, 3), (3, 0, 48, 16, 2, 1), (70, 5, 16, 16, 1, 3)])
+@pytest.mark.parametrize("G,prompt,gen,block,K,routes", [(1, 20, 32, 16, 0, 3), (5, 33, 64, 16, 4, 3), (3, 0, 48, 16, 2, 1), (70, 5, 16, 16, 1, 3),
+                                                        (4, 40, 48, 16, 8, 1)])      # room for many more drafts than there are
 def test_decode_is_its_rounds(G, prompt, gen, block, K, routes):
     """pvf_decode leaves state, tokens and counts as the same rounds called one by one do, although a round more is enqueued."""
     cfg = B.DecodeCfg(block_len=block, prompt_len=prompt, gen_len=gen, K=K, tau_high=0.9, logit_scale=6.0, routes=routes)
