@@ -116,7 +116,8 @@ pvf_status launch_stage2(pvf_ctx *ctx, hipStream_t s, int G, int vocab, int mask
 pvf_status launch_state_init(pvf_ctx *ctx, hipStream_t s, const int32_t *prompt, int G,
                              int mask_id, const pvf_decode_cfg &cfg, const pvf_state &st);
 
-// builds seq_slot[] and row_pos[] for a round; n_seq entries are written (padding repeats slot 0)
+// builds seq_slot[] and row_pos[] for a round; n_seq entries are written (padding repeats the first live canvas, slot 0 where
+// none is)
 pvf_status launch_build_batch(pvf_ctx *ctx, hipStream_t s, int G, int n_seq,
                               const pvf_decode_cfg &cfg, const pvf_state &st,
                               int32_t *seq_slot, int32_t *row_pos);

@@ -782,8 +782,9 @@ constexpr int kNumCfg = 13;
 // Every shape for many rows runs 8 waves, two per SIMD (the two small ones 4 waves, two workgroups per CU):
 // with one wave per SIMD the 256 x 256 tile (wave tiles of 128 x 128, a third fewer LDS reads) measured 2-4 %
 // slower, smaller wave tiles far slower.
-// plain_only: wave tiles 32 columns wide, which the SwiGLU and rotary epilogues cannot pair up, or 80 rows high
-// (a last epilogue pass of 16 rows, which only the plain epilogues handle).
+// plain_only: wave tiles 32 columns wide, which the rotary epilogue cannot pair up, or 80 rows high (a last epilogue pass of 16
+// rows, which only the plain epilogues handle).  SwiGLU takes 192 x 128 among them (16 gate and 16 up columns a wave), by
+// few_rows_shape alone.
 constexpr TileCfg kCfg[kNumCfg] = {
     {256, 256, 64, 2, 1.00, false},   // the wide layers
     {128, 256, 64, 3, 0.89, false}, {256, 128, 64, 3, 0.891, false},
@@ -815,8 +816,8 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
     case 8: if constexpr (EPI != kEpiQkvRope) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 9: if constexpr (kPlain) return run<EPI, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 10: if constexpr (EPI == kEpiSwiglu) return run<EPI, 256, 192, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
-    case 11: return run<EPI, 64, 128, 64, 6, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);
-    case 12: if constexpr (kPlain) return run<EPI, 128, 64, 64, 6, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
+    case 11: if constexpr (EPI == kEpiSwiglu) return run<EPI, 64, 128, 64, 6, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
+    case 12: if constexpr (EPI == kEpiStore) return run<EPI, 128, 64, 64, 6, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     default: break;
   }
   return run<EPI, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);

@@ -271,7 +271,7 @@ extern "C" pvf_status pvf_create(pvf_ctx **out, const pvf_model_cfg *m, const pv
       {(void **)&c->n_live, 4},
       {(void **)&c->cos_sin, (int64_t)max_T * half * 8},
       // partial sums of the few-row GEMMs: rows x splits x row length, at most 384 x 49152 floats (up to 384 rows
-      // every layer GEMM may split, from there to 640 rows only those with rows of 4096 or less)
+      // every layer GEMM may split, from there to 640 rows only those of few columns: splitk_plan checks the room)
       {(void **)&c->splitk_ws, m->dtype == PVF_BF16 ? (int64_t)384 * 49152 * 4 : 0},
       {(void **)&c->row_ss, m->dtype == PVF_BF16 && d % 128 == 0 ? (d / 64) * M * 4 : 0}};
   for (auto &r : req) {
