@@ -114,10 +114,10 @@ struct RopeArgs {
 struct SplitK {
   float *partial;
   int32_t nk_per;                                    // k stages per split
-  int32_t turn = 0;                                  // undivided launches: columns of tiles may start anywhere in K
+  int32_t turn = 0;                                  // undivided launches: columns of tiles may start anywhere in K (host)
 };
 
-template <int EPI, int BM, int BN, int BK, int kStages, int WM, int WN, bool kPairs, bool kHint>
+template <int EPI, int BM, int BN, int BK, int kStages, int WM, int WN, bool kPairs, bool kHint, bool kTurn>
 __global__ void __launch_bounds__(64 * WM * WN)
 __attribute__((amdgpu_waves_per_eu(waves_per_simd(kStages * (BM + BN) * BK * 2, WM * WN),
                                    waves_per_simd(kStages * (BM + BN) * BK * 2, WM * WN))))
@@ -209,9 +209,9 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   // of a launch, add their k in the same order, and equal rows stay equal.  Cached rounds 2.0 and 2.6 % faster.
   // So do launches of few rows that do not split K, every column of tiles from a place of its own: the 64-row tiles read the
   // activations from L2 wherever they are (64 rows: gate/up of 24576 weight rows 42.5 -> 35.5 us, QKV 24.5 -> 22.9).
-  constexpr bool kWhole = EPI != kEpiPartial && ((EPI == kEpiSwiglu && BM == 128 && BN == 128) || (BM == 64 && BN == 128 && kStages == 6) ||
-                                                 (BM == 64 && BN == 64) || (BM == 128 && BN == 64));
-  const int turn = EPI == kEpiPartial ? nk / 8 * (tile_n * 8 / tiles_n) : kWhole && sk.turn ? (int)((int64_t)tile_n * nk / tiles_n) : 0;
+  // An instance of its own: a division and a wrap per load in launches that do not turn cost 128 x 128 SwiGLU tiles 4-7 % at K <= 1024
+  // (512 rows x 1408 columns, K = 512, 7.4 and 7.9 us).  tile_n nk < 2^19, as W is smaller than 4 GiB.
+  const int turn = EPI == kEpiPartial ? nk / 8 * (tile_n * 8 / tiles_n) : kTurn ? (int)((uint32_t)(tile_n * nk) / (uint32_t)tiles_n) : 0;
   constexpr int kWAux = kHint ? 2 : 0;               // weights with the non-temporal hint (run)
   // The quadrant schedule loads through buffer descriptors: base + 32-bit lane offset + scalar offset, where the compiler
   // turns the global form into a 64-bit address per load and lane (16 registers that are not there).
@@ -222,7 +222,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
 #endif
   auto issue_one = [&](int kt, int i) {                      // load i (A loads first, then W) of stage kt
     unsigned char *dst = lds + (kt % kStages) * kStage + wave * 1024;
-    const int kr = !(EPI == kEpiPartial || kWhole) || kt + turn < nk ? kt + turn : kt + turn - nk;
+    const int kr = !(EPI == kEpiPartial || kTurn) || kt + turn < nk ? kt + turn : kt + turn - nk;
     if constexpr (kQuad) {
 #ifdef __HIP_DEVICE_COMPILE__
       if (i < LA) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lptr_t *)(dst + i * kInstrBytes), 16, a_off[i], kr * (BK * 2), 0, 0);
@@ -753,8 +753,8 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   constexpr int kBand = BM > BN ? 4 : 8;
   const int n_bands = (tiles_m + kBand - 1) / kBand;
   const int group_m = (tiles_m + n_bands - 1) / n_bands;
-  auto launch = [&](auto hint) -> pvf_status {
-    const auto kernel = gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN, kPairs, decltype(hint)::value>;
+  auto launch = [&](auto hint, auto turn) -> pvf_status {
+    const auto kernel = gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN, kPairs, decltype(hint)::value, decltype(turn)::value>;
     // once per kernel instance; a function-local static is initialised exactly once even with concurrent callers
     static const hipError_t configured =
         hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
@@ -770,10 +770,13 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   // hint and 34.4 without, K = 8192 132 and 121; 4100 rows of 12288 columns, K = 4096, 352 and 335.
   constexpr bool kFewRows = EPI == kEpiPartial ? BM == 64 : BN == 64 || ST == 6;                 // shapes for up to 128 rows
   constexpr bool kTwoRows = (EPI == kEpiPartial && BN == 192) || (EPI == kEpiStore && BM == 160);
-  if constexpr (kFewRows) return launch(std::true_type{});
+  // shapes that the launches taking the whole of K behind few rows are made of
+  constexpr bool kTurns = (EPI == kEpiStore && BN == 64) || (EPI == kEpiSwiglu && BN == 128 && (ST == 6 || BM == 128));
+  if constexpr (kTurns) if (sk.turn) return launch(std::bool_constant<kFewRows>{}, std::true_type{});
+  if constexpr (kFewRows) return launch(std::true_type{}, std::false_type{});
   else {
-    if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{});
-    return launch(std::false_type{});
+    if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{}, std::false_type{});
+    return launch(std::false_type{}, std::false_type{});
   }
 }
 
@@ -1119,7 +1122,7 @@ int gemm_mfma_norm_slots(GemmEpilogue epi, int M, int N, int K) {
   return N / (kCfg[c].bn == 256 ? 256 : 64);
 }
 
-// turn: the order in which an element's k are added may depend on the launch (few rows, see kWhole).
+// turn: the order in which an element's k are added may depend on the launch (few rows, see kTurns).
 pvf_status launch_gemm_mfma(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const void *A,
                             const void *W, void *C, const void *residual, int M, int N, int K, const NormArgs *na, bool turn) {
   const uintptr_t al = (uintptr_t)A | (uintptr_t)W | (uintptr_t)C | (uintptr_t)residual;
