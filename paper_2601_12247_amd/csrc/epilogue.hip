@@ -367,7 +367,7 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
 // so the row is counted into LDS, 8192 counters for both signs of 32 exponents, and the float64 exponential is taken once
 // per value that occurs instead of once per element -- the same terms as EntropySums adds, each weighted by its count.  The
 // range ends four exponents above the largest one of a sample, 4096 elements at equal distances over the row; what lies outside
-// goes to a list (1024 entries, counted afterwards range by range) or, from -1.7e38 down, adds nothing beside any value above
+// goes to a list (1024 entries, added in one order afterwards) or, from -1.7e38 down, adds nothing beside any value above
 // -1e38 (they are 700 apart at scales from 1e-35 on).  Rows of which this does not hold (more such elements, NaN, a maximum as low
 // as that, a smaller scale) are left to stage1_vec_kernel in a launch behind this one (4.5 us where there are none), at once where
 // the sample holds more than 1024 / vocab of them; so are rows of few values, told by equal elements of the sample: equal values
@@ -415,23 +415,24 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
   const uint4 *__restrict__ p = reinterpret_cast<const uint4 *>(row + head);
   const int nvec = (vocab - head) / N;
   const int mask_vec = mask_id >= head ? (mask_id - head) / N : INT_MAX, mask_lane = mask_id >= head ? (mask_id - head) % N : 0;
-  // 64 pieces of 64 elements (whole lines), at equal distances over the row: nvec >= 2499
-  const uint4 sample = p[tid / 8 * ((nvec - 8) / 63) + tid % 8];
+  // 64 pieces of 64 elements (whole lines), at equal distances over the row: nvec >= 3499
+  const int sample_vec = tid / 8 * ((nvec - 8) / 63) + tid % 8;
+  const uint4 sample = p[sample_vec];
   for (int i = tid; i < kHistBins / 4; i += kHistBlock) reinterpret_cast<uint4 *>(s_hist)[i] = make_uint4(0, 0, 0, 0);
   if (tid == 0) s_n = s_low = s_nan = s_ranges = s_match = s_top = s_out = 0;
   __syncthreads();
+  const uint32_t sw[4] = {sample.x, sample.y, sample.z, sample.w};
   {
-    const uint32_t w[4] = {sample.x, sample.y, sample.z, sample.w};
     int match = 0, top = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t o = __shfl(w[i], (lane + 8) & (kWave - 1));      // of the next piece
+      const uint32_t o = __shfl(sw[i], (lane + 8) & (kWave - 1));     // of the next piece
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const uint32_t a = h ? w[i] >> 16 : w[i] & 0xffffu, b = h ? o >> 16 : o & 0xffffu;
+        const uint32_t a = h ? sw[i] >> 16 : sw[i] & 0xffffu, b = h ? o >> 16 : o & 0xffffu;
         match += __popcll(__ballot(a == b && a < 0xff00u));
         const int e = (int)(a >> 7) & 0xff;
-        if (e < 254 && !(tid == mask_vec && 2 * i + h == mask_lane)) top = max(top, e);
+        if (e < 254 && !(sample_vec == mask_vec && 2 * i + h == mask_lane)) top = max(top, e);
       }
     }
 #pragma unroll
@@ -441,11 +442,10 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
   __syncthreads();
   const uint32_t low = (uint32_t)max((s_top ? s_top : 127) - 27, 0) << 7;      // bits of the smallest value counted
   {
-    const uint32_t w[4] = {sample.x, sample.y, sample.z, sample.w};
     int out = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const uint32_t a = i & 1 ? w[i / 2] >> 16 : w[i / 2] & 0xffffu;
+      const uint32_t a = i & 1 ? sw[i / 2] >> 16 : sw[i / 2] & 0xffffu;
       out += __popcll(__ballot(((a - low) & 0x7000u) != 0 && !(a >= 0xff00u && a <= 0xff80u)));
     }
     if (lane == 0 && out) atomicAdd(&s_out, out);
@@ -475,8 +475,9 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
     if (v > m) { m = v; first = id; cnt = 0; }
     count_one(__float_as_uint(v) >> 16);
   };
-  // UV vectors of this thread from `base`, BLOCK apart
-  auto vectors = [&](int base, auto uv, auto check_mask) {
+  // UV vectors of this thread from `base`, BLOCK apart; check_mask (uniform): the [MASK] column may lie in one.  (One instance of
+  // the loop's body: with four of them their length showed in launches of few rows.)
+  auto vectors = [&](int base, auto uv, bool check_mask) {
     constexpr int UV = decltype(uv)::value;
     uint4 w[UV];
 #pragma unroll
@@ -486,7 +487,7 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
 #pragma unroll
     for (int u = 0; u < UV; ++u) {
       b[u][0] = w[u].x; b[u][1] = w[u].y; b[u][2] = w[u].z; b[u][3] = w[u].w;
-      if (decltype(check_mask)::value && base + u * kHistBlock == mask_vec) {
+      if (check_mask && base + u * kHistBlock == mask_vec) {
 #pragma unroll
         for (int i = 0; i < N; ++i)
           if (i == mask_lane) b[u][i / 2] = i & 1 ? (b[u][i / 2] & 0xffffu) | 0xff800000u : (b[u][i / 2] & 0xffff0000u) | 0xff80u;
@@ -548,11 +549,8 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
   if (tid < head) single(tid);
   const int nfull = nvec / kStride, it_mask = mask_vec / kStride;
   const std::integral_constant<int, U> all{};
-  const int split = it_mask < nfull ? it_mask : nfull;
-  for (int it = 0; it < split && !full; ++it) vectors(it * kStride + tid, all, std::false_type{});
-  if (it_mask < nfull && !full) vectors(it_mask * kStride + tid, all, std::true_type{});
-  for (int it = split + 1; it < nfull && !full; ++it) vectors(it * kStride + tid, all, std::false_type{});
-  for (int idx = nfull * kStride + tid; idx < nvec; idx += kHistBlock) vectors(idx, std::integral_constant<int, 1>{}, std::true_type{});
+  for (int it = 0; it < nfull && !full; ++it) vectors(it * kStride + tid, all, it == it_mask);
+  for (int idx = nfull * kStride + tid; idx < nvec; idx += kHistBlock) vectors(idx, std::integral_constant<int, 1>{}, true);
   if (tid < vocab - head - nvec * N) single(head + nvec * N + tid);
   float M = wave_max(m);
   if (lane == 0) s_f[wid] = M;
@@ -582,9 +580,20 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
     }
   };
   add_counts(low);
-  // The list is in the order of the atomics, so its elements are counted like the others, 32 exponents after 32: sums of counts
-  // have one order.
-  if (s_n) {                                             // uniform
+  // The list is in the order of the atomics.  Up to 64 elements are sorted by their places in a wave; more are counted like the
+  // others, 32 exponents after 32 (1.5-2 us for each such range that occurs): either way sums have one order.
+  if (s_n <= kWave) {
+    if (wid == 0) {
+      const uint32_t v = lane < s_n ? s_list[lane] : 0u;
+      int at = 0;
+      for (int i = 0; i < s_n; ++i) {
+        const uint32_t o = __shfl(v, i);
+        at += o < v || (o == v && i < lane);
+      }
+      const uint32_t sorted = __builtin_amdgcn_ds_permute((lane < s_n ? at : lane) * 4, v);
+      if (lane < s_n) add(__uint_as_float(sorted << 16), 1.0);
+    }
+  } else {
     for (int i = tid; i < s_n; i += kHistBlock) atomicOr(&s_ranges, 1 << (((s_list[i] - low) >> 12) & 7));
     __syncthreads();
     for (int r = 1; r < 8; ++r) {
@@ -698,9 +707,11 @@ static bool launch_vec(hipStream_t s, const T *logits, int64_t n_rows, int vocab
       return true;
     }
   }
-  // Counting pays from 20000 elements a row on (2112 rows: 16384 34.7 us either way, 20000 44 -> 40, 32768 61 -> 46).
+  // Counting pays from 28000 elements a row on, whatever the number of rows (which must not decide: a row's last bit would follow its
+  // batch).  2112 rows: 16384 34.7 us either way, 20000 40 and 39, 32000 56 and 45; 64 rows, where the second launch shows: 20000 10.3
+  // without and 11.7 with, 32000 15.1 and 13.2, 50257 14.0 and 14.2, 126464 28.5 and 21.4.
   if constexpr (kEnt && sizeof(T) == 2) {
-    if (nvec >= 2500) {
+    if (nvec >= 3500) {
       stage1_hist_kernel<<<grid, kHistBlock, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
       stage1_vec_kernel<T, kWide, 2, true, true, true><<<grid, kWide, 0, s>>>(logits, vocab, mask_id, scale, rf, conf, tok, ent);
       return true;

@@ -7,7 +7,8 @@ from paper_2601_12247_amd import binding as B
 from tests.test_gpu_logit_rows import reference
 
 pytestmark = pytest.mark.gpu
-V = 20_011                                                   # just above the limit; rows begin anywhere
+V = 28_011                                                   # just above the limit; rows begin anywhere
+
 
 
 def rows_of(seed):
@@ -54,16 +55,17 @@ def test_scales_so_small_that_no_value_is_negligible():
             assert abs(g - w) <= 2e-6 * abs(w) + 1e-38, (name, scale, g, w)
 
 
-def test_listed_elements_are_added_in_one_order():
+@pytest.mark.parametrize("listed", [2, 63, 64, 65, 900])
+def test_listed_elements_are_added_in_one_order(listed):
     """Equal rows, whose elements beyond the counters' range reach the list in any order: one value above them, the others 30-33
     below it, so that the order of the sums shows in the entropy."""
-    n = 20_032
+    n = 28_032
     rng = np.random.default_rng(6)
     x = 0.1 * rng.standard_normal(n).astype(np.float32)
     at = np.arange(4096, n)
-    at = rng.permutation(at[(at // 8 % 39 >= 12) & (at // 8 % 39 < 34)])[:900]      # between the places that the range is taken from
-    x[at] = 40 + rng.integers(0, 13, 900) / 4
-    x[at[450]] = 73
+    at = rng.permutation(at[(at // 8 % 55 >= 12) & (at // 8 % 55 < 50)])[:listed]      # between the places that the range is taken from
+    x[at] = 40 + rng.integers(0, 13, listed) / 4
+    x[at[listed // 2]] = 73
     rows = torch.from_numpy(x).to(torch.bfloat16).cuda()[None].repeat(512, 1)
     first = B.entropy(rows, 3, 1.0)
     for _ in range(8):
@@ -73,7 +75,7 @@ def test_listed_elements_are_added_in_one_order():
     assert abs(first[0].item() - ent[0]) <= 1e-5 * ent[0]    # S is 1 and a few 1e-11, rounded at 2^-53
 
 
-@pytest.mark.parametrize("n", [V, 20_032, 126_464])
+@pytest.mark.parametrize("n", [V, 28_032, 126_464])
 def test_rows_that_change_along_the_way(n):
     """Rows whose front says nothing about what follows, and values in any number of the counters' ranges."""
     rng = np.random.default_rng(n)
@@ -97,6 +99,14 @@ def test_rows_that_change_along_the_way(n):
         _, _, ent = reference(x.float().numpy(), 1.0, mask_id)
         got = B.entropy(x.cuda(), mask_id, 1.0).cpu().numpy()
         np.testing.assert_allclose(got, ent, rtol=2e-6, atol=1e-38)      # the bound of the tests above
+
+
+@pytest.mark.parametrize("n", [27_999, 28_000, 28_007, 28_008])
+def test_limit_of_counting(n):
+    """Rows of 3500 vectors are counted, shorter ones are not; rows begin anywhere."""
+    x = torch.from_numpy(np.random.default_rng(n).standard_normal((9, n)).astype(np.float32)).to(torch.bfloat16)
+    _, _, ent = reference(x.float().numpy(), 1.5, n // 3)
+    np.testing.assert_allclose(B.entropy(x.cuda(), n // 3, 1.5).cpu().numpy(), ent, rtol=2e-6)
 
 
 def test_rows_without_numbers():
