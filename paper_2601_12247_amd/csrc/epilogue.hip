@@ -366,11 +366,11 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
 // Entropy, confidence and top-1 token of long bf16 rows (calibration) from a histogram: a bf16 row holds few distinct values,
 // so the row is counted into LDS, 8192 counters for both signs of 32 exponents, and the float64 exponential is taken once
 // per value that occurs instead of once per element -- the same terms as EntropySums adds, each weighted by its count.  The
-// range ends four exponents above the largest one of a sample, 4096 elements at equal distances over the row; what lies outside
+// range ends four exponents above the largest one of a sample, 2048 elements at equal distances over the row; what lies outside
 // goes to a list (1024 entries, added in one order afterwards) or, from -1.7e38 down, adds nothing beside any value above
 // -1e38 (they are 700 apart at scales from 1e-35 on).  Rows of which this does not hold (more such elements, NaN, a maximum as low
 // as that, a smaller scale) are left to stage1_vec_kernel in a launch behind this one (4.5 us where there are none), at once where
-// the sample holds more than 1024 / vocab of them; so are rows of few values, told by equal elements of the sample: equal values
+// the sample holds more than 1280 / vocab of them; so are rows of few values, told by equal elements of the sample: equal values
 // of a wave wait for each other at their counter, and from a chance of 1 / 16 for two elements to be equal on an exponential for
 // each is the quicker way (2112 rows of 126464: one value 170 against 970 us, 11 values 230 against 720, the last tenth of a row
 // of one value 195 against 190).
@@ -397,7 +397,7 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
   __shared__ uint32_t s_hist[kHistBins];
   __shared__ uint16_t s_list[kHistList];
   __shared__ int s_n, s_low, s_nan, s_ranges;            // list entries; whether an element below -1.7e38, a NaN occurred; ranges listed
-  __shared__ int s_match, s_top, s_out;                  // of the sample: equal neighbours, largest exponent, elements for the list
+  __shared__ int s_match, s_top, s_deep, s_out;          // of the sample: equal neighbours, largest exponent, 255 - the smallest, elements for the list
   __shared__ float s_f[kHistBlock / kWave];
   __shared__ int s_i[kHistBlock / kWave];
   __shared__ double s_d[2 * (kHistBlock / kWave)];
@@ -415,15 +415,17 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
   const uint4 *__restrict__ p = reinterpret_cast<const uint4 *>(row + head);
   const int nvec = (vocab - head) / N;
   const int mask_vec = mask_id >= head ? (mask_id - head) / N : INT_MAX, mask_lane = mask_id >= head ? (mask_id - head) % N : 0;
-  // 64 pieces of 64 elements (whole lines), at equal distances over the row: nvec >= 3499
-  const int sample_vec = tid / 8 * ((nvec - 8) / 63) + tid % 8;
-  const uint4 sample = p[sample_vec];
+  // The sample: 32 pieces of 64 elements (whole lines) at equal distances over the row, nvec >= 3499, by the first waves.  Its lines
+  // come from memory twice where many rows are under way (13824 rows of 71808: 0.6 % of the launch, 64 pieces 2.8 %).
+  constexpr int kSample = kHistBlock / 2;
+  const int sample_vec = tid / 8 * ((nvec - 8) / (kSample / 8 - 1)) + tid % 8;
+  const uint4 sample = tid < kSample ? p[sample_vec] : make_uint4(0, 0, 0, 0);
   for (int i = tid; i < kHistBins / 4; i += kHistBlock) reinterpret_cast<uint4 *>(s_hist)[i] = make_uint4(0, 0, 0, 0);
-  if (tid == 0) s_n = s_low = s_nan = s_ranges = s_match = s_top = s_out = 0;
+  if (tid == 0) s_n = s_low = s_nan = s_ranges = s_match = s_top = s_deep = s_out = 0;
   __syncthreads();
   const uint32_t sw[4] = {sample.x, sample.y, sample.z, sample.w};
-  {
-    int match = 0, top = 0;
+  if (tid < kSample) {                                   // whole waves
+    int match = 0, top = 0, deep = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t o = __shfl(sw[i], (lane + 8) & (kWave - 1));     // of the next piece
@@ -433,25 +435,28 @@ stage1_hist_kernel(const bf16_t *__restrict__ logits, int vocab, int mask_id, fl
         match += __popcll(__ballot(a == b && a < 0xff00u));
         const int e = (int)(a >> 7) & 0xff;
         if (e < 254 && !(sample_vec == mask_vec && 2 * i + h == mask_lane)) top = max(top, e);
+        if (a - 0xff00u > 0x80u) deep = max(deep, e < 254 ? 255 - e : 255);
       }
     }
+    ushort2v td = {(unsigned short)top, (unsigned short)deep};
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, kWave));
-    if (lane == 0) { atomicAdd(&s_match, match); atomicMax(&s_top, top); }
+    for (int o = kWave / 2; o > 0; o >>= 1)
+      td = __builtin_elementwise_max(td, __builtin_bit_cast(ushort2v, __shfl_xor(__builtin_bit_cast(uint32_t, td), o, kWave)));
+    if (lane == 0) { atomicAdd(&s_match, match); atomicMax(&s_top, (int)td.x); atomicMax(&s_deep, (int)td.y); }
   }
   __syncthreads();
   const uint32_t low = (uint32_t)max((s_top ? s_top : 127) - 27, 0) << 7;      // bits of the smallest value counted
-  {
+  if (255 - s_deep < (int)(low >> 7)) {                  // uniform: elements below the range, or beyond the ones that make it
     int out = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const uint32_t a = i & 1 ? sw[i / 2] >> 16 : sw[i / 2] & 0xffffu;
       out += __popcll(__ballot(((a - low) & 0x7000u) != 0 && !(a >= 0xff00u && a <= 0xff80u)));
     }
-    if (lane == 0 && out) atomicAdd(&s_out, out);
+    if (lane == 0 && out && tid < kSample) atomicAdd(&s_out, out);
+    __syncthreads();
   }
-  __syncthreads();
-  if (s_match > kHistBlock * N / 16 || (int64_t)s_out * (vocab / (kHistBlock * N)) > kHistList) {      // uniform
+  if (s_match > kSample * N / 16 || (int64_t)s_out * (vocab / (kSample * N)) > kHistList * 5 / 4) {      // uniform
     if (tid == 0) ent[out_row] = __uint_as_float(kRereadRow);
     return;
   }

@@ -63,7 +63,7 @@ def test_listed_elements_are_added_in_one_order(listed):
     rng = np.random.default_rng(6)
     x = 0.1 * rng.standard_normal(n).astype(np.float32)
     at = np.arange(4096, n)
-    at = rng.permutation(at[(at // 8 % 55 >= 12) & (at // 8 % 55 < 50)])[:listed]      # between the places that the range is taken from
+    at = rng.permutation(at[(at // 8 % 112 >= 12) & (at // 8 % 112 < 108)])[:listed]      # between the places that the range is taken from
     x[at] = 40 + rng.integers(0, 13, listed) / 4
     x[at[listed // 2]] = 73
     rows = torch.from_numpy(x).to(torch.bfloat16).cuda()[None].repeat(512, 1)
