@@ -377,7 +377,7 @@ stage1_vec_kernel(const T *__restrict__ logits, int vocab, int mask_id, float sc
 // Bound by HBM and the LDS atomics together (2112 rows of 126464 of normal distribution 205-230 -> 108-115 us, 5 TB/s): per two
 // elements 4 packed instructions for the counters' addresses, 3 for the maximum, 4 more, and 2 atomics.  Elements outside the range
 // send their thread's 16 through a slower loop: 0.2 % of zeros 162 us, 0.5 % 210 (185-195 without counting); rows that are left at once
-// take 5-15 us longer than without the attempt, and where the list just overflows, 40 % longer (1 % of zeros).
+// take 5-15 us longer than without the attempt, and where the list just overflows, 40-60 % longer (1 % of zeros).
 constexpr int kHistBlock = 512, kHistBins = 8192, kHistList = 1024;
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
