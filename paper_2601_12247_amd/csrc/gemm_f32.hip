@@ -3,26 +3,31 @@
 // float32 path: operands are widened to float64 in registers and multiplied by v_mfma_f64_16x16x4_f64, so a
 // product is exact and a sum carries 53 bits, as on the plain kernel this replaces.
 //
-// What bounds it: in the small parity model latency -- a launch of 384 rows is 0.2 GFLOP, 3 us of the chip's
-// matrix rate (78 TFLOP/s in float64) -- and from a few thousand rows on that rate.  So
+// What bounds it: in the small parity model latency (a launch of 384 rows is 0.2 GFLOP, 3 us of the chip's matrix rate, 78
+// TFLOP/s in float64, behind 2.4 us that any launch takes), and from a few thousand rows on the SIMDs' issue: while a float64
+// MFMA runs (64 cycles) its SIMD issues no vector instruction of any wave, so every one of them, the conversions of the operands
+// above all, adds its 5 cycles to the MFMAs' (4 MFMAs with 4 conversions 71 TFLOP/s, with 16 float32 operations 60).  So
 //   * operands go from global memory straight into registers in operand layout, with no LDS and no barrier
 //     in the loop: a lane holds four consecutive k of its row (one 16-byte load) and feeds them to four MFMAs,
-//     the contraction index being permuted alike on both operands;
+//     the contraction index being permuted alike on both operands.  The loads take a lane offset that stays and a scalar one
+//     for k, which costs no vector instruction, and nothing is loaded that is not multiplied but for a chunk of waves with an odd
+//     number of them: two chunks past the end, loaded so that the loop had no other form, cost 10 % at K = 256;
 //   * the four waves of a workgroup share K, each taking every fourth 16-k chunk, and their tiles are added through LDS in wave
 //     order.  Small launches get short loops that way, and large ones many equal workgroups.  The order in which an
 //     element's k are added is the same for every tile shape, so a row's bits do not depend on the launch's size;
-//   * tiles of 32 x 32, at most 128 registers: four workgroups a CU instead of three cover each other's
-//     prologue and epilogue, which are half of a loop over 256 k (6 236 rows: QKV 60 -> 52 us, down projection 57 -> 52).  SwiGLU
-//     takes 32 rows x 16 gate and the same 16 up columns for the same reason (32 + 32 columns need 230 registers: 108 -> 89 us);
-//   * launches of at most 512 such tiles (two a CU) take 16 x 32 instead: twice as many workgroups with
-//     half the work each (384 rows: QKV 9.7 -> 8.2 us, down 12.1 -> 7.9; above, the bigger tile reads less: 52 against 62 us);
-//   * one or two chunks are on their way while another is multiplied (one chunk ahead, fetched under a condition, every chunk was
-//     waited for whole; with that and the rows of the fused norm read eight loads at a time, rounds of 1-3 canvases x 128
-//     tokens 131 -> 120 us, of 8-40 canvases x 229 539 -> 525).
-// Measured on the small model's shapes (us per launch, plain vector-ALU kernel -> this one): QKV of 384 rows 42 -> 8, gate/up
-// 62 -> 11, down 81 -> 8; gate/up of 6 236 rows 89 (50 TFLOP/s), output head of 1 743 rows 75 (49 TFLOP/s).
+//   * tiles of 32 x 32, at most 128 registers: four workgroups a CU cover each other's prologue and epilogue, which are half of a
+//     loop over 256 k.  64 x 32 tiles (three workgroups, a quarter fewer conversions) gain 4 % at 9160 rows of 4096 columns, nothing at
+//     768 and lose at 256; workgroups that loop over tiles, the next one's loads behind the epilogue, lose 0-10 %.  SwiGLU
+//     takes 32 rows x 16 gate and the same 16 up columns (32 + 32 columns need 230 registers: 108 -> 89 us);
+//   * launches of few tiles take 16 rows where that leaves less to the fullest CU (run_epi);
+//   * one or two chunks are on their way while another is multiplied, none behind a condition: the wait would then be for all of them.
+// Measured on the small model's shapes, K = 256 but for the down projection's 704 (us per launch; plain vector-ALU kernel, loads by
+// 64-bit addresses past the end too, now): QKV of 384 rows 42, 8.0, 6.9, of 4 580 rows 41 -> 38, of 9 160 75 -> 68 (53 TFLOP/s);
+// gate/up of 384 rows 62, 10.9, 10.0, of 9 160 136 -> 121; down of 384 rows 81, 6.8, 6.5, of 916 11.5 -> 8.8; output head of 1 374 rows
+// 63 -> 56, of 9 160 386 -> 329 (58 TFLOP/s; K = 4096 65 -> 69).
 #include "common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace pvf {
@@ -94,9 +99,18 @@ __device__ __forceinline__ int tile_col(int tile, int c, int half) {
   return head * 2 * half + j * 16 + (c >= 16 ? half : 0) + (c & 15);
 }
 
+// Orders LDS accesses of the workgroup without waiting for loads from global memory that are on their way.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // NORM: the operand is RMSNorm(A) * gain, each row's 1 / rms from float64 sums taken by the workgroup itself while its first
 // chunks are on the way, the elements rounded to float32 as the norm's own pass rounds them.  MAP: rows through RowsF32::map.
-template <int EPI, bool VEC, bool NORM, bool MAP, int MT, int NT>
+// LOAD: kLoadAny element by element; otherwise 16 bytes through buffer descriptors, kLoadFour for K % 4 == 0, kLoadChunks for K % 16 == 0.
+enum { kLoadAny, kLoadFour, kLoadChunks };
+template <int EPI, int LOAD, bool NORM, bool MAP, int MT, int NT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float *__restrict__ C,
                 const float *__restrict__ Res, int M, int N, int K, RopeF32 ra, RowsF32 rw) {
@@ -107,6 +121,7 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 15, fq = lane >> 4;
   const int tiles_n = (N + TN - 1) / TN;
+  const int n_chunks = (K + 15) / 16;
   const int tile_n = blockIdx.x % tiles_n, m0 = blockIdx.x / tiles_n * TM;
 
   auto src_row = [&](int m, bool *ok) -> int64_t {                  // row of A and Res behind row m
@@ -116,46 +131,69 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
     *ok = pos >= 0 && pos < rw.T;
     return (int64_t)s * rw.T + (*ok ? pos : 0);
   };
-  const float *ap[MT], *wp[NB], *gp = rw.gain;
+  const float *ap[MT], *wp[NB];                                     // kLoadAny
+  uint32_t ao[MT], wo[NB];                                          // otherwise: byte offsets of the lane's four k in chunk 0
+  const uint32_t tail_back = LOAD == kLoadFour ? 4u * max(0, (n_chunks - 1) * 16 + 4 * fq + 4 - K) : 0u;   // lanes past K: the row's last four
   bool a_ok[MT];
+  // descriptors from the tile's own first rows of A and W on, so that a lane's offset has 32 bits whatever the matrix
+  const int64_t first = MAP ? (int64_t)(m0 / rw.R) * rw.T : m0, n_src = MAP ? (int64_t)(M / rw.R) * rw.T : M;
+  const int w_first = tile_col<EPI, TN>(tile_n, 0, ra.half);
+#ifdef __HIP_DEVICE_COMPILE__                                       // the descriptor type does not exist in the host pass
+  auto rows_from = [&](const float *x, int64_t row, int64_t rows) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(x + row * K), 0, (int)(uint32_t)min((rows - row) * K * 4, (int64_t)0xfffffff0), 0x00020000);
+  };
+  const __amdgpu_buffer_rsrc_t rsA = rows_from(A, first, n_src), rsG = rows_from(rw.gain, 0, 1), rsW = rows_from(W, w_first, N);
+  const __amdgpu_buffer_rsrc_t rsU = rows_from(W + (int64_t)(EPI == kEpiSwiglu ? N : 0) * K, w_first, N);      // SwiGLU: the up rows
+#endif
 #pragma unroll
-  for (int t = 0; t < MT; ++t) ap[t] = A + src_row(min(m0 + t * 16 + fr, M - 1), &a_ok[t]) * K;   // ragged edge: a valid row again
+  for (int t = 0; t < MT; ++t) {
+    const int64_t r = src_row(min(m0 + t * 16 + fr, M - 1), &a_ok[t]);           // ragged edge: a valid row again
+    ap[t] = A + r * K;
+    ao[t] = (uint32_t)(r - first) * (uint32_t)K * 4u + 16u * fq;
+  }
 #pragma unroll
   for (int t = 0; t < NB; ++t) {
     const int n = min(tile_col<EPI, TN>(tile_n, (t % NT) * 16 + fr, ra.half), N - 1);
     wp[t] = W + (int64_t)(t >= NT ? N + n : n) * K;
+    wo[t] = (uint32_t)(n - w_first) * (uint32_t)K * 4u + 16u * fq;
   }
   doublex4 acc[MT][NB];
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
 
   struct Chunk { float a[MT][4], w[NB][4], g[NORM ? 4 : 1]; };
-  const int n_chunks = (K + 15) / 16;
   // 16 k from ch * 16.  The loads are unconditional (a chunk past the end is the last one again, and never multiplied), so that
   // the wait for a chunk lets the loads of the next one stay in flight; with the fetch behind a condition it waited for them all.
   auto fetch = [&](Chunk &c, int ch) {
-    const int k = min(ch, n_chunks - 1) * 16 + 4 * fq;
-    const int kv = VEC ? min(k, K - 4) : k;
-    auto one = [&](const float *p, float *v) {
-      if (VEC) {
-        const float4 x = *reinterpret_cast<const float4 *>(p + kv);
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-      } else {
+    ch = min(ch, n_chunks - 1);
+    if constexpr (LOAD == kLoadAny) {
+      const int k = ch * 16 + 4 * fq;
+      auto one = [&](const float *p, float *v) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = k + e < K ? p[k + e] : 0.f;
-      }
-    };
+      };
 #pragma unroll
-    for (int t = 0; t < MT; ++t) one(ap[t], c.a[t]);
+      for (int t = 0; t < MT; ++t) one(ap[t], c.a[t]);
 #pragma unroll
-    for (int t = 0; t < NB; ++t) one(wp[t], c.w[t]);
-    if constexpr (NORM) one(gp, c.g);
+      for (int t = 0; t < NB; ++t) one(wp[t], c.w[t]);
+      if constexpr (NORM) one(rw.gain, c.g);
+    } else {
+#ifdef __HIP_DEVICE_COMPILE__
+      const uint32_t back = LOAD == kLoadFour && ch == n_chunks - 1 ? tail_back : 0u;
+      auto one = [&](__amdgpu_buffer_rsrc_t rs, uint32_t o, float *v) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, LOAD == kLoadFour ? o - back : o, ch * 64, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(x[e]);
+      };
+#pragma unroll
+      for (int t = 0; t < MT; ++t) one(rsA, ao[t], c.a[t]);
+#pragma unroll
+      for (int t = 0; t < NB; ++t) one(t >= NT ? rsU : rsW, wo[t], c.w[t]);
+      if constexpr (NORM) one(rsG, 16u * fq, c.g);
+#endif
+    }
   };
   float rnorm[MT];
   auto multiply = [&](Chunk &c, int ch) {
-    if (VEC && K % 16 != 0 && ch == n_chunks - 1) {                 // uniform: lanes past K bring nothing
+    if (LOAD == kLoadFour && ch == n_chunks - 1) {                  // uniform: lanes past K bring nothing
       const bool in = ch * 16 + 4 * fq < K;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -166,50 +204,62 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
       }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int e = 0; e < 4; ++e) {
+      double w[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) w[j] = (double)c.w[j][e];
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         float a = c.a[i][e];
         if constexpr (NORM) a = a * rnorm[i] * c.g[NORM ? e : 0];
         if (MAP && !a_ok[i]) a = 0.f;
+        const double ad = (double)a;
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)c.w[j][e], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ad, w[j], acc[i][j], 0, 0, 0);
       }
+    }
   };
-  // this wave's chunks wave, wave + 4, ...: one or two on their way while another is multiplied
+  __shared__ double part[WK][MT * NB][4][64];
+  __shared__ float s_r[NORM ? TM : 1];
   Chunk c0, c1;
   fetch(c0, wave);
+  __builtin_amdgcn_sched_barrier(0);                                // one chunk's loads behind the other's
   fetch(c1, wave + WK);
+  __builtin_amdgcn_sched_barrier(0);
   if (rw.n_live && m0 >= *rw.n_live * rw.per_seq) return;           // uniform
   if constexpr (NORM) {
-    __shared__ float s_r[TM];
     const int row = threadIdx.x >> 3, j = threadIdx.x & 7;          // eight threads a row
     if (row < TM) {
       const float r = row_rnorm(A + (int64_t)min(m0 + row, M - 1) * K, j, K, rw.inv_k, rw.eps);
       if (j == 0) s_r[row] = r;
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int t = 0; t < MT; ++t) rnorm[t] = s_r[t * 16 + fr];
   }
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+  // this wave's chunks: one or two on their way while another is multiplied
+  int ch = wave;
 #pragma unroll 1
-  for (int ch = wave; ch < n_chunks; ch += 2 * WK) {
+  for (; ch + 2 * WK < n_chunks; ch += 2 * WK) {
     multiply(c0, ch);
     fetch(c0, ch + 2 * WK);
-    if (ch + WK < n_chunks) multiply(c1, ch + WK);
+    multiply(c1, ch + WK);
     fetch(c1, ch + 3 * WK);
   }
-
+  if (ch < n_chunks) multiply(c0, ch);
+  if (ch + WK < n_chunks) multiply(c1, ch + WK);
   // ---- wave w adds up register w of every tile (rows 4 w + lane / 16) over the four waves, in wave order ----
-  __shared__ double part[WK][MT * NB][4][64];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) part[wave][i * NB + j][e][lane] = acc[i][j][e];
-  __syncthreads();
+  lds_barrier();
   double v[MT][NB];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -256,24 +306,32 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
 template <int EPI, bool NORM = false, bool MAP = false>
 pvf_status run_epi(pvf_ctx *ctx, hipStream_t s, const float *A, const float *W, float *C, const float *res, int M, int N, int K,
                    const RopeF32 &ra, const RowsF32 &rw = RowsF32{}) {
-  const bool vec = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)rw.gain) & 15u) == 0;
+  const bool aligned = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)rw.gain) & 15u) == 0;
+  // the rows of a tile, of a head, or of the canvases that a tile's rows are picked from lie within 32-bit offsets
+  const bool vec = aligned && std::max<int64_t>(256, MAP ? ((int64_t)32 / std::max(rw.R, 1) + 2) * rw.T : 0) * K * 4 < (1ll << 32);
+  PVF_REQUIRE(ctx, !NORM || aligned, PVF_ESHAPE, "gemm_f32: the fused norm takes 16-byte aligned rows");
   auto launch = [&](auto mt, auto nt) -> pvf_status {
     constexpr int MT = decltype(mt)::value, NT = decltype(nt)::value;
     const int64_t tiles = (int64_t)((N + 16 * NT - 1) / (16 * NT)) * ((M + 16 * MT - 1) / (16 * MT));
     PVF_REQUIRE(ctx, tiles < (1ll << 31), PVF_ESHAPE, "gemm_f32: M=%d N=%d", M, N);
     const unsigned grid = (unsigned)tiles;
-    if (vec) gemm_f32_kernel<EPI, true, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
-    else if constexpr (!NORM) gemm_f32_kernel<EPI, false, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
-    else PVF_REQUIRE(ctx, false, PVF_ESHAPE, "gemm_f32: the fused norm takes 16-byte aligned rows");
+    if (vec && K % 16 == 0) gemm_f32_kernel<EPI, kLoadChunks, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
+    else if (vec) gemm_f32_kernel<EPI, kLoadFour, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
+    else gemm_f32_kernel<EPI, kLoadAny, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
     PVF_LAUNCH_CHECK(ctx, "gemm_f32");
     return PVF_OK;
   };
   using std::integral_constant;
   constexpr integral_constant<int, 1> k1{};
   constexpr integral_constant<int, 2> k2{};
-  const int64_t tiles32 = (int64_t)((N + 31) / 32) * ((M + 31) / 32);
-  if constexpr (EPI == kEpiSwiglu) return launch(k2, k1);
-  else return tiles32 <= 512 ? launch(k1, k2) : launch(k2, k2);
+  constexpr integral_constant<int, EPI == kEpiSwiglu ? 1 : 2> nt{};
+  // 16 or 32 rows a tile by workgroups on the fullest CU: one of 16 rows takes 1.5 us of a CU's matrix units at K = 256 and one of 32
+  // rows 2.5 (4.2 and 6.5 at K = 704).  K = 256, QKV of 768 columns: 384 rows 6.8 us (16) and 7.5 (32), 576 rows 8.5 and 7.7, 1145 rows
+  // 12.9 and 12.5; gate/up of 704: 64 rows 3.9 and 5.2, 160 rows 5.5 and 5.4, 384 rows 10.0 and 10.5, 687 rows 14.3 and 12.8.  K = 704, 256
+  // columns: 512 rows 6.5 and 8.8, 576 rows 10.7 and 8.7, 2290 rows 23.1 and 21.9.
+  const int64_t cols = (N + 16 * decltype(nt)::value - 1) / (16 * decltype(nt)::value);
+  const int64_t c1 = (cols * ((M + 15) / 16) + 255) / 256, c2 = (cols * ((M + 31) / 32) + 255) / 256;
+  return (K <= 512 ? 3 * c1 <= 5 * c2 : 2 * c1 <= 3 * c2) ? launch(k1, nt) : launch(k2, nt);
 }
 
 }  // namespace

@@ -62,3 +62,24 @@ def test_attention_f32_of_infinite_values(T, dh):
     want = O.attention(O.rope(q, 1e4), O.rope(k, 1e4), v).reshape(T, d)
     inf = np.isinf(want)
     assert inf.sum() == 3 * T and np.array_equal(got[inf], want[inf]) and np.abs(got[~inf] - want[~inf]).max() <= 2e-5
+
+
+# 16- and 32-row tiles, chunks of 16 k (whole, cut at a multiple of 4, element by element) and their odd and even numbers per wave
+@pytest.mark.parametrize("K", [16, 60, 64, 130, 192, 256, 260, 704])
+@pytest.mark.parametrize("kind", ["store", "residual", "swiglu"])
+def test_rows_of_launches_of_any_size(kind, K):
+    """A row has the same bits whatever the launch: tile heights follow the number of workgroups, the order of k does not."""
+    rng = np.random.default_rng(K)
+    N = 352                                    # 1 100 rows: 11 (22) columns of tiles, 16 rows for the short launches and 32 for the long one
+    A, W, R = (dev(rng.standard_normal(s, dtype=np.float32)) for s in ((1100, K), (2 * N, K), (1100, N)))
+
+    def run(rows):
+        a, r = A[rows].contiguous(), R[rows].clone()
+        return B.gemm_swiglu(a, W) if kind == "swiglu" else B.gemm(a, W[:N].contiguous(), residual=r if kind == "residual" else None, out=r)
+
+    whole = run(slice(0, 1100))
+    for rows in (slice(0, 1), slice(3, 50), slice(1071, 1100), slice(500, 900)):
+        assert torch.equal(run(rows), whole[rows])
+    want = A.double() @ W.double().T
+    want = torch.nn.functional.silu(want[:, :N]) * want[:, N:] if kind == "swiglu" else want[:, :N] + (R.double() if kind == "residual" else 0)
+    assert bool(((whole.double() - want).abs() <= 2.0 ** -23 * want.abs() + 1e-12).all())
