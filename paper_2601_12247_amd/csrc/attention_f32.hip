@@ -3,17 +3,20 @@
 // Full canvases, or the window rows of a K/V-cached round, whose keys come from the window itself or from the
 // cache of the canvas' group.  d_head a multiple of 16, any T whose scores fit into LDS.
 //
-// One workgroup = 16 queries of one (canvas, head), four waves.  Bound by the float64 matrix rate (64 cycles per
-// v_mfma_f64_16x16x4_f64) and, in the small parity model, by latency:
+// One workgroup = 16 queries of one (canvas, head), four waves.  Bound by the SIMDs' issue (a v_mfma_f64_16x16x4_f64 takes 64
+// cycles, in which its SIMD issues no vector instruction of any wave) and, in the small parity model, by latency:
 //   * scores: the waves take every fourth tile of 16 keys; operands come from global memory in operand layout
 //     (16 bytes per lane = four consecutive d, the contraction permuted alike in q and k), the next tile's while
 //     this one's are multiplied; scores are rounded to float32 into LDS, rows padded against bank conflicts;
-//   * softmax in float32 like the plain kernel: four rows per wave side by side, divided by their sum where they are read;
+//   * softmax in float32 like the plain kernel: four rows per wave side by side; weights are divided by their row's sum before
+//     the four waves read them, each of which would divide all of them again;
 //   * out: the waves take every fourth 16 columns of the head, all keys, so that nothing is added across waves;
 //     two accumulators alternate because a float64 MFMA that waits for the previous one idles the pipe; values are
-//     fetched four tiles ahead, the first ones before the softmax (a tile is 256 cycles of MFMA, a load 1500).
-// Measured (per layer; plain kernel, one row at a time with values one tile ahead, now): 1-3 canvases x 128 tokens 28, 11, 9 us;
-// 8-40 canvases x 229 tokens 199, 53, 41 us on average.
+//     fetched four tiles ahead, the first ones before the softmax (a tile is 256 cycles of MFMA, a load 1500);
+//   * loads of whole canvases are a lane offset that stays and a descriptor whose base moves by scalar arithmetic: with 64-bit
+//     addresses a tile of values (4 MFMAs) took 57 vector instructions, 300 cycles beside the MFMAs' 256, now 17.
+// Measured (per layer; plain kernel, 64-bit addresses, now): 1-3 canvases x 128 tokens 28, 8.8, 8.5 us; 20 canvases x 229 tokens 39 ->
+// 36, 40 x 229 72 -> 65; 4 x 512 with 8 heads of 128 121 -> 107.
 #include "common.h"
 
 namespace pvf {
@@ -29,19 +32,25 @@ struct WinF32 {
   int32_t slots_per_group, prompt_len, block_len;
 };
 
+#ifdef __HIP_DEVICE_COMPILE__          // the descriptor type does not exist in the host pass
+// Descriptor of what begins at x; every offset used with it lies inside the caller's canvas.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(const float *x) {
+  return __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, -16, 0x00020000);
+}
+#endif
+
 template <int KC, bool WIN>            // KC = d_head / 16
 __global__ void __launch_bounds__(256)
 attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int n_rows, int T, int n_heads,
                      float inv_sqrt_dh, const int32_t *__restrict__ n_live, WinF32 wa) {
   constexpr int dh = KC * 16;
   extern __shared__ float s_p[];       // [TQ][T16 + 4]
-  __shared__ float s_inv[TQ];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 15, fq = lane >> 4;
   const int q0 = blockIdx.x * TQ, head = blockIdx.y, seq = blockIdx.z;
   const int d = n_heads * dh;
   const int64_t ld = 3 * (int64_t)d;
-  if (n_live && seq >= *n_live) return;
+  const int live = n_live ? *n_live : 0;              // asked for beside the first loads, not in front of them
   const float *fresh = qkv + (int64_t)seq * n_rows * ld + (int64_t)head * dh;      // q; k at + d, v at + 2 d
   const int n_tiles = (T + 15) / 16, stride = n_tiles * 16 + 4;
   int w0 = 0, w1 = T;                  // keys [w0, w1) are rows of this launch
@@ -62,6 +71,16 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
     return (!WIN || (key >= w0 && key < w1)) ? fresh + 2 * d + (int64_t)(key - w0) * ld : vcb + (int64_t)key * d;
   };
 
+  // Whole canvases: keys and values through descriptors whose base is the tile's first row (scalar arithmetic), so that a load
+  // costs no vector instruction; the last tile's rows past the end are the canvas' last one.
+  const uint32_t ld4 = (uint32_t)ld * 4u;
+  const int last_rows = T - (n_tiles - 1) * 16;                     // 1..16
+  const uint32_t k_off = fr * ld4 + 16u * fq, k_last = min(fr, last_rows - 1) * ld4 + 16u * fq;
+  const uint32_t v_off = 4 * fq * ld4 + 4u * fr;
+  uint32_t v_last[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v_last[e] = min(4 * fq + e, last_rows - 1) * ld4 - e * ld4 + 4u * fr;     // added to e * ld4: inside the canvas
+
   // ---- scores ----
   float4 q[KC];
   {
@@ -71,6 +90,15 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
   }
   float4 kb[2][KC];
   auto fetch_k = [&](int buf, int kt) {
+    if constexpr (!WIN) {
+#ifdef __HIP_DEVICE_COMPILE__
+      const auto rs = rows_from(fresh + d + (int64_t)kt * 16 * ld);
+      const uint32_t o = kt == n_tiles - 1 ? k_last : k_off;
+#pragma unroll
+      for (int c = 0; c < KC; ++c) kb[buf][c] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, o + 64 * c, 0, 0));
+#endif
+      return;
+    }
     const float *kr = k_row(kt * 16 + fr);
 #pragma unroll
     for (int c = 0; c < KC; ++c) kb[buf][c] = *reinterpret_cast<const float4 *>(kr + c * 16 + 4 * fq);
@@ -89,21 +117,37 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
     for (int e = 0; e < 4; ++e)        // row 4 e + lane / 16 = query, column lane % 16 = key
       s_p[(4 * e + fq) * stride + key] = key < T ? (float)((s0[e] + s1[e]) * (double)inv_sqrt_dh) : -INFINITY;
   };
-  // tiles past the end are the last one again: loads behind a condition would be waited for with the tile before them
+  // loads behind a condition would be waited for with the tile before them; a chunk past the end is the last one again
   fetch_k(0, min(wave, n_tiles - 1));
+  __builtin_amdgcn_sched_barrier(0);
   fetch_k(1, min(wave + 4, n_tiles - 1));
+  __builtin_amdgcn_sched_barrier(0);
+  if (n_live && seq >= live) return;
+  int kt = wave;
 #pragma unroll 1
-  for (int kt = wave; kt < n_tiles; kt += 8) {
+  for (; kt + 8 < n_tiles; kt += 8) {
     score(0, kt);
-    fetch_k(0, min(kt + 8, n_tiles - 1));
-    if (kt + 4 < n_tiles) score(1, kt + 4);
+    fetch_k(0, kt + 8);
+    score(1, kt + 4);
     fetch_k(1, min(kt + 12, n_tiles - 1));
   }
+  if (kt < n_tiles) score(0, kt);
+  if (kt + 4 < n_tiles) score(1, kt + 4);
   // values of the first kVRing tiles: on the way while the softmax runs
   constexpr int kVRing = 4;
   float vb[kVRing][4];
   auto fetch_v = [&](float *v, int dt, int kt) {
     kt = min(kt, n_tiles - 1);
+    if constexpr (!WIN) {
+#ifdef __HIP_DEVICE_COMPILE__
+      const auto rs = rows_from(fresh + 2 * d + dt * 16 + (int64_t)kt * 16 * ld);
+      const bool last = kt == n_tiles - 1;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, last ? v_last[e] : v_off, e * ld4, 0));
+#endif
+      return;
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = v_row(kt * 16 + 4 * fq + e)[dt * 16 + fr];
   };
@@ -141,10 +185,18 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
     float t = (z[0] + z[2]) + (z[1] + z[3]);
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o);
-    if (fr == 0) s_inv[wave * 4 + fq] = 1.0f / t;
+    const float inv = 1.0f / t;
+    // multiplied here once, not by each of the four waves that read them
+    for (kt = 0; kt + 8 <= n_tiles; kt += 8) {
+      float e[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) e[i] = pr[(kt + i) * 16 + fr];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pr[(kt + i) * 16 + fr] = e[i] * inv;
+    }
+    for (; kt < n_tiles; ++kt) pr[kt * 16 + fr] *= inv;
   }
   __syncthreads();
-  const float inv = s_inv[fr];         // of the query whose weights this lane reads
 
   // ---- out: row = query, column = lane % 16 of the wave's 16 columns ----
   for (int dt = wave; dt < KC; dt += 4) {
@@ -155,10 +207,10 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
         for (int e = 0; e < 4; ++e) vb[buf][e] = kt * 16 + 4 * fq + e < T ? vb[buf][e] : 0.f;
       }
       const float4 p = *reinterpret_cast<const float4 *>(s_p + fr * stride + kt * 16 + 4 * fq);
-      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.x * inv), (double)vb[buf][0], o0, 0, 0, 0);
-      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.y * inv), (double)vb[buf][1], o1, 0, 0, 0);
-      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.z * inv), (double)vb[buf][2], o0, 0, 0, 0);
-      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(p.w * inv), (double)vb[buf][3], o1, 0, 0, 0);
+      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.x, (double)vb[buf][0], o0, 0, 0, 0);
+      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.y, (double)vb[buf][1], o1, 0, 0, 0);
+      o0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.z, (double)vb[buf][2], o0, 0, 0, 0);
+      o1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p.w, (double)vb[buf][3], o1, 0, 0, 0);
     };
     if (dt != wave) {
 #pragma unroll
