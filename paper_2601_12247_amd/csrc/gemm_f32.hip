@@ -51,15 +51,21 @@ __device__ __forceinline__ float4 four(const float *x, int k, int K) {
 template <bool VEC = true>
 __device__ __forceinline__ float row_rnorm(const float *x, int j, int K, double inv_k, float eps) {
   double ss = 0.0;
-  for (int k0 = 4 * j; k0 < K; k0 += 256) {                         // eight loads on their way together
-    float4 v[8];
+  auto add = [&](int k0, auto n, auto whole) {                      // n loads on their way together
+    constexpr int kN = decltype(n)::value;
+    float4 v[kN];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = four<VEC>(x, k0 + 32 * i, K);
+    for (int i = 0; i < kN; ++i) v[i] = four<VEC>(x, k0 + 32 * i, K);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (k0 + 32 * i < K)
-        ss += ((double)v[i].x * v[i].x + (double)v[i].y * v[i].y) + ((double)v[i].z * v[i].z + (double)v[i].w * v[i].w);
-  }
+    for (int i = 0; i < kN; ++i) {
+      const double q = ((double)v[i].x * v[i].x + (double)v[i].y * v[i].y) + ((double)v[i].z * v[i].z + (double)v[i].w * v[i].w);
+      ss += decltype(whole)::value || k0 + 32 * i < K ? q : 0.0;
+    }
+  };
+  // the first 256 outside of the loop, in front of which the compiler waits for every load on its way
+  if (K >= 256) add(4 * j, std::integral_constant<int, 8>{}, std::true_type{});
+#pragma unroll 1
+  for (int k0 = K >= 256 ? 256 : 0; k0 < K; k0 += 128) add(k0 + 4 * j, std::integral_constant<int, 4>{}, std::false_type{});
   ss += __shfl_xor(ss, 1); ss += __shfl_xor(ss, 2); ss += __shfl_xor(ss, 4);
   // the hardware's estimate of 1 / sqrt (relative error below 2^-22) and one Newton step, 1.5 times its square: below 2^-43, in a
   // tenth of the instructions of sqrt and divide
@@ -107,7 +113,8 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // NORM: the operand is RMSNorm(A) * gain, each row's 1 / rms from float64 sums taken by the workgroup itself while its first
-// chunks are on the way, the elements rounded to float32 as the norm's own pass rounds them.  MAP: rows through RowsF32::map.
+// chunks are on the way (and before it knows whether its rows are live: the count's load would stand in front of the rows'; rounds of
+// 1-3 canvases x 128 tokens 4 % faster), the elements rounded to float32 as the norm's own pass rounds them.  MAP: rows through RowsF32::map.
 // LOAD: kLoadAny element by element; otherwise 16 bytes through buffer descriptors, kLoadFour for K % 4 == 0, kLoadChunks for K % 16 == 0.
 enum { kLoadAny, kLoadFour, kLoadChunks };
 template <int EPI, int LOAD, bool NORM, bool MAP, int MT, int NT>
@@ -226,17 +233,18 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
   __builtin_amdgcn_sched_barrier(0);                                // one chunk's loads behind the other's
   fetch(c1, wave + WK);
   __builtin_amdgcn_sched_barrier(0);
-  if (rw.n_live && m0 >= *rw.n_live * rw.per_seq) return;           // uniform
+  // uniform; the count is asked for beside the loads, not in front of them
+  const int live = rw.n_live ? *rw.n_live : 0;
   if constexpr (NORM) {
     const int row = threadIdx.x >> 3, j = threadIdx.x & 7;          // eight threads a row
-    if (row < TM) {
-      const float r = row_rnorm(A + (int64_t)min(m0 + row, M - 1) * K, j, K, rw.inv_k, rw.eps);
-      if (j == 0) s_r[row] = r;
-    }
+    float r = 0.f;
+    if (row < TM) r = row_rnorm(A + (int64_t)min(m0 + row, M - 1) * K, j, K, rw.inv_k, rw.eps);
+    if (rw.n_live && m0 >= live * rw.per_seq) return;
+    if (row < TM && j == 0) s_r[row] = r;
     lds_barrier();
 #pragma unroll
     for (int t = 0; t < MT; ++t) rnorm[t] = s_r[t * 16 + fr];
-  }
+  } else if (rw.n_live && m0 >= live * rw.per_seq) return;
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
