@@ -12,7 +12,7 @@
 //     256 x 192, also with 8 waves, where they put (nearly) one tile on every CU; 64 x 64 and 64 x 128 with
 //     4 waves and 128 x 64 with 8 for launches with few rows, which stream the weights and want many bytes on
 //     the way (pick_config); launches of up to 640 rows may also split K over several workgroups per tile, as
-//     nine shapes of which 160 x 192 and 160 x 128 exist only there (splitk_plan);
+//     nine shapes (splitk_plan); SwiGLU of 257-320 rows also takes 160 x 192 (swiglu_160x192_pays);
 //   * both operands are K-contiguous in memory, so a 16-byte chunk is 8 consecutive k of one
 //     row.  K advances in stages of BK = 64 (whole 128-byte lines per row: half the L2 requests
 //     of 64-byte pieces) through a ring of LDS buffers; tiles go from
@@ -62,11 +62,14 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// Whether a wave of WT columns holds the gate and the up column of an output: an even number of 16-column sub-tiles.
+constexpr bool pairs_in_wave(int WT) { return WT / 16 % 2 == 0; }
+
 // Row of W that feeds row r (0..BN-1) of the workgroup's W tile.
 //  plain:   consecutive rows tile_n*BN + r.
 //  SwiGLU:  the tile covers BN/2 output columns; the lower half of each wave's BN/WN tile rows is gate, the
 //           upper half up for the same columns, so silu(g)*u pairs accumulators of one lane (16-row MFMA
-//           sub-tiles c with NT16/2 + c).
+//           sub-tiles c with NT16/2 + c).  Waves with an odd number of sub-tiles cannot: all gate columns of the tile come first.
 //  QKV with rotary embedding (ff = 3 d): in the q and k thirds a wave's 64 tile rows are columns
 //           [32g, 32g + 32) of a head followed by their rotation partners [64 + 32g, 64 + 32g + 32)
 //           (g = wave % 2), so the pair (i, i + 64) meets in one lane (sub-tiles t and t + 2).
@@ -79,6 +82,7 @@ __device__ __forceinline__ int w_row(int r, int tile_n, int ff) {
   }
   if (EPI != kEpiSwiglu) return tile_n * BN + r;
   constexpr int WT = BN / WN;
+  if (!pairs_in_wave(WT)) return (r < BN / 2 ? 0 : ff - BN / 2) + tile_n * (BN / 2) + r;
   const int wn = r / WT, e = r % (WT / 2);
   const int col = tile_n * (BN / 2) + wn * (WT / 2) + e;
   return r % WT >= WT / 2 ? ff + col : col;
@@ -152,8 +156,9 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   constexpr bool kStepW = kQuad && (BN / 2) % RPI == 0;
   constexpr int kAhead = kLate ? kStages : kStages - 1;     // stages in flight after the prologue
   static_assert(BM % (RPI / 2) == 0 && (!kHalfA || LA >= 2) && BN % RPI == 0 && BK == 64 && BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "tile shape");
-  static_assert((EPI != kEpiQkvRope && EPI != kEpiSwiglu) || BM % (32 * WM) == 0, "the rotary and SwiGLU epilogues take whole 32-row passes");
-  static_assert(EPI != kEpiSwiglu || NT16 % 2 == 0, "SwiGLU pairs the halves of a wave's columns");
+  // SwiGLU whose waves cannot pair gate and up turns the whole tile around through LDS.
+  constexpr bool kTileStage = EPI == kEpiSwiglu && !pairs_in_wave(BN / WN);
+  static_assert((EPI != kEpiQkvRope && (EPI != kEpiSwiglu || kTileStage)) || BM % (32 * WM) == 0, "the rotary and SwiGLU epilogues take whole 32-row passes");
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: LDS targets become scalar arithmetic
@@ -465,6 +470,31 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   for (; kt < nk; ++kt) run_stage(kt, std::false_type{});
   }
 
+  if constexpr (kTileStage) {
+    // 160 x 192: the sums as float32 rows in the free ring (16 bytes of padding: rows start 4 banks apart), then gate and up from
+    // there.  Against float32 partial sums through memory and a launch that pairs them: 320 rows of gate/up, 2 x 12288 columns, K =
+    // 4096, 68.3 -> 58.3 us.
+    constexpr int kRow = BN * 4 + 16, kCols8 = BN / 16;       // 8-column pieces of an output row
+    static_assert(BM * kRow <= kStages * kStage && BN % 16 == 0, "the tile exceeds the LDS ring");
+    __syncthreads();                                                 // every wave is done with the ring
+#pragma unroll
+    for (int mt = 0; mt < MT16; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT16; ++nt)
+        *reinterpret_cast<floatx4 *>(lds + (wm * (BM / WM) + mt * 16 + fr) * kRow + (wn * (BN / WN) + nt * 16 + 4 * fq) * 4) = acc[nt][mt];
+    __syncthreads();
+    for (int i = tid; i < BM * kCols8; i += kThreads) {
+      const int r = i / kCols8, c = i % kCols8 * 8, m = m0 + r;
+      if (m >= M) break;                                             // rows only grow
+      const floatx4 *g = reinterpret_cast<const floatx4 *>(lds + r * kRow + c * 4), *u = reinterpret_cast<const floatx4 *>(lds + r * kRow + (BN / 2 + c) * 4);
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = silu_f(g[e >> 2][e & 3]) * u[e >> 2][e & 3];
+      *reinterpret_cast<uint4 *>(C + (int64_t)m * N_out + tile_n * (BN / 2) + c) =
+          make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+    }
+    return;
+  }
   // ---- epilogue ----
   // A lane holds, for sub-tile (nt, mt), the 4 consecutive columns nt*16 + 4*(lane/16) + {0..3}
   // of row mt*16 + lane%16, so a direct store would write 8-byte pieces.  Instead each wave turns 32 rows at a time
@@ -485,7 +515,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   // row (of the 32 of a pass) and columns that this lane stores with instruction j
   auto st_row = [&](int j) { return kWholeRows ? j * kRowsPerInstr + rd_row : (j * 64 + lane) / LPR; };
   auto st_col = [&](int j) { return kWholeRows ? rd_col0 : (j * 64 + lane) % LPR * 8; };
-  static_assert(32 * LPR % 64 == 0 && (kWholeRows || WTM % 32 == 0 || EPI == kEpiPartial), "whole store instructions per pass");
+  static_assert(kTileStage || (32 * LPR % 64 == 0 && (kWholeRows || WTM % 32 == 0 || EPI == kEpiPartial)), "whole store instructions per pass");
   // The residual rows of the whole wave tile are requested at once, before the staging starts:
   // fetched 32 rows at a time where they are added, each piece cost a full memory latency.
   constexpr int kRowIters = 32 * LPR / 64;
@@ -768,11 +798,16 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   // push the activations and the partial sums out of L2 (cached rounds of 64 and 320 rows 4.4 and 2.5 % faster).  With more rows of
   // tiles they may be gone before the last one reads them: 160 x 256 tiles at 1311 rows of 6144 columns, K = 2048, 40.1 us with the
   // hint and 34.4 without, K = 8192 132 and 121; 4100 rows of 12288 columns, K = 4096, 352 and 335.
+  constexpr bool kTileStage = EPI == kEpiSwiglu && !pairs_in_wave(BN / WN);
   constexpr bool kFewRows = EPI == kEpiPartial ? BM == 64 : BN == 64 || ST == 6;                 // shapes for up to 128 rows
-  constexpr bool kTwoRows = (EPI == kEpiPartial && BN == 192) || (EPI == kEpiStore && BM == 160);
+  constexpr bool kTwoRows = (EPI == kEpiPartial && BN == 192) || (EPI == kEpiStore && BM == 160) || kTileStage;
   // shapes that the launches taking the whole of K behind few rows are made of
-  constexpr bool kTurns = (EPI == kEpiStore && BN == 64) || (EPI == kEpiSwiglu && BN == 128 && (ST == 6 || BM == 128));
-  if constexpr (kTurns) if (sk.turn) return launch(std::bool_constant<kFewRows>{}, std::true_type{});
+  constexpr bool kTurns = (EPI == kEpiStore && BN == 64) || (EPI == kEpiSwiglu && BN == 128 && (ST == 6 || BM == 128)) ||
+                          kTileStage;
+  if constexpr (kTurns) if (sk.turn) {
+    if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{}, std::true_type{});
+    return launch(std::bool_constant<kFewRows>{}, std::true_type{});
+  }
   if constexpr (kFewRows) return launch(std::true_type{}, std::false_type{});
   else {
     if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{}, std::false_type{});
@@ -781,7 +816,7 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
 }
 
 struct TileCfg { int bm, bn, bk, stages; double eff; bool plain_only, pairs_only = false; };   // pairs_only: SwiGLU with K % 128 == 0 (the quadrant schedule)
-constexpr int kNumCfg = 13;
+constexpr int kNumCfg = 14;
 // Every shape for many rows runs 8 waves, two per SIMD (the two small ones 4 waves, two workgroups per CU):
 // with one wave per SIMD the 256 x 256 tile (wave tiles of 128 x 128, a third fewer LDS reads) measured 2-4 %
 // slower, smaller wave tiles far slower.
@@ -799,12 +834,13 @@ constexpr TileCfg kCfg[kNumCfg] = {
     {192, 128, 64, 3, 0.86, true},    // 1536 rows = 8 tile rows: with N = 4096 one tile per CU; SwiGLU of 129-192 rows (pick_config)
     {160, 256, 64, 3, 0.85, true},   // 2560 rows = 16 tile rows: one tile per CU like 320 x 128, with room for a third stage
     {256, 192, 64, 2, 0.965, false, true},   // gate/up of 24576 weight rows = 128 tile columns: 512 rows are one tile per CU
-    {64, 128, 64, 6, 0.0, false}, {128, 64, 64, 6, 0.0, true}};   // the whole of K behind one workgroup a CU: rings of 144 KB
+    {64, 128, 64, 6, 0.0, false}, {128, 64, 64, 6, 0.0, true},   // the whole of K behind one workgroup a CU: rings of 144 KB
+    {160, 192, 64, 3, 0.0, true}};                               // SwiGLU of 257-320 rows (swiglu_160x192_pays)
 
 template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
                    const void *Res, int M, int N, int K, const RopeArgs &ra = RopeArgs{}, const NormArgs &na = NormArgs{}, bool turn = false) {
-  const SplitK whole{nullptr, 0, turn && M <= 128 && K >= 1024};
+  const SplitK whole{nullptr, 0, turn && (M <= 128 || cfg == 13) && K >= 1024};
   constexpr bool kPlain = EPI != kEpiSwiglu && EPI != kEpiQkvRope;
   if (K % 128 != 0 && cfg == 0) return run<EPI, 256, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
   if (K % 128 != 0 && cfg == 4) return run<EPI, 192, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
@@ -820,10 +856,23 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
     case 9: if constexpr (kPlain) return run<EPI, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 10: if constexpr (EPI == kEpiSwiglu) return run<EPI, 256, 192, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 11: if constexpr (EPI == kEpiSwiglu) return run<EPI, 64, 128, 64, 6, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
+    case 13: if constexpr (EPI == kEpiSwiglu) return run<EPI, 160, 192, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     case 12: if constexpr (EPI == kEpiStore) return run<EPI, 128, 64, 64, 6, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     default: break;
   }
   return run<EPI, 128, 128, 64, 5, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);
+}
+
+// Gate/up of 257-320 rows on two rows of 160 x 192 tiles over the whole of K.  By times of both ways at 264 and 320 rows, N = 1536-24576
+// and K = 512-8192 (320 rows here): where the tiles make most of a round, or the loop is short.  2 x 12288 columns, K = 4096,
+// 68.3 us divided and 58.3 whole; 9216, K = 8192, 113 and 106, K = 1024 30.8 and 19.2; 24576, K = 4096, 196 (64 x 128 tiles) and 122.  The
+// other side: 7680, K = 8192, 88 and 102; 6144, K = 4096, 44.6 and 54.0; 4608, K = 2048, 29.2 and 30.0; 13824 (a second round for a
+// few), K = 1024, 36.6 and 36.9.
+bool swiglu_160x192_pays(int N, int K) {
+  if (N % 96 != 0) return false;
+  const int tiles = N / 48;
+  if (tiles > 256) return N > 16384 || K <= 512 || (tiles >= 320 && K <= 1024);      // wider than 2 x 16384: K is not divided
+  return tiles >= 192 || K <= (tiles >= 160 ? 4096 : tiles >= 128 ? 2048 : tiles >= 64 ? 1024 : 0);
 }
 
 // Undivided shapes for few rows; -1: by the estimate.  Up to 128 rows rings of 5-6 stages (64-120 KB of weights on the way per CU) where
@@ -835,6 +884,7 @@ int few_rows_shape(GemmEpilogue epi, int M, int N, int K) {
   if (epi == kEpiSwiglu) {
     if (M <= 64) return N >= 9216 && (N <= 16384 || K >= 2048) ? 11 : 7;
     if (M <= 128) return N >= 8192 && K >= (N <= 16384 ? 1024 : 2048) ? 3 : 7;
+    if (M > 256 && M <= 320 && swiglu_160x192_pays(N, K)) return 13;
     if (N < 8192 || N > 16384 || N % 128 != 0 || (M > 256 && M <= 320)) return 7;
     return M <= 192 ? 8 : M <= 256 ? 2 : 4;
   }
@@ -853,7 +903,8 @@ bool takes_whole_k(GemmEpilogue epi, int M, int N, int K) {
   if (epi == kEpiSwiglu) {
     if (M <= 64) return wgs >= 144;
     if (M <= 128) return wgs >= 144 || (wgs >= 128 && K >= 1024 && K <= 2048);
-    if (M > 384 || (M > 256 && M <= 320) || wgs < 128 || wgs > 256 || N % 128 != 0) return false;
+    if (M > 256 && M <= 320) return swiglu_160x192_pays(N, K);
+    if (M > 384 || wgs < 128 || wgs > 256 || N % 128 != 0) return false;
     if (wgs < 144 || K <= 1024) return K <= 1024;
     if (M <= 192) return K <= (wgs < 256 ? 8192 : 3072);       // 256: gate and up columns a power of two apart, 6-15 % slower from K = 4096 on
     if (M <= 256) return K <= (wgs < 160 ? 4096 : wgs < 224 ? 8192 : INT_MAX);
@@ -1110,7 +1161,7 @@ bool gemm_mfma_supported(int dtype, GemmEpilogue epi, int M, int N, int K) {
 }
 
 // Tile shapes with room for the folded-norm exchange (every 8-wave shape).
-bool gemm_mfma_norm_capable(int cfg) { return cfg >= 0 && cfg != 6 && cfg != 7 && cfg != 11; }
+bool gemm_mfma_norm_capable(int cfg) { return cfg >= 0 && cfg != 6 && cfg != 7 && cfg != 11 && cfg != 13; }
 
 // Slots of row sums of squares a kEpiResidual launch writes, 256 columns each or (tiles 128 wide) 64; 0: no folded norm for
 // this launch.
