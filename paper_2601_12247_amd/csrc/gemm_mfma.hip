@@ -214,6 +214,9 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   // of a launch, add their k in the same order, and equal rows stay equal.  Cached rounds 2.0 and 2.6 % faster.
   // So do launches of few rows that do not split K, every column of tiles from a place of its own: the 64-row tiles read the
   // activations from L2 wherever they are (64 rows: gate/up of 24576 weight rows 42.5 -> 35.5 us, QKV 24.5 -> 22.9).
+  // And launches of 129-384 rows from K = 2048 on (gate/up of 2 x 12288, K = 4096: 192 rows 57.1 -> 53.0 us, 256 61.5 -> 58.4, 384 76.0
+  // -> 72.5; 2 x 11520, K = 8192, 5-6 %; QKV of 384 rows 3 %; cached rounds of 192, 256 and 384 rows 1.3-2.3 %).  The other side: K = 1024
+  // 2 % slower, 512 rows nothing in a round, 640 rows from 5 % quicker to 3 % slower.
   // An instance of its own: a division and a wrap per load in launches that do not turn cost 128 x 128 SwiGLU tiles 4-7 % at K <= 1024
   // (512 rows x 1408 columns, K = 512, 7.4 and 7.9 us).  tile_n nk < 2^19, as W is smaller than 4 GiB.
   const int turn = EPI == kEpiPartial ? nk / 8 * (tile_n * 8 / tiles_n) : kTurn ? (int)((uint32_t)(tile_n * nk) / (uint32_t)tiles_n) : 0;
@@ -803,7 +806,7 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   constexpr bool kTwoRows = (EPI == kEpiPartial && BN == 192) || (EPI == kEpiStore && BM == 160) || kTileStage;
   // shapes that the launches taking the whole of K behind few rows are made of
   constexpr bool kTurns = (EPI == kEpiStore && BN == 64) || (EPI == kEpiSwiglu && BN == 128 && (ST == 6 || BM == 128)) ||
-                          kTileStage;
+                          (EPI == kEpiSwiglu && kPairs && (BM == 192 || BM == 160 || (BM == 256 && BN == 128))) || (EPI == kEpiStore && BM == 192 && BN == 128);
   if constexpr (kTurns) if (sk.turn) {
     if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{}, std::true_type{});
     return launch(std::bool_constant<kFewRows>{}, std::true_type{});
@@ -840,19 +843,19 @@ constexpr TileCfg kCfg[kNumCfg] = {
 template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
                    const void *Res, int M, int N, int K, const RopeArgs &ra = RopeArgs{}, const NormArgs &na = NormArgs{}, bool turn = false) {
-  const SplitK whole{nullptr, 0, turn && (M <= 128 || cfg == 13) && K >= 1024};
+  const SplitK whole{nullptr, 0, turn && (M <= 128 ? K >= 1024 : M <= 384 && K >= 2048)};
   constexpr bool kPlain = EPI != kEpiSwiglu && EPI != kEpiQkvRope;
   if (K % 128 != 0 && cfg == 0) return run<EPI, 256, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
   if (K % 128 != 0 && cfg == 4) return run<EPI, 192, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
   switch (cfg) {
     case 0: return run<EPI, 256, 256, 64, 2, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
     case 1: return run<EPI, 128, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
-    case 2: return run<EPI, 256, 128, 64, 3, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
-    case 4: return run<EPI, 192, 256, 64, 2, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
+    case 2: return run<EPI, 256, 128, 64, 3, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);
+    case 4: return run<EPI, 192, 256, 64, 2, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na);
     case 5: if constexpr (kPlain) return run<EPI, 320, 128, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 6: if constexpr (kPlain) return run<EPI, 64, 64, 64, 5, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     case 7: return run<EPI, 64, 128, 64, 3, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
-    case 8: if constexpr (EPI != kEpiQkvRope) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
+    case 8: if constexpr (EPI != kEpiQkvRope) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     case 9: if constexpr (kPlain) return run<EPI, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 10: if constexpr (EPI == kEpiSwiglu) return run<EPI, 256, 192, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 11: if constexpr (EPI == kEpiSwiglu) return run<EPI, 64, 128, 64, 6, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
