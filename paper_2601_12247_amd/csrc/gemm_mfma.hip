@@ -119,7 +119,51 @@ struct SplitK {
   float *partial;
   int32_t nk_per;                                    // k stages per split
   int32_t turn = 0;                                  // undivided launches: columns of tiles may start anywhere in K (host)
+  int32_t ahead = 0, ahead8 = 0;                     // workgroups per XCD that only touch weights, for so many of 8 stages (touch_weights)
 };
+
+// A workgroup of a launch that leaves CUs idle in its last round: it reads a word of every 128-byte line of ahead8 of 8 stages of the
+// weights of `tiles` tiles from `base` on, which its XCD runs in that round (every `ahead`-th column of tiles, from the p-th on), in the
+// order in which their workgroups get there, so that those find part of the lines in L2.  What bounds them is not latency as such
+// (deeper rings gain nothing; without MFMAs and LDS reads they take the same time) but that a CU has some 32 KB of loads on the way and
+// takes them in order: activations that lie in L2 wait behind weights from HBM.  An idle CU has 32 KB of its own.
+template <int EPI, int BN, int WN, int BK, int kThreads, bool kTurn>
+__device__ __forceinline__ void touch_weights(const bf16_t *W, int p, int base, int tiles, int nk, int N_out, int K, int tiles_m, int tiles_n,
+                                              int group_m, const SplitK &sk) {
+  constexpr int kSide = kThreads / BN, kSlots = 4;           // columns or stages side by side, and loads of a thread on the way
+  constexpr int kLines = 384;                                // lines to have on the way at least
+  auto column = [&](int L) {                                 // columns of tiles in the order of their workgroups, band by band
+    const int band = L / (group_m * tiles_n);
+    return band * tiles_n + (L - band * (group_m * tiles_n)) / min(group_m, tiles_m - band * group_m);
+  };
+  const int first = column(base) + p, my_cols = (column(base + tiles - 1) - first + sk.ahead) / sk.ahead;      // at most kSide * kSlots (run)
+  const int side = threadIdx.x / BN, row = threadIdx.x % BN;
+  if (my_cols < 1 || side >= kSide) return;
+  const int stages = max(1, min(kSide * kSlots / my_cols, (kLines + my_cols * BN - 1) / (my_cols * BN)));       // of an iteration
+  const char *src[kSlots];
+  int turn[kSlots], at[kSlots];
+#pragma unroll
+  for (int j = 0; j < kSlots; ++j) {
+    const int u = side + j * kSide, tile_n = (first + u % my_cols * sk.ahead) % tiles_n;
+    at[j] = u / my_cols;
+    src[j] = at[j] < stages ? reinterpret_cast<const char *>(W) + (size_t)w_row<EPI, BN, WN>(row, tile_n, N_out) * (uint32_t)K * 2u : nullptr;
+    turn[j] = kTurn ? (int)((uint32_t)(tile_n * nk) / (uint32_t)tiles_n) : 0;
+  }
+  constexpr int kFirst = 4;                                  // earlier stages are asked for by the time this workgroup runs
+  uint32_t last[kSlots] = {};
+  for (int i = 0; kFirst + i * 8 / sk.ahead8 < nk; i += stages) {
+    uint32_t x[kSlots];
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) {
+      const int kt = kFirst + (i + at[j]) * 8 / sk.ahead8, kr = kt + turn[j] < nk ? kt + turn[j] : kt + turn[j] - nk;
+      x[j] = src[j] && kt < nk ? *reinterpret_cast<const uint32_t *>(src[j] + kr * (BK * 2)) : 0;
+    }
+    asm volatile("" ::"v"(last[0]), "v"(last[1]), "v"(last[2]), "v"(last[3]));       // one iteration's words on the way while the next are asked for
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) last[j] = x[j];
+  }
+  asm volatile("" ::"v"(last[0]), "v"(last[1]), "v"(last[2]), "v"(last[3]));
+}
 
 template <int EPI, int BM, int BN, int BK, int kStages, int WM, int WN, bool kPairs, bool kHint, bool kTurn>
 __global__ void __launch_bounds__(64 * WM * WN)
@@ -167,7 +211,14 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   // ---- XCD-aware tile assignment ----
   const int total = tiles_m * tiles_n;
   const int chunk = (total + 7) >> 3;
-  const int L = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+  const int base = (blockIdx.x & 7) * chunk;
+  if (EPI != kEpiPartial && (int)(blockIdx.x >> 3) >= chunk) {
+    const int before = chunk & ~31, tiles = min(chunk, total - base) - before;           // in the rounds before the last, and in the last
+    if (tiles > 0)
+      touch_weights<EPI, BN, WN, BK, kThreads, kTurn>(W, (int)(blockIdx.x >> 3) - chunk, base + before, tiles, K / BK, N_out, K, tiles_m, tiles_n, group_m, sk);
+    return;
+  }
+  const int L = base + (blockIdx.x >> 3);
   if (L >= total) return;
   const int band = L / (group_m * tiles_n);
   const int within = L - band * (group_m * tiles_n);
@@ -772,20 +823,37 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
 
 template <int EPI, int BM, int BN, int BK, int ST, int WM, int WN, bool kPairs = true>
 pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *C, const void *Res,
-               int M, int N_out, int K, const RopeArgs &ra, const SplitK &sk = SplitK{nullptr, 0}, int splits = 1,
+               int M, int N_out, int K, const RopeArgs &ra, const SplitK &split = SplitK{nullptr, 0}, int splits = 1,
                const NormArgs &na = NormArgs{}) {
   constexpr int kLdsBytes = ST * (BM + BN) * BK * 2;
   static_assert(kLdsBytes <= 160 * 1024, "LDS ring exceeds the 160 KB of a CU");
   const int tiles_m = (M + BM - 1) / BM;
   const int tiles_n = (EPI == kEpiSwiglu) ? N_out / (BN / 2) : N_out / BN;
   const int total = tiles_m * tiles_n;
-  const int grid = 8 * ((total + 7) / 8);
   // bands of at most kBand tile rows, all of (nearly) the same height: the 32 workgroups that run
   // together on an XCD then cover a patch of kBand x 32/kBand tiles in every band, whose operand rows
   // that XCD's L2 fetches once.  The patch that fetches least has rows : columns = BN : BM.
   constexpr int kBand = BM > BN ? 4 : 8;
   const int n_bands = (tiles_m + kBand - 1) / kBand;
   const int group_m = (tiles_m + n_bands - 1) / n_bands;
+  // Workgroups that touch weights ahead on the CUs of the last round that have no tile (touch_weights).  They read as fast as a tile's
+  // own loads go (47 GB/s a CU), so they take all stages where that ends before the tiles do (in_time, in eighths), every second one
+  // where half of it does, and none otherwise: every third or fourth is slower than none.  K = 4096 unless noted: QKV of 128
+  // rows 29.8 -> 28.6 us, 384 47.2 -> 44.2, 512 55.5 -> 48.2; gate/up of 2 x 12288 columns, 128 rows 46.1 -> 42.0, 192 53.5 -> 49.8, 2 x
+  // 9216, K = 3072, 256 rows 49.7 -> 40.0; O of 768 rows 37.9 -> 32.6, down (K = 12288) 111 -> 86, of 1311 rows 132 -> 124.  Not up to 64
+  // rows, which HBM itself bounds (33 rows of 9216 columns, K = 3072, 15.4 -> 17.4); not with weights below 16 MB, which most tiles find in L2
+  // (1311 rows of 1024 columns, K = 2048, 14.7 -> 15.6); not behind tiles of 256 x 256, which the MFMAs bound (1024 rows 80-85 either way).
+  const int chunk = (total + 7) / 8, in_last = chunk % 32, idle = 32 - in_last;     // tiles and idle CUs of an XCD in the last round
+  const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;
+  SplitK sk = split;
+  if (EPI != kEpiPartial && M > 64 && in_last > 0 && idle >= 4 && K >= 1024 && BM * BN < 256 * 256 && (int64_t)w_rows * K >= 8 << 20) {
+    const int rows = std::min(tiles_m, group_m), n_cols = 1 + (in_last + rows - 2) / rows;       // at most
+    sk.ahead = std::min(idle, n_cols);
+    const int in_time = 32 * (BM + BN) / (5 * BN * ((n_cols + sk.ahead - 1) / sk.ahead));
+    sk.ahead8 = in_time >= 8 ? 8 : 4;
+    if (in_time < 4) sk.ahead = 0;
+  }
+  const int grid = 8 * (chunk + sk.ahead);
   auto launch = [&](auto hint, auto turn) -> pvf_status {
     const auto kernel = gemm_bf16_mfma_kernel<EPI, BM, BN, BK, ST, WM, WN, kPairs, decltype(hint)::value, decltype(turn)::value>;
     // once per kernel instance; a function-local static is initialised exactly once even with concurrent callers
