@@ -68,8 +68,8 @@ __device__ __forceinline__ void split3(const float *p, bf16x8 *x) {
 struct WinArgs {
   const bf16_t *kc, *vtc;
   int64_t group_stride;
-  const int32_t *seq_slot, *k_active;
-  int32_t slots_per_group, prompt_len, block_len, R, Rv;
+  const int32_t *seq_slot, *row_pos;                         // row_pos[seq * R]: first position of the window
+  int32_t slots_per_group, R, Rv;
 };
 
 // SPLIT (window mode, launches that leave CUs idle): a workgroup takes 64 queries, which need only two of the four waves, and
@@ -105,7 +105,7 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
   const bf16_t *kcb = nullptr, *vtcb = nullptr;
   if (WIN) {
     const int g = wa.seq_slot[seq] / wa.slots_per_group;
-    w0 = wa.prompt_len + wa.k_active[g] * wa.block_len;
+    w0 = wa.row_pos[(int64_t)seq * wa.R];
     w1 = w0 + min(wa.R, T - w0);
     v0 = w0 & ~15; v1 = (w1 + 15) & ~15;
     kcb = wa.kc + g * wa.group_stride + (int64_t)head * DH;
@@ -433,7 +433,8 @@ rope_vt_kernel(bf16_t *__restrict__ qkv, bf16_t *__restrict__ vt, int T, int H, 
 // that boundary; positions of a boundary group that lie outside the window come from the cache.
 // PART: q, k and v come as the float32 partial sums of the split-K projection, part[split][row][3 d], added in split order and
 // rounded to bf16 here; the v third of qkv is then not written (only the attention reads these rows).  Bound by latency:
-// 64 rows, 8 splits: 9.4 us, where a reduction of its own and 64-row workgroups took 5.4 + 6.4; 320 rows, 2 splits: 11.4, 7.1 + 7.7.
+// 64 rows, 8 splits: 9.4 us, where a reduction of its own and 64-row workgroups took 5.4 + 6.4; 320 rows, 2 splits: 10.8, and 10.0 with
+// all that a thread needs asked for at once, behind one load (row_pos) for where the window lies.
 template <bool PART>
 __global__ void __launch_bounds__(256)
 rope_vt_rows_kernel(bf16_t *__restrict__ qkv, const float *__restrict__ part, int splits, int M, bf16_t *__restrict__ vt, int T, int H,
@@ -442,48 +443,61 @@ rope_vt_rows_kernel(bf16_t *__restrict__ qkv, const float *__restrict__ part, in
   const int tid = threadIdx.x, head = blockIdx.y, seq = blockIdx.z;
   const int d = H * DH;
   const int g = wa.seq_slot[seq] / wa.slots_per_group;
-  const int w0 = wa.prompt_len + wa.k_active[g] * wa.block_len, w1 = w0 + min(wa.R, T - w0);
+  const int w0 = wa.row_pos[(int64_t)seq * wa.R], w1 = w0 + min(wa.R, T - w0);
   const int p0 = (w0 & ~15) + blockIdx.x * 16;               // first position of the group
   const int64_t row0 = (int64_t)seq * wa.R;
-  auto load8 = [&](int64_t row, int col) -> uint4 {          // 8 elements of a row of the projection, in bf16
-    if constexpr (!PART) return *reinterpret_cast<const uint4 *>(qkv + row * 3 * d + col);
-    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  // What a thread needs of the projection, in one go: 8 pairs of a rotated row (16 rows x 2 tensors x 8 chunks) and 8 d of a v row (16
+  // rows x 16 chunks).  Threads without one read the window's first row.
+  const int qk_ch = tid & 7, which = (tid >> 3) & 1, r = p0 - w0 + (tid >> 4), v_ch = tid >> 4, pos = p0 + (tid & 15);
+  const bool qk_ok = r >= 0 && r < wa.R, v_ok = pos >= w0 && pos < w1;
+  const int qk_col = which * d + head * DH + qk_ch * 8;
+  const int64_t at[3] = {(row0 + (qk_ok ? r : 0)) * 3 * d + qk_col, (row0 + (qk_ok ? r : 0)) * 3 * d + qk_col + 64,
+                         (row0 + (v_ok ? pos - w0 : 0)) * 3 * d + 2 * d + head * DH + v_ch * 8};
+  uint4 in[3];
+  if constexpr (!PART) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) in[i] = *reinterpret_cast<const uint4 *>(qkv + at[i]);
+  } else {
+    float a[3][8] = {};
     for (int z0 = 0; z0 < splits; z0 += 4) {                 // 4 splits in flight at a time
-      float4 x[4], y[4];
+      float4 x[3][4], y[3][4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float4 *p = reinterpret_cast<const float4 *>(part + ((int64_t)min(z0 + j, splits - 1) * M + row) * 3 * d + col);
-        x[j] = p[0]; y[j] = p[1];
-      }
+      for (int i = 0; i < 3; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (z0 + j < splits) {
-          a[0] += x[j].x; a[1] += x[j].y; a[2] += x[j].z; a[3] += x[j].w;
-          a[4] += y[j].x; a[5] += y[j].y; a[6] += y[j].z; a[7] += y[j].w;
+        for (int j = 0; j < 4; ++j) {
+          const float4 *p = reinterpret_cast<const float4 *>(part + (int64_t)min(z0 + j, splits - 1) * M * 3 * d + at[i]);
+          x[i][j] = p[0]; y[i][j] = p[1];
         }
-    }
-    uint32_t w[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      w[e] = (uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)a[2 * e]) | ((uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)a[2 * e + 1]) << 16);
-    return make_uint4(w[0], w[1], w[2], w[3]);
-  };
-  {                                                          // rotate q and k: 16 rows x 2 tensors x 8 chunks of 8 pairs
-    const int ch = tid & 7, which = (tid >> 3) & 1, r = p0 - w0 + (tid >> 4);
-    if (r >= 0 && r < wa.R) {
-      const int col = which * d + head * DH + ch * 8;
-      uint4 ro, rh;
-      rotate8(load8(row0 + r, col), load8(row0 + r, col + 64), cos_sin + (int64_t)min(w0 + r, T - 1) * 64 + ch * 8, &ro, &rh);
-      bf16_t *p = qkv + (row0 + r) * 3 * d + col;
-      *reinterpret_cast<uint4 *>(p) = ro;
-      *reinterpret_cast<uint4 *>(p + 64) = rh;
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (z0 + j < splits) {
+            a[i][0] += x[i][j].x; a[i][1] += x[i][j].y; a[i][2] += x[i][j].z; a[i][3] += x[i][j].w;
+            a[i][4] += y[i][j].x; a[i][5] += y[i][j].y; a[i][6] += y[i][j].z; a[i][7] += y[i][j].w;
+          }
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        w[e] = (uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)a[i][2 * e]) | ((uint32_t)__builtin_bit_cast(uint16_t, (bf16_t)a[i][2 * e + 1]) << 16);
+      in[i] = make_uint4(w[0], w[1], w[2], w[3]);
     }
   }
-  {                                                          // v through LDS: 16 rows x 16 chunks of 8 d
-    const int rr = tid & 15, ch = tid >> 4, pos = p0 + rr;
+  if (qk_ok) {
+    uint4 ro, rh;
+    rotate8(in[0], in[1], cos_sin + (int64_t)min(w0 + r, T - 1) * 64 + qk_ch * 8, &ro, &rh);
+    bf16_t *p = qkv + (row0 + r) * 3 * d + qk_col;
+    *reinterpret_cast<uint4 *>(p) = ro;
+    *reinterpret_cast<uint4 *>(p + 64) = rh;
+  }
+  {                                                          // v through LDS
+    const int rr = tid & 15, ch = v_ch;
     uint4 v8 = make_uint4(0, 0, 0, 0);
-    if (pos >= w0 && pos < w1) {
-      v8 = load8(row0 + pos - w0, 2 * d + head * DH + ch * 8);
+    if (v_ok) {
+      v8 = in[2];
     } else if (pos < T && pos < ((w1 + 15) & ~15)) {
       const bf16_t *vtcb = wa.vtc + g * wa.group_stride + ((int64_t)head * DH + ch * 8) * vt_stride + vt_pos(pos);
       uint16_t x[8];
@@ -529,14 +543,13 @@ static bool split_pays(int S, int rows, int n_heads) {
 
 // part: NULL, or the float32 partial sums of the split-K QKV projection [splits][S * R][3 d] that qkv_w is to be made from.
 pvf_status launch_window_attention_mfma(pvf_ctx *ctx, hipStream_t s, void *qkv_w, const float *part, int splits, void *vt_w, const void *kc,
-                                        const void *vtc, int64_t group_stride, const int32_t *seq_slot, const int32_t *k_active,
+                                        const void *vtc, int64_t group_stride, const int32_t *seq_slot, const int32_t *row_pos,
                                         const pvf_decode_cfg &cfg, int S, int n_heads, const float2 *cos_sin, void *out) {
   if (S == 0) return PVF_OK;
   const int T = cfg.prompt_len + cfg.gen_len, R = window_rows(cfg), vts = vt_keys(T);
   WinArgs wa;
   wa.kc = (const bf16_t *)kc; wa.vtc = (const bf16_t *)vtc; wa.group_stride = group_stride;
-  wa.seq_slot = seq_slot; wa.k_active = k_active; wa.slots_per_group = 1 + cfg.K;
-  wa.prompt_len = cfg.prompt_len; wa.block_len = cfg.block_len; wa.R = R;
+  wa.seq_slot = seq_slot; wa.row_pos = row_pos; wa.slots_per_group = 1 + cfg.K; wa.R = R;
   wa.Rv = window_vt_stride(R, cfg.block_len, cfg.prompt_len);
   // groups up to the end of the last key tile: the rest of the buffer's row (nothing, or groups behind the window) holds zeros
   const dim3 rgrid(wa.Rv / 16, n_heads, S);

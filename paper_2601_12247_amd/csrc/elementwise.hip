@@ -245,38 +245,46 @@ reduce_residual_rmsnorm_kernel(const float *__restrict__ partial, int splits, in
   uint4 *hr = reinterpret_cast<uint4 *>(h + m * d);
   const uint4 *gr = reinterpret_cast<const uint4 *>(gain);
   uint4 *orow = reinterpret_cast<uint4 *>(out + m * d);
-  uint4 v[MAXV];
+  // Bound by latency: everything that depends on nothing is asked for first, the gains too, then the partial sums of the whole row (320
+  // rows 7.5 -> 7.2 us, 64 5.8 -> 5.6).
+  uint4 v[MAXV], g4[MAXV];
+#pragma unroll
+  for (int k = 0; k < MAXV; ++k) {
+    const int i = min((int)threadIdx.x + k * 256, nvec - 1);
+    v[k] = hr[i];
+    g4[k] = gr[i];
+  }
+  float a[MAXV][8] = {};
+  for (int z0 = 0; z0 < splits; z0 += 4) {                 // 4 splits in flight at a time, added in split order
+    float4 p0[MAXV][4], p1[MAXV][4];
+#pragma unroll
+    for (int k = 0; k < MAXV; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = min((int)threadIdx.x + k * 256, nvec - 1), z = min(z0 + j, splits - 1);
+        const float4 *pr = reinterpret_cast<const float4 *>(partial + ((int64_t)z * M + m) * d + (int64_t)i * 8);
+        p0[k][j] = pr[0]; p1[k][j] = pr[1];
+      }
+#pragma unroll
+    for (int k = 0; k < MAXV; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (z0 + j < splits) {
+          a[k][0] += p0[k][j].x; a[k][1] += p0[k][j].y; a[k][2] += p0[k][j].z; a[k][3] += p0[k][j].w;
+          a[k][4] += p1[k][j].x; a[k][5] += p1[k][j].y; a[k][6] += p1[k][j].z; a[k][7] += p1[k][j].w;
+        }
+  }
   float ss = 0.f;
 #pragma unroll
   for (int k = 0; k < MAXV; ++k) {
     const int i = threadIdx.x + k * 256;
     if (i < nvec) {
-      float a[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) a[e] = 0.f;
-      for (int z0 = 0; z0 < splits; z0 += 4) {             // 4 splits in flight at a time, added in split order
-        float4 p0[4], p1[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int z = min(z0 + j, splits - 1);
-          const float4 *pr = reinterpret_cast<const float4 *>(partial + ((int64_t)z * M + m) * d + (int64_t)i * 8);
-          p0[j] = pr[0]; p1[j] = pr[1];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (z0 + j < splits) {
-            a[0] += p0[j].x; a[1] += p0[j].y; a[2] += p0[j].z; a[3] += p0[j].w;
-            a[4] += p1[j].x; a[5] += p1[j].y; a[6] += p1[j].z; a[7] += p1[j].w;
-          }
-        }
-      }
-      const uint4 r4 = hr[i];
-      const uint32_t rw[4] = {r4.x, r4.y, r4.z, r4.w};
+      const uint32_t rw[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
       uint32_t o[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const bf16_t lo = (bf16_t)(a[2 * q] + __uint_as_float(rw[q] << 16));
-        const bf16_t hi = (bf16_t)(a[2 * q + 1] + __uint_as_float(rw[q] & 0xffff0000u));
+        const bf16_t lo = (bf16_t)(a[k][2 * q] + __uint_as_float(rw[q] << 16));
+        const bf16_t hi = (bf16_t)(a[k][2 * q + 1] + __uint_as_float(rw[q] & 0xffff0000u));
         o[q] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
         const float x = __uint_as_float(o[q] << 16), y = __uint_as_float(o[q] & 0xffff0000u);
         ss += x * x + y * y;
@@ -294,16 +302,15 @@ reduce_residual_rmsnorm_kernel(const float *__restrict__ partial, int splits, in
   for (int k = 0; k < MAXV; ++k) {
     const int i = threadIdx.x + k * 256;
     if (i < nvec) {
-      const uint4 g4 = gr[i];
       const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-      const uint32_t gw[4] = {g4.x, g4.y, g4.z, g4.w};
+      const uint32_t gw[4] = {g4[k].x, g4[k].y, g4[k].z, g4[k].w};
       uint32_t o[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float a = __uint_as_float(w[q] << 16) * r * __uint_as_float(gw[q] << 16);
-        const float b = __uint_as_float(w[q] & 0xffff0000u) * r * __uint_as_float(gw[q] & 0xffff0000u);
-        const bf16_t ab = (bf16_t)a, bb = (bf16_t)b;
-        o[q] = (uint32_t)__builtin_bit_cast(uint16_t, ab) | ((uint32_t)__builtin_bit_cast(uint16_t, bb) << 16);
+        const float x = __uint_as_float(w[q] << 16) * r * __uint_as_float(gw[q] << 16);
+        const float y = __uint_as_float(w[q] & 0xffff0000u) * r * __uint_as_float(gw[q] & 0xffff0000u);
+        const bf16_t xb = (bf16_t)x, yb = (bf16_t)y;
+        o[q] = (uint32_t)__builtin_bit_cast(uint16_t, xb) | ((uint32_t)__builtin_bit_cast(uint16_t, yb) << 16);
       }
       orow[i] = make_uint4(o[0], o[1], o[2], o[3]);
     }

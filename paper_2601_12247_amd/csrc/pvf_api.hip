@@ -618,7 +618,7 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)R * T * d, 0.0);
       if (c->cache_vt) {
         RUN(launch_window_attention_mfma(c, s, c->qkv, splits ? c->splitk_ws : nullptr, splits, c->vt, (const char *)c->kcache + layer_off,
-                                         (const char *)c->vcache + layer_off, gstride, seq_slot, state.k_active, cfg, S, H, c->cos_sin, c->att));
+                                         (const char *)c->vcache + layer_off, gstride, seq_slot, row_pos, cfg, S, H, c->cos_sin, c->att));
       } else {
         if (!f32_rope) RUN(launch_rope_rows(c, s, dt, c->qkv, row_pos, M, T, H, dh, c->cos_sin));
         if (attention_f32_supported(dt, T, dh))
