@@ -529,7 +529,7 @@ rope_vt_rows_kernel(bf16_t *__restrict__ qkv, const float *__restrict__ part, in
 bool attention_mfma_supported(int dtype, int d_head) { return dtype == PVF_BF16 && d_head == DH; }
 
 // Keys per row of the window rows' value buffer: whole key tiles from the 16-key boundary below the window.
-static int window_vt_stride(int R, int block_len, int prompt_len) {
+int window_vt_stride(int R, int block_len, int prompt_len) {
   const int before = block_len % 16 == 0 && prompt_len % 16 == 0 ? 0 : 15;
   return (before + R + 63) / 64 * 64;
 }
@@ -541,21 +541,24 @@ static bool split_pays(int S, int rows, int n_heads) {
   return (int64_t)S * rows <= 640 && (int64_t)S * n_heads * ((rows + TQ / 2 - 1) / (TQ / 2)) <= 256;
 }
 
-// part: NULL, or the float32 partial sums of the split-K QKV projection [splits][S * R][3 d] that qkv_w is to be made from.
+// part: NULL, or the float32 partial sums of the split-K QKV projection [splits][S * R][3 d] that qkv_w is to be made from.  rotated:
+// qkv_w and vt_w are what the attention reads.
 pvf_status launch_window_attention_mfma(pvf_ctx *ctx, hipStream_t s, void *qkv_w, const float *part, int splits, void *vt_w, const void *kc,
                                         const void *vtc, int64_t group_stride, const int32_t *seq_slot, const int32_t *row_pos,
-                                        const pvf_decode_cfg &cfg, int S, int n_heads, const float2 *cos_sin, void *out) {
+                                        const pvf_decode_cfg &cfg, int S, int n_heads, const float2 *cos_sin, void *out, bool rotated) {
   if (S == 0) return PVF_OK;
   const int T = cfg.prompt_len + cfg.gen_len, R = window_rows(cfg), vts = vt_keys(T);
   WinArgs wa;
   wa.kc = (const bf16_t *)kc; wa.vtc = (const bf16_t *)vtc; wa.group_stride = group_stride;
   wa.seq_slot = seq_slot; wa.row_pos = row_pos; wa.slots_per_group = 1 + cfg.K; wa.R = R;
   wa.Rv = window_vt_stride(R, cfg.block_len, cfg.prompt_len);
-  // groups up to the end of the last key tile: the rest of the buffer's row (nothing, or groups behind the window) holds zeros
+  // groups up to the end of the last key tile; what lies behind the window is not read
   const dim3 rgrid(wa.Rv / 16, n_heads, S);
-  if (part) rope_vt_rows_kernel<true><<<rgrid, 256, 0, s>>>((bf16_t *)qkv_w, part, splits, S * R, (bf16_t *)vt_w, T, n_heads, vts, cos_sin, wa);
-  else rope_vt_rows_kernel<false><<<rgrid, 256, 0, s>>>((bf16_t *)qkv_w, nullptr, 0, S * R, (bf16_t *)vt_w, T, n_heads, vts, cos_sin, wa);
-  PVF_LAUNCH_CHECK(ctx, "rope_vt_rows");
+  if (!rotated) {
+    if (part) rope_vt_rows_kernel<true><<<rgrid, 256, 0, s>>>((bf16_t *)qkv_w, part, splits, S * R, (bf16_t *)vt_w, T, n_heads, vts, cos_sin, wa);
+    else rope_vt_rows_kernel<false><<<rgrid, 256, 0, s>>>((bf16_t *)qkv_w, nullptr, 0, S * R, (bf16_t *)vt_w, T, n_heads, vts, cos_sin, wa);
+    PVF_LAUNCH_CHECK(ctx, "rope_vt_rows");
+  }
   // even: whole key tiles, whole 64-row blocks of window rows, windows that begin and end with a 16-key group
   const bool even = T % TK == 0 && R % 64 == 0 && cfg.block_len % 16 == 0 && cfg.prompt_len % 16 == 0;
   const bool split = R <= 64 || split_pays(S, R, n_heads);

@@ -73,6 +73,8 @@ constexpr bool pairs_in_wave(int WT) { return WT / 16 % 2 == 0; }
 //  QKV with rotary embedding (ff = 3 d): in the q and k thirds a wave's 64 tile rows are columns
 //           [32g, 32g + 32) of a head followed by their rotation partners [64 + 32g, 64 + 32g + 32)
 //           (g = wave % 2), so the pair (i, i + 64) meets in one lane (sub-tiles t and t + 2).
+//  QKV of window rows (ff = 3 d, tiles of 64 columns): in the q and k thirds a tile is columns [32g, 32g + 32) of a head and
+//           their partners (g = tile_n % 2), 16 and 16 a wave.
 template <int EPI, int BN, int WN>
 __device__ __forceinline__ int w_row(int r, int tile_n, int ff) {
   if (EPI == kEpiQkvRope) {
@@ -80,6 +82,8 @@ __device__ __forceinline__ int w_row(int r, int tile_n, int ff) {
     const int wn = r >> 6, t = (r >> 4) & 3, e = r & 15;
     return tile_n * BN + (wn >> 1) * 128 + (t >> 1) * 64 + (wn & 1) * 32 + (t & 1) * 16 + e;
   }
+  if (EPI == kEpiQkvWindow && tile_n * BN < 2 * (ff / 3))
+    return (tile_n >> 1) * 128 + ((r >> 4) & 1) * 64 + (tile_n & 1) * 32 + (r >> 5) * 16 + (r & 15);
   if (EPI != kEpiSwiglu) return tile_n * BN + r;
   constexpr int WT = BN / WN;
   if (!pairs_in_wave(WT)) return (r < BN / 2 ? 0 : ff - BN / 2) + tile_n * (BN / 2) + r;
@@ -111,6 +115,8 @@ struct RopeArgs {
   bf16_t *vt;
   int32_t T, Tv, H;
   int32_t store_v;                                   // 0: the v third of C is not written (only vt)
+  const int32_t *row_pos = nullptr;                  // kEpiQkvWindow: canvas position of each row (negative: padding, rotated like position T - 1)
+  int32_t R = 0;                                     // rows a canvas; Tv = keys of a row of vt
 };
 
 // kEpiPartial: the launch is split along K (blockIdx.y = split); every split stores its tile of float32
@@ -524,6 +530,63 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   for (; kt < nk; ++kt) run_stage(kt, std::false_type{});
   }
 
+  if constexpr (EPI == kEpiQkvWindow) {
+    // Window rows of K/V-cached rounds whose windows are whole 16-key groups: q and k rotated, v key-contiguous, each from the wave's
+    // own piece of the free ring, rounded as the rotary pass would find and leave them.  Saves that pass (4.9 us a layer at 64 rows) and
+    // its launch: cached rounds of 64 rows 4.10 -> 4.04 ms, 128 rows 4.84 -> 4.63 (four canvases), 4.80 -> 4.73 (one).
+    static_assert(BN == 64 && WN == 2 && MT16 == 2 && NT16 == 2, "waves of 32 x 32");
+    constexpr int kRow = 32 * 2 + 16;
+    const int d = N_out / 3, third = tile_n * BN / d;
+    unsigned char *my = lds + wave * 32 * kRow;
+    float4 cs[2][2];
+    if (third < 2)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int pos = ra.row_pos[min(m0 + wm * 32 + h * 16 + fr, M - 1)];
+        const float4 *p = reinterpret_cast<const float4 *>(ra.cos_sin + (int64_t)(pos < 0 ? ra.T - 1 : pos) * 64 + (tile_n & 1) * 32 + wn * 16 + 4 * fq);
+        cs[h][0] = p[0]; cs[h][1] = p[1];
+      }
+    __syncthreads();                                                 // every wave is done with the ring
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uint32_t lo[2], up[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        lo[e] = pack_bf16x2(acc[0][h][2 * e], acc[0][h][2 * e + 1]);
+        up[e] = pack_bf16x2(acc[1][h][2 * e], acc[1][h][2 * e + 1]);
+        if (third < 2) {
+          const float2 r0 = rotate_pair(__uint_as_float(lo[e] << 16), __uint_as_float(up[e] << 16), cs[h][e].x, cs[h][e].y);
+          const float2 r1 = rotate_pair(__uint_as_float(lo[e] & 0xffff0000u), __uint_as_float(up[e] & 0xffff0000u), cs[h][e].z, cs[h][e].w);
+          lo[e] = pack_bf16x2(r0.x, r1.x);
+          up[e] = pack_bf16x2(r0.y, r1.y);
+        }
+      }
+      unsigned char *row = my + (h * 16 + fr) * kRow + 4 * fq * 2;
+      *reinterpret_cast<uint2 *>(row) = make_uint2(lo[0], lo[1]);
+      *reinterpret_cast<uint2 *>(row + 32) = make_uint2(up[0], up[1]);
+    }
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const int piece = it * 64 + lane;
+      if (third < 2) {                                               // row piece / 4: 16 columns below, 16 above
+        const int r = piece >> 2, c = piece & 3, m = m0 + wm * 32 + r;
+        if (m < M) *reinterpret_cast<uint4 *>(C + (int64_t)m * N_out + (tile_n >> 1) * 128 + (c >> 1) * 64 + (tile_n & 1) * 32 + wn * 16 + (c & 1) * 8) =
+                       *reinterpret_cast<const uint4 *>(my + r * kRow + c * 16);
+      } else {                                                       // column piece / 4: chunk piece % 4 of its 32 keys
+        const int c = piece >> 2, kg = piece & 3, m = m0 + wm * 32 + 16 * (kg >> 1), col = tile_n * BN - 2 * d + wn * 32 + c;
+        const unsigned char *src = my + (16 * (kg >> 1) + 4 * (kg & 1)) * kRow + c * 2;
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int kr = (e & 1) * 2 + (e >> 1) * 8;
+          w[e] = *reinterpret_cast<const uint16_t *>(src + kr * kRow) | ((uint32_t)*reinterpret_cast<const uint16_t *>(src + (kr + 1) * kRow) << 16);
+        }
+        if (m < M)
+          *reinterpret_cast<uint4 *>(ra.vt + (((int64_t)(m / ra.R) * ra.H + (col >> 7)) * 128 + (col & 127)) * ra.Tv + m % ra.R + (kg & 1) * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+    }
+    return;
+  }
   if constexpr (kTileStage) {
     // 160 x 192: the sums as float32 rows in the free ring (16 bytes of padding: rows start 4 banks apart), then gate and up from
     // there.  Against float32 partial sums through memory and a launch that pairs them: 320 rows of gate/up, 2 x 12288 columns, K =
@@ -573,7 +636,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   // The residual rows of the whole wave tile are requested at once, before the staging starts:
   // fetched 32 rows at a time where they are added, each piece cost a full memory latency.
   constexpr int kRowIters = 32 * LPR / 64;
-  static_assert(kWholeRows || EPI == kEpiPartial || EPI == kEpiSwiglu, "the other epilogues store whole rows per instruction");
+  static_assert(kWholeRows || EPI == kEpiPartial || EPI == kEpiSwiglu || EPI == kEpiQkvWindow, "the other epilogues store whole rows per instruction");
   uint4 rs[EPI == kEpiResidual ? MT : 1][kRowIters];
   if (EPI == kEpiResidual) {
 #pragma unroll
@@ -873,7 +936,7 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   constexpr bool kFewRows = EPI == kEpiPartial ? BM == 64 : BN == 64 || ST == 6;                 // shapes for up to 128 rows
   constexpr bool kTwoRows = (EPI == kEpiPartial && BN == 192) || (EPI == kEpiStore && BM == 160) || kTileStage;
   // shapes that the launches taking the whole of K behind few rows are made of
-  constexpr bool kTurns = (EPI == kEpiStore && BN == 64) || (EPI == kEpiSwiglu && BN == 128 && (ST == 6 || BM == 128)) ||
+  constexpr bool kTurns = ((EPI == kEpiStore || EPI == kEpiQkvWindow) && BN == 64) || (EPI == kEpiSwiglu && BN == 128 && (ST == 6 || BM == 128)) ||
                           (EPI == kEpiSwiglu && kPairs && (BM == 192 || BM == 160 || (BM == 256 && BN == 128))) || (EPI == kEpiStore && BM == 192 && BN == 128);
   if constexpr (kTurns) if (sk.turn) {
     if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{}, std::true_type{});
@@ -1224,6 +1287,26 @@ pvf_status launch_gemm_mfma_qkv_rope(pvf_ctx *ctx, hipStream_t s, const void *A,
   return run_cfg<kEpiQkvRope>(ctx, s, cfg, A, W, qkv, nullptr, M, N, K, ra, na ? *na : NormArgs{});
 }
 
+// QKV projection of the window rows of S canvases (R rows each, R and the windows whole 16-key groups) with the rotary embedding
+// and the key-contiguous v (vt [S][H][128][Rv]) in its epilogue, where the launch takes tiles of 64 columns.
+bool gemm_mfma_qkv_window_supported(int M, int N, int K) {
+  if (!gemm_mfma_supported(PVF_BF16, kEpiStore, M, N, K) || N % 384 != 0) return false;
+  const int cfg = pick_config(kEpiStore, M, N, K);
+  return cfg == 6 || cfg == 12;
+}
+
+pvf_status launch_gemm_mfma_qkv_window(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *qkv, void *vt, const float2 *cos_sin,
+                                       const int32_t *row_pos, int M, int N, int K, int T, int R, int Rv, int H) {
+  const uintptr_t al = (uintptr_t)A | (uintptr_t)W | (uintptr_t)qkv | (uintptr_t)vt;
+  PVF_REQUIRE(ctx, (al & 15u) == 0, PVF_EINVAL, "gemm_mfma: operands must be 16-byte aligned");
+  PVF_REQUIRE(ctx, R % 16 == 0 && M % R == 0 && N == 3 * H * 128 && Rv >= R, PVF_ESHAPE, "gemm_mfma: window rows M=%d R=%d Rv=%d N=%d H=%d", M, R, Rv, N, H);
+  RopeArgs ra{};
+  ra.cos_sin = cos_sin; ra.vt = (bf16_t *)vt; ra.T = T; ra.Tv = Rv; ra.H = H; ra.row_pos = row_pos; ra.R = R;
+  const SplitK whole{nullptr, 0, K >= 1024};
+  if (pick_config(kEpiStore, M, N, K) == 12) return run<kEpiQkvWindow, 128, 64, 64, 6, 4, 2>(ctx, s, A, W, qkv, nullptr, M, N, K, ra, whole);
+  return run<kEpiQkvWindow, 64, 64, 64, 5, 2, 2>(ctx, s, A, W, qkv, nullptr, M, N, K, ra, whole);
+}
+
 bool gemm_mfma_supported(int dtype, GemmEpilogue epi, int M, int N, int K) {
   if (dtype != PVF_BF16 || M < 1 || K < 64 || K % 64 != 0) return false;
   const int64_t w_rows = (epi == kEpiSwiglu) ? 2 * (int64_t)N : N;
@@ -1258,6 +1341,7 @@ pvf_status launch_gemm_mfma(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const
     case kEpiResidual: return run_cfg<kEpiResidual>(ctx, s, cfg, A, W, C, residual, M, N, K, RopeArgs{}, nrm);
     case kEpiSwiglu: return run_cfg<kEpiSwiglu>(ctx, s, cfg, A, W, C, residual, M, N, K, RopeArgs{}, nrm, turn);
     case kEpiQkvRope: break;                     // has its own entry (launch_gemm_mfma_qkv_rope)
+    case kEpiQkvWindow: break;                   // launch_gemm_mfma_qkv_window
     case kEpiPartial: break;                     // launch_gemm_mfma_splitk
   }
   return PVF_EINVAL;

@@ -117,7 +117,11 @@ bool attention_mfma_supported(int dtype, int d_head);
 pvf_status launch_attention_mfma(pvf_ctx *, hipStream_t, const void *, const void *, void *, int, int, int);
 pvf_status launch_rope_vt(pvf_ctx *, hipStream_t, void *, void *, int, int, int, const float2 *);
 pvf_status launch_window_attention_mfma(pvf_ctx *, hipStream_t, void *, const float *, int, void *, const void *, const void *, int64_t,
-                                        const int32_t *, const int32_t *, const pvf_decode_cfg &, int, int, const float2 *, void *);
+                                        const int32_t *, const int32_t *, const pvf_decode_cfg &, int, int, const float2 *, void *, bool rotated);
+int window_vt_stride(int R, int block_len, int prompt_len);
+bool gemm_mfma_qkv_window_supported(int M, int N, int K);
+pvf_status launch_gemm_mfma_qkv_window(pvf_ctx *, hipStream_t, const void *, const void *, void *, void *, const float2 *, const int32_t *, int, int,
+                                       int, int, int, int, int);
 
 pvf_status launch_gemm_mfma_splitk_partial(pvf_ctx *, hipStream_t, const void *, const void *, int, int, int, float *, size_t, int *);
 
@@ -604,9 +608,15 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
   for (int l = 0; l < m.n_layers; ++l) {
     const int64_t layer_off = (int64_t)l * vt_keys(T) * d * c->esize;
     int splits = 0;                    // > 0: the QKV projection left partial sums in splitk_ws, which the rotary pass adds up
+    bool rotated = false;              // its epilogue has rotated q and k and written v key-contiguous
     if (c->cache_vt && c->splitk_ws && gemm_mfma_splitk_supported(dt, kEpiStore, M, 3 * d, d, c->splitk_floats)) {
       ProfScope ps(c, s, PVF_PROF_GEMM, 6.0 * M * (double)d * d, (double)c->esize * (4.0 * M * d + 3.0 * d * d));
       RUN(launch_gemm_mfma_splitk_partial(c, s, c->xn, c->wqkv[l], M, 3 * d, d, c->splitk_ws, c->splitk_floats, &splits));
+    } else if (c->cache_vt && cfg.block_len % 16 == 0 && cfg.prompt_len % 16 == 0 && gemm_mfma_qkv_window_supported(M, 3 * d, d)) {
+      ProfScope ps(c, s, PVF_PROF_GEMM, 6.0 * M * (double)d * d, (double)c->esize * (4.0 * M * d + 3.0 * d * d));
+      RUN(launch_gemm_mfma_qkv_window(c, s, c->xn, c->wqkv[l], c->qkv, c->vt, c->cos_sin, row_pos, M, 3 * d, d, T, R,
+                                      window_vt_stride(R, cfg.block_len, cfg.prompt_len), H));
+      rotated = true;
     } else if (f32_rope) {
       ProfScope ps(c, s, PVF_PROF_GEMM, 6.0 * M * (double)d * d, (double)c->esize * (4.0 * M * d + 3.0 * d * d));
       RUN(launch_gemm_f32_qkv_rope(c, s, (const float *)c->xn, (const float *)c->wqkv[l], (float *)c->qkv, M, d, d,
@@ -618,7 +628,7 @@ static pvf_status forward_window_impl(pvf_ctx *c, hipStream_t s, const pvf_decod
       ProfScope ps(c, s, PVF_PROF_ATTENTION, 4.0 * S * (double)R * T * d, 0.0);
       if (c->cache_vt) {
         RUN(launch_window_attention_mfma(c, s, c->qkv, splits ? c->splitk_ws : nullptr, splits, c->vt, (const char *)c->kcache + layer_off,
-                                         (const char *)c->vcache + layer_off, gstride, seq_slot, row_pos, cfg, S, H, c->cos_sin, c->att));
+                                         (const char *)c->vcache + layer_off, gstride, seq_slot, row_pos, cfg, S, H, c->cos_sin, c->att, rotated));
       } else {
         if (!f32_rope) RUN(launch_rope_rows(c, s, dt, c->qkv, row_pos, M, T, H, dh, c->cos_sin));
         if (attention_f32_supported(dt, T, dh))
