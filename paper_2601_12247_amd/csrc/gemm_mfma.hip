@@ -128,6 +128,9 @@ struct SplitK {
   int32_t ahead = 0, ahead8 = 0;                     // workgroups per XCD that only touch weights, for so many of 8 stages (touch_weights)
 };
 
+// Whether launches of a shape may have workgroups that touch weights (run): not the split ones, which fill the chip, nor 256 x 256.
+constexpr bool touches(int epi, int bm, int bn) { return epi != kEpiPartial && bm * bn < 256 * 256; }
+
 // A workgroup of a launch that leaves CUs idle in its last round: it reads a word of every 128-byte line of ahead8 of 8 stages of the
 // weights of `tiles` tiles from `base` on, which its XCD runs in that round (every `ahead`-th column of tiles, from the p-th on), in the
 // order in which their workgroups get there, so that those find part of the lines in L2.  What bounds them is not latency as such
@@ -218,7 +221,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   const int total = tiles_m * tiles_n;
   const int chunk = (total + 7) >> 3;
   const int base = (blockIdx.x & 7) * chunk;
-  if (EPI != kEpiPartial && (int)(blockIdx.x >> 3) >= chunk) {
+  if constexpr (touches(EPI, BM, BN)) if ((int)(blockIdx.x >> 3) >= chunk) {
     const int before = chunk & ~31, tiles = min(chunk, total - base) - before;           // in the rounds before the last, and in the last
     if (tiles > 0)
       touch_weights<EPI, BN, WN, BK, kThreads, kTurn>(W, (int)(blockIdx.x >> 3) - chunk, base + before, tiles, K / BK, N_out, K, tiles_m, tiles_n, group_m, sk);
@@ -909,7 +912,7 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   const int chunk = (total + 7) / 8, in_last = chunk % 32, idle = 32 - in_last;     // tiles and idle CUs of an XCD in the last round
   const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;
   SplitK sk = split;
-  if (EPI != kEpiPartial && M > 64 && in_last > 0 && idle >= 4 && K >= 1024 && BM * BN < 256 * 256 && (int64_t)w_rows * K >= 8 << 20) {
+  if (touches(EPI, BM, BN) && M > 64 && in_last > 0 && idle >= 4 && K >= 1024 && (int64_t)w_rows * K >= 8 << 20) {
     const int rows = std::min(tiles_m, group_m), n_cols = 1 + (in_last + rows - 2) / rows;       // at most
     sk.ahead = std::min(idle, n_cols);
     const int in_time = 32 * (BM + BN) / (5 * BN * ((n_cols + sk.ahead - 1) / sk.ahead));
