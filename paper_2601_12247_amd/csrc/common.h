@@ -159,7 +159,7 @@ pvf_status launch_gather_rows(pvf_ctx *ctx, hipStream_t s, int dtype, const void
                               const int32_t *row_pos, int S, int T, int R, int d, void *out);
 pvf_status launch_rope(pvf_ctx *ctx, hipStream_t s, int dtype, void *qkv, int M, int T,
                        int n_heads, int d_head, const float2 *cos_sin);
-enum GemmEpilogue { kEpiStore = 0, kEpiResidual = 1, kEpiSwiglu = 2, kEpiQkvRope = 3, kEpiPartial = 4, kEpiQkvWindow = 5 };
+enum GemmEpilogue { kEpiStore = 0, kEpiResidual = 1, kEpiSwiglu = 2, kEpiQkvRope = 3, kEpiPartial = 4, kEpiQkvWindow = 5, kEpiQkvRopeWin = 6 };
 // RMSNorm folded into the projections around it (bf16 MFMA GEMMs of launches above the split-K range):
 // the projection that writes the residual stream also writes, per `slot` of 256 (or 64) columns, the sum of
 // squares of each row's (rounded) values, ss[slot * ld + m]; the projection that reads the stream takes h

@@ -65,6 +65,8 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // Whether a wave of WT columns holds the gate and the up column of an output: an even number of 16-column sub-tiles.
 constexpr bool pairs_in_wave(int WT) { return WT / 16 % 2 == 0; }
 
+constexpr bool is_rope(int epi) { return epi == kEpiQkvRope || epi == kEpiQkvRopeWin; }
+
 // Row of W that feeds row r (0..BN-1) of the workgroup's W tile.
 //  plain:   consecutive rows tile_n*BN + r.
 //  SwiGLU:  the tile covers BN/2 output columns; the lower half of each wave's BN/WN tile rows is gate, the
@@ -77,7 +79,7 @@ constexpr bool pairs_in_wave(int WT) { return WT / 16 % 2 == 0; }
 //           their partners (g = tile_n % 2), 16 and 16 a wave.
 template <int EPI, int BN, int WN>
 __device__ __forceinline__ int w_row(int r, int tile_n, int ff) {
-  if (EPI == kEpiQkvRope) {
+  if (is_rope(EPI)) {
     if (tile_n * BN >= 2 * (ff / 3)) return tile_n * BN + r;           // v third: as it is
     const int wn = r >> 6, t = (r >> 4) & 3, e = r & 15;
     return tile_n * BN + (wn >> 1) * 128 + (t >> 1) * 64 + (wn & 1) * 32 + (t & 1) * 16 + e;
@@ -115,8 +117,9 @@ struct RopeArgs {
   bf16_t *vt;
   int32_t T, Tv, H;
   int32_t store_v;                                   // 0: the v third of C is not written (only vt)
-  const int32_t *row_pos = nullptr;                  // kEpiQkvWindow: canvas position of each row (negative: padding, rotated like position T - 1)
-  int32_t R = 0;                                     // rows a canvas; Tv = keys of a row of vt
+  // window rows (kEpiQkvWindow, kEpiQkvRopeWin), windows of whole 16-key groups
+  const int32_t *row_pos = nullptr;                  // canvas position of each row (negative: padding, rotated like position T - 1)
+  int32_t R = 0;                                     // rows a canvas, a multiple of 16; Tv = keys of a row of vt
 };
 
 // kEpiPartial: the launch is split along K (blockIdx.y = split); every split stores its tile of float32
@@ -211,7 +214,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   static_assert(BM % (RPI / 2) == 0 && (!kHalfA || LA >= 2) && BN % RPI == 0 && BK == 64 && BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "tile shape");
   // SwiGLU whose waves cannot pair gate and up turns the whole tile around through LDS.
   constexpr bool kTileStage = EPI == kEpiSwiglu && !pairs_in_wave(BN / WN);
-  static_assert((EPI != kEpiQkvRope && (EPI != kEpiSwiglu || kTileStage)) || BM % (32 * WM) == 0, "the rotary and SwiGLU epilogues take whole 32-row passes");
+  static_assert((!is_rope(EPI) && (EPI != kEpiSwiglu || kTileStage)) || BM % (32 * WM) == 0, "the rotary and SwiGLU epilogues take whole 32-row passes");
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: LDS targets become scalar arithmetic
@@ -347,7 +350,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   // while the first stages are in flight (8 loads at a time, slot order), and keeps 1 / rms for the epilogue.
   static_assert(BM <= kThreads, "one thread per tile row");
   float my_rnorm = 1.f;
-  if ((EPI == kEpiSwiglu || EPI == kEpiQkvRope) && na.ss_in != nullptr && tid < BM) {
+  if ((EPI == kEpiSwiglu || is_rope(EPI)) && na.ss_in != nullptr && tid < BM) {
     const float *src = na.ss_in + min(m0 + tid, M - 1);
     float t = 0.f;
     for (int s0 = 0; s0 < na.n_slots_in; s0 += 8) {
@@ -659,40 +662,42 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
   constexpr int kNormOff = 80 * 1024;
   constexpr bool kNormRoom = kNormOff + WN * BM * 4 <= kStages * kStage;
   float *norm_x = reinterpret_cast<float *>(lds + kNormOff);
-  const bool norm_in = kNormRoom && (EPI == kEpiSwiglu || EPI == kEpiQkvRope) && na.ss_in != nullptr;     // uniform
+  const bool norm_in = kNormRoom && (EPI == kEpiSwiglu || is_rope(EPI)) && na.ss_in != nullptr;     // uniform
   const bool norm_out = kNormRoom && kWholeRows && EPI == kEpiResidual && na.ss_out != nullptr;                         // uniform
   if (norm_in) {
     if (tid < BM) norm_x[tid] = my_rnorm;
     __syncthreads();
   }
-  const int rope_third = EPI == kEpiQkvRope ? (tile_n * BN) / (N_out / 3) : 2;   // 0 = q, 1 = k, 2 = v (uniform per workgroup)
+  const int rope_third = is_rope(EPI) ? (tile_n * BN) / (N_out / 3) : 2;   // 0 = q, 1 = k, 2 = v (uniform per workgroup)
   // v third of the QKV projection: a wave keeps two passes (64 keys) in its staging area, so that the
   // key-contiguous copy is written in whole 128-byte lines; columns are XOR-swizzled by the 16-key block
   // of the row, which makes the transposing 2-byte reads free of bank conflicts.
-  constexpr int kVPasses = (EPI == kEpiQkvRope && WTM % 64 == 0) ? 2 : 1;
+  constexpr int kVPasses = (is_rope(EPI) && WTM % 64 == 0) ? 2 : 1;
   static_assert(WM * WN * kVPasses * 32 * kStride <= kStages * kStage, "v staging area exceeds the LDS ring");
   static_assert(!kNormRoom || WM * WN * kVPasses * 32 * kStride <= kNormOff, "staging area reaches into the norm exchange area");
-  const bool v_tile = EPI == kEpiQkvRope && rope_third == 2;
+  const bool v_tile = is_rope(EPI) && rope_third == 2;
   unsigned char *my = lds + wave * ((v_tile ? kVPasses : 1) * 32 * kStride);
   // rotary epilogue: cos / sin of the lane's rows (2 halves of 16) and columns (2 sub-tiles x 4 pairs) of a
   // pass, requested one pass ahead
   const int rope_g = wn & 1;
-  float4 csr[EPI == kEpiQkvRope ? 2 : 1][2][2][2];
+  float4 csr[is_rope(EPI) ? 2 : 1][2][2][2];
   auto load_cs = [&](int mt) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) {
         const int m = m0 + wm * WTM + mt * 32 + h * 16 + fr;
-        const float4 *cs4 = reinterpret_cast<const float4 *>(ra.cos_sin + (int64_t)(min(m, M - 1) % ra.T) * 64 + rope_g * 32 + nt * 16 + 4 * fq);
-        csr[EPI == kEpiQkvRope ? mt & 1 : 0][h][nt][0] = cs4[0];
-        csr[EPI == kEpiQkvRope ? mt & 1 : 0][h][nt][1] = cs4[1];
+        int pos = EPI == kEpiQkvRopeWin ? ra.row_pos[min(m, M - 1)] : min(m, M - 1) % ra.T;
+        if (EPI == kEpiQkvRopeWin && pos < 0) pos = ra.T - 1;
+        const float4 *cs4 = reinterpret_cast<const float4 *>(ra.cos_sin + (int64_t)pos * 64 + rope_g * 32 + nt * 16 + 4 * fq);
+        csr[is_rope(EPI) ? mt & 1 : 0][h][nt][0] = cs4[0];
+        csr[is_rope(EPI) ? mt & 1 : 0][h][nt][1] = cs4[1];
       }
   };
-  if (EPI == kEpiQkvRope && rope_third < 2) load_cs(0);
+  if (is_rope(EPI) && rope_third < 2) load_cs(0);
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    if (EPI == kEpiQkvRope && rope_third < 2 && mt + 1 < MT) load_cs(mt + 1);
+    if (is_rope(EPI) && rope_third < 2 && mt + 1 < MT) load_cs(mt + 1);
     // lane: row h*16 + lane%16 of the pass (h = 16-row half), 4 consecutive columns per n sub-tile
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -708,7 +713,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[nt][m16][e] *= rs;
       }
-      if (EPI == kEpiQkvRope && rope_third < 2) {
+      if (is_rope(EPI) && rope_third < 2) {
         // a = column i of the head (sub-tile nt), b = column i + 64 (sub-tile nt + 2), both rounded to bf16 first
         // (the values a separate rotary pass would read): i <- a cos - b sin, i + 64 <- b cos + a sin
 #pragma unroll
@@ -720,7 +725,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
           uint32_t lo[2], up[2];
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
-            const float4 c4 = csr[EPI == kEpiQkvRope ? mt & 1 : 0][h][nt][e];
+            const float4 c4 = csr[is_rope(EPI) ? mt & 1 : 0][h][nt][e];
             const float a0 = __uint_as_float(aw[e] << 16), a1 = __uint_as_float(aw[e] & 0xffff0000u);
             const float b0 = __uint_as_float(bw[e] << 16), b1 = __uint_as_float(bw[e] & 0xffff0000u);
             const float2 r0 = rotate_pair(a0, b0, c4.x, c4.y), r1 = rotate_pair(a1, b1, c4.z, c4.w);
@@ -750,8 +755,8 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
         }
       }
     }
-    if (EPI == kEpiQkvRope) {
-      static_assert(EPI != kEpiQkvRope || (WTN == 64 && WN % 2 == 0), "a head is two wave tiles wide");
+    if (is_rope(EPI)) {
+      static_assert(!is_rope(EPI) || (WTN == 64 && WN % 2 == 0), "a head is two wave tiles wide");
       const int d_model = N_out / 3;
       const int m_base = m0 + wm * WTM + mt * 32;
       if (rope_third < 2) {
@@ -782,11 +787,12 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
         if ((vp == kVPasses - 1 || mt == MT - 1) && key0 < M) {
           const int vcol0 = out_col0 - 2 * d_model;                  // column inside the v third; 64 columns of one head
           bf16_t *vt_head = ra.vt + (int64_t)(vcol0 & 127) * ra.Tv;
-          if (ra.T % 16 == 0) {
+          const int per_seq = EPI == kEpiQkvRopeWin ? ra.R : ra.T;   // rows a canvas
+          if (EPI == kEpiQkvRopeWin || ra.T % 16 == 0) {
             const int chunks = 4 * (vp + 1);                         // 16-byte chunks per column: 4 or 8
             const int g = lane % chunks, blk = g >> 1;
-            int seq = key0 / ra.T, t0 = key0 % ra.T + 16 * blk;
-            if (ra.T % 64 != 0) { seq = (key0 + 16 * blk) / ra.T; t0 = (key0 + 16 * blk) % ra.T; }   // a group of 64 keys may straddle canvases
+            int seq = key0 / per_seq, t0 = key0 % per_seq + 16 * blk;
+            if (per_seq % 64 != 0) { seq = (key0 + 16 * blk) / per_seq; t0 = (key0 + 16 * blk) % per_seq; }   // a group of 64 keys may straddle canvases
             const unsigned char *src = my + (16 * blk + 4 * (g & 1)) * kStride;
             bf16_t *dst = vt_head + ((int64_t)seq * ra.H + (vcol0 >> 7)) * 128 * ra.Tv + t0 + (g & 1) * 8;
             if (key0 + 16 * blk < M)
@@ -808,7 +814,7 @@ gemm_bf16_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W
             const int keys = 32 * (vp + 1);                          // lane = key; 4 columns per LDS read
             const int key = lane % keys, m = key0 + key;
             if (m < M) {
-              const int seq = m / ra.T, t = m % ra.T;
+              const int seq = m / per_seq, t = m % per_seq;
               const unsigned char *src = my + key * kStride;
               bf16_t *dst = vt_head + ((int64_t)seq * ra.H + (vcol0 >> 7)) * 128 * ra.Tv + ((t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1));
 #pragma unroll 4
@@ -978,7 +984,7 @@ template <int EPI>
 pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const void *W, void *C,
                    const void *Res, int M, int N, int K, const RopeArgs &ra = RopeArgs{}, const NormArgs &na = NormArgs{}, bool turn = false) {
   const SplitK whole{nullptr, 0, turn && (M <= 128 ? K >= 1024 : M <= 384 && K >= 2048)};
-  constexpr bool kPlain = EPI != kEpiSwiglu && EPI != kEpiQkvRope;
+  constexpr bool kPlain = EPI != kEpiSwiglu && !is_rope(EPI);
   if (K % 128 != 0 && cfg == 0) return run<EPI, 256, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
   if (K % 128 != 0 && cfg == 4) return run<EPI, 192, 256, 64, 2, 2, 4, false>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
   switch (cfg) {
@@ -989,7 +995,7 @@ pvf_status run_cfg(pvf_ctx *ctx, hipStream_t s, int cfg, const void *A, const vo
     case 5: if constexpr (kPlain) return run<EPI, 320, 128, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 6: if constexpr (kPlain) return run<EPI, 64, 64, 64, 5, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     case 7: return run<EPI, 64, 128, 64, 3, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na);
-    case 8: if constexpr (EPI != kEpiQkvRope) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
+    case 8: if constexpr (!is_rope(EPI)) return run<EPI, 192, 128, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
     case 9: if constexpr (kPlain) return run<EPI, 160, 256, 64, 3, 2, 4>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 10: if constexpr (EPI == kEpiSwiglu) return run<EPI, 256, 192, 64, 2, 4, 2>(ctx, s, A, W, C, Res, M, N, K, ra, SplitK{nullptr, 0}, 1, na); break;
     case 11: if constexpr (EPI == kEpiSwiglu) return run<EPI, 64, 128, 64, 6, 2, 2>(ctx, s, A, W, C, Res, M, N, K, ra, whole, 1, na); break;
@@ -1290,21 +1296,28 @@ pvf_status launch_gemm_mfma_qkv_rope(pvf_ctx *ctx, hipStream_t s, const void *A,
   return run_cfg<kEpiQkvRope>(ctx, s, cfg, A, W, qkv, nullptr, M, N, K, ra, na ? *na : NormArgs{});
 }
 
-// QKV projection of the window rows of S canvases (R rows each, R and the windows whole 16-key groups) with the rotary embedding
-// and the key-contiguous v (vt [S][H][128][Rv]) in its epilogue, where the launch takes tiles of 64 columns.
-bool gemm_mfma_qkv_window_supported(int M, int N, int K) {
-  if (!gemm_mfma_supported(PVF_BF16, kEpiStore, M, N, K) || N % 384 != 0) return false;
+// QKV projection of the window rows of canvases (R rows each; windows of whole 16-key groups) with the rotary embedding and the
+// key-contiguous v (vt [S][H][128][Rv]) in its epilogue: on tiles of 64 columns up to 128 rows, on the tiles of whole canvases above 384,
+// where K is not divided (512 rows, cached rounds 8.65 -> 8.50 ms, 576 rows 10.66 -> 10.52).  Windows that share groups with the cache
+// would have to complete them and write key by key: built, the time of the pass.
+static bool window_small_tiles(int M, int N, int K) {
   const int cfg = pick_config(kEpiStore, M, N, K);
   return cfg == 6 || cfg == 12;
+}
+bool gemm_mfma_qkv_window_supported(int M, int N, int K) {
+  if (!gemm_mfma_supported(PVF_BF16, kEpiStore, M, N, K) || N % 768 != 0) return false;
+  return M > 384 ? pick_config(kEpiQkvRope, M, N, K) >= 0 && gemm_mfma_qkv_rope_pays(M, N, K) : window_small_tiles(M, N, K);
 }
 
 pvf_status launch_gemm_mfma_qkv_window(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *qkv, void *vt, const float2 *cos_sin,
                                        const int32_t *row_pos, int M, int N, int K, int T, int R, int Rv, int H) {
   const uintptr_t al = (uintptr_t)A | (uintptr_t)W | (uintptr_t)qkv | (uintptr_t)vt;
   PVF_REQUIRE(ctx, (al & 15u) == 0, PVF_EINVAL, "gemm_mfma: operands must be 16-byte aligned");
-  PVF_REQUIRE(ctx, R % 16 == 0 && M % R == 0 && N == 3 * H * 128 && Rv >= R, PVF_ESHAPE, "gemm_mfma: window rows M=%d R=%d Rv=%d N=%d H=%d", M, R, Rv, N, H);
+  PVF_REQUIRE(ctx, R > 0 && R % 16 == 0 && M % R == 0 && N == 3 * H * 128 && Rv >= R, PVF_ESHAPE, "gemm_mfma: window rows M=%d R=%d Rv=%d N=%d H=%d", M, R, Rv, N, H);
+  PVF_REQUIRE(ctx, gemm_mfma_qkv_window_supported(M, N, K), PVF_ESHAPE, "gemm_mfma: window rows M=%d N=%d K=%d", M, N, K);
   RopeArgs ra{};
   ra.cos_sin = cos_sin; ra.vt = (bf16_t *)vt; ra.T = T; ra.Tv = Rv; ra.H = H; ra.row_pos = row_pos; ra.R = R;
+  if (M > 384) return run_cfg<kEpiQkvRopeWin>(ctx, s, pick_config(kEpiQkvRope, M, N, K), A, W, qkv, nullptr, M, N, K, ra);
   const SplitK whole{nullptr, 0, K >= 1024};
   if (pick_config(kEpiStore, M, N, K) == 12) return run<kEpiQkvWindow, 128, 64, 64, 6, 4, 2>(ctx, s, A, W, qkv, nullptr, M, N, K, ra, whole);
   return run<kEpiQkvWindow, 64, 64, 64, 5, 2, 2>(ctx, s, A, W, qkv, nullptr, M, N, K, ra, whole);
@@ -1344,7 +1357,7 @@ pvf_status launch_gemm_mfma(pvf_ctx *ctx, hipStream_t s, GemmEpilogue epi, const
     case kEpiResidual: return run_cfg<kEpiResidual>(ctx, s, cfg, A, W, C, residual, M, N, K, RopeArgs{}, nrm);
     case kEpiSwiglu: return run_cfg<kEpiSwiglu>(ctx, s, cfg, A, W, C, residual, M, N, K, RopeArgs{}, nrm, turn);
     case kEpiQkvRope: break;                     // has its own entry (launch_gemm_mfma_qkv_rope)
-    case kEpiQkvWindow: break;                   // launch_gemm_mfma_qkv_window
+    case kEpiQkvWindow: case kEpiQkvRopeWin: break;      // launch_gemm_mfma_qkv_window
     case kEpiPartial: break;                     // launch_gemm_mfma_splitk
   }
   return PVF_EINVAL;
