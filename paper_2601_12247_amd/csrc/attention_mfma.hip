@@ -68,8 +68,13 @@ __device__ __forceinline__ void split3(const float *p, bf16x8 *x) {
 struct WinArgs {
   const bf16_t *kc, *vtc;
   int64_t group_stride;
-  const int32_t *seq_slot, *row_pos;                         // row_pos[seq * R]: first position of the window
+  const int32_t *seq_slot, *row_pos;
   int32_t slots_per_group, R, Rv;
+  // first position of a canvas' window; row_pos is -1 where the active block lies behind the canvas: an empty window at its end
+  __device__ __forceinline__ int first(int seq, int T) const {
+    const int p = row_pos[(int64_t)seq * R];
+    return p < 0 ? T : p;
+  }
 };
 
 // SPLIT (window mode, launches that leave CUs idle): a workgroup takes 64 queries, which need only two of the four waves, and
@@ -105,7 +110,7 @@ attention_mfma_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__
   const bf16_t *kcb = nullptr, *vtcb = nullptr;
   if (WIN) {
     const int g = wa.seq_slot[seq] / wa.slots_per_group;
-    w0 = wa.row_pos[(int64_t)seq * wa.R];
+    w0 = wa.first(seq, T);
     w1 = w0 + min(wa.R, T - w0);
     v0 = w0 & ~15; v1 = (w1 + 15) & ~15;
     kcb = wa.kc + g * wa.group_stride + (int64_t)head * DH;
@@ -443,7 +448,7 @@ rope_vt_rows_kernel(bf16_t *__restrict__ qkv, const float *__restrict__ part, in
   const int tid = threadIdx.x, head = blockIdx.y, seq = blockIdx.z;
   const int d = H * DH;
   const int g = wa.seq_slot[seq] / wa.slots_per_group;
-  const int w0 = wa.row_pos[(int64_t)seq * wa.R], w1 = w0 + min(wa.R, T - w0);
+  const int w0 = wa.first(seq, T), w1 = w0 + min(wa.R, T - w0);
   const int p0 = (w0 & ~15) + blockIdx.x * 16;               // first position of the group
   const int64_t row0 = (int64_t)seq * wa.R;
   // What a thread needs of the projection, in one go: 8 pairs of a rotated row (16 rows x 2 tensors x 8 chunks) and 8 d of a v row (16
