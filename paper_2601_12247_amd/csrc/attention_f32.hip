@@ -76,10 +76,9 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
   const uint32_t ld4 = (uint32_t)ld * 4u;
   const int last_rows = T - (n_tiles - 1) * 16;                     // 1..16
   const uint32_t k_off = fr * ld4 + 16u * fq, k_last = min(fr, last_rows - 1) * ld4 + 16u * fq;
-  const uint32_t v_off = 4 * fq * ld4 + 4u * fr;
-  uint32_t v_last[4];
+  uint32_t v_off[4], v_last[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) v_last[e] = min(4 * fq + e, last_rows - 1) * ld4 - e * ld4 + 4u * fr;     // added to e * ld4: inside the canvas
+  for (int e = 0; e < 4; ++e) v_off[e] = (4 * fq + e) * ld4 + 4u * fr, v_last[e] = min(4 * fq + e, last_rows - 1) * ld4 + 4u * fr;
 
   // ---- scores ----
   float4 q[KC];
@@ -144,7 +143,7 @@ attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, int
       const bool last = kt == n_tiles - 1;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, last ? v_last[e] : v_off, e * ld4, 0));
+        v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, last ? v_last[e] : v_off[e], 0, 0));
 #endif
       return;
     }

@@ -49,8 +49,8 @@ def test_attention_f32(S, T, H, dh):
         assert np.abs(got[s * T:(s + 1) * T] - want).max() <= 2e-5
 
 
-# the last tile of 16 keys whole, with one key, with 15; values that are read again for the padding keys are infinite
-@pytest.mark.parametrize("T,dh", [(16, 64), (17, 32), (31, 128), (229, 64)])
+# the last tile of 16 keys whole, with one to three keys (fewer than the four a lane takes), with 15; values that are read again for the padding keys are infinite
+@pytest.mark.parametrize("T,dh", [(16, 64), (17, 32), (18, 64), (35, 16), (31, 128), (229, 64)])
 def test_attention_f32_of_infinite_values(T, dh):
     """Every weight is above zero, so an infinite value of any key gives that infinity and no other column is touched."""
     rng = np.random.default_rng(T)
