@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,N,K", [(257, 3072, 512), (272, 9216, 1024), (319, 6144, 2048), (320, 12288, 4096), (300, 16512, 512),
-                                   (264, 7680, 8192), (311, 1536, 512), (256, 3072, 512), (321, 3072, 512),
+                                   (264, 7680, 8192), (311, 1536, 512), (300, 9216, 1088), (260, 3072, 576), (256, 3072, 512), (321, 3072, 512),
                                    (500, 3072, 2048), (192, 9216, 2048), (576, 6144, 2112)])
 def test_swiglu_every_element(ctx, M, N, K):  # noqa: F811
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
