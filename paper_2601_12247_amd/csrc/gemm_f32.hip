@@ -181,7 +181,6 @@ gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W, float 
       for (int t = 0; t < MT; ++t) one(ap[t], c.a[t]);
 #pragma unroll
       for (int t = 0; t < NB; ++t) one(wp[t], c.w[t]);
-      if constexpr (NORM) one(rw.gain, c.g);
     } else {
 #ifdef __HIP_DEVICE_COMPILE__
       const uint32_t back = LOAD == kLoadFour && ch == n_chunks - 1 ? tail_back : 0u;
@@ -317,7 +316,6 @@ pvf_status run_epi(pvf_ctx *ctx, hipStream_t s, const float *A, const float *W, 
   const bool aligned = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)rw.gain) & 15u) == 0;
   // the rows of a tile, of a head, or of the canvases that a tile's rows are picked from lie within 32-bit offsets
   const bool vec = aligned && std::max<int64_t>(256, MAP ? ((int64_t)32 / std::max(rw.R, 1) + 2) * rw.T : 0) * K * 4 < (1ll << 32);
-  PVF_REQUIRE(ctx, !NORM || aligned, PVF_ESHAPE, "gemm_f32: the fused norm takes 16-byte aligned rows");
   auto launch = [&](auto mt, auto nt) -> pvf_status {
     constexpr int MT = decltype(mt)::value, NT = decltype(nt)::value;
     const int64_t tiles = (int64_t)((N + 16 * NT - 1) / (16 * NT)) * ((M + 16 * MT - 1) / (16 * MT));
@@ -325,7 +323,8 @@ pvf_status run_epi(pvf_ctx *ctx, hipStream_t s, const float *A, const float *W, 
     const unsigned grid = (unsigned)tiles;
     if (vec && K % 16 == 0) gemm_f32_kernel<EPI, kLoadChunks, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
     else if (vec) gemm_f32_kernel<EPI, kLoadFour, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
-    else gemm_f32_kernel<EPI, kLoadAny, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
+    else if constexpr (!NORM) gemm_f32_kernel<EPI, kLoadAny, NORM, MAP, MT, NT><<<grid, 256, 0, s>>>(A, W, C, res, M, N, K, ra, rw);
+    else PVF_REQUIRE(ctx, false, PVF_ESHAPE, "gemm_f32: the fused norm takes 16-byte aligned rows of less than 4M elements");
     PVF_LAUNCH_CHECK(ctx, "gemm_f32");
     return PVF_OK;
   };
