@@ -941,16 +941,13 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   // push the activations and the partial sums out of L2 (cached rounds of 64 and 320 rows 4.4 and 2.5 % faster).  With more rows of
   // tiles they may be gone before the last one reads them: 160 x 256 tiles at 1311 rows of 6144 columns, K = 2048, 40.1 us with the
   // hint and 34.4 without, K = 8192 132 and 121; 4100 rows of 12288 columns, K = 4096, 352 and 335.
-  constexpr bool kTileStage = EPI == kEpiSwiglu && !pairs_in_wave(BN / WN);
-  constexpr bool kFewRows = EPI == kEpiPartial ? BM == 64 : BN == 64 || ST == 6;                 // shapes for up to 128 rows
-  constexpr bool kTwoRows = (EPI == kEpiPartial && BN == 192) || (EPI == kEpiStore && BM == 160) || kTileStage;
+  // shapes for at most two rows of tiles (160 x 192: a forced shape aside)
+  constexpr bool kFewRows = EPI == kEpiPartial ? BM == 64 : BN == 64 || ST == 6 || (EPI == kEpiSwiglu && BM == 160);
+  constexpr bool kTwoRows = (EPI == kEpiPartial && BN == 192) || (EPI == kEpiStore && BM == 160);
   // shapes that the launches taking the whole of K behind few rows are made of
   constexpr bool kTurns = ((EPI == kEpiStore || EPI == kEpiQkvWindow) && BN == 64) || (EPI == kEpiSwiglu && BN == 128 && (ST == 6 || BM == 128)) ||
                           (EPI == kEpiSwiglu && kPairs && (BM == 192 || BM == 160 || (BM == 256 && BN == 128))) || (EPI == kEpiStore && BM == 192 && BN == 128);
-  if constexpr (kTurns) if (sk.turn) {
-    if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{}, std::true_type{});
-    return launch(std::bool_constant<kFewRows>{}, std::true_type{});
-  }
+  if constexpr (kTurns) if (sk.turn) return launch(std::bool_constant<kFewRows>{}, std::true_type{});
   if constexpr (kFewRows) return launch(std::true_type{}, std::false_type{});
   else {
     if constexpr (kTwoRows) if (tiles_m <= 2) return launch(std::true_type{}, std::false_type{});
