@@ -438,8 +438,10 @@ rope_vt_kernel(bf16_t *__restrict__ qkv, bf16_t *__restrict__ vt, int T, int H, 
 // that boundary; positions of a boundary group that lie outside the window come from the cache.
 // PART: q, k and v come as the float32 partial sums of the split-K projection, part[split][row][3 d], added in split order and
 // rounded to bf16 here; the v third of qkv is then not written (only the attention reads these rows).  Bound by latency:
-// 64 rows, 8 splits: 9.4 us, where a reduction of its own and 64-row workgroups took 5.4 + 6.4; 320 rows, 2 splits: 10.8, and 10.0 with
-// all that a thread needs asked for at once, behind one load (row_pos) for where the window lies.
+// 64 rows, 8 splits: 9.4 us, where a reduction of its own and 64-row workgroups took 5.4 + 6.4.  All that a thread needs is asked for at
+// once, behind one load (row_pos) for where the window lies; the registers that this takes (PART 128 instead of 56) cost nothing at any
+// number of rows.  Windows that are and are not whole groups: 192 rows 8.8 -> 8.6 and 11.3 -> 10.9 us, 256 9.5 -> 9.2 and 13.3 -> 12.8, 320
+// 10.6 -> 10.5 and 15.2 -> 15.1; behind whole sums 384 rows 6.7 -> 6.9 and 8.2 -> 7.8, 512 (are not) 9.4 -> 9.0, 640 11.0 -> 10.4.
 template <bool PART>
 __global__ void __launch_bounds__(256)
 rope_vt_rows_kernel(bf16_t *__restrict__ qkv, const float *__restrict__ part, int splits, int M, bf16_t *__restrict__ vt, int T, int H,

@@ -245,8 +245,9 @@ reduce_residual_rmsnorm_kernel(const float *__restrict__ partial, int splits, in
   uint4 *hr = reinterpret_cast<uint4 *>(h + m * d);
   const uint4 *gr = reinterpret_cast<const uint4 *>(gain);
   uint4 *orow = reinterpret_cast<uint4 *>(out + m * d);
-  // Bound by latency: everything that depends on nothing is asked for first, the gains too, then the partial sums of the whole row (320
-  // rows 7.5 -> 7.2 us, 64 5.8 -> 5.6).
+  // Bound by latency: everything that depends on nothing is asked for first, the gains too, then the partial sums of the whole row (means
+  // over the O and down projections: 64 rows 5.1 -> 4.8 us, 192 7.1 -> 6.4, 256 7.8 -> 7.2, 320 7.1 -> 7.0, 512 8.5 -> 8.2, 640 10.1 -> 9.7;
+  // the 96 registers instead of 44 that this takes cost nothing at any of them).
   uint4 v[MAXV], g4[MAXV];
 #pragma unroll
   for (int k = 0; k < MAXV; ++k) {

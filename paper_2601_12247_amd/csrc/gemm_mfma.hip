@@ -915,6 +915,10 @@ pvf_status run(pvf_ctx *ctx, hipStream_t s, const void *A, const void *W, void *
   // 9216, K = 3072, 256 rows 49.7 -> 40.0; O of 768 rows 37.9 -> 32.6, down (K = 12288) 111 -> 86, of 1311 rows 132 -> 124.  Not up to 64
   // rows, which HBM itself bounds (33 rows of 9216 columns, K = 3072, 15.4 -> 17.4); not with weights below 16 MB, which most tiles find in L2
   // (1311 rows of 1024 columns, K = 2048, 14.7 -> 15.6); not behind tiles of 256 x 256, which the MFMAs bound (1024 rows 80-85 either way).
+  // Shapes of which two tiles fit a CU (64 x 64 and 64 x 128 rings of up to 80 KB) are counted like the others: the tiles past 32 of an
+  // XCD start at once, but on a CU that has one already, and gain by it.  K = 4096, without and with: 192 rows of 12416 columns 53.5 -> 49.7
+  // us, of 2 x 6208 54.2 -> 49.8, 128 rows of 9216 37.4 -> 33.4, 256 rows of 17280 (68 tiles) 83.4 -> 74.1; the other side, 192 rows of 11008
+  // (33 tiles) 40.0 -> 41.1 and 256 rows of 8832 46.0 -> 46.8.
   const int chunk = (total + 7) / 8, in_last = chunk % 32, idle = 32 - in_last;     // tiles and idle CUs of an XCD in the last round
   const int w_rows = EPI == kEpiSwiglu ? 2 * N_out : N_out;
   SplitK sk = split;
