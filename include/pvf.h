@@ -35,7 +35,9 @@
  *     Impact set, compatibility, C_total, commits and candidates all range over B_t.
  *   - Environment variables, each read once per process; none is needed in normal use:
  *     PVF_GEMM_TILE=<n>   force bf16 GEMM tile shape n wherever a launch can take it
- *                         (tile sweeps; every shape gives bit-identical results),
+ *                         (tile sweeps; every shape gives bit-identical results, but for
+ *                         launches of up to 384 rows in a context, where columns of some
+ *                         shapes begin inside K),
  *     PVF_FORCE_SIMPLE=1  run bf16 launches on the plain (non-MFMA) kernels,
  *     PVF_FOLD_NORM=0     keep every RMSNorm a launch of its own instead of folding it
  *                         into the projections around it (forwards above 640 rows).
