@@ -71,10 +71,7 @@ struct WinArgs {
   const int32_t *seq_slot, *row_pos;
   int32_t slots_per_group, R, Rv;
   // first position of a canvas' window; row_pos is -1 where the active block lies behind the canvas: an empty window at its end
-  __device__ __forceinline__ int first(int seq, int T) const {
-    const int p = row_pos[(int64_t)seq * R];
-    return p < 0 ? T : p;
-  }
+  __device__ __forceinline__ int first(int seq, int T) const { return (int)min((uint32_t)row_pos[(int64_t)seq * R], (uint32_t)T); }
 };
 
 // SPLIT (window mode, launches that leave CUs idle): a workgroup takes 64 queries, which need only two of the four waves, and
